@@ -143,6 +143,20 @@ static air_status hip_fail(air_ctx *ctx, hipError_t e, const char *what) {
     return fail(ctx, AIR_ERR_HIP, std::string(what) + ": " + hipGetErrorString(e));
 }
 
+// rows of a K' / V' region back in token order (host)
+template <typename E, int D>
+static void untile_k(const void *raw, void *dst, int len) {
+    constexpr int kVec = 16 / (int)sizeof(E);
+    for (int r = 0; r < len; ++r)
+        for (int col = 0; col < D; ++col) ((E *)dst)[(size_t)r * D + col] = ((const E *)raw)[k_tiled<D, kVec>(r, col)];
+}
+template <typename E, int D>
+static void untile_v(const void *raw, void *dst, int len) {
+    constexpr int kVec = 16 / (int)sizeof(E);
+    for (int r = 0; r < len; ++r)
+        for (int col = 0; col < D; ++col) ((E *)dst)[(size_t)r * D + col] = ((const E *)raw)[v_tiled<D, kVec>(r, col)];
+}
+
 extern "C" {
 
 const char *air_version(void) { return "aircache-mi355x 0.1"; }
@@ -493,11 +507,15 @@ air_status air_select_compact(air_ctx *ctx, void *stream, int32_t l0, int32_t l1
 // against 10.8 us at 10 % retention, 34.9 against 36.0 at 50 %, 75.3 against 78.2 with the full cache):
 // the merge of the waves through LDS is shorter and the streaming is bound by the CU, not by the number of waves.
 // air_set_tuning overrides the choice (tests, tuning).
+static int decode_tiles_of(const air_config &c) { return c.dtype == AIR_F32 && c.head_dim == 128 ? 2 : 4; }
+
 static void decode_shape(const air_ctx *ctx, int n_layers_in_launch, int appended, bool halves_ok, int *splits, int *waves,
                          int *tiles) {
     constexpr int kEnoughWorkgroups = 256, kEnoughWaves = 1536;
-    constexpr double kWorkgroupGBs = 100.0, kLaunchGBs = 6000.0, kSplitUs = 3.7;
+    constexpr double kLaunchGBs = 6000.0, kSplitUs = 3.7;
     const air_config &c = ctx->cfg;
+    // what one workgroup streams: fp32 is bound by its matrix products (4.7 MB in 100 us, 9.2 MB in 190)
+    const double workgroup_gbs = c.dtype == AIR_F32 ? 48.0 : (c.head_dim == 64 ? 77.0 : 100.0);
     double avg_len = 0.0;
     for (int b = 0; b < c.batch; ++b) {
         const air_seq &s = ctx->seqs[b];
@@ -512,10 +530,20 @@ static void decode_shape(const air_ctx *ctx, int n_layers_in_launch, int appende
     // halves: four waves, 64-key chunks): 4 units, us per launch against the splits, 360 keys 5.8 / 7.7, 870 keys
     // 8.1 / 8.4, 1600 keys 11.3 / 9.8, 3800 keys 20.7 / 10.8.
     // (The rule goes by the prompt's own length, so that a decode run keeps one shape from its first step to its last.)
-    const bool short_halves = units <= 16 && halves_ok && avg_len - appended < 896.0;
+    // The other storages (bf16 with heads of 64 elements, fp32) split from 288 KB a unit on: 4 units, us per launch as one
+    // workgroup of eight waves against the best split, bf16 d = 64 112 KB 5.9 / 7.0, 266 KB 7.2 / 7.5, 770 KB 12.8 / 8.4;
+    // fp32 d = 64 225 KB 8.1 / 8.4, 530 KB 13.1 / 8.9; fp32 d = 128 450 KB 13.9 (halves 11.1) / 9.6.
+    const double unit_bytes = avg_len * 2.0 * c.head_dim * (c.dtype == AIR_BF16 ? 2.0 : 4.0);
+    const bool other = !v_transposed(c.dtype, c.head_dim);
+    const bool short_unit = other && unit_bytes < 288.0 * 1024.0;
+    const bool short_halves = units <= 16 && halves_ok && (other ? short_unit : avg_len - appended < 896.0);
     const bool tiny_launch = units <= 16 && !short_halves;
-    int kt = tiny_launch ? 2 : 4;
-    if (ctx->tune.decode_tiles > 0) kt = ctx->tune.decode_tiles;
+    // 64 keys a wave and iteration (32 of the 512-byte fp32 rows); bf16 with heads of 128 elements has other sizes compiled too
+    int kt = decode_tiles_of(c);
+    if (v_transposed(c.dtype, c.head_dim)) {
+        if (tiny_launch) kt = 2;
+        if (ctx->tune.decode_tiles > 0) kt = ctx->tune.decode_tiles;
+    }
     const int64_t iters = (int64_t)((avg_len + 16.0 * kt - 1.0) / (16.0 * kt));
     // Waves per workgroup: enough for the launch to hold about 1536 waves, and beyond that one wave per 16
     // iterations of the unit, four at most (eight in a tiny launch).  Many short units run fastest with one wave
@@ -527,11 +555,10 @@ static void decode_shape(const air_ctx *ctx, int n_layers_in_launch, int appende
     if (kt == 8 && w == 8) w = 4;
     int64_t s = 1;
     if (tiny_launch) {
-        while (s < kMaxSplits && iters > 4 * s && units * s * 2 <= kEnoughWorkgroups) s *= 2;
+        while (!short_unit && s < kMaxSplits && iters > 4 * s && units * s * 2 <= kEnoughWorkgroups) s *= 2;
     } else if (!short_halves) {
-        const double unit_bytes = avg_len * 2.0 * c.head_dim * (c.dtype == AIR_BF16 ? 2.0 : 4.0);
         const double launch_us = (double)units * unit_bytes / (kLaunchGBs * 1e3);
-        auto cost = [&](int64_t n) { return fmax(launch_us, unit_bytes / n / (kWorkgroupGBs * 1e3)) + (n > 1 ? kSplitUs : 0.0); };
+        auto cost = [&](int64_t n) { return fmax(launch_us, unit_bytes / n / (workgroup_gbs * 1e3)) + (n > 1 ? kSplitUs : 0.0); };
         for (int64_t n = 2; n <= kMaxSplits && units * n <= kEnoughWorkgroups; n *= 2)
             if (cost(n) < cost(s)) s = n;
     }
@@ -569,7 +596,7 @@ static air_status decode_attn(air_ctx *ctx, void *stream, int32_t l0, int32_t l1
     // The MFMA kernel takes any number of layers per launch when they have all appended the same number of
     // tokens (the usual case: the layers decode in step), as long as the grid fits; otherwise the per-layer
     // counts travel with the launch, kMaxLayersPerLaunch layers at a time.
-    bool in_step = v_transposed(ctx->cfg.dtype, ctx->cfg.head_dim);
+    bool in_step = true;
     for (int l = l0 + 1; l < l1 && in_step; ++l) in_step = ctx->appended[l] == ctx->appended[l0];
     const int64_t units_per_layer = (int64_t)ctx->dm.B * ctx->dm.Hkv;
     const int max_nl = in_step ? (int)(65535 / units_per_layer) : layers_per_launch(ctx);  // grid.y <= 65535
@@ -577,7 +604,7 @@ static air_status decode_attn(air_ctx *ctx, void *stream, int32_t l0, int32_t l1
     auto shape_of = [&](int c0, int nl, int *splits, int *waves, int *tiles) {
         // a recorded launch is replayed at every cache length: its shape is chosen for the middle of the decode
         const int hkv = ctx->dm.Hkv;
-        const bool halves_ok = in_step && (hkv & (hkv - 1)) == 0 && ctx->tune.decode_halves != 1;
+        const bool halves_ok = in_step && ctx->cfg.head_dim == 128 && (hkv & (hkv - 1)) == 0 && ctx->tune.decode_halves != 1;
         decode_shape(ctx, nl, ctx->cfg.device_steps ? ctx->cfg.max_decode_steps / 2 : ctx->appended[c0], halves_ok, splits, waves,
                      tiles);
     };
@@ -588,7 +615,8 @@ static air_status decode_attn(air_ctx *ctx, void *stream, int32_t l0, int32_t l1
     // 3800 keys 33 / 45 against 35 / 55, 7400 keys 64 / 73 against 76 / 89.
     auto halves_of = [&](int nl, int splits, int waves, int tiles) {
         const int hkv = ctx->dm.Hkv;
-        const bool can = in_step && (hkv & (hkv - 1)) == 0 && splits == 1 && waves == 4 && tiles == 4;
+        const bool can = in_step && ctx->cfg.head_dim == 128 && (hkv & (hkv - 1)) == 0 && splits == 1 && waves == 4 &&
+                         tiles == decode_tiles_of(ctx->cfg);
         const bool few = 2 * ((nl * units_per_layer + 7) & ~7) <= 256;
         return can && ctx->tune.decode_halves != 1 && (few || ctx->tune.decode_halves == 2);
     };
@@ -596,7 +624,7 @@ static air_status decode_attn(air_ctx *ctx, void *stream, int32_t l0, int32_t l1
         const int nl = (l1 - c0 < max_nl) ? l1 - c0 : max_nl;
         int splits = 1, waves = 1, tiles = 4;
         shape_of(c0, nl, &splits, &waves, &tiles);
-        const bool exchanges = splits > 1 || !v_transposed(ctx->cfg.dtype, ctx->cfg.head_dim);  // the generic kernels always go through partials
+        const bool exchanges = splits > 1 || !v_transposed(ctx->cfg.dtype, ctx->cfg.head_dim);  // refused for the other storages whatever the splits
         if (exchanges && (int64_t)nl * units_per_layer * splits > (int64_t)kStaticSlots)
             return fail(ctx, AIR_ERR_SHAPE, "air_decode_attn_static: the launch needs " +
                                                 std::to_string((int64_t)nl * units_per_layer * splits) +
@@ -619,8 +647,8 @@ static air_status decode_attn(air_ctx *ctx, void *stream, int32_t l0, int32_t l1
         // A launch over every layer of many units of differing lengths takes them longest first (a table of the
         // layers by falling cache length per sequence, left by the budget kernel): the workgroups still running at
         // the end are then the short ones.  72B-shaped workload, 1280 units of 1475-2930 keys: 256 -> 248 us per step.
-        const bool whole = in_step && c0 == 0 && nl == ctx->cfg.n_layers && splits == 1 && tiles == 4 && (waves == 1 || waves == 4) &&
-                           v_transposed(ctx->cfg.dtype, ctx->cfg.head_dim) && !ctx->cfg.cache_in_place;
+        const bool whole = in_step && c0 == 0 && nl == ctx->cfg.n_layers && splits == 1 &&
+                           tiles == decode_tiles_of(ctx->cfg) && (waves == 1 || waves == 4) && !ctx->cfg.cache_in_place;
         const bool longest_first = whole && ctx->tune.decode_order != 1 &&
                                    (ctx->tune.decode_order == 2 || (int64_t)nl * units_per_layer >= 512);
         const bool column_halves = halves_of(nl, splits, waves, tiles);
@@ -845,26 +873,17 @@ air_status air_get_cache(air_ctx *ctx, int32_t l, int32_t b, int32_t h, void *k_
         vbase = (const char *)ctx->ip_layers[l].v;
         row0 = ((size_t)b * ctx->tab.ip_kv_b + (size_t)h * ctx->tab.ip_kv_h) / ctx->dm.D;
     }
-    if (!v_transposed(ctx->cfg.dtype, ctx->dm.D)) {
-        st = d2h(ctx, k_host, kbase + row0 * rb, (size_t)len * rb);
-        if (st != AIR_OK) return st;
-        return d2h(ctx, v_host, vbase + row0 * rb, (size_t)len * rb);
-    }
     // tiled K' and block-transposed V': fetch whole 32-token blocks and put the tokens back in row order
-    const int D = ctx->dm.D;
     const size_t n_blk = ((size_t)len + 31) / 32;
-    std::vector<uint16_t> raw(n_blk * 32 * D);
-    st = d2h(ctx, raw.data(), kbase + row0 * rb, raw.size() * 2);
+    std::vector<char> raw(n_blk * 32 * rb);
+    st = d2h(ctx, raw.data(), kbase + row0 * rb, raw.size());
     if (st != AIR_OK) return st;
-    uint16_t *kh = (uint16_t *)k_host;
-    for (int r = 0; r < len; ++r)
-        for (int col = 0; col < D; ++col) kh[(size_t)r * D + col] = raw[k_tiled(r, col)];
-    st = d2h(ctx, raw.data(), vbase + row0 * rb, raw.size() * 2);
+    if (esz == 2) ctx->dm.D == 128 ? untile_k<uint16_t, 128>(raw.data(), k_host, len) : untile_k<uint16_t, 64>(raw.data(), k_host, len);
+    else ctx->dm.D == 128 ? untile_k<uint32_t, 128>(raw.data(), k_host, len) : untile_k<uint32_t, 64>(raw.data(), k_host, len);
+    st = d2h(ctx, raw.data(), vbase + row0 * rb, raw.size());
     if (st != AIR_OK) return st;
-    uint16_t *vh = (uint16_t *)v_host;
-    for (int r = 0; r < len; ++r)
-        for (int col = 0; col < D; ++col)
-            vh[(size_t)r * D + col] = raw[v_tiled(r, col)];
+    if (esz == 2) ctx->dm.D == 128 ? untile_v<uint16_t, 128>(raw.data(), v_host, len) : untile_v<uint16_t, 64>(raw.data(), v_host, len);
+    else ctx->dm.D == 128 ? untile_v<uint32_t, 128>(raw.data(), v_host, len) : untile_v<uint32_t, 64>(raw.data(), v_host, len);
     return AIR_OK;
 }
 

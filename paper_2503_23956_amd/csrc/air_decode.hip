@@ -1,6 +1,6 @@
 // air_decode_attn: Eq.2 append, then softmax(q K'^T / sqrt(d)) V' over the compacted cache.
 //
-//   decode_mfma_kernel bf16, head_dim 128, ONE launch per call: one workgroup per (split, unit), the
+//   decode_mfma_kernel ONE launch per call, for both storage types and head sizes: one workgroup per (split, unit), the
 //                      grid laid out so that no block index needs an integer division.
 //                      The tiled K' and the block-transposed V' go from global memory straight
 //                      into MFMA operands, every load instruction reading 1 KB of consecutive
@@ -8,10 +8,9 @@
 //                      The token the call appends (Eq.2) is scored from k_new / v_new by one wave
 //                      of the split that owns its row, which also stores it into the cache; the
 //                      workgroup of a unit that finishes last merges the unit's split-K partials.
-//   append_kernel, decode_kernel, combine_kernel
-//                      generic fp32-ALU path (fp32 storage, head_dim 64): three launches.
 #include "air_device.h"
 #include "air_internal.h"
+#include "air_tile.h"
 
 #include <mutex>
 
@@ -73,40 +72,6 @@ hipError_t launch_zero_counters(hipStream_t s, int32_t *p, int n) {
     return hipGetLastError();
 }
 
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(4))) float f32x4;
-
-// key range of one split: ceil(len / splits) rounded up to whole 32-token blocks
-__device__ __forceinline__ void split_range(int len, int splits, int split, int &k0, int &k1) {
-    int cs = (len + splits - 1) / splits;
-    cs = (cs + 31) & ~31;
-    k0 = split * cs;
-    k1 = min(len, k0 + cs);
-}
-
-// ---------------------------------------------------------------------------------------
-// append (Eq.2)
-// ---------------------------------------------------------------------------------------
-template <typename T, int D>
-__global__ __launch_bounds__(128) void append_kernel(Dims dm, DevTables t, int l0, int lbase, LaunchLayers ll,
-                                                     const T *k_new, const T *v_new) {
-    const int u = blockIdx.x;
-    const int kvh = u % dm.Hkv;
-    const int b = (u / dm.Hkv) % dm.B;
-    const int li = u / (dm.Hkv * dm.B);
-    const int l = l0 + li;
-    const int row = t.base_len[(int64_t)b * dm.L + l] + ll.appended[li];
-    const int64_t row0 = ((int64_t)b * dm.Hkv + kvh) * dm.pool_rows + t.layer_off[(int64_t)b * dm.L + l];
-    const int64_t src = (((int64_t)(lbase + li) * dm.B + b) * dm.Hkv + kvh) * D;
-    constexpr int kVec = D * (int)sizeof(T) / 16;
-    const int tid = threadIdx.x;
-    if (tid < kVec) {
-        const int c = tid * (16 / (int)sizeof(T));
-        *reinterpret_cast<uint4 *>((T *)t.kcache + (row0 + row) * D + c) = *reinterpret_cast<const uint4 *>(k_new + src + c);
-        *reinterpret_cast<uint4 *>((T *)t.vcache + (row0 + row) * D + c) = *reinterpret_cast<const uint4 *>(v_new + src + c);
-    }
-}
-
 // ---------------------------------------------------------------------------------------
 // MFMA decode attention.  Workgroup (split, unit) of NW waves; wave w takes the chunks w, w+NW, ...
 // (16*KT keys each) of the split's key range.  Lane (n = lane % 16, c = lane / 16).
@@ -147,19 +112,29 @@ struct DecodeSteps {
     int32_t appended[kMaxLayersPerLaunch];
 };
 
+// 16-key tiles of a wave's chunk in launches that are not told otherwise: 16 KB of K' and V' (32 KB of the fp32 rows).
+// One launch on the matrix unit in place of three (append, attention on the vector unit with one row per thread, combine),
+// us per step: bf16 d = 64, 48 units of ~870 keys 157 -> 7.5; fp32 d = 128, 112 units of ~390 keys 154 -> 12.6.
+template <typename T, int D>
+constexpr int kDecodeTiles = sizeof(T) == 4 && D == 128 ? 2 : 4;
+
 // INPLACE: the cache is kept inside the layers' own K / V tensors (their addresses come from a table)
 // SORTED: a launch over all layers whose grid index z is not the layer but its rank by cache length within the
 // sequence (longest first); the layer comes with the table entry that carries the length
 // VH = 2: two workgroups per unit, each with one half of the columns of V' (see below); ONE_SEQ: the instance for B = 1
-template <int NW, int KT, bool SPLIT, bool INPLACE, bool SORTED = false, int VH = 1, bool ONE_SEQ = false>
+template <typename T, int D, int NW, int KT, bool SPLIT, bool INPLACE, bool SORTED = false, int VH = 1, bool ONE_SEQ = false>
 __global__ __launch_bounds__(64 * NW) void decode_mfma_kernel(Dims dm, DecodeTabs t, int l0, int lbase,
-                                                              DecodeSteps ll, const bf16_t *q_new,
-                                                              const bf16_t *k_new, const bf16_t *v_new, bf16_t *out,
+                                                              DecodeSteps ll, const T *q_new,
+                                                              const T *k_new, const T *v_new, T *out,
                                                               int splits, int lg_splits) {
-    constexpr int D = 128;
-    constexpr int kIter = 16 * KT;  // keys per loop iteration of one wave (KT score tiles, KT/2 token blocks)
-    constexpr int TB = KT / 2;
-    constexpr int NJ = 8 / VH;  // output tiles (16 columns each) of the workgroup
+    constexpr int kVec = Elem<T>::kVec, kVTok = Elem<T>::kVTok;
+    constexpr int NS = D / Elem<T>::kSlice;  // slices of the contraction over the head's elements
+    constexpr int kPieces = D / kVec;        // 16-byte pieces of a row
+    constexpr int kIter = 16 * KT;           // keys per loop iteration of one wave (KT score tiles, TB token blocks)
+    constexpr int TB = kIter / kVTok;
+    constexpr int NJ = D / 16 / VH;          // output tiles (16 columns each) of the workgroup
+    constexpr int kColsPer = D / 64 / VH;    // columns of the appended V' row per lane
+    static_assert(kIter % kVTok == 0 && kColsPer >= 1, "whole V' blocks per iteration, a column per lane");
     static_assert(VH == 1 || (!SPLIT && !SORTED && NJ % NW == 0), "column halves: one workgroup pair per unit");
     const int lane = threadIdx.x & 63, n = lane & 15, c = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // a scalar: the wave's chunk walk and its branches stay off the vector unit
@@ -208,15 +183,15 @@ __global__ __launch_bounds__(64 * NW) void decode_mfma_kernel(Dims dm, DecodeTab
     // addresses depend on the block index only), so they are long there when the wave that owns the
     // token needs them.
     const int64_t new_src = (((int64_t)(lbase + li) * dm.B + b) * dm.Hkv + kvh) * D;
-    uint4 knew[4], krow;
-    bf16_t vnew[NJ], vcol[2];
+    uint4 knew[NS], krow;
+    T vnew[NJ], vcol[kColsPer];
 #pragma unroll
-    for (int sl = 0; sl < 4; ++sl) knew[sl] = *reinterpret_cast<const uint4 *>(k_new + new_src + 32 * sl + 8 * c);
-    krow = *reinterpret_cast<const uint4 *>(k_new + new_src + 8 * n);
+    for (int sl = 0; sl < NS; ++sl) knew[sl] = *reinterpret_cast<const uint4 *>(k_new + new_src + Elem<T>::kSlice * sl + kVec * c);
+    krow = *reinterpret_cast<const uint4 *>(k_new + new_src + kVec * (lane & (kPieces - 1)));
 #pragma unroll
     for (int j = 0; j < NJ; ++j) vnew[j] = v_new[new_src + 16 * (j + NJ * vh) + n];
-    vcol[0] = v_new[new_src + 64 * vh + lane];
-    if (VH == 1) vcol[1] = v_new[new_src + 64 + lane];
+#pragma unroll
+    for (int h2 = 0; h2 < kColsPer; ++h2) vcol[h2] = v_new[new_src + 64 * (h2 + vh) + lane];
     const int64_t unit = ((int64_t)l * dm.B + b) * dm.Hkv + kvh;
     // tokens appended so far: from the host with the launch, or counted on the device (a recorded launch
     // that is replayed): the workgroup that finishes the unit advances the count, after every workgroup
@@ -233,7 +208,7 @@ __global__ __launch_bounds__(64 * NW) void decode_mfma_kernel(Dims dm, DecodeTab
     const int len = len_off.x + appended + 1;
     const int newrow = len - 1;  // the token appended by this call (Eq.2): scored from k_new / v_new, stored to the cache
     int k0 = 0, k1 = len;
-    if (SPLIT) {  // ceil(len / splits) rounded up to whole 32-token blocks, as split_range
+    if (SPLIT) {  // ceil(len / splits) rounded up to whole 32-token blocks
         const int cs = (((len + splits - 1) >> lg_splits) + 31) & ~31;
         k0 = split * cs;
         k1 = min(len, k0 + cs);
@@ -242,18 +217,18 @@ __global__ __launch_bounds__(64 * NW) void decode_mfma_kernel(Dims dm, DecodeTab
     // the unit's cache: its region of the workspace pool, or (kept in place) its rows of the layer's own K / V tensors
     const int64_t row0 = INPLACE ? 0 : ((int64_t)b * dm.Hkv + kvh) * dm.pool_rows + len_off.y;
     const int64_t ip0 = INPLACE ? (int64_t)b * t.kv_b + (int64_t)kvh * t.kv_h : 0;
-    bf16_t *kc = INPLACE ? (bf16_t *)cp.k + ip0 : (bf16_t *)t.kcache + row0 * D;
-    bf16_t *vc = INPLACE ? (bf16_t *)cp.v + ip0 : (bf16_t *)t.vcache + row0 * D;
-    bf16_t *o_unit = out + (((int64_t)(lbase + li) * dm.B + b) * dm.Hq + (int64_t)kvh * G) * D;
+    T *kc = INPLACE ? (T *)cp.k + ip0 : (T *)t.kcache + row0 * D;
+    T *vc = INPLACE ? (T *)cp.v + ip0 : (T *)t.vcache + row0 * D;
+    T *o_unit = out + (((int64_t)(lbase + li) * dm.B + b) * dm.Hq + (int64_t)kvh * G) * D;
 
-    bf16x8 qb[4];
+    uint4 qb[NS];
     {
         // MFMA columns past the group's heads re-read its last head: their results are never stored
-        const bf16_t *q = q_new + (((int64_t)(lbase + li) * dm.B + b) * dm.Hq + (int64_t)kvh * G + min(n, G - 1)) * D;
+        const T *q = q_new + (((int64_t)(lbase + li) * dm.B + b) * dm.Hq + (int64_t)kvh * G + min(n, G - 1)) * D;
 #pragma unroll
-        for (int s = 0; s < 4; ++s) qb[s] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(q + 32 * s + 8 * c));
+        for (int s = 0; s < NS; ++s) qb[s] = *reinterpret_cast<const uint4 *>(q + Elem<T>::kSlice * s + kVec * c);
     }
-    constexpr float kScale2 = 0.08838834764831845f * 1.4426950408889634f;  // log2(e) / sqrt(128)
+    constexpr float kScale2 = (float)((D == 128 ? 0.08838834764831845 : 0.125) * 1.4426950408889634);  // log2(e) / sqrt(d)
     float m_run = -INFINITY, l_run = 0.f;
     f32x4 acc[NJ];
 #pragma unroll
@@ -268,47 +243,39 @@ __global__ __launch_bounds__(64 * NW) void decode_mfma_kernel(Dims dm, DecodeTab
     // accumulator = v_new for every head.
     const bool owns_new = newrow >= k0 && newrow < k1 && wave == ((kend - k0 + kIter - 1) / kIter) % NW;
     if (owns_new) {
-        if (lane < 16 && vh == 0)  // the new K' row: 16 lanes x 16 bytes
-            *reinterpret_cast<uint4 *>(kc + k_tiled(newrow, 8 * lane)) = krow;
-        const int tok = newrow & 31;
+        if (lane < kPieces && vh == 0)  // the new K' row: 16 bytes a lane
+            *reinterpret_cast<uint4 *>(kc + k_tiled<D, kVec>(newrow, kVec * lane)) = krow;
+        const int tok = newrow & (kVTok - 1);
 #pragma unroll
-        for (int h2 = 0; h2 < 2 / VH; ++h2) {
+        for (int h2 = 0; h2 < kColsPer; ++h2) {
             const int col = lane + 64 * (h2 + vh);
             if (tok == 0) {  // a new block: the column's other slots are written as zeros
-                bf16_t *vcolp = vc + (int64_t)newrow * D + (col >> 4) * 512 + (col & 15) * 8;  // slot group 0; +128 per group
+                constexpr int kGroup = 16 * kVec;  // elements from one slot group to the next
+                T *vcolp = vc + (int64_t)newrow * D + (col >> 4) * (4 * kGroup) + (col & 15) * kVec;  // slot group 0
                 const uint4 z = make_uint4(0, 0, 0, 0);
-                *reinterpret_cast<uint4 *>(vcolp) = make_uint4(vcol[h2], 0, 0, 0);  // token 0 sits in slot 0
-                *reinterpret_cast<uint4 *>(vcolp + 128) = z;
-                *reinterpret_cast<uint4 *>(vcolp + 256) = z;
-                *reinterpret_cast<uint4 *>(vcolp + 384) = z;
+                *reinterpret_cast<uint4 *>(vcolp) = make_uint4(bits_of(vcol[h2]), 0, 0, 0);  // token 0 sits in slot 0
+                *reinterpret_cast<uint4 *>(vcolp + kGroup) = z;
+                *reinterpret_cast<uint4 *>(vcolp + 2 * kGroup) = z;
+                *reinterpret_cast<uint4 *>(vcolp + 3 * kGroup) = z;
             } else {
-                vc[v_tiled(newrow, col)] = vcol[h2];
+                vc[v_tiled<D, kVec>(newrow, col)] = vcol[h2];
             }
         }
         float sn = 0.f;
 #pragma unroll
-        for (int sl = 0; sl < 4; ++sl) {
-            const uint4 kx = knew[sl];
-            const uint4 qx = __builtin_bit_cast(uint4, qb[sl]);
-            const uint32_t kw[4] = {kx.x, kx.y, kx.z, kx.w}, qw[4] = {qx.x, qx.y, qx.z, qx.w};
-#pragma unroll
-            for (int w4 = 0; w4 < 4; ++w4) {
-                sn = fmaf(__uint_as_float(qw[w4] << 16), __uint_as_float(kw[w4] << 16), sn);
-                sn = fmaf(__uint_as_float(qw[w4] & 0xffff0000u), __uint_as_float(kw[w4] & 0xffff0000u), sn);
-            }
-        }
+        for (int sl = 0; sl < NS; ++sl) sn = dot_piece<T>(qb[sl], knew[sl], sn);
         sn += __shfl_xor(sn, 16, 64);
         sn += __shfl_xor(sn, 32, 64);
         m_run = sn * kScale2;
         l_run = c == 0 ? 1.f : 0.f;  // l_run is a per-lane partial of the head's sum: the token counts once
 #pragma unroll
         for (int j = 0; j < NJ; ++j) {
-            const float v = bf16_bits_to_float(vnew[j]);
+            const float v = ldf(&vnew[j]);
             acc[j] = (f32x4){v, v, v, v};
         }
     }
 
-    const int last16 = (kend - 1) & ~15, last32 = (kend - 1) & ~31;  // last tile / block with a cached key
+    const int last_tile = (kend - 1) & ~15, last_block = (kend - 1) & ~(kVTok - 1);  // last tile / block with a cached key
     // The chunks of the range are walked front to back on even steps and back to front on odd ones:
     // what a step read last is what the next step reads first, so the part of the cache that is
     // still in the L2 of the XCD (the unit-to-XCD mapping is the same every launch) gets reused
@@ -320,29 +287,28 @@ __global__ __launch_bounds__(64 * NW) void decode_mfma_kernel(Dims dm, DecodeTab
     auto has = [&](int kb) { return kb >= k0 && kb < kend; };
 
     // all loads of a chunk: the KT score tiles of K' and the V' operands of the TB token blocks
-    auto load_chunk = [&](uint4(&a)[KT][4], uint4(&vb)[TB][NJ], int kb) {
+    auto load_chunk = [&](uint4(&a)[KT][NS], uint4(&vb)[TB][NJ], int kb) {
 #pragma unroll
         for (int tile = 0; tile < KT; ++tile) {
-            const bf16_t *src = kc + (int64_t)min(kb + 16 * tile, last16) * D + 32 * n + 8 * c;
+            const T *src = kc + (int64_t)min(kb + 16 * tile, last_tile) * D + Elem<T>::kSlice * n + kVec * c;
 #pragma unroll
-            for (int sl = 0; sl < 4; ++sl) a[tile][sl] = *reinterpret_cast<const uint4 *>(src + 512 * sl);
+            for (int sl = 0; sl < NS; ++sl) a[tile][sl] = *reinterpret_cast<const uint4 *>(src + 64 * kVec * sl);
         }
 #pragma unroll
         for (int tb = 0; tb < TB; ++tb) {
-            const bf16_t *src = vc + (int64_t)min(kb + 32 * tb, last32) * D + 128 * c + 8 * n;
+            const T *src = vc + (int64_t)min(kb + kVTok * tb, last_block) * D + 16 * kVec * c + kVec * n;
 #pragma unroll
-            for (int j = 0; j < NJ; ++j) vb[tb][j] = *reinterpret_cast<const uint4 *>(src + 512 * (j + NJ * vh));
+            for (int j = 0; j < NJ; ++j) vb[tb][j] = *reinterpret_cast<const uint4 *>(src + 64 * kVec * (j + NJ * vh));
         }
     };
-    auto compute_chunk = [&](const uint4(&a)[KT][4], const uint4(&vb)[TB][NJ], int kb) {
+    auto compute_chunk = [&](const uint4(&a)[KT][NS], const uint4(&vb)[TB][NJ], int kb) {
         // ---- scores^T
         f32x4 s[KT];
 #pragma unroll
         for (int tile = 0; tile < KT; ++tile) {
             s[tile] = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int sl = 0; sl < 4; ++sl)
-                s[tile] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[tile][sl]), qb[sl], s[tile], 0, 0, 0);
+            for (int sl = 0; sl < NS; ++sl) s[tile] = mma<T>(a[tile][sl], qb[sl], s[tile]);
         }
         if (kb + kIter > kend) {  // the chunk with the tail (uniform over the wave)
 #pragma unroll
@@ -393,28 +359,41 @@ __global__ __launch_bounds__(64 * NW) void decode_mfma_kernel(Dims dm, DecodeTab
         // ---- P * V
 #pragma unroll
         for (int tb = 0; tb < TB; ++tb) {
-            bf16x8 pa;
+            if constexpr (sizeof(T) == 4) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                pa[i] = (__bf16)s[2 * tb][i];
-                pa[4 + i] = (__bf16)s[2 * tb + 1][i];
+                for (int j = 0; j < NJ; ++j) acc[j] = mma<T>(__builtin_bit_cast(uint4, s[tb]), vb[tb][j], acc[j]);
+            } else {
+                // bf16 operands.  Heads of 128 elements take the probabilities rounded to bf16; with heads of 64 they keep
+                // their 24 bits, as three bf16 terms (the matrix unit is idle most of the time: two more products a tile)
+                constexpr int kTerms = D == 128 ? 1 : 3;
+                bf16x8 pa[kTerms];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    float p = s[2 * tb + (i >> 2)][i & 3];
+#pragma unroll
+                    for (int k = 0; k < kTerms; ++k) {
+                        pa[k][i] = (__bf16)p;
+                        if (k + 1 < kTerms) p -= (float)pa[k][i];
+                    }
+                }
+#pragma unroll
+                for (int k = kTerms - 1; k >= 0; --k)
+#pragma unroll
+                    for (int j = 0; j < NJ; ++j) acc[j] = mma<T>(__builtin_bit_cast(uint4, pa[k]), vb[tb][j], acc[j]);
             }
-#pragma unroll
-            for (int j = 0; j < NJ; ++j)
-                acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pa, __builtin_bit_cast(bf16x8, vb[tb][j]), acc[j], 0, 0, 0);
         }
     };
     // Two chunk buffers: while one chunk is multiplied the loads of the wave's next chunk are in
     // flight.  Loads are issued only for chunks that exist, and the loop is laid out so that every
     // path reaches a compute step with the same loads behind it (the wait counts stay exact).
-    if constexpr (KT > 2 && VH == 1) {  // two buffers of this size do not fit the registers: load, then multiply
+    if constexpr (KT * NS + TB * NJ > 24) {  // two buffers of this size do not fit the registers: load, then multiply
         for (int kb = kb_first; has(kb); kb += kStep) {
-            uint4 a0[KT][4], v0[TB][NJ];
+            uint4 a0[KT][NS], v0[TB][NJ];
             load_chunk(a0, v0, kb);
             compute_chunk(a0, v0, kb);
         }
     } else if (has(kb_first)) {
-        uint4 a0[KT][4], v0[TB][NJ], a1[KT][4], v1[TB][NJ];
+        uint4 a0[KT][NS], v0[TB][NJ], a1[KT][NS], v1[TB][NJ];
         int kb = kb_first;
         load_chunk(a0, v0, kb);
         if (!has(kb + kStep)) {
@@ -446,6 +425,8 @@ __global__ __launch_bounds__(64 * NW) void decode_mfma_kernel(Dims dm, DecodeTab
     // ---- merge the NW waves of the workgroup through LDS.  Every wave first rescales its partial
     // to the workgroup's maximum, so that the merge is a plain sum: wave w ends up with output
     // tiles w, w+NW, ... (heads 4c..4c+3, column 16j+n), plus the merged (max, sum) of those heads.
+    constexpr int kTiles = NJ >= NW ? NJ / NW : 1;  // output tiles a wave owns after the merge: j = wave + NW*jj (of the workgroup's NJ)
+    const bool owns_tiles = NJ >= NW || wave < NJ;
     __shared__ f32x4 s_acc[NW][NJ][64];
     __shared__ float s_mw[kMaxGroup][NW], s_lw[kMaxGroup][NW];
     __shared__ int s_prev;
@@ -469,8 +450,8 @@ __global__ __launch_bounds__(64 * NW) void decode_mfma_kernel(Dims dm, DecodeTab
         for (int j = 0; j < NJ; ++j) s_acc[wave][j][lane] = acc[j];
         __syncthreads();
 #pragma unroll
-        for (int jj = 0; jj < NJ / NW; ++jj) {
-            const int j = wave + NW * jj;
+        for (int jj = 0; jj < kTiles; ++jj) {
+            const int j = NJ >= NW ? wave + NW * jj : min(wave, NJ - 1);  // waves without a tile (more waves than tiles) repeat the last one
             f32x4 sum = s_acc[0][j][lane];
 #pragma unroll
             for (int w = 1; w < NW; ++w) {
@@ -494,17 +475,14 @@ __global__ __launch_bounds__(64 * NW) void decode_mfma_kernel(Dims dm, DecodeTab
             mrg_l[i] = __shfl(l_run, 4 * c + i, 64);
         }
     }
-    constexpr int kTiles = NJ / NW;  // output tiles this wave owns after the merge: j = wave + NW*jj (of the workgroup's NJ)
-
     if (!SPLIT || splits == 1) {  // no partials: normalise and store
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int g = 4 * c + i;
-            if (g < G) {
-                const float inv = __builtin_amdgcn_rcpf(mrg_l[i]);
+            if (g < G && owns_tiles) {
+                const float inv = sizeof(T) == 4 ? 1.0f / mrg_l[i] : __builtin_amdgcn_rcpf(mrg_l[i]);
 #pragma unroll
-                for (int jj = 0; jj < kTiles; ++jj)
-                    o_unit[g * D + 16 * (NJ * vh + wave + NW * jj) + n] = float_to_bf16_bits(acc[jj][i] * inv);
+                for (int jj = 0; jj < kTiles; ++jj) stf(&o_unit[g * D + 16 * (NJ * vh + wave + NW * jj) + n], acc[jj][i] * inv);
             }
         }
         if (t.dec_steps && threadIdx.x == 0) {
@@ -532,7 +510,7 @@ __global__ __launch_bounds__(64 * NW) void decode_mfma_kernel(Dims dm, DecodeTab
     const int64_t part = xu * t.x_stride + split;
     float *pu = t.dec_o + xu * t.x_stride * (int64_t)kMaxGroup * D;
     const __amdgpu_buffer_rsrc_t prs = __builtin_amdgcn_make_buffer_rsrc(pu, 0, t.x_stride * kMaxGroup * D * 4, 0x00020000);
-    if (4 * c < G) {
+    if (4 * c < G && owns_tiles) {
 #pragma unroll
         for (int jj = 0; jj < kTiles; ++jj)
             __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[jj]), prs,
@@ -591,7 +569,7 @@ __global__ __launch_bounds__(64 * NW) void decode_mfma_kernel(Dims dm, DecodeTab
 #pragma unroll
             for (int jj = 0; jj < kTiles; ++jj) {
                 v[s2][jj] = (f32x4){0.f, 0.f, 0.f, 0.f};
-                if (s0 + s2 < splits && 4 * c < G)
+                if (s0 + s2 < splits && 4 * c < G && owns_tiles)
                     v[s2][jj] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
                         prs, ((s0 + s2) * kMaxGroup * D + ((wave + NW * jj) * 64 + lane) * 4) * 4, 0, kSysScope));
             }
@@ -610,263 +588,117 @@ __global__ __launch_bounds__(64 * NW) void decode_mfma_kernel(Dims dm, DecodeTab
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const int g = 4 * c + i;
-        if (g < G) {
+        if (g < G && owns_tiles) {
             const float inv = s_inv[g];
 #pragma unroll
-            for (int jj = 0; jj < kTiles; ++jj)
-                o_unit[g * D + 16 * (wave + NW * jj) + n] = float_to_bf16_bits(num[jj][i] * inv);
+            for (int jj = 0; jj < kTiles; ++jj) stf(&o_unit[g * D + 16 * (wave + NW * jj) + n], num[jj][i] * inv);
         }
     }
     if (t.dec_steps && threadIdx.x == 0) t.dec_steps[unit] = appended + 1;
 }
 
 // ---------------------------------------------------------------------------------------
-// generic decode attention: one workgroup per (split, unit), thread per key for q.K', thread
-// per output column for P.V', online softmax over blocks of 256 keys.
-// ---------------------------------------------------------------------------------------
-template <typename T, int D>
-__global__ __launch_bounds__(256) void decode_kernel(Dims dm, DevTables t, DecodeExchange x, int l0, int lbase,
-                                                     LaunchLayers ll, const T *q_new, int splits) {
-    constexpr int NP = 256 / D;  // key-parallel parts in the P*V phase
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const int split = blockIdx.x;
-    const int u = blockIdx.y;
-    const int kvh = u % dm.Hkv;
-    const int b = (u / dm.Hkv) % dm.B;
-    const int li = u / (dm.Hkv * dm.B);
-    const int l = l0 + li;
-    const int G = dm.G;
-    const int len = t.base_len[(int64_t)b * dm.L + l] + ll.appended[li] + 1;
-    int k0, k1;
-    split_range(len, splits, split, k0, k1);
-    const int64_t row0 = ((int64_t)b * dm.Hkv + kvh) * dm.pool_rows + t.layer_off[(int64_t)b * dm.L + l];
-    const T *kc = (const T *)t.kcache + row0 * D;
-    const T *vc = (const T *)t.vcache + row0 * D;
-    const int64_t unit = ((int64_t)l * dm.B + b) * dm.Hkv + kvh;
+struct DecodeLaunch {
+    hipStream_t s;
+    const Dims &dm;
+    const DecodeTabs &dt;
+    const DecodeSteps &ds;
+    int l0, nl, lbase, splits, lg_splits;
+    const void *q_new, *k_new, *v_new;
+    void *out;
+};
 
-    __shared__ float s_q[kMaxGroup][D];
-    __shared__ float s_p[kMaxGroup][256];
-    __shared__ float s_m[kMaxGroup], s_l[kMaxGroup], s_corr[kMaxGroup];
-    __shared__ float s_o[NP][kMaxGroup][D];
+template <typename T, int D, int NW, int KT, bool SPLIT, bool INPLACE, bool SORTED, int VH, bool ONE_SEQ>
+static void decode_launch(const DecodeLaunch &a, dim3 grid, int splits, int lg_splits) {
+    hipLaunchKernelGGL((decode_mfma_kernel<T, D, NW, KT, SPLIT, INPLACE, SORTED, VH, ONE_SEQ>), grid, dim3(64 * NW), 0, a.s, a.dm,
+                       a.dt, a.l0, a.lbase, a.ds, (const T *)a.q_new, (const T *)a.k_new, (const T *)a.v_new, (T *)a.out, splits,
+                       lg_splits);
+}
 
-    const T *q = q_new + (((int64_t)(lbase + li) * dm.B + b) * dm.Hq + (int64_t)kvh * G) * D;
-    for (int idx = tid; idx < G * D; idx += 256) s_q[idx / D][idx % D] = ldf(q + idx);
-    if (tid < kMaxGroup) {
-        s_m[tid] = -INFINITY;
-        s_l[tid] = 0.f;
-    }
-    const float scale = 1.0f / sqrtf((float)D);
-    const int dcol = tid % D, part = tid / D;
-    float acc[kMaxGroup];
-#pragma unroll
-    for (int g = 0; g < kMaxGroup; ++g) acc[g] = 0.f;
-    __syncthreads();
-
-    for (int kb = k0; kb < k1; kb += 256) {
-        const int nk = min(256, k1 - kb);
-        {
-            float kreg[D];
-            if (tid < nk) load_row<D>(kc + (int64_t)(kb + tid) * D, kreg);
-            for (int g = 0; g < G; ++g) {
-                float a = 0.f;
-                if (tid < nk) {
-#pragma unroll
-                    for (int cc = 0; cc < D; ++cc) a = fmaf(s_q[g][cc], kreg[cc], a);
-                }
-                s_p[g][tid] = tid < nk ? a * scale : -INFINITY;
-            }
+template <typename T, int D, int NW, int KT>
+static void decode_shape_launch(const DecodeLaunch &a, bool longest_first) {
+    const dim3 grid(a.splits * a.dm.Hkv, a.dm.B, a.nl);
+    if constexpr (sizeof(T) == 2 && D == 128) {  // the only storage that can keep its cache in place
+        if (a.dt.cache_ptrs) {
+            if (a.splits == 1) decode_launch<T, D, NW, KT, false, true, false, 1, false>(a, grid, 1, 0);
+            else decode_launch<T, D, NW, KT, true, true, false, 1, false>(a, grid, a.splits, a.lg_splits);
+            return;
         }
-        __syncthreads();
-        for (int g = wave; g < G; g += 4) {
-            float v0 = s_p[g][lane], v1 = s_p[g][lane + 64], v2 = s_p[g][lane + 128], v3 = s_p[g][lane + 192];
-            const float mb = wave_max(fmaxf(fmaxf(v0, v1), fmaxf(v2, v3)));
-            const float mo = s_m[g];
-            const float mn = fmaxf(mo, mb);
-            v0 = expf(v0 - mn);
-            v1 = expf(v1 - mn);
-            v2 = expf(v2 - mn);
-            v3 = expf(v3 - mn);
-            s_p[g][lane] = v0;
-            s_p[g][lane + 64] = v1;
-            s_p[g][lane + 128] = v2;
-            s_p[g][lane + 192] = v3;
-            const float lb = wave_sum((v0 + v1) + (v2 + v3));
-            if (lane == 0) {
-                const float corr = expf(mo - mn);  // 0 on the first block (mo = -inf)
-                s_corr[g] = corr;
-                s_l[g] = s_l[g] * corr + lb;
-                s_m[g] = mn;
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int g = 0; g < kMaxGroup; ++g)
-            if (g < G) acc[g] *= s_corr[g];
-        for (int tk = part; tk < nk; tk += NP) {
-            const float vv = ldf(vc + (int64_t)(kb + tk) * D + dcol);
-#pragma unroll
-            for (int g = 0; g < kMaxGroup; ++g)
-                if (g < G) acc[g] = fmaf(s_p[g][tk], vv, acc[g]);
-        }
-        __syncthreads();
     }
-#pragma unroll
-    for (int g = 0; g < kMaxGroup; ++g)
-        if (g < G) s_o[part][g][dcol] = acc[g];
-    __syncthreads();
-    const int64_t pidx = (x.local ? (int64_t)u : unit) * x.stride + split;
-    float *po = x.o + pidx * (int64_t)G * D;
-    for (int idx = tid; idx < G * D; idx += 256) {
-        const int g = idx / D, cc = idx % D;
-        float o = 0.f;
-#pragma unroll
-        for (int p = 0; p < NP; ++p) o += s_o[p][g][cc];
-        po[idx] = o;
+    if constexpr (KT == kDecodeTiles<T, D> && (NW == 1 || NW == 4)) {
+        if (longest_first && a.splits == 1) return decode_launch<T, D, NW, KT, false, false, true, 1, false>(a, grid, 1, 0);
     }
-    if (tid < G) x.ml[pidx * G + tid] = make_float2(s_m[tid], s_l[tid]);
+    if (a.splits == 1) decode_launch<T, D, NW, KT, false, false, false, 1, false>(a, grid, 1, 0);
+    else decode_launch<T, D, NW, KT, true, false, false, 1, false>(a, grid, a.splits, a.lg_splits);
 }
 
-template <typename T, int D>
-__global__ __launch_bounds__(256) void combine_kernel(Dims dm, DecodeExchange x, int l0, int lbase, T *out, int splits) {
-    const int u = blockIdx.x;
-    const int kvh = u % dm.Hkv;
-    const int b = (u / dm.Hkv) % dm.B;
-    const int li = u / (dm.Hkv * dm.B);
-    const int l = l0 + li;
-    const int G = dm.G;
-    const int64_t unit = ((int64_t)l * dm.B + b) * dm.Hkv + kvh;
-    const int64_t xu = x.local ? (int64_t)u : unit;
-    const float2 *ml = x.ml + xu * x.stride * G;
-    const float *po = x.o + xu * x.stride * (int64_t)G * D;
-    T *o = out + (((int64_t)(lbase + li) * dm.B + b) * dm.Hq + (int64_t)kvh * G) * D;
-    for (int idx = threadIdx.x; idx < G * D; idx += 256) {
-        const int g = idx / D;
-        float M = -INFINITY;
-        for (int s = 0; s < splits; ++s) M = fmaxf(M, ml[s * G + g].x);
-        float num = 0.f, den = 0.f;
-        for (int s = 0; s < splits; ++s) {
-            const float2 x = ml[s * G + g];
-            const float wgt = x.y > 0.f ? expf(x.x - M) : 0.f;
-            num = fmaf(wgt, po[(int64_t)s * G * D + idx], num);
-            den = fmaf(wgt, x.y, den);
+// Heads of 128 elements: two workgroups per unit, each with one half of the columns of V' (the caller has checked what
+// this variant asks for)
+template <typename T, int KT>
+static void decode_halves_launch(const DecodeLaunch &a) {
+    const int units = a.nl * a.dm.B * a.dm.Hkv;
+    int lg_h = 0;
+    while ((1 << lg_h) < a.dm.Hkv) ++lg_h;
+    const dim3 grid(2 * ((units + 7) & ~7));
+    if constexpr (sizeof(T) == 2) {
+        if (a.dt.cache_ptrs) {
+            if (a.dm.B == 1) decode_launch<T, 128, 4, KT, false, true, false, 2, true>(a, grid, units, lg_h);
+            else decode_launch<T, 128, 4, KT, false, true, false, 2, false>(a, grid, units, lg_h);
+            return;
         }
-        stf(o + idx, num / den);
     }
+    if (a.dm.B == 1) decode_launch<T, 128, 4, KT, false, false, false, 2, true>(a, grid, units, lg_h);
+    else decode_launch<T, 128, 4, KT, false, false, false, 2, false>(a, grid, units, lg_h);
 }
 
-template <typename T, int D>
-static hipError_t append_launch(hipStream_t s, const Dims &dm, const DevTables &t, int l0, int nl, int lbase,
-                                const LaunchLayers &ll, const void *k_new, const void *v_new) {
-    hipLaunchKernelGGL((append_kernel<T, D>), dim3(nl * dm.B * dm.Hkv), dim3(128), 0, s, dm, t, l0, lbase, ll,
-                       (const T *)k_new, (const T *)v_new);
-    return hipGetLastError();
+template <typename T, int D, int KT>
+static void decode_waves_launch(const DecodeLaunch &a, int waves, bool longest_first) {
+    if (waves == 8 && KT < 8) decode_shape_launch<T, D, 8, KT < 8 ? KT : 4>(a, longest_first);
+    else if (waves >= 4) decode_shape_launch<T, D, 4, KT>(a, longest_first);
+    else if (waves == 2) decode_shape_launch<T, D, 2, KT>(a, longest_first);
+    else decode_shape_launch<T, D, 1, KT>(a, longest_first);
 }
 
-static hipError_t launch_append(hipStream_t s, const Dims &dm, const DevTables &t, int dtype, int l0, int nl, int lbase,
-                         const LaunchLayers &ll, const void *k_new, const void *v_new) {
-    if (dtype == AIR_BF16) return append_launch<bf16_t, 64>(s, dm, t, l0, nl, lbase, ll, k_new, v_new);  // head_dim 128 takes the MFMA kernel
-    return dm.D == 128 ? append_launch<float, 128>(s, dm, t, l0, nl, lbase, ll, k_new, v_new)
-                       : append_launch<float, 64>(s, dm, t, l0, nl, lbase, ll, k_new, v_new);
-}
-
-template <typename T, int D>
-static hipError_t decode_launch(hipStream_t s, const Dims &dm, const DevTables &t, const DecodeExchange &x, int l0, int nl,
-                                int lbase, const LaunchLayers &ll, const void *q_new, void *out, int splits) {
-    const int units = nl * dm.B * dm.Hkv;
-    hipLaunchKernelGGL((decode_kernel<T, D>), dim3(splits, units), dim3(256), 0, s, dm, t, x, l0, lbase, ll,
-                       (const T *)q_new, splits);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((combine_kernel<T, D>), dim3(units), dim3(256), 0, s, dm, x, l0, lbase, (T *)out, splits);
-    return hipGetLastError();
-}
-
-// Generic path: append, split-K attention, combine (three launches).
 hipError_t launch_decode(hipStream_t s, const Dims &dm, const DevTables &t, const DecodeExchange &x, int dtype, int l0,
                          int nl, int lbase, const LaunchLayers &ll, const void *q_new, const void *k_new,
                          const void *v_new, void *out, int splits, int waves, int tiles, int uniform_appended,
                          bool longest_first, bool column_halves) {
-    if (v_transposed(dtype, dm.D)) {  // one launch: append, attention and merge of the partials
-        if (splits < 1 || (splits & (splits - 1)) != 0) return hipErrorInvalidValue;  // the kernel shifts by log2(splits)
-        int lg_splits = 0;
-        while ((1 << lg_splits) < splits) ++lg_splits;
-        const dim3 grid(splits * dm.Hkv, dm.B, nl);
-        DecodeTabs dt;
-        dt.len_off = t.len_off;
-        dt.by_length = t.by_length;
-        dt.kcache = t.kcache;
-        dt.vcache = t.vcache;
-        dt.dec_o = x.o;
-        dt.dec_ml = x.ml;
-        dt.dec_cnt = x.cnt;
-        dt.x_local = x.local;
-        dt.x_stride = x.stride;
-        dt.dec_steps = t.dec_steps;
-        dt.cache_ptrs = t.cache_ptrs;
-        dt.kv_b = t.ip_kv_b;
-        dt.kv_h = t.ip_kv_h;
-        dt.n_units = dm.L * dm.B * dm.Hkv;
-        DecodeSteps ds;
-        ds.uniform = uniform_appended;
-        for (int i = 0; i < kMaxLayersPerLaunch; ++i) ds.appended[i] = ll.appended[i];
-#define AIR_LAUNCH_DECODE_(NW, KT, SP, IP)                                                                          \
-    hipLaunchKernelGGL((decode_mfma_kernel<NW, KT, SP, IP>), grid, dim3(64 * NW), 0, s, dm, dt, l0, lbase, ds,      \
-                       (const bf16_t *)q_new, (const bf16_t *)k_new, (const bf16_t *)v_new, (bf16_t *)out, splits,  \
-                       lg_splits)
-#define AIR_LAUNCH_DECODE(NW, KT)                                                       \
-    do {                                                                                \
-        if (splits == 1 && !t.cache_ptrs) AIR_LAUNCH_DECODE_(NW, KT, false, false);     \
-        else if (splits == 1) AIR_LAUNCH_DECODE_(NW, KT, false, true);                  \
-        else if (!t.cache_ptrs) AIR_LAUNCH_DECODE_(NW, KT, true, false);                \
-        else AIR_LAUNCH_DECODE_(NW, KT, true, true);                                    \
-    } while (0)
-        if (column_halves) {  // the caller has checked what this variant asks for
-            const int units = nl * dm.B * dm.Hkv;
-            int lg_h = 0;
-            while ((1 << lg_h) < dm.Hkv) ++lg_h;
-            const dim3 grid2(2 * ((units + 7) & ~7));
-#define AIR_LAUNCH_HALVES_(IP, ONE)                                                                                        \
-    hipLaunchKernelGGL((decode_mfma_kernel<4, 4, false, IP, false, 2, ONE>), grid2, dim3(256), 0, s, dm, dt, l0, lbase, ds, \
-                       (const bf16_t *)q_new, (const bf16_t *)k_new, (const bf16_t *)v_new, (bf16_t *)out, units, lg_h)
-            if (t.cache_ptrs) {
-                if (dm.B == 1) AIR_LAUNCH_HALVES_(true, true);
-                else AIR_LAUNCH_HALVES_(true, false);
-            } else {
-                if (dm.B == 1) AIR_LAUNCH_HALVES_(false, true);
-                else AIR_LAUNCH_HALVES_(false, false);
-            }
-#undef AIR_LAUNCH_HALVES_
-            return hipGetLastError();
-        }
-        if (longest_first && splits == 1 && !t.cache_ptrs && tiles == 4 && (waves == 1 || waves == 4)) {
-            if (waves == 4)
-                hipLaunchKernelGGL((decode_mfma_kernel<4, 4, false, false, true>), grid, dim3(256), 0, s, dm, dt, l0, lbase, ds,
-                                   (const bf16_t *)q_new, (const bf16_t *)k_new, (const bf16_t *)v_new, (bf16_t *)out, splits, lg_splits);
-            else
-                hipLaunchKernelGGL((decode_mfma_kernel<1, 4, false, false, true>), grid, dim3(64), 0, s, dm, dt, l0, lbase, ds,
-                                   (const bf16_t *)q_new, (const bf16_t *)k_new, (const bf16_t *)v_new, (bf16_t *)out, splits, lg_splits);
-            return hipGetLastError();
-        }
-        if (waves == 8 && tiles == 4) AIR_LAUNCH_DECODE(8, 4);
-        else if (waves == 4 && tiles == 4) AIR_LAUNCH_DECODE(4, 4);
-        else if (waves == 2 && tiles == 4) AIR_LAUNCH_DECODE(2, 4);
-        else if (waves == 1 && tiles == 4) AIR_LAUNCH_DECODE(1, 4);
-        else if (waves == 8 && tiles == 2) AIR_LAUNCH_DECODE(8, 2);
-        else if (waves == 4 && tiles == 2) AIR_LAUNCH_DECODE(4, 2);
-        else if (waves == 2 && tiles == 2) AIR_LAUNCH_DECODE(2, 2);
-        else if (waves == 1 && tiles == 2) AIR_LAUNCH_DECODE(1, 2);
-        else if (waves == 4) AIR_LAUNCH_DECODE(4, 8);
-        else if (waves == 2) AIR_LAUNCH_DECODE(2, 8);
-        else AIR_LAUNCH_DECODE(1, 8);
-#undef AIR_LAUNCH_DECODE
-#undef AIR_LAUNCH_DECODE_
-        return hipGetLastError();
+    if (splits < 1 || (splits & (splits - 1)) != 0) return hipErrorInvalidValue;  // the kernel shifts by log2(splits)
+    int lg_splits = 0;
+    while ((1 << lg_splits) < splits) ++lg_splits;
+    DecodeTabs dt;
+    dt.len_off = t.len_off;
+    dt.by_length = t.by_length;
+    dt.kcache = t.kcache;
+    dt.vcache = t.vcache;
+    dt.dec_o = x.o;
+    dt.dec_ml = x.ml;
+    dt.dec_cnt = x.cnt;
+    dt.x_local = x.local;
+    dt.x_stride = x.stride;
+    dt.dec_steps = t.dec_steps;
+    dt.cache_ptrs = t.cache_ptrs;
+    dt.kv_b = t.ip_kv_b;
+    dt.kv_h = t.ip_kv_h;
+    dt.n_units = dm.L * dm.B * dm.Hkv;
+    DecodeSteps ds;
+    ds.uniform = uniform_appended;
+    for (int i = 0; i < kMaxLayersPerLaunch; ++i) ds.appended[i] = ll.appended[i];
+    const DecodeLaunch a = {s, dm, dt, ds, l0, nl, lbase, splits, lg_splits, q_new, k_new, v_new, out};
+    if (dtype == AIR_BF16 && dm.D == 128) {
+        if (column_halves) decode_halves_launch<bf16_t, 4>(a);
+        else if (tiles == 4) decode_waves_launch<bf16_t, 128, 4>(a, waves, longest_first);
+        else if (tiles == 2) decode_waves_launch<bf16_t, 128, 2>(a, waves, longest_first);
+        else decode_waves_launch<bf16_t, 128, 8>(a, waves, longest_first);
+    } else if (dtype == AIR_BF16) {  // the other storages have one chunk size each: about 16 KB of K' and V' a wave
+        decode_waves_launch<bf16_t, 64, kDecodeTiles<bf16_t, 64>>(a, waves, longest_first);
+    } else if (dm.D == 128) {
+        if (column_halves) decode_halves_launch<float, 2>(a);
+        else decode_waves_launch<float, 128, kDecodeTiles<float, 128>>(a, waves, longest_first);
+    } else {
+        decode_waves_launch<float, 64, kDecodeTiles<float, 64>>(a, waves, longest_first);
     }
-    hipError_t e = launch_append(s, dm, t, dtype, l0, nl, lbase, ll, k_new, v_new);
-    if (e != hipSuccess) return e;
-    if (dtype == AIR_BF16) return decode_launch<bf16_t, 64>(s, dm, t, x, l0, nl, lbase, ll, q_new, out, splits);
-    return dm.D == 128 ? decode_launch<float, 128>(s, dm, t, x, l0, nl, lbase, ll, q_new, out, splits)
-                       : decode_launch<float, 64>(s, dm, t, x, l0, nl, lbase, ll, q_new, out, splits);
+    return hipGetLastError();
 }
 
 }  // namespace air

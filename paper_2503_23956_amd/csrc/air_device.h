@@ -27,6 +27,8 @@ __device__ __forceinline__ float ldf(const float *p) { return *p; }
 __device__ __forceinline__ float ldf(const bf16_t *p) { return bf16_bits_to_float(*p); }
 __device__ __forceinline__ void stf(float *p, float v) { *p = v; }
 __device__ __forceinline__ void stf(bf16_t *p, float v) { *p = float_to_bf16_bits(v); }
+__device__ __forceinline__ uint32_t bits_of(float v) { return __float_as_uint(v); }
+__device__ __forceinline__ uint32_t bits_of(bf16_t v) { return v; }
 
 // Load one row of D elements (16-byte aligned) into fp32 registers.
 template <int D>

@@ -13,7 +13,6 @@ constexpr int kChunkKeys = 256;       // visual keys per workgroup in the score 
 constexpr int kMaxLayersPerLaunch = 32;
 constexpr int kMaxSplits = 16;        // largest split-K factor of the decode attention
 constexpr int kCacheRowAlign = 32;    // layer regions of the compacted cache start on multiples of this
-constexpr int kGatherRows = 32;       // rows copied per workgroup in the compaction gather
 constexpr int kFinishChunks = 4;      // chunks finished (and summed into one moment entry) per workgroup of air_score's last kernel
 constexpr int kStashRows = 32;        // window rows per unit up to which air_score stashes exponentials (one pass over K_v)
 
@@ -126,28 +125,35 @@ hipError_t launch_decode(hipStream_t s, const Dims &dm, const DevTables &t, cons
 hipError_t static_exchange(DecodeExchange *x);
 hipError_t launch_zero_counters(hipStream_t s, int32_t *p, int n);
 
-// The bf16 / head_dim 128 cache is laid out so that the decode kernel can feed it to MFMA straight
-// from global memory, every load instruction of a wave reading 1 KB of consecutive memory, and so
-// that one token touches few cache lines (appending a token costs by the line it writes).
+// The cache is laid out so that the decode kernel can feed it to MFMA straight from global memory, every load
+// instruction of a wave reading 1 KB of consecutive memory, and so that one token touches few cache lines (appending a
+// token costs by the line it writes).  vec = elements in 16 bytes (8 bf16, 4 fp32).
 //
-// K' in tiles of 16 tokens, [4 slices][16 tokens][32 elements]: lane (token n, part c) of a wave finds
+// K' in tiles of 16 tokens, [d / (4 vec) slices][16 tokens][4 vec elements]: lane (token n, part c) of a wave finds
 // the 16 bytes it feeds to MFMA for slice sl at byte 1024 sl + 64 n + 16 c of the tile.  A token's
-// row is four runs of 64 bytes.
+// row is runs of 64 bytes.
 //
-// V' transposed in blocks of 32 tokens, [8 column tiles][4 slot groups][16 columns][8 slots]: token t
-// of the block sits in slot v_slot(t).  With this order the 8 probabilities a lane holds after the
-// two 16-key score tiles of a block are exactly the 8 contraction slots it must supply, and lane
-// (column n of tile j, group c) finds its 16 bytes at byte 1024 j + 256 c + 16 n of the block.
-// A token touches 2 bytes in every 16 of one 256-byte run per column tile.
+// V' transposed in blocks of 4 vec tokens, [d / 16 column tiles][4 slot groups][16 columns][vec slots]: token t
+// of the block sits in slot v_slot(t).  With this order the vec probabilities a lane holds after the
+// 16-key score tiles of a block (two of them with bf16, one with fp32) are exactly the vec contraction slots it must
+// supply, and lane (column n of tile j, group c) finds its 16 bytes at byte 1024 j + 256 c + 16 n of the block.
+// A token touches one element in every 16 bytes of one 256-byte run per column tile.
 inline bool v_transposed(int dtype, int head_dim) { return dtype == AIR_BF16 && head_dim == 128; }
-__host__ __device__ inline int v_slot(int t) { return ((t & 15) >> 2) * 8 + (t >> 4) * 4 + (t & 3); }
-// element offsets from the unit's base of element e of K' row r / column col of V' row r
-__host__ __device__ inline int64_t k_tiled(int64_t r, int e) {
-    return (r >> 4) * 2048 + (e >> 5) * 512 + (r & 15) * 32 + (e & 31);
+template <int VEC>
+__host__ __device__ inline int v_slot(int t) {
+    return VEC == 4 ? t : ((t & 15) >> 2) * 8 + (t >> 4) * 4 + (t & 3);
 }
+// element offsets from the unit's base of element e of K' row r / column col of V' row r
+template <int D, int VEC>
+__host__ __device__ inline int64_t k_tiled(int64_t r, int e) {
+    constexpr int kLgSlice = VEC == 4 ? 4 : 5;
+    return (r >> 4) * (16 * D) + (e >> kLgSlice) * (64 * VEC) + (r & 15) * (4 * VEC) + (e & (4 * VEC - 1));
+}
+template <int D, int VEC>
 __host__ __device__ inline int64_t v_tiled(int64_t r, int col) {
-    const int slot = v_slot((int)(r & 31));
-    return (r >> 5) * 4096 + (col >> 4) * 512 + (slot >> 3) * 128 + (col & 15) * 8 + (slot & 7);
+    constexpr int kTok = 4 * VEC, kLgTok = VEC == 4 ? 4 : 5, kLgVec = kLgTok - 2;
+    const int slot = v_slot<VEC>((int)(r & (kTok - 1)));
+    return (r >> kLgTok) * (kTok * D) + (col >> 4) * (16 * kTok) + (slot >> kLgVec) * (16 * VEC) + (col & 15) * VEC + (slot & (VEC - 1));
 }
 
 }  // namespace air

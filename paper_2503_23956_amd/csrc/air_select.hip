@@ -4,7 +4,7 @@
 //                  select on the fp32 bit patterns (importance is non-negative, so unsigned
 //                  integer order is value order), then an ordered compaction that keeps
 //                  everything above the k-th value and the lowest-index ties at it.
-//   gather_kernel  K' = [K_sys ; K_v[idx] ; K_t], V' likewise, as 16-byte vector copies.
+//   gather_vt_kernel  K' = [K_sys ; K_v[idx] ; K_t], V' likewise, in the order the decode kernel reads.
 #include "air_device.h"
 #include "air_internal.h"
 
@@ -195,49 +195,16 @@ __global__ __launch_bounds__(NT) void select_kernel(Dims dm, DevTables t, int l0
     }
 }
 
-// One workgroup copies kGatherRows rows of K and of V; workgroups stride over the rows of a unit.
-template <typename T, int D>
-__global__ __launch_bounds__(256) void gather_kernel(Dims dm, DevTables t, int l0, LaunchLayers ll, air_strides st) {
-    const int u = blockIdx.y;
-    const int kvh = u % dm.Hkv;
-    const int b = (u / dm.Hkv) % dm.B;
-    const int li = u / (dm.Hkv * dm.B);
-    const int l = l0 + li;
-    const air_seq sq = t.seq_tab[b];
-    const int kl = t.budgets[(int64_t)b * dm.L + l];
-    const int n_rows = sq.seq_len - sq.vis_len + kl;
-    const int64_t unit = ((int64_t)l * dm.B + b) * dm.Hkv + kvh;
-    const int32_t *idx = t.indices + unit * dm.max_vis;
-    const T *ksrc = (const T *)ll.p[li].k + (int64_t)b * st.kv_b + (int64_t)kvh * st.kv_h;
-    const T *vsrc = (const T *)ll.p[li].v + (int64_t)b * st.kv_b + (int64_t)kvh * st.kv_h;
-    const int64_t dst_row0 = ((int64_t)b * dm.Hkv + kvh) * dm.pool_rows + t.layer_off[(int64_t)b * dm.L + l];
-    T *kdst = (T *)t.kcache + dst_row0 * D;
-    T *vdst = (T *)t.vcache + dst_row0 * D;
-    constexpr int kVecPerRow = D * (int)sizeof(T) / 16;
-    constexpr int kElemPerVec = 16 / (int)sizeof(T);
-    for (int r0 = blockIdx.x * kGatherRows; r0 < n_rows; r0 += gridDim.x * kGatherRows) {
-        for (int v = threadIdx.x; v < kGatherRows * kVecPerRow; v += 256) {
-            const int j = r0 + v / kVecPerRow, c = (v % kVecPerRow) * kElemPerVec;
-            if (j >= n_rows) break;
-            int tok;
-            if (j < sq.vis_start) tok = j;
-            else if (j < sq.vis_start + kl) tok = sq.vis_start + idx[j - sq.vis_start];
-            else tok = sq.vis_start + sq.vis_len + (j - sq.vis_start - kl);
-            const uint4 kx = *reinterpret_cast<const uint4 *>(ksrc + (int64_t)tok * st.kv_t + c);
-            const uint4 vx = *reinterpret_cast<const uint4 *>(vsrc + (int64_t)tok * st.kv_t + c);
-            *reinterpret_cast<uint4 *>(kdst + (int64_t)j * D + c) = kx;
-            *reinterpret_cast<uint4 *>(vdst + (int64_t)j * D + c) = vx;
-        }
-    }
-}
-
-// bf16 / head_dim 128: the cache is written in the layouts the decode kernel feeds to MFMA.  One
-// workgroup stages the 32 gathered K and V rows of a block in LDS and writes K' as two 16-token
-// tiles (see k_tiled) and V' block-transposed (see v_tiled).
+// The cache is written in the layouts the decode kernel feeds to MFMA.  One
+// workgroup stages 32 gathered K and V rows in LDS and writes K' as two 16-token
+// tiles (see k_tiled) and V' block-transposed (see v_tiled; one block of 32 tokens with bf16, two of 16 with fp32).
 // Slots of the last block that have no token yet are written as zeros.
+template <typename T, int D>
 __global__ __launch_bounds__(256) void gather_vt_kernel(Dims dm, DevTables t, int l0, LaunchLayers ll, air_strides st) {
-    constexpr int D = 128;
-    typedef bf16_t T;
+    constexpr int kVec = 16 / (int)sizeof(T);  // elements in 16 bytes
+    constexpr int kPieces = D / kVec;          // 16-byte pieces of a row
+    constexpr int kIt = 32 * kPieces / 256;    // pieces of K and of V per thread and 32 rows
+    constexpr int kVTok = 4 * kVec;            // tokens of a V' block
     const int kvh = blockIdx.y;  // grid (workgroup of the unit, KV head, sequence + B * layer)
     int b, li;
     seq_layer_of(dm, (int)blockIdx.z, b, li);
@@ -256,17 +223,17 @@ __global__ __launch_bounds__(256) void gather_vt_kernel(Dims dm, DevTables t, in
         t.dec_steps[unit] = 0;
         if (blockIdx.y == 0 && blockIdx.z == 0) t.dec_steps[(int64_t)dm.L * dm.B * dm.Hkv] = 0;
     }
-    __shared__ bf16_t tile[32][D + 8];   // V rows, indexed [slot][column]; +8 keeps the 16-byte row alignment and spreads banks
-    __shared__ bf16_t ktile[32][D + 8];  // K rows, indexed [row][column]
-    // Two 16-byte pieces of K and of V per thread and block of 32 rows.  The rows of the workgroup's next block are
+    __shared__ __align__(16) T tile[32][D + kVec];   // V rows, indexed [block, slot][column]; the pad keeps the 16-byte row alignment and spreads banks
+    __shared__ __align__(16) T ktile[32][D + kVec];  // K rows, indexed [row][column]
+    // The rows of the workgroup's next block are
     // requested before the current block is written out, so that its index and row reads (two dependent
     // round trips) run under the stores.
-    uint4 kx[2], vx[2];
+    uint4 kx[kIt], vx[kIt];
     auto fetch = [&](int r0) __attribute__((always_inline)) {
 #pragma unroll
-        for (int it = 0; it < 2; ++it) {
+        for (int it = 0; it < kIt; ++it) {
             const int v = threadIdx.x + 256 * it;
-            const int row = v >> 4, c = (v & 15) * 8;
+            const int row = v / kPieces, c = (v % kPieces) * kVec;
             const int j = r0 + row;
             kx[it] = make_uint4(0, 0, 0, 0);
             vx[it] = kx[it];
@@ -284,28 +251,37 @@ __global__ __launch_bounds__(256) void gather_vt_kernel(Dims dm, DevTables t, in
     if ((int)blockIdx.x * 32 < n_rows) fetch(blockIdx.x * 32);
     for (int r0 = blockIdx.x * 32; r0 < n_rows; r0 += stride) {
 #pragma unroll
-        for (int it = 0; it < 2; ++it) {
+        for (int it = 0; it < kIt; ++it) {
             const int v = threadIdx.x + 256 * it;
-            const int row = v >> 4, c = (v & 15) * 8;
+            const int row = v / kPieces, c = (v % kPieces) * kVec;
             *reinterpret_cast<uint4 *>(&ktile[row][c]) = kx[it];
-            *reinterpret_cast<uint4 *>(&tile[v_slot(row)][c]) = vx[it];
+            *reinterpret_cast<uint4 *>(&tile[(row & ~(kVTok - 1)) + v_slot<kVec>(row & (kVTok - 1))][c]) = vx[it];
         }
         if (r0 + stride < n_rows) fetch(r0 + stride);
         lds_barrier();  // LDS traffic only: the requested rows of the next block stay in flight
-        // K': the two 16-token tiles of the block in k_tiled order, 16 bytes per thread, consecutive in memory
-        for (int v = threadIdx.x; v < 32 * 16; v += 256) {
-            const int tl = v >> 8, sl = (v >> 6) & 3, n = (v >> 2) & 15, c = v & 3;
-            *reinterpret_cast<uint4 *>(kdst + (int64_t)r0 * D + (int64_t)v * 8) =
-                *reinterpret_cast<const uint4 *>(&ktile[16 * tl + n][32 * sl + 8 * c]);
-        }
-        // V': the block in v_tiled order, 8 slots of one column per thread, consecutive in memory
-        for (int v = threadIdx.x; v < D * 4; v += 256) {
-            const int j = v >> 6, c = (v >> 4) & 3, col = 16 * j + (v & 15);
-            uint32_t w[4];
+        // K': the two 16-token tiles in k_tiled order, 16 bytes per thread, consecutive in memory
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-                w[i] = (uint32_t)tile[8 * c + 2 * i][col] | ((uint32_t)tile[8 * c + 2 * i + 1][col] << 16);
-            *reinterpret_cast<uint4 *>(vdst + (int64_t)r0 * D + (int64_t)v * 8) = make_uint4(w[0], w[1], w[2], w[3]);
+        for (int it = 0; it < kIt; ++it) {
+            const int v = threadIdx.x + 256 * it;
+            const int tl = v / (16 * kPieces), sl = (v % (16 * kPieces)) >> 6, n = (v >> 2) & 15, c = v & 3;
+            *reinterpret_cast<uint4 *>(kdst + (int64_t)r0 * D + (int64_t)v * kVec) =
+                *reinterpret_cast<const uint4 *>(&ktile[16 * tl + n][4 * kVec * sl + kVec * c]);
+        }
+        // V': in v_tiled order, the slots of one column and slot group per thread, consecutive in memory
+#pragma unroll
+        for (int it = 0; it < kIt; ++it) {
+            const int v = threadIdx.x + 256 * it;
+            const int vb = v / (kVTok * kPieces), w = v % (kVTok * kPieces);
+            const int j = w >> 6, c = (w >> 4) & 3, col = 16 * j + (w & 15), row = kVTok * vb + kVec * c;
+            uint4 x;
+            if constexpr (sizeof(T) == 4)
+                x = make_uint4(bits_of(tile[row][col]), bits_of(tile[row + 1][col]), bits_of(tile[row + 2][col]), bits_of(tile[row + 3][col]));
+            else
+                x = make_uint4(bits_of(tile[row][col]) | (bits_of(tile[row + 1][col]) << 16),
+                               bits_of(tile[row + 2][col]) | (bits_of(tile[row + 3][col]) << 16),
+                               bits_of(tile[row + 4][col]) | (bits_of(tile[row + 5][col]) << 16),
+                               bits_of(tile[row + 6][col]) | (bits_of(tile[row + 7][col]) << 16));
+            *reinterpret_cast<uint4 *>(vdst + (int64_t)r0 * D + (int64_t)v * kVec) = x;
         }
         lds_barrier();  // LDS traffic only: the requested rows of the next block stay in flight
     }
@@ -372,7 +348,7 @@ __global__ __launch_bounds__(256) void gather_in_place_kernel(Dims dm, DevTables
             const int v = threadIdx.x + 256 * it;
             const int row = v >> 4, c = (v & 15) * 8;
             *reinterpret_cast<uint4 *>(&ktile[row][c]) = kx[it];
-            *reinterpret_cast<uint4 *>(&tile[v_slot(row)][c]) = vx[it];
+            *reinterpret_cast<uint4 *>(&tile[v_slot<8>(row)][c]) = vx[it];
         }
         if (r0 + 32 < n_rows) fetch(r0 + 32);  // rows >= r0 + 32: untouched by the stores below
         __syncthreads();  // every thread's rows of this block are in LDS (and therefore read) before the block is overwritten
@@ -428,29 +404,25 @@ hipError_t launch_select(hipStream_t s, const Dims &dm, const DevTables &t, int 
 }
 
 template <typename T, int D>
-static hipError_t gather_launch(hipStream_t s, const Dims &dm, const DevTables &t, int l0, int nl,
-                                const LaunchLayers &ll, const air_strides &st) {
-    hipLaunchKernelGGL((gather_kernel<T, D>), dim3(32, nl * dm.B * dm.Hkv), dim3(256), 0, s, dm, t, l0, ll, st);
+static hipError_t gather_launch(hipStream_t s, const Dims &dm, const DevTables &t, int l0, int nl, const LaunchLayers &ll,
+                                const air_strides &st, int gx) {
+    hipLaunchKernelGGL((gather_vt_kernel<T, D>), dim3(gx, dm.Hkv, nl * dm.B), dim3(256), 0, s, dm, t, l0, ll, st);
     return hipGetLastError();
 }
 
 hipError_t launch_gather(hipStream_t s, const Dims &dm, const DevTables &t, int dtype, int l0, int nl,
                          const LaunchLayers &ll, const air_strides &st, int wgs_per_unit) {
-    if (v_transposed(dtype, dm.D)) {
-        // workgroups per unit: about 4096 in the launch, so that with many units each workgroup walks several
-        // blocks of 32 rows (the next block's reads run under the current block's stores); wgs_per_unit > 0 overrides
-        const int units = nl * dm.B * dm.Hkv;
-        int gx = (4096 + units - 1) / units;
-        gx = gx < 2 ? 2 : (gx > 32 ? 32 : gx);
-        if (wgs_per_unit >= 1 && wgs_per_unit <= 64) gx = wgs_per_unit;
-        hipLaunchKernelGGL(gather_vt_kernel, dim3(gx, dm.Hkv, nl * dm.B), dim3(256), 0, s, dm, t, l0, ll, st);
-        return hipGetLastError();
-    }
+    // workgroups per unit: about 4096 in the launch, so that with many units each workgroup walks several
+    // blocks of 32 rows (the next block's reads run under the current block's stores); wgs_per_unit > 0 overrides
+    const int units = nl * dm.B * dm.Hkv;
+    int gx = (4096 + units - 1) / units;
+    gx = gx < 2 ? 2 : (gx > 32 ? 32 : gx);
+    if (wgs_per_unit >= 1 && wgs_per_unit <= 64) gx = wgs_per_unit;
     if (dtype == AIR_BF16)
-        return dm.D == 128 ? gather_launch<bf16_t, 128>(s, dm, t, l0, nl, ll, st)
-                           : gather_launch<bf16_t, 64>(s, dm, t, l0, nl, ll, st);
-    return dm.D == 128 ? gather_launch<float, 128>(s, dm, t, l0, nl, ll, st)
-                       : gather_launch<float, 64>(s, dm, t, l0, nl, ll, st);
+        return dm.D == 128 ? gather_launch<bf16_t, 128>(s, dm, t, l0, nl, ll, st, gx)
+                           : gather_launch<bf16_t, 64>(s, dm, t, l0, nl, ll, st, gx);
+    return dm.D == 128 ? gather_launch<float, 128>(s, dm, t, l0, nl, ll, st, gx)
+                       : gather_launch<float, 64>(s, dm, t, l0, nl, ll, st, gx);
 }
 
 }  // namespace air

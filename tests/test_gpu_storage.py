@@ -1,0 +1,44 @@
+"""The storages beside bf16 with heads of 128 elements (bf16 with heads of 64, fp32 with either): every compiled launch
+shape of their decode kernel, caches whose ends fall on every side of a tile, a block and a split, against the oracle."""
+import pytest
+
+import synth
+from tests.test_gpu_parity import _run_case
+
+pytestmark = pytest.mark.gpu
+
+STORAGES = [("bf16", 64), ("f32", 64), ("f32", 128)]
+
+
+def _workload(dtype, d, **kw):
+    return synth.get_workload(2).scaled(dtype=dtype, head_dim=d, **kw)
+
+
+@pytest.mark.parametrize("dtype,d", STORAGES)
+@pytest.mark.parametrize("splits,waves,halves", [(1, 1, 1), (1, 2, 1), (1, 4, 1), (1, 8, 1), (4, 4, 1), (16, 8, 1), (2, 1, 1), (1, 4, 2)])
+def test_decode_launch_shapes(dtype, d, splits, waves, halves):
+    # 225 + 51 rows: appends cross blocks of 16 and of 32 tokens, splits of which some hold a single block or none
+    w = _workload(dtype, d, n_layers=2, n_vis=900, n_text=37, decode_steps=36)
+    _run_case(w, 0.25, steps=36, oracle_steps=[0, 1, 12, 13, 28, 29, 35],
+              tuning=dict(decode_splits=splits, decode_waves=waves, decode_halves=halves))
+
+
+@pytest.mark.parametrize("dtype,d", STORAGES)
+@pytest.mark.parametrize("waves", [1, 4])
+def test_decode_longest_cache_first_in_a_ragged_batch(dtype, d, waves):
+    w = synth.get_workload(3).scaled(dtype=dtype, head_dim=d, batch=3, n_layers=5, n_vis=700, n_text=40, decode_steps=18)
+    _run_case(w, 0.25, steps=18, oracle_steps=[0, 16, 17], token_major=True,
+              tuning=dict(decode_order=2, decode_splits=1, decode_waves=waves))
+
+
+@pytest.mark.parametrize("dtype,d", STORAGES)
+@pytest.mark.parametrize("n_vis,n_text,n_sys,steps", [(1, 1, 0, 40), (2, 1, 1, 2), (15, 1, 0, 2), (33, 2, 0, 3), (257, 3, 0, 17)])
+def test_small_caches(dtype, d, n_vis, n_text, n_sys, steps):
+    w = _workload(dtype, d, n_layers=2, n_vis=n_vis, n_text=n_text, n_sys=n_sys, decode_steps=steps)
+    _run_case(w, 1.0 if n_vis < 30 else 0.3, steps=steps)
+
+
+@pytest.mark.parametrize("dtype,d", STORAGES)
+def test_one_head_per_group_and_sixteen(dtype, d):
+    _run_case(_workload(dtype, d, n_layers=1, n_q_heads=3, n_kv_heads=3, n_vis=300, n_text=20, decode_steps=2), 0.2, steps=2)
+    _run_case(_workload(dtype, d, n_layers=1, n_q_heads=16, n_kv_heads=1, n_vis=300, n_text=20, decode_steps=2), 0.2, steps=2)
