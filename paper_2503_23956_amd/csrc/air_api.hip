@@ -94,8 +94,8 @@ WsLayout make_layout(const air_config &c) {
     w.cache_ptrs = take(L * sizeof(CachePtrs));
     w.dec_o = take(L * B * Hkv * kMaxSplits * 16 * D * 4);  // per (unit, split): 16 head rows x D
     w.dec_ml = take(L * B * Hq * kMaxSplits * 8);
-    w.stash = v_transposed(c.dtype, c.head_dim) ? take(L * B * Hkv * (size_t)w.n_chunks * kStashRows * kChunkKeys * 4) : off;
-    w.row_f = v_transposed(c.dtype, c.head_dim) ? take(L * B * Hkv * (size_t)kStashRows * w.n_chunks * 4) : off;
+    w.stash = take(L * B * Hkv * (size_t)w.n_chunks * kStashRows * kChunkKeys * 4);
+    w.row_f = take(L * B * Hkv * (size_t)kStashRows * w.n_chunks * 4);
     w.unit_R = take(L * B * Hkv * 4);
     w.len_off = take(B * L * 8);
     w.by_length = take(B * L * 16);
@@ -107,11 +107,9 @@ WsLayout make_layout(const air_config &c) {
 
 using namespace air;
 
-// Eq.11 in the tail of air_score's last kernel: the MFMA score path, the layers within one wave, the KV heads of a layer
-// within one round of sixteen loads
-static bool can_fuse_budget(const air_config &c) {
-    return v_transposed(c.dtype, c.head_dim) && c.n_layers <= 64 && c.n_kv_heads <= 16;
-}
+// Eq.11 in the tail of air_score's last kernel: the layers within one wave, the KV heads of a layer within one round of
+// sixteen loads
+static bool can_fuse_budget(const air_config &c) { return c.n_layers <= 64 && c.n_kv_heads <= 16; }
 
 struct air_ctx {
     air_config cfg;
@@ -339,7 +337,6 @@ air_status air_score(air_ctx *ctx, void *stream, int32_t l0, int32_t l1, const a
     memset(&sa, 0, sizeof(sa));
     memcpy(sa.s, seqs, sizeof(air_seq) * ctx->cfg.batch);
     const int dt = ctx->cfg.dtype;
-    const bool mfma = v_transposed(dt, ctx->cfg.head_dim);  // bf16, head_dim 128
     if (ctx->need_zero) {  // a prompt that was dropped half-way left partial counts of finished units
         hipError_t e = launch_zero_counters(s, ctx->tab.seq_cnt, ctx->dm.B);
         if (e != hipSuccess) return hip_fail(ctx, e, "air_score: clearing the arrival counters");
@@ -352,10 +349,10 @@ air_status air_score(air_ctx *ctx, void *stream, int32_t l0, int32_t l1, const a
     const int inline_rows = ctx->cfg.alpha > 0.0 && !ctx->dm.vis_window && ctx->tune.score_rows_kernel != 1;
     // Windows that are known to exceed the stash (alpha = 0 turns the whole candidate span into rows)
     // read K_v twice: run the two kernels over groups of layers whose keys fit the memory-side cache.
-    const int many_rows = mfma && ctx->cfg.alpha == 0.0 && (int64_t)ctx->dm.G * ctx->cfg.max_window > kStashRows;
+    const int many_rows = ctx->cfg.alpha == 0.0 && (int64_t)ctx->dm.G * ctx->cfg.max_window > kStashRows;
     if (many_rows) {
         double layer_bytes = 0.0;
-        for (int b = 0; b < ctx->cfg.batch; ++b) layer_bytes += (double)seqs[b].vis_len * ctx->cfg.n_kv_heads * 128 * 2;
+        for (int b = 0; b < ctx->cfg.batch; ++b) layer_bytes += (double)seqs[b].vis_len * ctx->cfg.n_kv_heads * ctx->cfg.head_dim * (dt == AIR_BF16 ? 2 : 4);
         const double block = (double)(ctx->tune.score_block_mb > 0 ? ctx->tune.score_block_mb : 160) * 1048576.0;
         const int n_groups = (int)ceil(layer_bytes * (l1 - l0) / block);
         group = (l1 - l0 + (n_groups > 0 ? n_groups : 1) - 1) / (n_groups > 0 ? n_groups : 1);
@@ -372,23 +369,18 @@ air_status air_score(air_ctx *ctx, void *stream, int32_t l0, int32_t l1, const a
             ll.p[i].v = layers[c0 - l0 + i].v;
         }
         hipError_t e = ctx->dm.vis_window ? launch_window_rows(s, ctx->dm, ctx->tab, c0, nl, sa)
-                       : mfma             ? launch_elite_mfma(s, ctx->dm, ctx->tab, c0, nl, ll, *strides, sa, ctx->cfg.alpha)
-                                          : launch_elite(s, ctx->dm, ctx->tab, dt, c0, nl, ll, *strides, sa, ctx->cfg.alpha);
-        if (e == hipSuccess && !mfma) {
-            e = launch_score_pass1(s, ctx->dm, ctx->tab, dt, c0, nl, ll, *strides);
-            if (e == hipSuccess) e = launch_score_rows(s, ctx->dm, ctx->tab, c0, nl);
-            if (e == hipSuccess) e = launch_score_pass2(s, ctx->dm, ctx->tab, dt, c0, nl, ll, *strides);
-            if (e == hipSuccess) e = launch_stats(s, ctx->dm, ctx->tab, c0, nl);
-        }
-        // MFMA path: stream kernel, then finish kernel, per group of layers (one group unless the
+                       : dt == AIR_BF16   ? launch_elite_mfma(s, ctx->dm, ctx->tab, c0, nl, ll, *strides, sa, ctx->cfg.alpha)
+                                          : launch_elite(s, ctx->dm, ctx->tab, c0, nl, ll, *strides, sa, ctx->cfg.alpha);
+        // stream kernel, then finish kernel, per group of layers (one group unless the
         // window is known to need the second read of K_v)
-        for (int g0 = 0; mfma && e == hipSuccess && g0 < nl; g0 += group) {
+        for (int g0 = 0; e == hipSuccess && g0 < nl; g0 += group) {
             const int gn = (nl - g0 < group) ? nl - g0 : group;
             LaunchLayers lg;
             memset(&lg, 0, sizeof(lg));
             for (int i = 0; i < gn; ++i) lg.p[i] = ll.p[g0 + i];
-            e = launch_score_mfma(s, ctx->dm, ctx->tab, 1, c0 + g0, gn, lg, *strides, sa, inline_rows, many_rows);
-            if (e == hipSuccess) e = launch_score_mfma(s, ctx->dm, ctx->tab, 2, c0 + g0, gn, lg, *strides, sa, inline_rows, many_rows);
+            for (int pass = 1; pass <= 2 && e == hipSuccess; ++pass)
+                e = dt == AIR_BF16 ? launch_score_mfma(s, ctx->dm, ctx->tab, pass, c0 + g0, gn, lg, *strides, sa, inline_rows, many_rows)
+                                   : launch_score_f32(s, ctx->dm, ctx->tab, pass, c0 + g0, gn, lg, *strides, sa);
         }
         if (e != hipSuccess) return hip_fail(ctx, e, "air_score launch");
     }

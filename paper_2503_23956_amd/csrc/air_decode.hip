@@ -228,7 +228,11 @@ __global__ __launch_bounds__(64 * NW) void decode_mfma_kernel(Dims dm, DecodeTab
 #pragma unroll
         for (int s = 0; s < NS; ++s) qb[s] = *reinterpret_cast<const uint4 *>(q + Elem<T>::kSlice * s + kVec * c);
     }
-    constexpr float kScale2 = (float)((D == 128 ? 0.08838834764831845 : 0.125) * 1.4426950408889634);  // log2(e) / sqrt(d)
+    constexpr double kScale2D = (D == 128 ? 0.08838834764831845 : 0.125) * 1.4426950408889634;  // log2(e) / sqrt(d)
+    // fp32 takes it to 46 bits; the second term is not negative, so that a masked score stays -inf
+    constexpr float kScale2 = (float)(sizeof(T) == 4 ? kScale2D * (1.0 - 1.2e-7) : kScale2D);
+    constexpr float kScale2Lo = (float)(kScale2D - (double)kScale2);
+    static_assert(sizeof(T) == 2 || kScale2Lo >= 0.f, "sign of the second term");
     float m_run = -INFINITY, l_run = 0.f;
     f32x4 acc[NJ];
 #pragma unroll
@@ -351,7 +355,9 @@ __global__ __launch_bounds__(64 * NW) void decode_mfma_kernel(Dims dm, DecodeTab
         for (int tile = 0; tile < KT; ++tile)
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const float p = __builtin_amdgcn_exp2f(fmaf(s[tile][i], kScale2, -m_run));
+                float x = fmaf(s[tile][i], kScale2, -m_run);
+                if (sizeof(T) == 4) x = fmaf(s[tile][i], kScale2Lo, x);
+                const float p = __builtin_amdgcn_exp2f(x);
                 s[tile][i] = p;
                 lb += p;
             }
@@ -480,9 +486,10 @@ __global__ __launch_bounds__(64 * NW) void decode_mfma_kernel(Dims dm, DecodeTab
         for (int i = 0; i < 4; ++i) {
             const int g = 4 * c + i;
             if (g < G && owns_tiles) {
-                const float inv = sizeof(T) == 4 ? 1.0f / mrg_l[i] : __builtin_amdgcn_rcpf(mrg_l[i]);
+                const float inv = __builtin_amdgcn_rcpf(mrg_l[i]);
 #pragma unroll
-                for (int jj = 0; jj < kTiles; ++jj) stf(&o_unit[g * D + 16 * (NJ * vh + wave + NW * jj) + n], acc[jj][i] * inv);
+                for (int jj = 0; jj < kTiles; ++jj)
+                    stf(&o_unit[g * D + 16 * (NJ * vh + wave + NW * jj) + n], sizeof(T) == 4 ? acc[jj][i] / mrg_l[i] : acc[jj][i] * inv);
             }
         }
         if (t.dec_steps && threadIdx.x == 0) {

@@ -97,17 +97,13 @@ constexpr size_t kStaticSlots = 1024;  // (unit, split) pairs per launch that th
 WsLayout make_layout(const air_config &cfg);
 
 // ---- kernel launchers (each returns the hipError_t of its launch) ----
-hipError_t launch_elite(hipStream_t s, const Dims &dm, const DevTables &t, int dtype, int l0, int nl,
-                        const LaunchLayers &ll, const air_strides &st, const SeqArgs &seqs, double alpha);
+hipError_t launch_elite(hipStream_t s, const Dims &dm, const DevTables &t, int l0, int nl, const LaunchLayers &ll,
+                        const air_strides &st, const SeqArgs &seqs, double alpha);
 hipError_t launch_window_rows(hipStream_t s, const Dims &dm, const DevTables &t, int l0, int nl, const SeqArgs &seqs);
-hipError_t launch_score_pass1(hipStream_t s, const Dims &dm, const DevTables &t, int dtype, int l0, int nl,
-                              const LaunchLayers &ll, const air_strides &st);
-hipError_t launch_score_rows(hipStream_t s, const Dims &dm, const DevTables &t, int l0, int nl);
-hipError_t launch_score_pass2(hipStream_t s, const Dims &dm, const DevTables &t, int dtype, int l0, int nl,
-                              const LaunchLayers &ll, const air_strides &st);
-hipError_t launch_stats(hipStream_t s, const Dims &dm, const DevTables &t, int l0, int nl);
 hipError_t launch_elite_mfma(hipStream_t s, const Dims &dm, const DevTables &t, int l0, int nl, const LaunchLayers &ll,
                              const air_strides &st, const SeqArgs &seqs, double alpha);
+hipError_t launch_score_f32(hipStream_t s, const Dims &dm, const DevTables &t, int pass, int l0, int nl, const LaunchLayers &ll,
+                            const air_strides &st, const SeqArgs &seqs);
 hipError_t launch_score_mfma(hipStream_t s, const Dims &dm, const DevTables &t, int pass, int l0, int nl,
                              const LaunchLayers &ll, const air_strides &st, const SeqArgs &seqs, int inline_rows, int many_rows);
 hipError_t launch_budget(hipStream_t s, const Dims &dm, const DevTables &t, double retention, int mode,

@@ -42,3 +42,25 @@ def test_small_caches(dtype, d, n_vis, n_text, n_sys, steps):
 def test_one_head_per_group_and_sixteen(dtype, d):
     _run_case(_workload(dtype, d, n_layers=1, n_q_heads=3, n_kv_heads=3, n_vis=300, n_text=20, decode_steps=2), 0.2, steps=2)
     _run_case(_workload(dtype, d, n_layers=1, n_q_heads=16, n_kv_heads=1, n_vis=300, n_text=20, decode_steps=2), 0.2, steps=2)
+
+
+@pytest.mark.parametrize("dtype,d", STORAGES)
+@pytest.mark.parametrize("n_vis,n_text,alpha,visual", [
+    (255, 9, None, None), (256, 9, None, None), (257, 9, None, None), (1024, 24, None, None), (1025, 24, None, None),
+    (1100, 40, 0.02, None),      # an elite window of more rows than a unit's stash holds
+    (700, 4, 0.0, None),         # 28 rows: a stash of several rounds
+    (1300, 5, 0.0, None),        # 35 rows: one more round than the stash
+    (600, 40, 0.0, None),        # 280 rows
+    (780, 12, 0.0, (250, 12)),   # visual window across a chunk boundary
+    (1100, 3, 0.0, (-3, 3)),
+])
+def test_scoring_at_the_edges_of_chunks_and_of_the_stash(dtype, d, n_vis, n_text, alpha, visual):
+    w = _workload(dtype, d, n_layers=2, n_vis=n_vis, n_text=n_text, decode_steps=1)
+    _run_case(w, 0.10, alpha=alpha, steps=1, visual_window=visual)
+
+
+@pytest.mark.parametrize("dtype,d", STORAGES)
+def test_scoring_strided_ragged_batch_layer_by_layer(dtype, d):
+    w = synth.get_workload(3).scaled(dtype=dtype, head_dim=d, batch=3, n_layers=3, n_vis=900, n_text=30, decode_steps=1)
+    _run_case(w, 0.10, steps=1, layer_chunk=1, token_major=True)
+    _run_case(w, 0.10, steps=1, causal_text=True, alpha=0.0)
