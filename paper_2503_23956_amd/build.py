@@ -17,6 +17,7 @@ SOURCES = {
     "air_score.hip": [],
     "air_score_mfma.hip": [],
     "air_score_f32.hip": [],
+    "air_score_window.hip": [],
     "air_budget.hip": ["-ffp-contract=off"],
     "air_select.hip": [],
     "air_decode.hip": [],

@@ -347,14 +347,16 @@ air_status air_score(air_ctx *ctx, void *stream, int32_t l0, int32_t l1, const a
     // The elite window (alpha > 0) leaves a unit a handful of rows: the finish kernel forms their
     // parameters itself.  A window that turns its whole span into rows gets the row-parameter kernel.
     const int inline_rows = ctx->cfg.alpha > 0.0 && !ctx->dm.vis_window && ctx->tune.score_rows_kernel != 1;
-    // Windows that are known to exceed the stash (alpha = 0 turns the whole candidate span into rows)
-    // read K_v twice: run the two kernels over groups of layers whose keys fit the memory-side cache.
+    // Windows that are known to exceed the stash (alpha = 0 turns the whole candidate span into rows) read K_v twice, in
+    // kernels that are bound by their exponentials: all layers in one pair of passes (224 rows, 28 x 4 x 7290 keys: one pair
+    // beats two of 14 layers, whose second read would come from the memory-side cache, by a quarter: fewer half-filled
+    // rounds of workgroups).  air_tuning.score_block_mb cuts the layers into groups.
     const int many_rows = ctx->cfg.alpha == 0.0 && (int64_t)ctx->dm.G * ctx->cfg.max_window > kStashRows;
-    if (many_rows) {
+    if (many_rows && ctx->tune.score_block_mb > 0) {
         double layer_bytes = 0.0;
-        for (int b = 0; b < ctx->cfg.batch; ++b) layer_bytes += (double)seqs[b].vis_len * ctx->cfg.n_kv_heads * ctx->cfg.head_dim * (dt == AIR_BF16 ? 2 : 4);
-        const double block = (double)(ctx->tune.score_block_mb > 0 ? ctx->tune.score_block_mb : 160) * 1048576.0;
-        const int n_groups = (int)ceil(layer_bytes * (l1 - l0) / block);
+        for (int b = 0; b < ctx->cfg.batch; ++b)
+            layer_bytes += (double)seqs[b].vis_len * ctx->cfg.n_kv_heads * ctx->cfg.head_dim * (dt == AIR_BF16 ? 2 : 4);
+        const int n_groups = (int)ceil(layer_bytes * (l1 - l0) / ((double)ctx->tune.score_block_mb * 1048576.0));
         group = (l1 - l0 + (n_groups > 0 ? n_groups : 1) - 1) / (n_groups > 0 ? n_groups : 1);
         if (group < 1) group = 1;
         if (group > lpl) group = lpl;
@@ -379,8 +381,9 @@ air_status air_score(air_ctx *ctx, void *stream, int32_t l0, int32_t l1, const a
             memset(&lg, 0, sizeof(lg));
             for (int i = 0; i < gn; ++i) lg.p[i] = ll.p[g0 + i];
             for (int pass = 1; pass <= 2 && e == hipSuccess; ++pass)
-                e = dt == AIR_BF16 ? launch_score_mfma(s, ctx->dm, ctx->tab, pass, c0 + g0, gn, lg, *strides, sa, inline_rows, many_rows)
-                                   : launch_score_f32(s, ctx->dm, ctx->tab, pass, c0 + g0, gn, lg, *strides, sa);
+                e = dt != AIR_BF16 ? launch_score_f32(s, ctx->dm, ctx->tab, pass, c0 + g0, gn, lg, *strides, sa)
+                    : many_rows    ? launch_score_window(s, ctx->dm, ctx->tab, pass, c0 + g0, gn, lg, *strides, sa)
+                                   : launch_score_mfma(s, ctx->dm, ctx->tab, pass, c0 + g0, gn, lg, *strides, sa, inline_rows);
         }
         if (e != hipSuccess) return hip_fail(ctx, e, "air_score launch");
     }

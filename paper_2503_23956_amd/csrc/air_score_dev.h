@@ -72,17 +72,23 @@ __device__ __forceinline__ void unit_statistics(__amdgpu_buffer_rsrc_t ers, int 
 }
 
 // Moments of a workgroup's scores, every sum in a fixed order: S1 = sum x, the workgroup mean S1 / n, then
-// M2 = sum (x - mean)^2 and M3 = sum (x - mean)^3 in fp64.  One entry (S1, mean, M2, M3) per workgroup of four waves.
+// M2 = sum (x - mean)^2 and M3 = sum (x - mean)^3 in fp64.  One entry (S1, mean, M2, M3) per workgroup (of NW waves).
 // x, ok: the thread's own scores and which of them exist (n_wg in the workgroup); n_ent workgroups share the unit.
-template <int NX>
+template <int NX, int NW>
 __device__ __forceinline__ void leave_moments(const Dims &dm, const DevTables &t, int64_t unit, int b, const air_seq &sq, int n_wg,
-                                              int n_ent, const float (&x)[NX], const bool (&ok)[NX], double (&s_mom)[4][3]) {
+                                              int n_ent, const float (&x)[NX], const bool (&ok)[NX], double (&s_mom)[NW][3]) {
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    auto over_waves = [&](int slot) {
+        double v = s_mom[0][slot];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) v += s_mom[w][slot];
+        return v;
+    };
     auto wg_sum = [&](double v, int slot) {
         v = wave_sum(v);
         if (lane == 0) s_mom[wave][slot] = v;
         lds_barrier();
-        return ((s_mom[0][slot] + s_mom[1][slot]) + s_mom[2][slot]) + s_mom[3][slot];
+        return over_waves(slot);
     };
                     double s1 = 0.0;
     #pragma unroll
@@ -112,7 +118,7 @@ __device__ __forceinline__ void leave_moments(const Dims &dm, const DevTables &t
             double *mo_unit = t.moments + unit * dm.n_entries * 4;
             const __amdgpu_buffer_rsrc_t ers = __builtin_amdgcn_make_buffer_rsrc(mo_unit, 0, dm.n_entries * 32, 0x00020000);
             if (lane < 4) {
-                const double r = lane == 0 ? S1 : (lane == 1 ? mean : ((s_mom[0][lane - 1] + s_mom[1][lane - 1]) + s_mom[2][lane - 1]) + s_mom[3][lane - 1]);
+                const double r = lane == 0 ? S1 : (lane == 1 ? mean : over_waves(lane - 1));
                 __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, r), ers, (int)blockIdx.x * 32 + lane * 8, 0, kSysScope);
             }
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");

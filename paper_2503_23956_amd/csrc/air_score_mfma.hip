@@ -28,40 +28,12 @@
 //       goes on to Eq.11 and the cache layout (air_budget_dev.h).
 #include "air_device.h"
 #include "air_internal.h"
-#include "air_score_dev.h"
-#include "air_tile.h"
+#include "air_score_mfma_dev.h"
 #include <type_traits>
 
 namespace air {
 
 constexpr int kRowsLds = 512;  // rows whose (M, w) are staged in LDS at a time (recompute path)
-
-struct UnitCtx {
-    int kvh, b, li, l, chunk, t0, G, W, R_total;
-    int qbase;  // token that row 0 of the query tensor belongs to (start of the text span, or of a visual window)
-    air_seq sq;
-    const bf16_t *q, *k;
-    int64_t hrow0, unit;
-};
-
-// row-list offsets of the heads of the group: s_pref[g] .. s_pref[g+1] are the rows of head g
-__device__ __forceinline__ void head_prefix(const DevTables &t, int64_t hrow0, int G, int *s_pref) {
-    if (threadIdx.x == 0) {
-        int run = 0;
-        for (int g = 0; g < G; ++g) {
-            s_pref[g] = run;
-            run += t.elite_cnt[hrow0 + g];
-        }
-        s_pref[G] = run;
-    }
-    lds_barrier();
-}
-
-__device__ __forceinline__ int head_of_row(const int *s_pref, int G, int rho) {
-    int g = 0;
-    while (g + 1 < G && s_pref[g + 1] <= rho) ++g;
-    return g;
-}
 
 // keys of one wave: tiles of 16, as MFMA B operands.  Keys past the end of the visual span re-read
 // the last one (no predication in front of the loads); `valid` masks their logits.
@@ -78,41 +50,9 @@ __device__ __forceinline__ void load_keys(const UnitCtx &u, const air_strides &s
     }
 }
 
-// A operand of one block of 16 window rows.  MFMA row m = 4c'+i' carries list row rbase + 4i' + c'
-// (c' = m / 4, i' = m % 4), so that output lane group c holds rows rbase + c, rbase + 4 + c, ...:
-// with fewer than 16 rows in the block every lane group has the same number of live rows and
-// loops over i stop early.
-template <int NS>
-__device__ __forceinline__ void load_rows(const DevTables &t, const UnitCtx &u, const air_strides &st,
-                                          const int *s_pref, int rbase, int n, int c, uint4 (&qa)[NS]) {
-    const int rho = rbase + 4 * (n & 3) + (n >> 2);
-    const int g = head_of_row(s_pref, u.G, rho);
-    const bool have = rho < u.R_total;
-    int tok = u.qbase;
-    if (have) tok = t.elite_idx[(u.hrow0 + g) * u.W + (rho - s_pref[g])];
-    const bf16_t *qr = u.q + (int64_t)(u.kvh * u.G + g) * st.q_h + (int64_t)(tok - u.qbase) * st.q_t;
-#pragma unroll
-    for (int sl = 0; sl < NS; ++sl) {
-        qa[sl] = make_uint4(0, 0, 0, 0);
-        if (have) qa[sl] = *reinterpret_cast<const uint4 *>(qr + 32 * sl + 8 * c);
-    }
-}
-
 // RAW logits (dot products, before the 1/sqrt(d) scale) of a block of 16 rows against the wave's 64
 // keys: lane (key n, c) gets rows rbase + 4i + c.  Maxima are taken and exchanged in raw units and
 // the scale is folded into the exponential, exp((s - M) / sqrt(d)) = 2^((s - M) * kC).
-template <int D>
-struct Log2Scale {  // log2(e) / sqrt(d), split
-    static constexpr double kC = 1.4426950408889634 * (D == 128 ? 0.08838834764831845 : 0.125);
-    static constexpr float kHi = (float)kC, kLo = (float)(kC - (double)kHi);
-};
-template <int D>
-__device__ __forceinline__ float exp_raw(float d) { return exp2_scaled(d, Log2Scale<D>::kHi, Log2Scale<D>::kLo); }
-// The per-key exponentials take the one-multiply form: its rounding of d * kHi costs a relative
-// 0.7 * 2^-24 * |log2 of the result|, below 6e-6 down to the smallest fp32 the result can be.
-template <int D>
-__device__ __forceinline__ float exp_key(float d) { return __builtin_amdgcn_exp2f(d * Log2Scale<D>::kHi); }
-
 template <int NS>
 __device__ __forceinline__ void logits_of(const uint4 (&qa)[NS], const uint4 (&kreg)[4][NS], f32x4 (&s)[4]) {
 #pragma unroll
@@ -132,60 +72,6 @@ __device__ __forceinline__ void block_logits(const DevTables &t, const UnitCtx &
     logits_of(qa, kreg, s);
 }
 
-// Windows with many rows per unit (a continuous or all-text window: every span token of every head is a row) keep
-// the query rows of up to QRows::kRows rows (32 KB) in LDS, so that a block of 16 rows costs a few LDS reads per lane instead
-// of two dependent trips to memory (row token, then row).  Rows are padded by 16 bytes: the sixteen rows a
-// load touches then fall into different banks.
-template <int D>
-struct QRows {
-    static constexpr int kRows = 32768 / (D * 2);
-    bf16_t row[kRows][D + 8];
-};
-
-// rows [r0, r0 + count) of the unit's row list into s_q.row[0 .. count); a thread per 16 bytes
-template <int D>
-__device__ __forceinline__ void stage_query_rows(const DevTables &t, const UnitCtx &u, const air_strides &st, const int *s_pref,
-                                                 int r0, int count, QRows<D> &s_q) {
-    constexpr int kPieces = D / 8;
-    for (int p = threadIdx.x; p < count * kPieces; p += blockDim.x) {
-        const int rr = (unsigned)p / kPieces, piece = (unsigned)p % kPieces;
-        const int rho = r0 + rr;
-        const int g = head_of_row(s_pref, u.G, rho);
-        const int tok = t.elite_idx[(u.hrow0 + g) * u.W + (rho - s_pref[g])];
-        const bf16_t *qr = u.q + (int64_t)(u.kvh * u.G + g) * st.q_h + (int64_t)(tok - u.qbase) * st.q_t;
-        *reinterpret_cast<uint4 *>(&s_q.row[rr][8 * piece]) = *reinterpret_cast<const uint4 *>(qr + 8 * piece);
-    }
-}
-// A operand of the block of 16 rows that starts at staged row rb (see load_rows for the row order); rows past `count` are zero
-template <int D, int NS>
-__device__ __forceinline__ void load_rows_lds(const QRows<D> &s_q, int rb, int count, int n, int c, uint4 (&qa)[NS]) {
-    const int rr = rb + 4 * (n & 3) + (n >> 2);
-#pragma unroll
-    for (int sl = 0; sl < NS; ++sl) {
-        qa[sl] = make_uint4(0, 0, 0, 0);
-        if (rr < count) qa[sl] = *reinterpret_cast<const uint4 *>(&s_q.row[rr][32 * sl + 8 * c]);
-    }
-}
-
-__device__ __forceinline__ bool unit_setup(const Dims &dm, const SeqArgs &seqs, int l0, const LaunchLayers &ll,
-                                           const air_strides &st, UnitCtx &u, int chunks_per_wg) {
-    u.chunk = blockIdx.x * chunks_per_wg;  // first chunk of this workgroup
-    u.kvh = blockIdx.y;  // grid (chunk group, KV head, sequence + B * layer)
-    seq_layer_of(dm, (int)blockIdx.z, u.b, u.li);
-    u.l = l0 + u.li;
-    u.sq = seqs.s[u.b];  // from the kernel arguments: no table read in front of the key loads
-    if (u.chunk * kChunkKeys >= u.sq.vis_len) return false;
-    u.t0 = u.sq.vis_start + u.sq.vis_len;
-    u.qbase = dm.vis_window ? u.sq.win_start : u.t0;
-    u.G = dm.G;
-    u.W = dm.max_window;
-    u.q = (const bf16_t *)ll.p[u.li].q + (int64_t)u.b * st.q_b;
-    u.k = (const bf16_t *)ll.p[u.li].k + (int64_t)u.b * st.kv_b + (int64_t)u.kvh * st.kv_h;
-    u.hrow0 = ((int64_t)u.l * dm.B + u.b) * dm.Hq + (int64_t)u.kvh * u.G;
-    u.unit = ((int64_t)u.l * dm.B + u.b) * dm.Hkv + u.kvh;
-    return true;
-}
-
 // ---------------------------------------------------------------------------------------
 // One workgroup per 256-key chunk of a unit.
 // Stash layout of one (unit, chunk, row): 256 floats, key 64w + 16 tile + n at position 64w + 4n + tile,
@@ -193,9 +79,7 @@ __device__ __forceinline__ bool unit_setup(const Dims &dm, const SeqArgs &seqs, 
 // VIS: the rows are the tokens of a visual window (all heads have the same win_len rows); row rho sits at
 // visual index prow0 + rho % win_len and sees the keys up to itself.  A (row, chunk) pair that lies wholly
 // behind the row leaves the partial (-inf, 0) and zeros in the stash.
-// MANY: launches whose window turns its whole span into rows (dozens to hundreds of rows per unit): the query rows are
-// staged in LDS, QRows::kRows at a time.
-template <int D, bool VIS, bool MANY>
+template <int D, bool VIS>
 __global__ __launch_bounds__(256, 4) void score_stream_kernel(Dims dm, DevTables t, int l0, LaunchLayers ll,
                                                               air_strides st, SeqArgs seqs) {
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, n = lane & 15, c = lane >> 4;
@@ -213,7 +97,7 @@ __global__ __launch_bounds__(256, 4) void score_stream_kernel(Dims dm, DevTables
     u.R_total = s_pref[u.G];
     const bool stash = u.R_total <= kStashRows;
     uint4 qa0[NS];
-    if (!MANY) load_rows(t, u, st, s_pref, 0, n, c, qa0);
+    load_rows(t, u, st, s_pref, 0, n, c, qa0);
 
     {
         float *stash_base = t.stash + ((u.unit * dm.n_chunks + chunk) * (int64_t)kStashRows) * kChunkKeys;
@@ -275,28 +159,11 @@ __global__ __launch_bounds__(256, 4) void score_stream_kernel(Dims dm, DevTables
                 t.part[slot * dm.n_chunks + chunk] = make_float2(s_mw[tid], Z);
             }
         };
-        if constexpr (!MANY) {
-            for (int rb = 0; rb < u.R_total; rb += 16) {
-                f32x4 s[4];
-                if (rb == 0) logits_of(qa0, kreg, s);
-                else block_logits(t, u, st, s_pref, rb, n, c, kreg, s);
-                reduce_block(rb, s);
-            }
-        } else {
-            __shared__ __align__(16) QRows<D> s_q;
-            for (int rs = 0; rs < u.R_total; rs += s_q.kRows) {
-                const int cnt = min(s_q.kRows, u.R_total - rs);
-                if (rs) lds_barrier();  // the blocks of the rows staged before have been read
-                stage_query_rows(t, u, st, s_pref, rs, cnt, s_q);
-                lds_barrier();
-                for (int rb = 0; rb < cnt; rb += 16) {
-                    uint4 qa[NS];
-                    load_rows_lds(s_q, rb, cnt, n, c, qa);
-                    f32x4 s[4];
-                    logits_of(qa, kreg, s);
-                    reduce_block(rs + rb, s);
-                }
-            }
+        for (int rb = 0; rb < u.R_total; rb += 16) {
+            f32x4 s[4];
+            if (rb == 0) logits_of(qa0, kreg, s);
+            else block_logits(t, u, st, s_pref, rb, n, c, kreg, s);
+            reduce_block(rb, s);
         }
     }
 }
@@ -373,8 +240,7 @@ __global__ __launch_bounds__(64 * kRowWaves) void score_rows_mfma_kernel(Dims dm
 // INLINE: no row-parameter kernel has run; every workgroup forms the parameters of the unit's rows
 // itself from the chunk partials (the elite window's handful of rows: cheaper than a launch).
 
-// MANY: as in the stream kernel, the query rows of the recompute path are staged in LDS.
-template <int D, bool VIS, bool INLINE, bool MANY>
+template <int D, bool VIS, bool INLINE>
 __global__ __launch_bounds__(256, 4) void score_finish_kernel(Dims dm, DevTables t, int l0, LaunchLayers ll,
                                                            air_strides st, SeqArgs seqs) {
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, n = lane & 15, c = lane >> 4;
@@ -539,28 +405,12 @@ __global__ __launch_bounds__(256, 4) void score_finish_kernel(Dims dm, DevTables
         bool valid[4];
         load_keys(u, st, key0, n, c, kreg, valid);
         float acc[4] = {0.f, 0.f, 0.f, 0.f};
-        const bool fresh = chunk == first;
         for (int rs = 0; rs < u.R_total; rs += kRowsLds) {
             const int rows_here = min(kRowsLds, u.R_total - rs);
-            if (fresh || u.R_total > kRowsLds) stage_rows(rs, rows_here);
+            if (chunk == first || u.R_total > kRowsLds) stage_rows(rs, rows_here);
             for (int rb = 0; rb < rows_here; rb += 16) {
                 f32x4 s[4];
-                if constexpr (MANY) {
-                    // the query rows of rows rs + [qs, qs + kRows) are in LDS; they are staged once per workgroup when the
-                    // unit has no more rows than that, else again for every chunk
-                    __shared__ __align__(16) QRows<D> s_q;
-                    const int qs = rb / s_q.kRows * s_q.kRows, cnt = min(s_q.kRows, rows_here - qs);
-                    if (rb == qs && (fresh || u.R_total > s_q.kRows)) {
-                        lds_barrier();  // the blocks of the rows staged before have been read
-                        stage_query_rows(t, u, st, s_pref, rs + qs, cnt, s_q);
-                        lds_barrier();
-                    }
-                    uint4 qa[NS];
-                    load_rows_lds(s_q, rb - qs, cnt, n, c, qa);
-                    logits_of(qa, kreg, s);
-                } else {
-                    block_logits(t, u, st, s_pref, rs + rb, n, c, kreg, s);
-                }
+                block_logits(t, u, st, s_pref, rs + rb, n, c, kreg, s);
                 const int n_i = min(4, (rows_here - rb + 3) >> 2);
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
@@ -791,22 +641,17 @@ hipError_t launch_elite_mfma(hipStream_t s, const Dims &dm, const DevTables &t, 
 
 template <int D>
 static hipError_t score_launch(hipStream_t s, const Dims &dm, const DevTables &t, int pass, int l0, int nl,
-                               const LaunchLayers &ll, const air_strides &st, const SeqArgs &seqs, int inline_rows, int many_rows) {
+                               const LaunchLayers &ll, const air_strides &st, const SeqArgs &seqs, int inline_rows) {
     const dim3 block(256);
     if (pass == 1) {
         const dim3 grid(dm.n_chunks, dm.Hkv, nl * dm.B);
-        if (dm.vis_window) {
-            if (many_rows) hipLaunchKernelGGL((score_stream_kernel<D, true, true>), grid, block, 0, s, dm, t, l0, ll, st, seqs);
-            else hipLaunchKernelGGL((score_stream_kernel<D, true, false>), grid, block, 0, s, dm, t, l0, ll, st, seqs);
-        } else {
-            if (many_rows) hipLaunchKernelGGL((score_stream_kernel<D, false, true>), grid, block, 0, s, dm, t, l0, ll, st, seqs);
-            else hipLaunchKernelGGL((score_stream_kernel<D, false, false>), grid, block, 0, s, dm, t, l0, ll, st, seqs);
-        }
+        if (dm.vis_window) hipLaunchKernelGGL((score_stream_kernel<D, true>), grid, block, 0, s, dm, t, l0, ll, st, seqs);
+        else hipLaunchKernelGGL((score_stream_kernel<D, false>), grid, block, 0, s, dm, t, l0, ll, st, seqs);
         return hipGetLastError();
     }
     const dim3 grid((dm.n_chunks + kFinishChunks - 1) / kFinishChunks, dm.Hkv, nl * dm.B);
     if (inline_rows && !dm.vis_window) {
-        hipLaunchKernelGGL((score_finish_kernel<D, false, true, false>), grid, block, 0, s, dm, t, l0, ll, st, seqs);
+        hipLaunchKernelGGL((score_finish_kernel<D, false, true>), grid, block, 0, s, dm, t, l0, ll, st, seqs);
         return hipGetLastError();
     }
     // a wave per row when the launch has few units; with many units, 4 waves walk the rows
@@ -814,20 +659,15 @@ static hipError_t score_launch(hipStream_t s, const Dims &dm, const DevTables &t
                        dim3(nl * dm.B * dm.Hkv >= 512 ? 256 : 64 * kRowWaves), 0, s, dm, t, l0, seqs);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    if (dm.vis_window) {
-        if (many_rows) hipLaunchKernelGGL((score_finish_kernel<D, true, false, true>), grid, block, 0, s, dm, t, l0, ll, st, seqs);
-        else hipLaunchKernelGGL((score_finish_kernel<D, true, false, false>), grid, block, 0, s, dm, t, l0, ll, st, seqs);
-    } else {
-        if (many_rows) hipLaunchKernelGGL((score_finish_kernel<D, false, false, true>), grid, block, 0, s, dm, t, l0, ll, st, seqs);
-        else hipLaunchKernelGGL((score_finish_kernel<D, false, false, false>), grid, block, 0, s, dm, t, l0, ll, st, seqs);
-    }
+    if (dm.vis_window) hipLaunchKernelGGL((score_finish_kernel<D, true, false>), grid, block, 0, s, dm, t, l0, ll, st, seqs);
+    else hipLaunchKernelGGL((score_finish_kernel<D, false, false>), grid, block, 0, s, dm, t, l0, ll, st, seqs);
     return hipGetLastError();
 }
 
 hipError_t launch_score_mfma(hipStream_t s, const Dims &dm, const DevTables &t, int pass, int l0, int nl,
-                             const LaunchLayers &ll, const air_strides &st, const SeqArgs &seqs, int inline_rows, int many_rows) {
-    return dm.D == 128 ? score_launch<128>(s, dm, t, pass, l0, nl, ll, st, seqs, inline_rows, many_rows)
-                       : score_launch<64>(s, dm, t, pass, l0, nl, ll, st, seqs, inline_rows, many_rows);
+                             const LaunchLayers &ll, const air_strides &st, const SeqArgs &seqs, int inline_rows) {
+    return dm.D == 128 ? score_launch<128>(s, dm, t, pass, l0, nl, ll, st, seqs, inline_rows)
+                       : score_launch<64>(s, dm, t, pass, l0, nl, ll, st, seqs, inline_rows);
 }
 
 }  // namespace air
