@@ -510,7 +510,8 @@ static void decode_shape(const air_ctx *ctx, int n_layers_in_launch, int appende
     constexpr double kLaunchGBs = 6000.0, kSplitUs = 3.7;
     const air_config &c = ctx->cfg;
     // what one workgroup streams: fp32 is bound by its matrix products (4.7 MB in 100 us, 9.2 MB in 190)
-    const double workgroup_gbs = c.dtype == AIR_F32 ? 48.0 : (c.head_dim == 64 ? 77.0 : 100.0);
+    // (heads of 128 elements in column parts: 64 units of 642 keys 14.6 us in four parts, 17.9 in two splits)
+    const double workgroup_gbs = c.dtype == AIR_F32 ? (c.head_dim == 128 && halves_ok ? 90.0 : 48.0) : (c.head_dim == 64 ? 77.0 : 100.0);
     double avg_len = 0.0;
     for (int b = 0; b < c.batch; ++b) {
         const air_seq &s = ctx->seqs[b];
@@ -521,17 +522,17 @@ static void decode_shape(const air_ctx *ctx, int n_layers_in_launch, int appende
     // A launch of a handful of units (one layer of one sequence) is bound by what one CU can stream: the unit
     // is cut into splits of about one 32-key chunk per wave, which beats the exchange of the partials (4 units
     // of ~900 keys: 8.4 us against 9.9 us as single workgroups).
-    // Short units of such a launch do better still as two workgroups each with half of V' and no exchange (the column
-    // halves: four waves, 64-key chunks): 4 units, us per launch against the splits, 360 keys 5.8 / 7.7, 870 keys
-    // 8.1 / 8.4, 1600 keys 11.3 / 9.8, 3800 keys 20.7 / 10.8.
+    // Short units of such a launch do better still as eight (four) workgroups each with its part of V' and no exchange (the
+    // column parts: four waves, 64-key chunks): 4 units, us per launch against the splits, 642 keys 6.5 / 7.7, 1242 keys
+    // 7.8 / 9.5, 1642 keys 9.1 / 9.7, 2442 keys 12.1 / 10.2.
     // (The rule goes by the prompt's own length, so that a decode run keeps one shape from its first step to its last.)
     // The other storages (bf16 with heads of 64 elements, fp32) split from 288 KB a unit on: 4 units, us per launch as one
     // workgroup of eight waves against the best split, bf16 d = 64 112 KB 5.9 / 7.0, 266 KB 7.2 / 7.5, 770 KB 12.8 / 8.4;
-    // fp32 d = 64 225 KB 8.1 / 8.4, 530 KB 13.1 / 8.9; fp32 d = 128 450 KB 13.9 (halves 11.1) / 9.6.
+    // fp32 d = 64 225 KB 8.1 / 8.4, 530 KB 13.1 / 8.9; fp32 d = 128 450 KB 13.9 (two parts 11.1) / 9.6.
     const double unit_bytes = avg_len * 2.0 * c.head_dim * (c.dtype == AIR_BF16 ? 2.0 : 4.0);
     const bool other = !v_transposed(c.dtype, c.head_dim);
     const bool short_unit = other && unit_bytes < 288.0 * 1024.0;
-    const bool short_halves = units <= 16 && halves_ok && (other ? short_unit : avg_len - appended < 896.0);
+    const bool short_halves = units <= 16 && halves_ok && (other ? short_unit : avg_len - appended < 1750.0);
     const bool tiny_launch = units <= 16 && !short_halves;
     // 64 keys a wave and iteration (32 of the 512-byte fp32 rows); bf16 with heads of 128 elements has other sizes compiled too
     int kt = decode_tiles_of(c);
@@ -599,21 +600,26 @@ static air_status decode_attn(air_ctx *ctx, void *stream, int32_t l0, int32_t l1
     auto shape_of = [&](int c0, int nl, int *splits, int *waves, int *tiles) {
         // a recorded launch is replayed at every cache length: its shape is chosen for the middle of the decode
         const int hkv = ctx->dm.Hkv;
-        const bool halves_ok = in_step && ctx->cfg.head_dim == 128 && (hkv & (hkv - 1)) == 0 && ctx->tune.decode_halves != 1;
+        const bool halves_ok = in_step && (hkv & (hkv - 1)) == 0 && ctx->tune.decode_halves != 1;
         decode_shape(ctx, nl, ctx->cfg.device_steps ? ctx->cfg.max_decode_steps / 2 : ctx->appended[c0], halves_ok, splits, waves,
                      tiles);
     };
-    // Two workgroups per unit, each with all of K' and one half of the columns of V' (air_decode.hip), wherever a
-    // launch of four-wave workgroups leaves half the CUs idle (with more workgroups than CUs it loses: 448 units
-    // 47.8 against 42.4 us, 1280 units 256 against 250).  112 units, warm / cold cache: 215 keys per
+    // Several workgroups per unit, each with all of K' and its part of the columns of V' (air_decode.hip), wherever a
+    // launch of four-wave workgroups leaves CUs idle: as many parts (2, 4, 8; an output tile of 16 columns is the smallest)
+    // as leave a workgroup a CU of its own.  Beyond 128 units it loses (448 units
+    // 47.8 against 42.4 us, 1280 units 256 against 250).  Two parts, 112 units, warm / cold cache: 215 keys per
     // unit 6.4 / 8.7 us against 6.5 / 8.4 with one workgroup per unit, 870 keys 9.6 / 11.6 against 10.7 / 13.3,
-    // 3800 keys 33 / 45 against 35 / 55, 7400 keys 64 / 73 against 76 / 89.
-    auto halves_of = [&](int nl, int splits, int waves, int tiles) {
+    // 3800 keys 33 / 45 against 35 / 55, 7400 keys 64 / 73 against 76 / 89.  Eight, four and two parts: 4 units of ~870 keys
+    // (one layer) 6.65 / 6.9 / 7.5 us a launch, 32 units of 2142 keys 12.6 / 12.6 / 13.4, 64 units 21.6 / 13.7 / 14.2;
+    // bf16 with heads of 64 elements, 48 units of ~870 keys, four / two / one 6.85 / 7.1 / 7.8.
+    auto parts_of = [&](int nl, int splits, int waves, int tiles) {
         const int hkv = ctx->dm.Hkv;
-        const bool can = in_step && ctx->cfg.head_dim == 128 && (hkv & (hkv - 1)) == 0 && splits == 1 && waves == 4 &&
-                         tiles == decode_tiles_of(ctx->cfg);
-        const bool few = 2 * ((nl * units_per_layer + 7) & ~7) <= 256;
-        return can && ctx->tune.decode_halves != 1 && (few || ctx->tune.decode_halves == 2);
+        const bool can = in_step && (hkv & (hkv - 1)) == 0 && splits == 1 && waves == 4 && tiles == decode_tiles_of(ctx->cfg);
+        const int64_t units = (nl * units_per_layer + 7) & ~7;
+        if (!can || ctx->tune.decode_halves == 1 || (units > 128 && ctx->tune.decode_halves != 2)) return 1;
+        int parts = ctx->cfg.head_dim == 128 ? 8 : 4;
+        while (parts > 2 && parts * units > 256) parts >>= 1;
+        return parts;
     };
     for (int c0 = l0; use_static && c0 < l1; c0 += max_nl) {
         const int nl = (l1 - c0 < max_nl) ? l1 - c0 : max_nl;
@@ -646,13 +652,13 @@ static air_status decode_attn(air_ctx *ctx, void *stream, int32_t l0, int32_t l1
                            tiles == decode_tiles_of(ctx->cfg) && (waves == 1 || waves == 4) && !ctx->cfg.cache_in_place;
         const bool longest_first = whole && ctx->tune.decode_order != 1 &&
                                    (ctx->tune.decode_order == 2 || (int64_t)nl * units_per_layer >= 512);
-        const bool column_halves = halves_of(nl, splits, waves, tiles);
-        // with device-counted steps the two workgroups of a unit meet at the unit's arrival counter
-        if (e == hipSuccess && use_static && column_halves && ctx->cfg.device_steps && splits == 1)
+        const int column_parts = parts_of(nl, splits, waves, tiles);
+        // with device-counted steps the workgroups of a unit meet at the unit's arrival counter
+        if (e == hipSuccess && use_static && column_parts > 1 && ctx->cfg.device_steps && splits == 1)
             e = launch_zero_counters(s, xch.cnt, (int)(nl * units_per_layer));
         if (e == hipSuccess)
             e = launch_decode(s, ctx->dm, ctx->tab, xch, ctx->cfg.dtype, c0, nl, c0 - l0, ll, q_new, k_new, v_new, out,
-                              splits, waves, tiles, in_step ? ctx->appended[l0] : -1, longest_first, column_halves);
+                              splits, waves, tiles, in_step ? ctx->appended[l0] : -1, longest_first, column_parts);
         if (e != hipSuccess) return hip_fail(ctx, e, "air_decode_attn launch");
     }
     for (int l = l0; l < l1; ++l) {

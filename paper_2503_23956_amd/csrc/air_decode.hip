@@ -121,7 +121,7 @@ constexpr int kDecodeTiles = sizeof(T) == 4 && D == 128 ? 2 : 4;
 // INPLACE: the cache is kept inside the layers' own K / V tensors (their addresses come from a table)
 // SORTED: a launch over all layers whose grid index z is not the layer but its rank by cache length within the
 // sequence (longest first); the layer comes with the table entry that carries the length
-// VH = 2: two workgroups per unit, each with one half of the columns of V' (see below); ONE_SEQ: the instance for B = 1
+// VH > 1: VH workgroups per unit, each with its part of the columns of V' (see below); ONE_SEQ: the instance for B = 1
 template <typename T, int D, int NW, int KT, bool SPLIT, bool INPLACE, bool SORTED = false, int VH = 1, bool ONE_SEQ = false>
 __global__ __launch_bounds__(64 * NW) void decode_mfma_kernel(Dims dm, DecodeTabs t, int l0, int lbase,
                                                               DecodeSteps ll, const T *q_new,
@@ -133,9 +133,10 @@ __global__ __launch_bounds__(64 * NW) void decode_mfma_kernel(Dims dm, DecodeTab
     constexpr int kIter = 16 * KT;           // keys per loop iteration of one wave (KT score tiles, TB token blocks)
     constexpr int TB = kIter / kVTok;
     constexpr int NJ = D / 16 / VH;          // output tiles (16 columns each) of the workgroup
-    constexpr int kColsPer = D / 64 / VH;    // columns of the appended V' row per lane
-    static_assert(kIter % kVTok == 0 && kColsPer >= 1, "whole V' blocks per iteration, a column per lane");
-    static_assert(VH == 1 || (!SPLIT && !SORTED && NJ % NW == 0), "column halves: one workgroup pair per unit");
+    constexpr int kCols = D / VH;            // columns of V' of the workgroup
+    constexpr int kColsPer = kCols > 64 ? kCols / 64 : 1;  // columns of the appended V' row per lane (lanes < kCols)
+    static_assert(kIter % kVTok == 0 && kCols >= 16, "whole V' blocks per iteration, whole output tiles");
+    static_assert(VH == 1 || (!SPLIT && !SORTED), "column parts: VH workgroups per unit, no exchange");
     const int lane = threadIdx.x & 63, n = lane & 15, c = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // a scalar: the wave's chunk walk and its branches stay off the vector unit
     // grid (split + splits * KV head, sequence, layer): the linear order of the workgroups is (split, unit) and
@@ -146,17 +147,17 @@ __global__ __launch_bounds__(64 * NW) void decode_mfma_kernel(Dims dm, DecodeTab
     int li = blockIdx.z;
     int vh = 0;
     bool live = true;
-    if (VH == 2) {
-        // Two workgroups per unit, each with all of K' and one half of the columns of V' and of the output: no partials to
-        // exchange, and a workgroup moves three quarters of the unit's bytes (a CU takes in about 140 GB/s, which is what
-        // bounds a launch of few units).  A 1-D grid: the two workgroups of a unit get ids 16 p + x and 16 p + 8 + x, the
-        // same XCD (ids are dealt round-robin over the 8 XCDs) at neighbouring dispatch slots, so that the K' tiles both
+    if (VH > 1) {
+        // VH workgroups per unit, each with all of K' and 1 / VH of the columns of V' and of the output: no partials to
+        // exchange, and a workgroup moves (1 + 1 / VH) / 2 of the unit's bytes (a CU takes in about 140 GB/s, which is what
+        // bounds a launch of few units).  A 1-D grid: the workgroups of a unit get ids 8 (VH p + part) + x, the
+        // same XCD (ids are dealt round-robin over the 8 XCDs) at neighbouring dispatch slots, so that the K' tiles they all
         // stream come through that XCD's L2 once.  `splits` carries the units of the launch (the grid is rounded up to
-        // whole groups of 16: the workgroups past the end redo the last unit and store nothing), `lg_splits` log2 of
+        // whole groups of 8 units: the workgroups past the end redo the last unit and store nothing), `lg_splits` log2 of
         // the KV heads.
         const int wid = blockIdx.x, slot = wid >> 3;
-        int pair = ((slot >> 1) << 3) | (wid & 7);
-        vh = slot & 1;
+        int pair = ((slot / VH) << 3) | (wid & 7);
+        vh = slot & (VH - 1);
         live = pair < splits;
         pair = min(pair, splits - 1);
         kvh = pair & (dm.Hkv - 1);
@@ -191,7 +192,7 @@ __global__ __launch_bounds__(64 * NW) void decode_mfma_kernel(Dims dm, DecodeTab
 #pragma unroll
     for (int j = 0; j < NJ; ++j) vnew[j] = v_new[new_src + 16 * (j + NJ * vh) + n];
 #pragma unroll
-    for (int h2 = 0; h2 < kColsPer; ++h2) vcol[h2] = v_new[new_src + 64 * (h2 + vh) + lane];
+    for (int h2 = 0; h2 < kColsPer; ++h2) vcol[h2] = v_new[new_src + kCols * vh + 64 * h2 + (kCols < 64 ? lane & (kCols - 1) : lane)];
     const int64_t unit = ((int64_t)l * dm.B + b) * dm.Hkv + kvh;
     // tokens appended so far: from the host with the launch, or counted on the device (a recorded launch
     // that is replayed): the workgroup that finishes the unit advances the count, after every workgroup
@@ -204,7 +205,7 @@ __global__ __launch_bounds__(64 * NW) void decode_mfma_kernel(Dims dm, DecodeTab
             return;
         }
     }
-    if (VH == 2 && !live) return;
+    if (VH > 1 && !live) return;
     const int len = len_off.x + appended + 1;
     const int newrow = len - 1;  // the token appended by this call (Eq.2): scored from k_new / v_new, stored to the cache
     int k0 = 0, k1 = len;
@@ -252,7 +253,8 @@ __global__ __launch_bounds__(64 * NW) void decode_mfma_kernel(Dims dm, DecodeTab
         const int tok = newrow & (kVTok - 1);
 #pragma unroll
         for (int h2 = 0; h2 < kColsPer; ++h2) {
-            const int col = lane + 64 * (h2 + vh);
+            if (kCols < 64 && lane >= kCols) break;
+            const int col = kCols * vh + 64 * h2 + lane;
             if (tok == 0) {  // a new block: the column's other slots are written as zeros
                 constexpr int kGroup = 16 * kVec;  // elements from one slot group to the next
                 T *vcolp = vc + (int64_t)newrow * D + (col >> 4) * (4 * kGroup) + (col & 15) * kVec;  // slot group 0
@@ -496,9 +498,9 @@ __global__ __launch_bounds__(64 * NW) void decode_mfma_kernel(Dims dm, DecodeTab
             if (VH == 1) {
                 t.dec_steps[unit] = appended + 1;
             } else {
-                // the workgroup of the pair that finishes second advances the count: the other one has read it by then
+                // the last workgroup of the unit to finish advances the count: the others have read it by then
                 const int64_t xu = t.x_local ? ((int64_t)li * dm.B + b) * dm.Hkv + kvh : unit;
-                if (__hip_atomic_fetch_add(&t.dec_cnt[xu], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 1) {
+                if (__hip_atomic_fetch_add(&t.dec_cnt[xu], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == VH - 1) {
                     __hip_atomic_store(&t.dec_cnt[xu], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // next launch
                     t.dec_steps[unit] = appended + 1;
                 }
@@ -639,23 +641,31 @@ static void decode_shape_launch(const DecodeLaunch &a, bool longest_first) {
     else decode_launch<T, D, NW, KT, true, false, false, 1, false>(a, grid, a.splits, a.lg_splits);
 }
 
-// Heads of 128 elements: two workgroups per unit, each with one half of the columns of V' (the caller has checked what
-// this variant asks for)
-template <typename T, int KT>
-static void decode_halves_launch(const DecodeLaunch &a) {
+// VH workgroups per unit, each with its part of the columns of V' (the caller has checked what this variant asks for)
+template <typename T, int D, int VH>
+static void decode_parts_launch_(const DecodeLaunch &a) {
+    constexpr int KT = kDecodeTiles<T, D>;
     const int units = a.nl * a.dm.B * a.dm.Hkv;
     int lg_h = 0;
     while ((1 << lg_h) < a.dm.Hkv) ++lg_h;
-    const dim3 grid(2 * ((units + 7) & ~7));
-    if constexpr (sizeof(T) == 2) {
+    const dim3 grid(VH * ((units + 7) & ~7));
+    if constexpr (sizeof(T) == 2 && D == 128) {
         if (a.dt.cache_ptrs) {
-            if (a.dm.B == 1) decode_launch<T, 128, 4, KT, false, true, false, 2, true>(a, grid, units, lg_h);
-            else decode_launch<T, 128, 4, KT, false, true, false, 2, false>(a, grid, units, lg_h);
+            if (a.dm.B == 1) decode_launch<T, D, 4, KT, false, true, false, VH, true>(a, grid, units, lg_h);
+            else decode_launch<T, D, 4, KT, false, true, false, VH, false>(a, grid, units, lg_h);
             return;
         }
     }
-    if (a.dm.B == 1) decode_launch<T, 128, 4, KT, false, false, false, 2, true>(a, grid, units, lg_h);
-    else decode_launch<T, 128, 4, KT, false, false, false, 2, false>(a, grid, units, lg_h);
+    if (a.dm.B == 1) decode_launch<T, D, 4, KT, false, false, false, VH, true>(a, grid, units, lg_h);
+    else decode_launch<T, D, 4, KT, false, false, false, VH, false>(a, grid, units, lg_h);
+}
+template <typename T, int D>
+static void decode_parts_launch(const DecodeLaunch &a, int parts) {
+    if constexpr (D == 128) {
+        if (parts == 8) return decode_parts_launch_<T, D, 8>(a);
+    }
+    if (parts >= 4) decode_parts_launch_<T, D, 4>(a);
+    else decode_parts_launch_<T, D, 2>(a);
 }
 
 template <typename T, int D, int KT>
@@ -669,7 +679,7 @@ static void decode_waves_launch(const DecodeLaunch &a, int waves, bool longest_f
 hipError_t launch_decode(hipStream_t s, const Dims &dm, const DevTables &t, const DecodeExchange &x, int dtype, int l0,
                          int nl, int lbase, const LaunchLayers &ll, const void *q_new, const void *k_new,
                          const void *v_new, void *out, int splits, int waves, int tiles, int uniform_appended,
-                         bool longest_first, bool column_halves) {
+                         bool longest_first, int column_parts) {
     if (splits < 1 || (splits & (splits - 1)) != 0) return hipErrorInvalidValue;  // the kernel shifts by log2(splits)
     int lg_splits = 0;
     while ((1 << lg_splits) < splits) ++lg_splits;
@@ -693,17 +703,19 @@ hipError_t launch_decode(hipStream_t s, const Dims &dm, const DevTables &t, cons
     for (int i = 0; i < kMaxLayersPerLaunch; ++i) ds.appended[i] = ll.appended[i];
     const DecodeLaunch a = {s, dm, dt, ds, l0, nl, lbase, splits, lg_splits, q_new, k_new, v_new, out};
     if (dtype == AIR_BF16 && dm.D == 128) {
-        if (column_halves) decode_halves_launch<bf16_t, 4>(a);
+        if (column_parts > 1) decode_parts_launch<bf16_t, 128>(a, column_parts);
         else if (tiles == 4) decode_waves_launch<bf16_t, 128, 4>(a, waves, longest_first);
         else if (tiles == 2) decode_waves_launch<bf16_t, 128, 2>(a, waves, longest_first);
         else decode_waves_launch<bf16_t, 128, 8>(a, waves, longest_first);
-    } else if (dtype == AIR_BF16) {  // the other storages have one chunk size each: about 16 KB of K' and V' a wave
-        decode_waves_launch<bf16_t, 64, kDecodeTiles<bf16_t, 64>>(a, waves, longest_first);
+    } else if (dtype == AIR_BF16) {  // the other storages have one chunk size each
+        if (column_parts > 1) decode_parts_launch<bf16_t, 64>(a, column_parts);
+        else decode_waves_launch<bf16_t, 64, kDecodeTiles<bf16_t, 64>>(a, waves, longest_first);
     } else if (dm.D == 128) {
-        if (column_halves) decode_halves_launch<float, 2>(a);
+        if (column_parts > 1) decode_parts_launch<float, 128>(a, column_parts);
         else decode_waves_launch<float, 128, kDecodeTiles<float, 128>>(a, waves, longest_first);
     } else {
-        decode_waves_launch<float, 64, kDecodeTiles<float, 64>>(a, waves, longest_first);
+        if (column_parts > 1) decode_parts_launch<float, 64>(a, column_parts);
+        else decode_waves_launch<float, 64, kDecodeTiles<float, 64>>(a, waves, longest_first);
     }
     return hipGetLastError();
 }

@@ -64,3 +64,39 @@ def test_scoring_strided_ragged_batch_layer_by_layer(dtype, d):
     w = synth.get_workload(3).scaled(dtype=dtype, head_dim=d, batch=3, n_layers=3, n_vis=900, n_text=30, decode_steps=1)
     _run_case(w, 0.10, steps=1, layer_chunk=1, token_major=True)
     _run_case(w, 0.10, steps=1, causal_text=True, alpha=0.0)
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 128)] + STORAGES)
+@pytest.mark.parametrize("base,batch,n_layers", [(2, 1, 3), (2, 1, 11), (2, 1, 18), (3, 2, 5), (3, 3, 6)])
+def test_decode_column_parts_equal_one_workgroup_per_unit(dtype, d, base, batch, n_layers):
+    # 12 (eight parts), 40 and 44 (four), 72 (two) units, one sequence and ragged batches: a workgroup of a part does the same
+    # arithmetic per output column, so outputs and appended rows agree bit for bit
+    import numpy as np
+    import torch
+
+    import paper_2503_23956_amd as A
+    from paper_2503_23956_amd.device_inputs import config_for, to_device, to_host
+
+    dev = torch.device("cuda:0")
+    steps = 34
+    w = synth.get_workload(base).scaled(dtype=dtype, head_dim=d, batch=batch, n_layers=n_layers, n_vis=400, n_text=21, decode_steps=steps)
+    seqs, L = w.seqs(), w.n_layers
+    layers = [synth.layer_inputs(w, l, seqs) for l in range(L)]
+    q, k, v = ([to_device(getattr(li, name), dev) for li in layers] for name in ("q_text", "k", "v"))
+    ins = [[to_device(np.stack(x), dev) for x in zip(*[synth.decode_inputs(w, l, t) for l in range(L)])] for t in range(steps)]
+    seen = []
+    for halves in (1, 2):
+        ac = A.AirCache(config_for(w, 0.25, seqs=seqs, max_decode_steps=steps), dev)
+        ac.air_set_tuning(decode_splits=1, decode_waves=4, decode_tiles=4, decode_halves=halves)
+        ac.air_score(0, L, q, k, v, seqs)
+        ac.air_budget()
+        ac.air_select_compact(0, L, k, v)
+        out = torch.empty((steps, L, batch, w.n_q_heads, d), dtype=q[0].dtype, device=dev)
+        for t in range(steps):
+            ac.air_decode_attn(0, L, *ins[t], out[t])
+        lens = ac.air_get_lengths()
+        seen.append((to_host(out), [ac.air_get_cache(l, b, h, int(lens[b, l])) for l in (0, L - 1) for b in range(batch) for h in (0, w.n_kv_heads - 1)]))
+        ac.close()
+    assert np.array_equal(seen[0][0], seen[1][0]) and not np.isnan(synth.storage_to_f64(seen[0][0])).any()
+    for (k1, v1), (k2, v2) in zip(seen[0][1], seen[1][1]):
+        assert np.array_equal(k1, k2) and np.array_equal(v1, v2)
