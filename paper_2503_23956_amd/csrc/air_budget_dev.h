@@ -32,6 +32,23 @@ __device__ __forceinline__ double ordered_sum(const double *a, int n) {
     }
     return sum;
 }
+// two of them side by side: their chains of additions do not wait for each other
+__device__ __forceinline__ void ordered_sums(const double *a, const double *b, int n, double &sum_a, double &sum_b) {
+    sum_a = sum_b = 0.0;
+    for (int l = 0; l < n; l += 8) {
+        double v[8], w[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            v[j] = a[l + j];
+            w[j] = b[l + j];
+        }
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            sum_a += v[j];
+            sum_b += w[j];
+        }
+    }
+}
 __device__ __forceinline__ int int_sum(const int *a, int n) {  // n a multiple of 8, zeros past the last layer
     int sum = 0;
     for (int l = 0; l < n; l += 8) {
@@ -44,6 +61,9 @@ __device__ __forceinline__ int int_sum(const int *a, int n) {  // n a multiple o
     return sum;
 }
 
+// (Up to 64 layers a wave counts by ballot and adds whole numbers by a scan over its lanes; the sums of the clamping
+// round are formed only if some layer is out of range.)
+//
 // Called by the threads 0 .. max(64, L rounded up) of a workgroup (ONE_WAVE: by one wave, for up to 64 layers; the
 // exchanges through LDS then need no workgroup barrier, a wave's LDS accesses complete in program order, only the
 // compiler is kept from moving them).  a0, a1, frac, i0, i1: LDS arrays of one slot per calling thread.
@@ -87,7 +107,8 @@ __device__ __forceinline__ void allocate_and_lay_out(const Dims &dm, const DevTa
         a0[tid] = st;   // threads past the last layer hold exact zeros
         a1[tid] = skp;
         sync();
-        const double sum_t = ordered_sum(a0, L8), sum_k = ordered_sum(a1, L8);
+        double sum_t, sum_k;
+        ordered_sums(a0, a1, L8, sum_t, sum_k);
         long long k_tot = (long long)floor(retention * (double)n_vis * (double)L + 0.5);
         const long long k_lo = (long long)L * lo_i, k_hi = (long long)L * n_vis;
         k_tot = k_tot < k_lo ? k_lo : (k_tot > k_hi ? k_hi : k_tot);
@@ -105,9 +126,9 @@ __device__ __forceinline__ void allocate_and_lay_out(const Dims &dm, const DevTa
         for (int it = 0; it < L + 1; ++it) {
             sync();  // the sums of the round before (or of the shares) have been read
             a0[tid] = is_free ? wl : 0.0;  // a pinned layer adds an exact zero
-            i0[tid] = is_free ? 1 : 0;
+            if (!ONE_WAVE) i0[tid] = is_free ? 1 : 0;
             sync();
-            const int n_free = int_sum(i0, L8);
+            const int n_free = ONE_WAVE ? __popcll(__ballot(is_free)) : int_sum(i0, L8);
             if (n_free == 0) break;
             const double w_free = ordered_sum(a0, L8);
             double vo = 0.0, vu = 0.0;
@@ -116,11 +137,13 @@ __device__ __forceinline__ void allocate_and_lay_out(const Dims &dm, const DevTa
                 if (x > hi) vo = x - hi;
                 else if (x < lo) vu = lo - x;
             }
+            if (ONE_WAVE && __ballot(vo > 0.0 || vu > 0.0) == 0ull) break;  // nobody out of range: both sums are zero
             sync();
             a0[tid] = vo;
             a1[tid] = vu;
             sync();
-            const double over = ordered_sum(a0, L8), under = ordered_sum(a1, L8);
+            double over, under;
+            ordered_sums(a0, a1, L8, over, under);
             const int pin = (over == 0.0 && under == 0.0) ? 0 : (over >= under ? 1 : 2);
             if (pin == 0) break;
             bool pinned = false;
@@ -132,10 +155,10 @@ __device__ __forceinline__ void allocate_and_lay_out(const Dims &dm, const DevTa
                 pinned = true;
             }
             is_free = is_free && !pinned;
-            i1[tid] = pinned ? 1 : 0;
+            if (!ONE_WAVE) i1[tid] = pinned ? 1 : 0;
             sync();
             // k_free stays an integer-valued double: the bound is subtracted once per pinned layer
-            const int n_pin = int_sum(i1, L8);
+            const int n_pin = ONE_WAVE ? __popcll(__ballot(pinned)) : int_sum(i1, L8);
             const double bound = pin == 1 ? hi : lo;
             for (int q = 0; q < n_pin; ++q) k_free -= bound;
         }
@@ -149,8 +172,9 @@ __device__ __forceinline__ void allocate_and_lay_out(const Dims &dm, const DevTa
         i0[tid] = mine ? kk : 0;
         i1[tid] = (mine && kk < n_vis) ? 1 : 0;  // eligible for a leftover token
         sync();
-        const long long left = k_tot - (long long)int_sum(i0, L8);
-        const int n_elig = int_sum(i1, L8);
+        const int floors = ONE_WAVE ? __builtin_amdgcn_readlane(wave_incl_scan(mine ? kk : 0), 63) : int_sum(i0, L8);
+        const long long left = k_tot - (long long)floors;
+        const int n_elig = ONE_WAVE ? __popcll(__ballot(mine && kk < n_vis)) : int_sum(i1, L8);
         if (left > 0 && left <= (long long)n_elig) {
             // largest remainder: the `left` eligible layers that come first by (fraction descending, layer ascending)
             if (mine && kk < n_vis) {
@@ -187,17 +211,19 @@ __device__ __forceinline__ void allocate_and_lay_out(const Dims &dm, const DevTa
     // cache layout: each layer's region holds system + kept + text rows and room for the decode
     // appends, and starts on a multiple of kCacheRowAlign rows
     const int nonvis = sq.seq_len - sq.vis_len;
-    i0[tid] = mine ? (nonvis + kk + dm.max_steps + kCacheRowAlign - 1) / kCacheRowAlign * kCacheRowAlign : 0;
+    const int region = mine ? (nonvis + kk + dm.max_steps + kCacheRowAlign - 1) / kCacheRowAlign * kCacheRowAlign : 0;
+    if (!ONE_WAVE) i0[tid] = region;
     i1[tid] = mine ? kk : -1;
     sync();
+    int off = ONE_WAVE ? wave_incl_scan(region) - region : 0;
     if (mine) {
         // one pass over the layers gives the layer's row offset and its rank by falling cache length (ties: the
         // lower layer first); the table by rank serves decode launches that take their longest units first
-        int off = 0, rank = 0;
+        int rank = 0;
         for (int l0 = 0; l0 < L8; l0 += 8) {
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
-                off += l0 + j < tid ? i0[l0 + j] : 0;
+                if (!ONE_WAVE) off += l0 + j < tid ? i0[l0 + j] : 0;
                 rank += (int)(i1[l0 + j] > kk) | ((int)(i1[l0 + j] == kk) & (int)(l0 + j < tid));
             }
         }

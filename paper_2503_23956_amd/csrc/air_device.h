@@ -109,6 +109,18 @@ __device__ __forceinline__ double sum16(double v) {  // over each row of 16 lane
     AIR_DPP_STEP64(add_d, v, 0x140)
     return v;
 }
+// over each group of 8 consecutive lanes
+__device__ __forceinline__ float max8(float v) {
+    v = AIR_DPP_STEP(fmaxf, v, 0xB1);
+    v = AIR_DPP_STEP(fmaxf, v, 0x4E);
+    return AIR_DPP_STEP(fmaxf, v, 0x141);
+}
+__device__ __forceinline__ double sum8(double v) {
+    AIR_DPP_STEP64(add_d, v, 0xB1)
+    AIR_DPP_STEP64(add_d, v, 0x4E)
+    AIR_DPP_STEP64(add_d, v, 0x141)
+    return v;
+}
 __device__ __forceinline__ double wave_sum(double v) {
     v = sum16(v);
     v += __shfl_xor(v, 16, 64);
@@ -166,21 +178,24 @@ __device__ __forceinline__ void lds_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// Inclusive prefix sum of one int per lane over a wave: shifts inside each row of 16 lanes on DPP (lanes shifted in from
+// outside the row read 0), then the totals of the rows in front are added from lanes 15, 31 and 47.
+__device__ __forceinline__ int wave_incl_scan(int v) {
+    const int lane = threadIdx.x & 63;
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true);  // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, true);  // row_shr:2
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, true);  // row_shr:4
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, true);  // row_shr:8
+    const int t0 = __builtin_amdgcn_readlane(v, 15), t1 = __builtin_amdgcn_readlane(v, 31), t2 = __builtin_amdgcn_readlane(v, 47);
+    return v + (lane >= 16 ? t0 : 0) + (lane >= 32 ? t1 : 0) + (lane >= 48 ? t2 : 0);
+}
+
 // Exclusive prefix sum of one int per thread over a workgroup of NW waves (thread order).
 // `scratch` holds NW + 1 ints; *total receives the sum.  Contains two barriers.
 template <int NW>
 __device__ __forceinline__ int block_excl_scan(int v, int *scratch, int *total) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    // inclusive scan over the wave: shifts inside each row of 16 lanes on DPP (lanes shifted in from outside the
-    // row read 0), then the totals of the rows in front are added from lanes 15, 31 and 47
-    int incl = v;
-    incl += __builtin_amdgcn_update_dpp(0, incl, 0x111, 0xf, 0xf, true);  // row_shr:1
-    incl += __builtin_amdgcn_update_dpp(0, incl, 0x112, 0xf, 0xf, true);  // row_shr:2
-    incl += __builtin_amdgcn_update_dpp(0, incl, 0x114, 0xf, 0xf, true);  // row_shr:4
-    incl += __builtin_amdgcn_update_dpp(0, incl, 0x118, 0xf, 0xf, true);  // row_shr:8
-    const int t0 = __builtin_amdgcn_readlane(incl, 15), t1 = __builtin_amdgcn_readlane(incl, 31),
-              t2 = __builtin_amdgcn_readlane(incl, 47);
-    incl += (lane >= 16 ? t0 : 0) + (lane >= 32 ? t1 : 0) + (lane >= 48 ? t2 : 0);
+    const int incl = wave_incl_scan(v);
     __syncthreads();
     if (lane == 63) scratch[wave] = incl;
     __syncthreads();

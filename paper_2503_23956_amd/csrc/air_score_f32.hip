@@ -23,6 +23,7 @@ namespace air {
 
 constexpr int kGroupRows = 32;  // window rows whose logits a thread holds at a time
 constexpr int kSliceElems = 32; // elements of a key staged at a time: 128 bytes
+static_assert(kGroupRows * 8 == 256, "eight lanes to a row of the group");
 static_assert(kGroupRows == kStashRows, "a unit with a stash has one group of rows");
 
 struct F32Unit {
@@ -219,19 +220,27 @@ __global__ __launch_bounds__(256) void score_finish_f32(Dims dm, DevTables t, in
         const int nb = min(kGroupRows, R_total - r0);
         if (stash) stage_rows<D, false>(dm, t, u, st, r0, nb, s);
         else stage_rows<D, true>(dm, t, u, st, r0, nb, s);
-        // row maximum over the chunks and the elite-text columns, normaliser in fp64, weight: sixteen lanes to a row
-        const int gl = tid & 15;
-        for (int rb = 0; rb < nb; rb += 16) {
-            const int r = min(rb + (tid >> 4), nb - 1);
+        // Row maximum over the chunks and the elite-text columns, normaliser in fp64, weight: eight lanes to a row, all rows of
+        // the group at once; the text columns are the item in front of the chunks.  (Sixteen lanes in two rounds, and the
+        // stash read chunk by chunk below: 13.1 us for the kernel on the tiny workload, where it is all latency, 24.5 on 112
+        // units of 2304 keys with heads of 128 elements; so 12.3 and 21.7.)
+        {
+            const int r = min(tid >> 3, nb - 1), gl = tid & 7;
             const int64_t slot = s.slot[r];
             const float2 *p = t.part + slot * dm.n_chunks;
-            const float mt = t.row_mtext[slot] * (1.0f / sqrtf((float)D));  // stored unscaled
-            float M = mt;
-            for (int c = gl; c < u.nch; c += 16) M = fmaxf(M, p[c].x);
-            M = max16(M);
-            double Z = gl == 0 ? (double)t.row_ztext[slot] * exp((double)mt - (double)M) : 0.0;
-            for (int c = gl; c < u.nch; c += 16) Z += (double)p[c].y * exp((double)p[c].x - (double)M);
-            Z = sum16(Z);
+            const float2 text = make_float2(t.row_mtext[slot] * (1.0f / sqrtf((float)D)), t.row_ztext[slot]);  // stored unscaled
+            auto item = [&](int c) { return c == 0 ? text : p[min(c, u.nch) - 1]; };
+            const float2 x0 = item(gl), x1 = item(gl + 8);
+            float M = fmaxf(text.x, fmaxf(x0.x, x1.x));  // an item past the last repeats it
+            for (int c = gl + 16; c <= u.nch; c += 8) M = fmaxf(M, item(c).x);
+            M = max8(M);
+            double Z = gl <= u.nch ? (double)x0.y * exp((double)x0.x - (double)M) : 0.0;
+            if (gl + 8 <= u.nch) Z += (double)x1.y * exp((double)x1.x - (double)M);
+            for (int c = gl + 16; c <= u.nch; c += 8) {
+                const float2 x = item(c);
+                Z += (double)x.y * exp((double)x.x - (double)M);
+            }
+            Z = sum8(Z);
             const int g = s.head[r];
             if (gl == 0) {
                 s_M[r] = M;
@@ -241,17 +250,19 @@ __global__ __launch_bounds__(256) void score_finish_f32(Dims dm, DevTables t, in
         __syncthreads();
         if (stash) {
             const float *sb = t.stash + ((u.unit * dm.n_chunks + first) * (int64_t)kStashRows) * kChunkKeys + tid;
+            for (int rb = 0; rb < nb; rb += 8) {
+                float a[kFinishChunks][8];
 #pragma unroll
-            for (int ci = 0; ci < kFinishChunks; ++ci) {
-                const int i = (first + ci) * kChunkKeys + tid;
-                const float *sc = sb + (int64_t)min(ci, last - 1 - first) * (kStashRows * kChunkKeys);  // a chunk past the last re-reads it
-                for (int rb = 0; rb < nb; rb += 8) {
-                    float a[8];
+                for (int ci = 0; ci < kFinishChunks; ++ci)
 #pragma unroll
-                    for (int r = 0; r < 8; ++r) a[r] = sc[min(rb + r, nb - 1) * kChunkKeys];
+                    for (int r = 0; r < 8; ++r)  // a chunk past the last and a row past the list re-read the last one
+                        a[ci][r] = sb[min(ci, last - 1 - first) * (kStashRows * kChunkKeys) + min(rb + r, nb - 1) * kChunkKeys];
+#pragma unroll
+                for (int ci = 0; ci < kFinishChunks; ++ci) {
+                    const int i = (first + ci) * kChunkKeys + tid;
 #pragma unroll
                     for (int r = 0; r < 8; ++r)
-                        if (rb + r < nb && i <= s.lim[rb + r]) imp[ci] = fmaf(s_w[rb + r], expf(a[r] - s_M[rb + r]), imp[ci]);
+                        if (rb + r < nb && i <= s.lim[rb + r]) imp[ci] = fmaf(s_w[rb + r], expf(a[ci][r] - s_M[rb + r]), imp[ci]);
                 }
             }
         } else {
