@@ -422,6 +422,14 @@ air_status air_budget(air_ctx *ctx, void *stream) {
     return AIR_OK;
 }
 
+// bytes of the context's whole compacted cache, by the prompts' lengths and the retention
+static double cache_bytes(const air_ctx *ctx) {
+    const air_config &c = ctx->cfg;
+    double rows = 0.0;
+    for (const air_seq &s : ctx->seqs) rows += (double)(s.seq_len - s.vis_len) + c.retention * (double)s.vis_len;
+    return rows * c.n_layers * c.n_kv_heads * 2.0 * c.head_dim * (c.dtype == AIR_BF16 ? 2.0 : 4.0);
+}
+
 air_status air_select_compact(air_ctx *ctx, void *stream, int32_t l0, int32_t l1, const air_layer *layers,
                               const air_strides *strides) {
     if (!ctx) return AIR_ERR_INVALID_ARG;
@@ -485,7 +493,8 @@ air_status air_select_compact(air_ctx *ctx, void *stream, int32_t l0, int32_t l1
         }
         if (e == hipSuccess)
             e = in_place ? launch_gather_in_place(s, ctx->dm, ctx->tab, c0, nl, ll, *strides)
-                         : launch_gather(s, ctx->dm, ctx->tab, ctx->cfg.dtype, c0, nl, ll, *strides, ctx->tune.gather_wgs);
+                         : launch_gather(s, ctx->dm, ctx->tab, ctx->cfg.dtype, c0, nl, ll, *strides, ctx->tune.gather_wgs,
+                                         cache_bytes(ctx));
         if (e != hipSuccess) return hip_fail(ctx, e, "air_select_compact launch");
     }
     for (int l = l0; l < l1; ++l) ctx->compacted[l] = 1;
@@ -658,7 +667,7 @@ static air_status decode_attn(air_ctx *ctx, void *stream, int32_t l0, int32_t l1
             e = launch_zero_counters(s, xch.cnt, (int)(nl * units_per_layer));
         if (e == hipSuccess)
             e = launch_decode(s, ctx->dm, ctx->tab, xch, ctx->cfg.dtype, c0, nl, c0 - l0, ll, q_new, k_new, v_new, out,
-                              splits, waves, tiles, in_step ? ctx->appended[l0] : -1, longest_first, column_parts);
+                              splits, waves, tiles, in_step ? ctx->appended[l0] : -1, longest_first, column_parts, cache_bytes(ctx) > kDecodeStreamBytes);
         if (e != hipSuccess) return hip_fail(ctx, e, "air_decode_attn launch");
     }
     for (int l = l0; l < l1; ++l) {

@@ -122,7 +122,9 @@ constexpr int kDecodeTiles = sizeof(T) == 4 && D == 128 ? 2 : 4;
 // SORTED: a launch over all layers whose grid index z is not the layer but its rank by cache length within the
 // sequence (longest first); the layer comes with the table entry that carries the length
 // VH > 1: VH workgroups per unit, each with its part of the columns of V' (see below); ONE_SEQ: the instance for B = 1
-template <typename T, int D, int NW, int KT, bool SPLIT, bool INPLACE, bool SORTED = false, int VH = 1, bool ONE_SEQ = false>
+// STREAM: a cache several times the size of the memory-side cache: its loads are marked as used once
+template <typename T, int D, int NW, int KT, bool SPLIT, bool INPLACE, bool SORTED = false, int VH = 1, bool ONE_SEQ = false,
+          bool STREAM = false>
 __global__ __launch_bounds__(64 * NW) void decode_mfma_kernel(Dims dm, DecodeTabs t, int l0, int lbase,
                                                               DecodeSteps ll, const T *q_new,
                                                               const T *k_new, const T *v_new, T *out,
@@ -156,7 +158,8 @@ __global__ __launch_bounds__(64 * NW) void decode_mfma_kernel(Dims dm, DecodeTab
         // whole groups of 8 units: the workgroups past the end redo the last unit and store nothing), `lg_splits` log2 of
         // the KV heads.
         const int wid = blockIdx.x, slot = wid >> 3;
-        int pair = ((slot / VH) << 3) | (wid & 7);
+        constexpr int kLgVH = VH == 8 ? 3 : (VH == 4 ? 2 : 1);
+        int pair = ((slot >> kLgVH) << 3) | (wid & 7);
         vh = slot & (VH - 1);
         live = pair < splits;
         pair = min(pair, splits - 1);
@@ -298,13 +301,19 @@ __global__ __launch_bounds__(64 * NW) void decode_mfma_kernel(Dims dm, DecodeTab
         for (int tile = 0; tile < KT; ++tile) {
             const T *src = kc + (int64_t)min(kb + 16 * tile, last_tile) * D + Elem<T>::kSlice * n + kVec * c;
 #pragma unroll
-            for (int sl = 0; sl < NS; ++sl) a[tile][sl] = *reinterpret_cast<const uint4 *>(src + 64 * kVec * sl);
+            for (int sl = 0; sl < NS; ++sl) {
+                if constexpr (STREAM) a[tile][sl] = load16<true>(src + 64 * kVec * sl);
+                else a[tile][sl] = *reinterpret_cast<const uint4 *>(src + 64 * kVec * sl);
+            }
         }
 #pragma unroll
         for (int tb = 0; tb < TB; ++tb) {
             const T *src = vc + (int64_t)min(kb + kVTok * tb, last_block) * D + 16 * kVec * c + kVec * n;
 #pragma unroll
-            for (int j = 0; j < NJ; ++j) vb[tb][j] = *reinterpret_cast<const uint4 *>(src + 64 * kVec * (j + NJ * vh));
+            for (int j = 0; j < NJ; ++j) {
+                if constexpr (STREAM) vb[tb][j] = load16<true>(src + 64 * kVec * (j + NJ * vh));
+                else vb[tb][j] = *reinterpret_cast<const uint4 *>(src + 64 * kVec * (j + NJ * vh));
+            }
         }
     };
     auto compute_chunk = [&](const uint4(&a)[KT][NS], const uint4(&vb)[TB][NJ], int kb) {
@@ -615,11 +624,12 @@ struct DecodeLaunch {
     int l0, nl, lbase, splits, lg_splits;
     const void *q_new, *k_new, *v_new;
     void *out;
+    bool stream;
 };
 
-template <typename T, int D, int NW, int KT, bool SPLIT, bool INPLACE, bool SORTED, int VH, bool ONE_SEQ>
+template <typename T, int D, int NW, int KT, bool SPLIT, bool INPLACE, bool SORTED, int VH, bool ONE_SEQ, bool STREAM = false>
 static void decode_launch(const DecodeLaunch &a, dim3 grid, int splits, int lg_splits) {
-    hipLaunchKernelGGL((decode_mfma_kernel<T, D, NW, KT, SPLIT, INPLACE, SORTED, VH, ONE_SEQ>), grid, dim3(64 * NW), 0, a.s, a.dm,
+    hipLaunchKernelGGL((decode_mfma_kernel<T, D, NW, KT, SPLIT, INPLACE, SORTED, VH, ONE_SEQ, STREAM>), grid, dim3(64 * NW), 0, a.s, a.dm,
                        a.dt, a.l0, a.lbase, a.ds, (const T *)a.q_new, (const T *)a.k_new, (const T *)a.v_new, (T *)a.out, splits,
                        lg_splits);
 }
@@ -635,7 +645,12 @@ static void decode_shape_launch(const DecodeLaunch &a, bool longest_first) {
         }
     }
     if constexpr (KT == kDecodeTiles<T, D> && (NW == 1 || NW == 4)) {
-        if (longest_first && a.splits == 1) return decode_launch<T, D, NW, KT, false, false, true, 1, false>(a, grid, 1, 0);
+        if (longest_first && a.splits == 1)
+            return a.stream ? decode_launch<T, D, NW, KT, false, false, true, 1, false, true>(a, grid, 1, 0)
+                            : decode_launch<T, D, NW, KT, false, false, true, 1, false>(a, grid, 1, 0);
+    }
+    if constexpr (KT == kDecodeTiles<T, D> && NW <= 4) {
+        if (a.stream && a.splits == 1) return decode_launch<T, D, NW, KT, false, false, false, 1, false, true>(a, grid, 1, 0);
     }
     if (a.splits == 1) decode_launch<T, D, NW, KT, false, false, false, 1, false>(a, grid, 1, 0);
     else decode_launch<T, D, NW, KT, true, false, false, 1, false>(a, grid, a.splits, a.lg_splits);
@@ -679,7 +694,7 @@ static void decode_waves_launch(const DecodeLaunch &a, int waves, bool longest_f
 hipError_t launch_decode(hipStream_t s, const Dims &dm, const DevTables &t, const DecodeExchange &x, int dtype, int l0,
                          int nl, int lbase, const LaunchLayers &ll, const void *q_new, const void *k_new,
                          const void *v_new, void *out, int splits, int waves, int tiles, int uniform_appended,
-                         bool longest_first, int column_parts) {
+                         bool longest_first, int column_parts, bool stream) {
     if (splits < 1 || (splits & (splits - 1)) != 0) return hipErrorInvalidValue;  // the kernel shifts by log2(splits)
     int lg_splits = 0;
     while ((1 << lg_splits) < splits) ++lg_splits;
@@ -701,7 +716,7 @@ hipError_t launch_decode(hipStream_t s, const Dims &dm, const DevTables &t, cons
     DecodeSteps ds;
     ds.uniform = uniform_appended;
     for (int i = 0; i < kMaxLayersPerLaunch; ++i) ds.appended[i] = ll.appended[i];
-    const DecodeLaunch a = {s, dm, dt, ds, l0, nl, lbase, splits, lg_splits, q_new, k_new, v_new, out};
+    const DecodeLaunch a = {s, dm, dt, ds, l0, nl, lbase, splits, lg_splits, q_new, k_new, v_new, out, stream};
     if (dtype == AIR_BF16 && dm.D == 128) {
         if (column_parts > 1) decode_parts_launch<bf16_t, 128>(a, column_parts);
         else if (tiles == 4) decode_waves_launch<bf16_t, 128, 4>(a, waves, longest_first);

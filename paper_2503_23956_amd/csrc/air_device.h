@@ -30,34 +30,16 @@ __device__ __forceinline__ void stf(bf16_t *p, float v) { *p = float_to_bf16_bit
 __device__ __forceinline__ uint32_t bits_of(float v) { return __float_as_uint(v); }
 __device__ __forceinline__ uint32_t bits_of(bf16_t v) { return v; }
 
-// Load one row of D elements (16-byte aligned) into fp32 registers.
-template <int D>
-__device__ __forceinline__ void load_row(const float *p, float (&r)[D]) {
-    const float4 *p4 = reinterpret_cast<const float4 *>(p);
-#pragma unroll
-    for (int i = 0; i < D / 4; ++i) {
-        float4 x = p4[i];
-        r[4 * i + 0] = x.x;
-        r[4 * i + 1] = x.y;
-        r[4 * i + 2] = x.z;
-        r[4 * i + 3] = x.w;
-    }
+// 16 bytes that are read (written) once and not soon again: marked to leave the caches first
+template <bool STREAM, typename P>
+__device__ __forceinline__ uint4 load16(const P *p) {
+    if (STREAM) return __builtin_bit_cast(uint4, __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p)));
+    return *reinterpret_cast<const uint4 *>(p);
 }
-template <int D>
-__device__ __forceinline__ void load_row(const bf16_t *p, float (&r)[D]) {
-    const uint4 *p4 = reinterpret_cast<const uint4 *>(p);
-#pragma unroll
-    for (int i = 0; i < D / 8; ++i) {
-        uint4 x = p4[i];
-        r[8 * i + 0] = __uint_as_float(x.x << 16);
-        r[8 * i + 1] = __uint_as_float(x.x & 0xffff0000u);
-        r[8 * i + 2] = __uint_as_float(x.y << 16);
-        r[8 * i + 3] = __uint_as_float(x.y & 0xffff0000u);
-        r[8 * i + 4] = __uint_as_float(x.z << 16);
-        r[8 * i + 5] = __uint_as_float(x.z & 0xffff0000u);
-        r[8 * i + 6] = __uint_as_float(x.w << 16);
-        r[8 * i + 7] = __uint_as_float(x.w & 0xffff0000u);
-    }
+template <bool STREAM, typename P>
+__device__ __forceinline__ void store16(P *p, const uint4 &v) {
+    if (STREAM) __builtin_nontemporal_store(__builtin_bit_cast(u32x4, v), reinterpret_cast<u32x4 *>(p));
+    else *reinterpret_cast<uint4 *>(p) = v;
 }
 
 // All-reduce over each group of 16 consecutive lanes with DPP modifiers (no LDS traffic):

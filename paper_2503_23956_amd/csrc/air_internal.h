@@ -92,6 +92,12 @@ struct DecodeExchange {
     int32_t local;   // 1: slots indexed by the unit inside the launch
     int32_t stride;  // slots per unit
 };
+// Where loads and stores are marked as used once, by the size of a context's whole compacted cache (the memory-side cache
+// holds 256 MB).  The gather from 128 MB on.  The decode attention (launches without column parts) from 512 MB on, us per step
+// marked / unmarked: 1.4 GB 233 / 255, 1.3 GB 248 / 252, 0.89 GB 163 / 167, 0.57 GB 104 / 108, 0.61 GB of heads of 64
+// elements 101 / 118; below, the memory-side cache still serves a part of every step: 0.46 GB 88 / 84, 0.24 GB 47 / 44,
+// 0.12 GB 23 / 20.
+constexpr double kGatherStreamBytes = 128e6, kDecodeStreamBytes = 512e6;
 constexpr size_t kStaticSlots = 1024;  // (unit, split) pairs per launch that the static exchange area holds
 
 WsLayout make_layout(const air_config &cfg);
@@ -112,13 +118,13 @@ hipError_t launch_budget(hipStream_t s, const Dims &dm, const DevTables &t, doub
                          int min_keep, int skip_allocation, const SeqArgs &seqs);
 hipError_t launch_select(hipStream_t s, const Dims &dm, const DevTables &t, int l0, int nl, int threads, int direct_max);
 hipError_t launch_gather(hipStream_t s, const Dims &dm, const DevTables &t, int dtype, int l0, int nl,
-                         const LaunchLayers &ll, const air_strides &st, int wgs_per_unit);
+                         const LaunchLayers &ll, const air_strides &st, int wgs_per_unit, double cache_bytes);
 hipError_t launch_gather_in_place(hipStream_t s, const Dims &dm, const DevTables &t, int l0, int nl, const LaunchLayers &ll,
                                   const air_strides &st);
 hipError_t launch_decode(hipStream_t s, const Dims &dm, const DevTables &t, const DecodeExchange &x, int dtype, int l0,
                          int nl, int lbase, const LaunchLayers &ll, const void *q_new, const void *k_new,
                          const void *v_new, void *out, int splits, int waves, int tiles, int uniform_appended,
-                         bool longest_first, int column_parts);
+                         bool longest_first, int column_parts, bool stream);
 // the exchange area inside the library's static device array, for the device that is current (looked up once per device)
 hipError_t static_exchange(DecodeExchange *x);
 hipError_t launch_zero_counters(hipStream_t s, int32_t *p, int n);

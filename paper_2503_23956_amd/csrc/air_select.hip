@@ -199,7 +199,11 @@ __global__ __launch_bounds__(NT) void select_kernel(Dims dm, DevTables t, int l0
 // workgroup stages 32 gathered K and V rows in LDS and writes K' as two 16-token
 // tiles (see k_tiled) and V' block-transposed (see v_tiled; one block of 32 tokens with bf16, two of 16 with fp32).
 // Slots of the last block that have no token yet are written as zeros.
-template <typename T, int D>
+// STREAM: caches too large to be passed on to the first decode step whole: loads and the V' stores marked as used once.  us for
+// select + gather + scoring, marked / unmarked: 460 MB of cache 489 / 514, 236 MB 317 / 333, 800 MB 619 / 643, 570 MB of
+// longer prompts 1633 / 1692; 50 MB loses (35.5 against 34.4 for select + gather, and the first decode step 15.3 against
+// 13.8).  With the K' stores marked as well nothing is left of it (519, 330, 656, 1711).
+template <typename T, int D, bool STREAM>
 __global__ __launch_bounds__(256) void gather_vt_kernel(Dims dm, DevTables t, int l0, LaunchLayers ll, air_strides st) {
     constexpr int kVec = 16 / (int)sizeof(T);  // elements in 16 bytes
     constexpr int kPieces = D / kVec;          // 16-byte pieces of a row
@@ -242,8 +246,8 @@ __global__ __launch_bounds__(256) void gather_vt_kernel(Dims dm, DevTables t, in
                 if (j < sq.vis_start) tok = j;
                 else if (j < sq.vis_start + kl) tok = sq.vis_start + idx[j - sq.vis_start];
                 else tok = sq.vis_start + sq.vis_len + (j - sq.vis_start - kl);
-                kx[it] = *reinterpret_cast<const uint4 *>(ksrc + (int64_t)tok * st.kv_t + c);
-                vx[it] = *reinterpret_cast<const uint4 *>(vsrc + (int64_t)tok * st.kv_t + c);
+                kx[it] = load16<STREAM>(ksrc + (int64_t)tok * st.kv_t + c);
+                vx[it] = load16<STREAM>(vsrc + (int64_t)tok * st.kv_t + c);
             }
         }
     };
@@ -264,8 +268,8 @@ __global__ __launch_bounds__(256) void gather_vt_kernel(Dims dm, DevTables t, in
         for (int it = 0; it < kIt; ++it) {
             const int v = threadIdx.x + 256 * it;
             const int tl = v / (16 * kPieces), sl = (v % (16 * kPieces)) >> 6, n = (v >> 2) & 15, c = v & 3;
-            *reinterpret_cast<uint4 *>(kdst + (int64_t)r0 * D + (int64_t)v * kVec) =
-                *reinterpret_cast<const uint4 *>(&ktile[16 * tl + n][4 * kVec * sl + kVec * c]);
+            store16<false>(kdst + (int64_t)r0 * D + (int64_t)v * kVec,
+                           *reinterpret_cast<const uint4 *>(&ktile[16 * tl + n][4 * kVec * sl + kVec * c]));
         }
         // V': in v_tiled order, the slots of one column and slot group per thread, consecutive in memory
 #pragma unroll
@@ -281,7 +285,7 @@ __global__ __launch_bounds__(256) void gather_vt_kernel(Dims dm, DevTables t, in
                                bits_of(tile[row + 2][col]) | (bits_of(tile[row + 3][col]) << 16),
                                bits_of(tile[row + 4][col]) | (bits_of(tile[row + 5][col]) << 16),
                                bits_of(tile[row + 6][col]) | (bits_of(tile[row + 7][col]) << 16));
-            *reinterpret_cast<uint4 *>(vdst + (int64_t)r0 * D + (int64_t)v * kVec) = x;
+            store16<STREAM>(vdst + (int64_t)r0 * D + (int64_t)v * kVec, x);
         }
         lds_barrier();  // LDS traffic only: the requested rows of the next block stay in flight
     }
@@ -405,24 +409,27 @@ hipError_t launch_select(hipStream_t s, const Dims &dm, const DevTables &t, int 
 
 template <typename T, int D>
 static hipError_t gather_launch(hipStream_t s, const Dims &dm, const DevTables &t, int l0, int nl, const LaunchLayers &ll,
-                                const air_strides &st, int gx) {
-    hipLaunchKernelGGL((gather_vt_kernel<T, D>), dim3(gx, dm.Hkv, nl * dm.B), dim3(256), 0, s, dm, t, l0, ll, st);
+                                const air_strides &st, int gx, bool stream) {
+    const dim3 grid(gx, dm.Hkv, nl * dm.B), block(256);
+    if (stream) hipLaunchKernelGGL((gather_vt_kernel<T, D, true>), grid, block, 0, s, dm, t, l0, ll, st);
+    else hipLaunchKernelGGL((gather_vt_kernel<T, D, false>), grid, block, 0, s, dm, t, l0, ll, st);
     return hipGetLastError();
 }
 
 hipError_t launch_gather(hipStream_t s, const Dims &dm, const DevTables &t, int dtype, int l0, int nl,
-                         const LaunchLayers &ll, const air_strides &st, int wgs_per_unit) {
+                         const LaunchLayers &ll, const air_strides &st, int wgs_per_unit, double cache_bytes) {
     // workgroups per unit: about 4096 in the launch, so that with many units each workgroup walks several
     // blocks of 32 rows (the next block's reads run under the current block's stores); wgs_per_unit > 0 overrides
     const int units = nl * dm.B * dm.Hkv;
     int gx = (4096 + units - 1) / units;
     gx = gx < 2 ? 2 : (gx > 32 ? 32 : gx);
     if (wgs_per_unit >= 1 && wgs_per_unit <= 64) gx = wgs_per_unit;
+    const bool stream = cache_bytes > kGatherStreamBytes;
     if (dtype == AIR_BF16)
-        return dm.D == 128 ? gather_launch<bf16_t, 128>(s, dm, t, l0, nl, ll, st, gx)
-                           : gather_launch<bf16_t, 64>(s, dm, t, l0, nl, ll, st, gx);
-    return dm.D == 128 ? gather_launch<float, 128>(s, dm, t, l0, nl, ll, st, gx)
-                       : gather_launch<float, 64>(s, dm, t, l0, nl, ll, st, gx);
+        return dm.D == 128 ? gather_launch<bf16_t, 128>(s, dm, t, l0, nl, ll, st, gx, stream)
+                           : gather_launch<bf16_t, 64>(s, dm, t, l0, nl, ll, st, gx, stream);
+    return dm.D == 128 ? gather_launch<float, 128>(s, dm, t, l0, nl, ll, st, gx, stream)
+                       : gather_launch<float, 64>(s, dm, t, l0, nl, ll, st, gx, stream);
 }
 
 }  // namespace air

@@ -100,3 +100,44 @@ def test_decode_column_parts_equal_one_workgroup_per_unit(dtype, d, base, batch,
     assert np.array_equal(seen[0][0], seen[1][0]) and not np.isnan(synth.storage_to_f64(seen[0][0])).any()
     for (k1, v1), (k2, v2) in zip(seen[0][1], seen[1][1]):
         assert np.array_equal(k1, k2) and np.array_equal(v1, v2)
+
+
+@pytest.mark.parametrize("dtype,d,n_layers", [("bf16", 128, 8), ("bf16", 64, 16), ("f32", 64, 8), ("f32", 128, 4)])
+def test_caches_several_times_the_memory_side_cache(dtype, d, n_layers):
+    # 660 MB of cache: loads and stores marked as used once, in the gather (retention 1: the compacted rows are the prompt's)
+    # and in every decode launch shape that has them, on sampled units
+    import numpy as np
+    import torch
+
+    import paper_2503_23956_amd as A
+    from oracle import aircache_oracle as O
+    from paper_2503_23956_amd.device_inputs import config_for, device_layer_inputs, to_device, to_host
+    from tests import parity_util as P
+
+    dev = torch.device("cuda:0")
+    shapes = [(1, 1), (1, 2), (2, 1), (4, 1), (4, 2)]  # (waves, order of the units)
+    w = synth.get_workload(3).scaled(dtype=dtype, head_dim=d, n_layers=n_layers, n_vis=2450, n_text=60, decode_steps=len(shapes))
+    seqs, L, G = w.seqs(), w.n_layers, w.group
+    q, k, v = zip(*[device_layer_inputs(w, l, seqs, dev) for l in range(L)])
+    ac = A.AirCache(config_for(w, 1.0, seqs=seqs, max_decode_steps=len(shapes)), dev)
+    ac.air_score(0, L, q, k, v, seqs)
+    ac.air_budget()
+    ac.air_select_compact(0, L, k, v)
+    units = [(0, 0, 0), (L // 2, 7, 2), (L - 1, w.batch - 1, w.n_kv_heads - 1)]
+    rows = {}
+    for (l, b, h) in units:
+        n = seqs[b].seq_len
+        rows[l, b, h] = [to_host(x[l][b, h, :n]) for x in (k, v)]
+        kk, vv = ac.air_get_cache(l, b, h, n)
+        assert np.array_equal(kk, rows[l, b, h][0]) and np.array_equal(vv, rows[l, b, h][1])
+    out = torch.empty((L, w.batch, w.n_q_heads, d), dtype=q[0].dtype, device=dev)
+    for t, (waves, order) in enumerate(shapes):
+        ac.air_set_tuning(decode_splits=1, decode_waves=waves, decode_tiles=4, decode_order=order)
+        qn, kn, vn = (np.stack(x) for x in zip(*[synth.decode_inputs(w, l, t) for l in range(L)]))
+        ac.air_decode_attn(0, L, to_device(qn, dev), to_device(kn, dev), to_device(vn, dev), out)
+        got = synth.storage_to_f64(to_host(out))
+        for (l, b, h) in units:
+            rows[l, b, h] = [np.concatenate([r, x[l, b, h][None]]) for r, x in zip(rows[l, b, h], (kn, vn))]
+            want = O.decode_attn(synth.storage_to_f64(qn[l, b, h * G:(h + 1) * G]), *(synth.storage_to_f64(r) for r in rows[l, b, h]))
+            assert np.abs(got[l, b, h * G:(h + 1) * G] - want).max() <= P.DECODE_ATOL[w.dtype], (t, l, b, h)
+    ac.close()
