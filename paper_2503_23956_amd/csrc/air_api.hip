@@ -626,7 +626,11 @@ static air_status decode_attn(air_ctx *ctx, void *stream, int32_t l0, int32_t l1
         const bool can = in_step && (hkv & (hkv - 1)) == 0 && splits == 1 && waves == 4 && tiles == decode_tiles_of(ctx->cfg);
         const int64_t units = (nl * units_per_layer + 7) & ~7;
         if (!can || ctx->tune.decode_halves == 1 || (units > 128 && ctx->tune.decode_halves != 2)) return 1;
-        int parts = ctx->cfg.head_dim == 128 ? 8 : 4;
+        // more than two parts only for caches of 640 keys on (by the prompt's own length): at 60-340 keys a unit the launch is all
+        // latency and more workgroups cost 0.4-1.4 us of it
+        const double keys = cache_bytes(ctx) / ((double)ctx->cfg.n_layers * ctx->cfg.batch * hkv * 2.0 * ctx->cfg.head_dim *
+                                                (ctx->cfg.dtype == AIR_BF16 ? 2.0 : 4.0));
+        int parts = keys < 640.0 ? 2 : (ctx->cfg.head_dim == 128 ? 8 : 4);
         while (parts > 2 && parts * units > 256) parts >>= 1;
         return parts;
     };

@@ -69,7 +69,7 @@ def test_scoring_strided_ragged_batch_layer_by_layer(dtype, d):
 @pytest.mark.parametrize("dtype,d", [("bf16", 128)] + STORAGES)
 @pytest.mark.parametrize("base,batch,n_layers", [(2, 1, 3), (2, 1, 11), (2, 1, 18), (3, 2, 5), (3, 3, 6)])
 def test_decode_column_parts_equal_one_workgroup_per_unit(dtype, d, base, batch, n_layers):
-    # 12 (eight parts), 40 and 44 (four), 72 (two) units, one sequence and ragged batches: a workgroup of a part does the same
+    # 12 (eight parts), 40 and 44 (four), 72 (two) units of ~690 keys, one sequence and ragged batches: a workgroup of a part does the same
     # arithmetic per output column, so outputs and appended rows agree bit for bit
     import numpy as np
     import torch
@@ -79,7 +79,7 @@ def test_decode_column_parts_equal_one_workgroup_per_unit(dtype, d, base, batch,
 
     dev = torch.device("cuda:0")
     steps = 34
-    w = synth.get_workload(base).scaled(dtype=dtype, head_dim=d, batch=batch, n_layers=n_layers, n_vis=400, n_text=21, decode_steps=steps)
+    w = synth.get_workload(base).scaled(dtype=dtype, head_dim=d, batch=batch, n_layers=n_layers, n_vis=1800, n_text=221, decode_steps=steps)
     seqs, L = w.seqs(), w.n_layers
     layers = [synth.layer_inputs(w, l, seqs) for l in range(L)]
     q, k, v = ([to_device(getattr(li, name), dev) for li in layers] for name in ("q_text", "k", "v"))
