@@ -202,6 +202,9 @@ __global__ __launch_bounds__(64 * NW) void decode_mfma_kernel(Dims dm, DecodeTab
     // of the unit has read it
     int appended = ll.uniform >= 0 ? ll.uniform : ll.appended[li];
     if (t.dec_steps) {
+        // a workgroup past the last unit is not counted at the unit's arrival counter: the count it would read may already be the
+        // next step's, and with it a cache that only looks full
+        if (VH > 1 && !live) return;
         appended = t.dec_steps[unit];
         if (appended >= dm.max_steps) {  // cache full: nothing is appended or written
             if (threadIdx.x == 0) t.dec_steps[t.n_units] = 1;

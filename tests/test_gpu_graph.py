@@ -180,3 +180,40 @@ def test_layers_out_of_step_in_one_call():
     assert np.array_equal(la, lb) and appended.tolist() == [2, 1, 1]
     one.close()
     ref.close()
+
+
+def test_last_permitted_step_on_a_busy_gpu_raises_no_flag():
+    """A launch of one unit in eight column parts has 56 workgroups past the last unit.  They start late where other work
+    fills the GPU, after the unit's own workgroups have counted the step: what they do must not depend on the count."""
+    import torch
+
+    import paper_2503_23956_amd as A
+    from paper_2503_23956_amd.device_inputs import config_for, to_device
+
+    dev = torch.device("cuda:0")
+    w = synth.get_workload(2).scaled(n_layers=1, n_q_heads=7, n_kv_heads=1, n_vis=700, n_text=24, decode_steps=1)
+    seqs = w.seqs()
+    li = synth.layer_inputs(w, 0, seqs)
+    q, k, v = ([to_device(x, dev)] for x in (li.q_text, li.k, li.v))
+    qn, kn, vn = (to_device(x[None], dev) for x in synth.decode_inputs(w, 0, 0))
+    out = torch.empty((1, 1, 7, w.head_dim), dtype=torch.bfloat16, device=dev)
+    ac = A.AirCache(config_for(w, 1.0, max_decode_steps=1, seqs=seqs, device_steps=1), dev)
+    other = torch.cuda.Stream()
+    a = torch.randn(2048, 2048, device=dev, dtype=torch.bfloat16)
+    want = seqs[0].seq_len + 1
+    first = None
+    for _ in range(60):
+        ac.air_reset()
+        ac.air_score(0, 1, q, k, v, seqs)
+        ac.air_budget()
+        ac.air_select_compact(0, 1, k, v)
+        with torch.cuda.stream(other):
+            for _ in range(4):
+                b = a @ a
+        ac.air_decode_attn(0, 1, qn, kn, vn, out)  # the first step is the last that the cache has room for
+        torch.cuda.synchronize()
+        assert ac.air_get_lengths().tolist() == [[want]]
+        first = out.clone() if first is None else first
+        assert torch.equal(out, first)
+    del b
+    ac.close()
