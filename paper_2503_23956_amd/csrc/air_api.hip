@@ -603,8 +603,11 @@ static air_status decode_attn(air_ctx *ctx, void *stream, int32_t l0, int32_t l1
     // counts travel with the launch, kMaxLayersPerLaunch layers at a time.
     bool in_step = true;
     for (int l = l0 + 1; l < l1 && in_step; ++l) in_step = ctx->appended[l] == ctx->appended[l0];
+    // (So are the storages beside bf16 with heads of 128 elements under a split that the caller has forced: what the static
+    // exchange area must hold is then that of kMaxLayersPerLaunch layers, however many the call has.)
     const int64_t units_per_layer = (int64_t)ctx->dm.B * ctx->dm.Hkv;
-    const int max_nl = in_step ? (int)(65535 / units_per_layer) : layers_per_launch(ctx);  // grid.y <= 65535
+    const bool any_layers = in_step && (v_transposed(ctx->cfg.dtype, ctx->cfg.head_dim) || ctx->tune.decode_splits <= 1);
+    const int max_nl = any_layers ? (int)(65535 / units_per_layer) : layers_per_launch(ctx);  // grid.y <= 65535
     // launch shapes first: a static exchange area that is too small must be found before anything is launched
     auto shape_of = [&](int c0, int nl, int *splits, int *waves, int *tiles) {
         // a recorded launch is replayed at every cache length: its shape is chosen for the middle of the decode
@@ -638,8 +641,7 @@ static air_status decode_attn(air_ctx *ctx, void *stream, int32_t l0, int32_t l1
         const int nl = (l1 - c0 < max_nl) ? l1 - c0 : max_nl;
         int splits = 1, waves = 1, tiles = 4;
         shape_of(c0, nl, &splits, &waves, &tiles);
-        const bool exchanges = splits > 1 || !v_transposed(ctx->cfg.dtype, ctx->cfg.head_dim);  // refused for the other storages whatever the splits
-        if (exchanges && (int64_t)nl * units_per_layer * splits > (int64_t)kStaticSlots)
+        if (splits > 1 && (int64_t)nl * units_per_layer * splits > (int64_t)kStaticSlots)
             return fail(ctx, AIR_ERR_SHAPE, "air_decode_attn_static: the launch needs " +
                                                 std::to_string((int64_t)nl * units_per_layer * splits) +
                                                 " (unit, split) exchange slots, the static area holds " +

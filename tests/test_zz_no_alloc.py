@@ -122,3 +122,30 @@ def test_static_entry_point_refuses_what_its_fixed_area_cannot_hold():
     assert torch.equal(out_r, out_s)
     ref.close()
     stat.close()
+
+
+@pytest.mark.parametrize("dtype,d", [("f32", 64), ("bf16", 64), ("f32", 128)])
+@pytest.mark.parametrize("n_layers,batch,heads,tuning", [
+    (80, 2, 8, {}),                       # 1280 units, one workgroup each: nothing is exchanged, nothing limits the call
+    (80, 2, 8, dict(decode_splits=2)),    # launches of 32 layers: 512 units of two splits fill the area
+    (34, 6, 8, dict(decode_splits=1)),    # more than 1024 units in 32 layers
+])
+def test_static_entry_point_takes_many_layers_of_the_other_storages(dtype, d, n_layers, batch, heads, tuning):
+    import torch
+
+    from paper_2503_23956_amd.device_inputs import to_device
+
+    dev = torch.device("cuda:0")
+    w = synth.get_workload(3).scaled(dtype=dtype, head_dim=d, batch=batch, n_layers=n_layers, n_q_heads=heads, n_kv_heads=heads,
+                                     n_vis=70, n_text=5, decode_steps=2, jitter=0.0)
+    ref, stat = _compressed_pair(w, dev, tuning)
+    out_r = torch.zeros((n_layers, batch, heads, d), dtype=torch.bfloat16 if dtype == "bf16" else torch.float32, device=dev)
+    out_s = torch.ones_like(out_r)
+    for step in range(2):
+        ins = [to_device(np.stack(x), dev) for x in zip(*[synth.decode_inputs(w, l, step) for l in range(n_layers)])]
+        ref.air_decode_attn(0, n_layers, *ins, out_r)
+        stat.air_decode_attn_static(0, n_layers, *ins, out_s)
+        torch.cuda.synchronize()
+        assert torch.equal(out_r, out_s) and not torch.isnan(out_s.float()).any()
+    ref.close()
+    stat.close()
