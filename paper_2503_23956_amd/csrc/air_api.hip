@@ -124,12 +124,12 @@ struct air_ctx {
     std::vector<char> scored, compacted, fixed_idx;  // fixed_idx: the layer's kept indices were set by the caller
     std::vector<int32_t> appended;
     air_tuning tune;  // launch-shape overrides (air_set_tuning); all automatic after air_create
-    std::vector<CachePtrs> ip_layers;
+    std::vector<CachePtrs> ip_layers;  // in-place cache: the K / V tensor each compacted layer lives in
     // Eq.11 done in the tail of air_score (Dims::fuse_budget): layers scored that way since the reset; broken: a layer was
-    // scored twice or with the fusion switched off, so air_budget launches its kernel; need_zero: the per-sequence
-    // arrival counters may hold a partial count and are cleared in front of the next air_score
+    // scored twice or with the fusion switched off, or the caller set budgets, so air_budget launches its kernel; need_zero:
+    // the per-sequence arrival counters may hold a partial count and are cleared in front of the next air_score
     int fused_count = 0;
-    bool fused_broken = false, need_zero = false;  // in-place cache: the K / V tensor each compacted layer lives in
+    bool fused_broken = false, need_zero = false;
     std::string err;
 };
 
@@ -342,6 +342,12 @@ air_status air_score(air_ctx *ctx, void *stream, int32_t l0, int32_t l1, const a
         if (e != hipSuccess) return hip_fail(ctx, e, "air_score: clearing the arrival counters");
         ctx->need_zero = false;
     }
+    // A layer that is scored again, or budgets that the caller has set (air_set_budgets): the tail of the last kernel must
+    // not write budgets and layout tables any more, air_budget launches its kernel for the prompt
+    for (int l = l0; l < l1; ++l)
+        if (ctx->scored[l]) ctx->fused_broken = true;
+    Dims dm = ctx->dm;
+    if (ctx->fused_broken) dm.fuse_budget = 0;
     const int lpl = layers_per_launch(ctx);
     int group = lpl;
     // The elite window (alpha > 0) leaves a unit a handful of rows: the finish kernel forms their
@@ -370,9 +376,9 @@ air_status air_score(air_ctx *ctx, void *stream, int32_t l0, int32_t l1, const a
             ll.p[i].k = layers[c0 - l0 + i].k;
             ll.p[i].v = layers[c0 - l0 + i].v;
         }
-        hipError_t e = ctx->dm.vis_window ? launch_window_rows(s, ctx->dm, ctx->tab, c0, nl, sa)
-                       : dt == AIR_BF16   ? launch_elite_mfma(s, ctx->dm, ctx->tab, c0, nl, ll, *strides, sa, ctx->cfg.alpha)
-                                          : launch_elite(s, ctx->dm, ctx->tab, c0, nl, ll, *strides, sa, ctx->cfg.alpha);
+        hipError_t e = dm.vis_window ? launch_window_rows(s, dm, ctx->tab, c0, nl, sa)
+                       : dt == AIR_BF16   ? launch_elite_mfma(s, dm, ctx->tab, c0, nl, ll, *strides, sa, ctx->cfg.alpha)
+                                          : launch_elite(s, dm, ctx->tab, c0, nl, ll, *strides, sa, ctx->cfg.alpha);
         // stream kernel, then finish kernel, per group of layers (one group unless the
         // window is known to need the second read of K_v)
         for (int g0 = 0; e == hipSuccess && g0 < nl; g0 += group) {
@@ -381,9 +387,9 @@ air_status air_score(air_ctx *ctx, void *stream, int32_t l0, int32_t l1, const a
             memset(&lg, 0, sizeof(lg));
             for (int i = 0; i < gn; ++i) lg.p[i] = ll.p[g0 + i];
             for (int pass = 1; pass <= 2 && e == hipSuccess; ++pass)
-                e = dt != AIR_BF16 ? launch_score_f32(s, ctx->dm, ctx->tab, pass, c0 + g0, gn, lg, *strides, sa)
-                    : many_rows    ? launch_score_window(s, ctx->dm, ctx->tab, pass, c0 + g0, gn, lg, *strides, sa)
-                                   : launch_score_mfma(s, ctx->dm, ctx->tab, pass, c0 + g0, gn, lg, *strides, sa, inline_rows);
+                e = dt != AIR_BF16 ? launch_score_f32(s, dm, ctx->tab, pass, c0 + g0, gn, lg, *strides, sa)
+                    : many_rows    ? launch_score_window(s, dm, ctx->tab, pass, c0 + g0, gn, lg, *strides, sa)
+                                   : launch_score_mfma(s, dm, ctx->tab, pass, c0 + g0, gn, lg, *strides, sa, inline_rows);
         }
         if (e != hipSuccess) return hip_fail(ctx, e, "air_score launch");
     }
@@ -391,11 +397,9 @@ air_status air_score(air_ctx *ctx, void *stream, int32_t l0, int32_t l1, const a
         ctx->seqs.assign(seqs, seqs + ctx->cfg.batch);
         ctx->have_seqs = true;
     }
-    for (int l = l0; l < l1; ++l) {
-        if (ctx->scored[l] || !ctx->dm.fuse_budget) ctx->fused_broken = true;
-        ctx->scored[l] = 1;
-    }
-    if (ctx->dm.fuse_budget) ctx->fused_count += l1 - l0;
+    for (int l = l0; l < l1; ++l) ctx->scored[l] = 1;
+    if (dm.fuse_budget) ctx->fused_count += l1 - l0;
+    else ctx->fused_broken = true;
     ctx->budgets_ready = false;
     return AIR_OK;
 }
@@ -806,6 +810,7 @@ air_status air_set_budgets(air_ctx *ctx, const int32_t *host) {
                                            ctx->cfg.min_keep, 1, sa);
     if (e == hipSuccess) e = hipDeviceSynchronize();
     if (e != hipSuccess) return hip_fail(ctx, e, "air_set_budgets");
+    ctx->fused_broken = true;  // the tables hold the caller's budgets from here on, not what air_score's tail left
     ctx->fixed_idx.assign(ctx->dm.L, 0);
     ctx->budgets_ready = true;
     return AIR_OK;

@@ -917,3 +917,50 @@ def test_skewness_of_rows_with_little_or_no_spread(base, n_vis, batch):
     print(f"[low spread base={base}] s_k gpu {np.round(g_sk[0], 6).tolist()} oracle {np.round(o_sk[0], 6).tolist()} "
           f"budgets {g_bud[0].tolist()}", flush=True)
     ac.close()
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("f32", 64)])
+def test_budgets_computed_again_after_the_caller_set_some(dtype, d):
+    """air_budget after air_set_budgets gives Eq.11's budgets back, and a layer scored after another one was compacted on
+    the caller's budgets leaves that layer's cache where it is (the allocation in the tail of scoring must not run)."""
+    import torch
+
+    import paper_2503_23956_amd as A
+    from paper_2503_23956_amd.device_inputs import config_for, to_device
+
+    dev = torch.device("cuda:0")
+    w = synth.get_workload(2).scaled(dtype=dtype, head_dim=d, n_layers=2, n_vis=700, n_text=24, decode_steps=1)
+    seqs, L = w.seqs(), w.n_layers
+    layers = [synth.layer_inputs(w, l, seqs) for l in range(L)]
+    q, k, v = ([to_device(getattr(li, name), dev) for li in layers] for name in ("q_text", "k", "v"))
+    ac = A.AirCache(config_for(w, 0.10, seqs=seqs, max_decode_steps=1), dev)
+    ac.air_score(0, L, q, k, v, seqs)
+    ac.air_budget()
+    want, stats = ac.air_get_budgets(), ac.air_get_stats()
+    ac.air_set_budgets(want - want // 2)
+    ac.air_budget()
+    assert np.array_equal(ac.air_get_budgets(), want)
+    assert all(np.array_equal(x, y) for x, y in zip(ac.air_get_stats(), stats))
+    ac.air_set_budgets(want - want // 2)
+    ac.air_score(0, L, q, k, v, seqs)
+    ac.air_budget()
+    ac.air_select_compact(0, L, k, v)
+    assert np.array_equal(ac.air_get_budgets(), want)
+
+    ins = [to_device(np.stack(x), dev) for x in zip(*[synth.decode_inputs(w, l, 0) for l in range(L)])]
+    outs, rows = [], []
+    for score_the_other in (False, True):
+        ac.air_reset()
+        ac.air_score(1, 2, q[1:], k[1:], v[1:], seqs)
+        ac.air_set_budgets(np.array([[3, 20]], dtype=np.int32))
+        ac.air_select_compact(1, 2, k[1:], v[1:])
+        if score_the_other:
+            ac.air_score(0, 1, q[:1], k[:1], v[:1], seqs)
+        out = torch.empty((1, 1, w.n_q_heads, d), dtype=q[0].dtype, device=dev)
+        ac.air_decode_attn(1, 2, *(x[1:] for x in ins), out)
+        outs.append(out)
+        rows.append(ac.air_get_cache(1, 0, 0, seqs[0].seq_len - seqs[0].vis_len + 21))
+    torch.cuda.synchronize()
+    assert torch.equal(*outs)
+    assert all(np.array_equal(x, y) for x, y in zip(*rows))
+    ac.close()
