@@ -139,6 +139,13 @@ __global__ __launch_bounds__(64 * NW) void decode_mfma_kernel(Dims dm, DecodeTab
     constexpr int kColsPer = kCols > 64 ? kCols / 64 : 1;  // columns of the appended V' row per lane (lanes < kCols)
     static_assert(kIter % kVTok == 0 && kCols >= 16, "whole V' blocks per iteration, whole output tiles");
     static_assert(VH == 1 || (!SPLIT && !SORTED), "column parts: VH workgroups per unit, no exchange");
+    // Non-finite values.  A logit of -inf weighs nothing, also in a chunk that has no other (its head then has no reference
+    // yet); an infinite element of V' makes its output column infinite: every factor of V' is at least kLeast, also the one
+    // of the last block read again behind the last key, whose infinities are in the column anyway (0 * inf would be NaN; of
+    // finite elements it adds 1e-38).  bf16 with heads of 128 elements goes without: such a chunk, or an infinite element
+    // in the last block, gives NaN there.
+    constexpr bool kNonFinite = sizeof(T) == 4 || D == 64;
+    constexpr float kLeast = 0x1p-126f;
     const int lane = threadIdx.x & 63, n = lane & 15, c = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // a scalar: the wave's chunk walk and its branches stay off the vector unit
     // grid (split + splits * KV head, sequence, layer): the linear order of the workgroups is (split, unit) and
@@ -350,8 +357,9 @@ __global__ __launch_bounds__(64 * NW) void decode_mfma_kernel(Dims dm, DecodeTab
         if (__ballot(mloc > m_run + kSlack) != 0ull) {  // uniform over the wave; always taken on a wave's first chunk
             float mb = fmaxf(mloc, __shfl_xor(mloc, 16, 64));
             mb = fmaxf(mb, __shfl_xor(mb, 32, 64));
-            const float m_new = fmaxf(m_run, mb);  // finite: key kb is valid
-            const float corr = __builtin_amdgcn_exp2f(m_run - m_new);
+            const float m_new = fmaxf(m_run, mb);  // finite for finite logits: key kb is valid
+            float corr = __builtin_amdgcn_exp2f(m_run - m_new);
+            if (kNonFinite && m_new == -INFINITY) corr = 1.0f;  // this head has seen logits of -inf only: its sums are zero
             l_run *= corr;
             m_run = m_new;
             // accumulator rows are heads 4c..4c+3: fetch their rescale factors from lanes 4c+i
@@ -364,15 +372,16 @@ __global__ __launch_bounds__(64 * NW) void decode_mfma_kernel(Dims dm, DecodeTab
                 }
             }
         }
+        const float m_ref = kNonFinite && m_run == -INFINITY ? 0.f : m_run;
         float lb = 0.f;
 #pragma unroll
         for (int tile = 0; tile < KT; ++tile)
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                float x = fmaf(s[tile][i], kScale2, -m_run);
+                float x = fmaf(s[tile][i], kScale2, -m_ref);
                 if (sizeof(T) == 4) x = fmaf(s[tile][i], kScale2Lo, x);
                 const float p = __builtin_amdgcn_exp2f(x);
-                s[tile][i] = p;
+                s[tile][i] = kNonFinite ? fmaxf(p, kLeast) : p;
                 lb += p;
             }
         l_run += lb;
@@ -383,18 +392,29 @@ __global__ __launch_bounds__(64 * NW) void decode_mfma_kernel(Dims dm, DecodeTab
 #pragma unroll
                 for (int j = 0; j < NJ; ++j) acc[j] = mma<T>(__builtin_bit_cast(uint4, s[tb]), vb[tb][j], acc[j]);
             } else {
-                // bf16 operands.  Heads of 128 elements take the probabilities rounded to bf16; with heads of 64 they keep
-                // their 24 bits, as three bf16 terms (the matrix unit is idle most of the time: two more products a tile)
+                // bf16 operands.  Heads of 128 elements take the probabilities rounded to bf16; with heads of 64 they keep their
+                // 24 bits, as three bf16 terms of 8, cut off, not rounded, so that none is negative (the matrix unit is idle most
+                // of the time: two more products a tile)
                 constexpr int kTerms = D == 128 ? 1 : 3;
                 bf16x8 pa[kTerms];
+                if constexpr (kTerms == 1) {
 #pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    float p = s[2 * tb + (i >> 2)][i & 3];
+                    for (int i = 0; i < 8; ++i) pa[0][i] = (__bf16)s[2 * tb + (i >> 2)][i & 3];
+                } else {
+                    u32x4 term[kTerms];
 #pragma unroll
-                    for (int k = 0; k < kTerms; ++k) {
-                        pa[k][i] = (__bf16)p;
-                        if (k + 1 < kTerms) p -= (float)pa[k][i];
+                    for (int w = 0; w < 4; ++w) {
+                        float p0 = s[2 * tb + (w >> 1)][2 * (w & 1)], p1 = s[2 * tb + (w >> 1)][2 * (w & 1) + 1];
+#pragma unroll
+                        for (int k = 0; k < kTerms; ++k) {
+                            const uint32_t t0 = __float_as_uint(p0) & 0xffff0000u, t1 = __float_as_uint(p1) & 0xffff0000u;
+                            term[k][w] = (t0 >> 16) | t1;
+                            p0 = fmaxf(p0 - __uint_as_float(t0), kLeast);
+                            p1 = fmaxf(p1 - __uint_as_float(t1), kLeast);
+                        }
                     }
+#pragma unroll
+                    for (int k = 0; k < kTerms; ++k) pa[k] = __builtin_bit_cast(bf16x8, term[k]);
                 }
 #pragma unroll
                 for (int k = kTerms - 1; k >= 0; --k)

@@ -141,3 +141,59 @@ def test_caches_several_times_the_memory_side_cache(dtype, d, n_layers):
             want = O.decode_attn(synth.storage_to_f64(qn[l, b, h * G:(h + 1) * G]), *(synth.storage_to_f64(r) for r in rows[l, b, h]))
             assert np.abs(got[l, b, h * G:(h + 1) * G] - want).max() <= P.DECODE_ATOL[w.dtype], (t, l, b, h)
     ac.close()
+
+
+@pytest.mark.parametrize("dtype,d", STORAGES)
+@pytest.mark.parametrize("splits,waves,halves", [(1, 1, 1), (1, 4, 1), (1, 8, 1), (4, 4, 1), (1, 4, 2)])
+def test_infinite_values_and_masked_runs_of_keys(dtype, d, splits, waves, halves):
+    # K': the first 70 rows have logits of -inf (whole chunks of every launch shape); V': infinite elements in the first block,
+    # in the last one (which the tail of a chunk reads again) and in appended tokens, next to finite columns
+    import numpy as np
+    import torch
+
+    import paper_2503_23956_amd as A
+    from oracle import aircache_oracle as O
+    from paper_2503_23956_amd.device_inputs import config_for, to_device, to_host
+    from tests import parity_util as P
+
+    dev = torch.device("cuda:0")
+    steps = 3
+    w = _workload(dtype, d, n_layers=1, n_sys=80, n_vis=400, n_text=21, decode_steps=steps)
+    seqs, G = w.seqs(), w.group
+    n0 = seqs[0].vis_start + seqs[0].vis_len
+    li = synth.layer_inputs(w, 0, seqs)
+    q, k, v = (to_device(x, dev) for x in (li.q_text, li.k, li.v))
+    k[:, :, :70, 0] = -np.inf
+    v[:, :, 3, 1] = np.inf
+    v[:, 1, 75, 2] = -np.inf
+    v[:, :, n0 + 20, 5] = -np.inf  # the last text token: the last row of the cache
+    v[:, :, 40, 7] = np.inf        # a row of zero weight: its column is infinite or no number
+    ac = A.AirCache(config_for(w, 0.25, seqs=seqs, max_decode_steps=steps), dev)
+    ac.air_set_tuning(decode_splits=splits, decode_waves=waves, decode_halves=halves)
+    ac.air_score(0, 1, [q], [k], [v], seqs)
+    ac.air_budget()
+    ac.air_select_compact(0, 1, [k], [v])
+    out = torch.empty((1, 1, w.n_q_heads, d), dtype=q.dtype, device=dev)
+    for t in range(steps):
+        qn, kn, vn = (to_device(x, dev)[None] for x in synth.decode_inputs(w, 0, t))
+        qn[..., 0] = 1.0
+        vn[..., 9 + t] = np.inf
+        ac.air_decode_attn(0, 1, qn, kn, vn, out)
+        got = synth.storage_to_f64(to_host(out))[0, 0]
+        q64 = synth.storage_to_f64(to_host(qn))[0, 0]
+        n = int(ac.air_get_lengths()[0, 0])
+        for h in range(w.n_kv_heads):
+            kk, vv = (synth.storage_to_f64(x) for x in ac.air_get_cache(0, 0, h, n))
+            assert np.isneginf(kk[:70, 0]).all() and np.isfinite(kk[70:]).all()
+            kk, vv, zero = kk[70:], vv[70:], vv[:70]
+            want = O.decode_attn(q64[h * G:(h + 1) * G], kk, np.where(np.isfinite(vv), vv, 0.0))
+            for col in range(d):
+                x = got[h * G:(h + 1) * G, col]
+                inf = vv[~np.isfinite(vv[:, col]), col]
+                if len(inf):
+                    assert (x == inf[0]).all(), (t, h, col, x)
+                elif np.isfinite(zero[:, col]).all():
+                    assert np.abs(x - want[:, col]).max() <= P.DECODE_ATOL[w.dtype], (t, h, col)
+                else:
+                    assert not np.isfinite(x).any()
+    ac.close()
