@@ -243,10 +243,11 @@ __global__ __launch_bounds__(64 * NW) void decode_mfma_kernel(Dims dm, DecodeTab
         for (int s = 0; s < NS; ++s) qb[s] = *reinterpret_cast<const uint4 *>(q + Elem<T>::kSlice * s + kVec * c);
     }
     constexpr double kScale2D = (D == 128 ? 0.08838834764831845 : 0.125) * 1.4426950408889634;  // log2(e) / sqrt(d)
-    // fp32 takes it to 46 bits; the second term is not negative, so that a masked score stays -inf
-    constexpr float kScale2 = (float)(sizeof(T) == 4 ? kScale2D * (1.0 - 1.2e-7) : kScale2D);
+    // fp32 and heads of 64 elements take it to 46 bits; the second term is positive, so that a masked score stays -inf
+    constexpr bool kTwoTerm = sizeof(T) == 4 || D == 64;
+    constexpr float kScale2 = (float)(kTwoTerm ? kScale2D * (1.0 - 1.2e-7) : kScale2D);
     constexpr float kScale2Lo = (float)(kScale2D - (double)kScale2);
-    static_assert(sizeof(T) == 2 || kScale2Lo >= 0.f, "sign of the second term");
+    static_assert(!kTwoTerm || kScale2Lo > 0.f, "sign of the second term");
     float m_run = -INFINITY, l_run = 0.f;
     f32x4 acc[NJ];
 #pragma unroll
@@ -257,8 +258,8 @@ __global__ __launch_bounds__(64 * NW) void decode_mfma_kernel(Dims dm, DecodeTab
     // loads: K' into its places of the tile, V' into its slot of the block (a token that opens a
     // block writes the block's other slots as zeros).  Other waves and splits never use these
     // places in this launch: their reads of them are masked or carry zero probability.  The
-    // token's own score (vector ALU) starts the wave's running softmax: max = score, sum = 1,
-    // accumulator = v_new for every head.
+    // token's own score (vector ALU) starts the wave's running softmax: max = score, sum = its weight against that maximum,
+    // formed as a cached key's is (1, but for the rounding of the maximum), accumulator = that times v_new for every head.
     const bool owns_new = newrow >= k0 && newrow < k1 && wave == ((kend - k0 + kIter - 1) / kIter) % NW;
     if (owns_new) {
         if (lane < kPieces && vh == 0)  // the new K' row: 16 bytes a lane
@@ -286,11 +287,17 @@ __global__ __launch_bounds__(64 * NW) void decode_mfma_kernel(Dims dm, DecodeTab
         sn += __shfl_xor(sn, 16, 64);
         sn += __shfl_xor(sn, 32, 64);
         m_run = sn * kScale2;
-        l_run = c == 0 ? 1.f : 0.f;  // l_run is a per-lane partial of the head's sum: the token counts once
+        float p = 1.f;
+        if constexpr (kTwoTerm) {
+            p = __builtin_amdgcn_exp2f(fmaf(sn, kScale2Lo, fmaf(sn, kScale2, -m_run)));
+            if (m_run == -INFINITY) p = 0.f;
+        }
+        l_run = c == 0 ? p : 0.f;  // l_run is a per-lane partial of the head's sum: the token counts once
 #pragma unroll
         for (int j = 0; j < NJ; ++j) {
             const float v = ldf(&vnew[j]);
-            acc[j] = (f32x4){v, v, v, v};
+#pragma unroll
+            for (int i = 0; i < 4; ++i) acc[j][i] = kTwoTerm ? v * __shfl(p, 4 * c + i, 64) : v;  // rows are heads 4c..4c+3
         }
     }
 
@@ -379,7 +386,7 @@ __global__ __launch_bounds__(64 * NW) void decode_mfma_kernel(Dims dm, DecodeTab
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 float x = fmaf(s[tile][i], kScale2, -m_ref);
-                if (sizeof(T) == 4) x = fmaf(s[tile][i], kScale2Lo, x);
+                if (kTwoTerm) x = fmaf(s[tile][i], kScale2Lo, x);
                 const float p = __builtin_amdgcn_exp2f(x);
                 s[tile][i] = kNonFinite ? fmaxf(p, kLeast) : p;
                 lb += p;

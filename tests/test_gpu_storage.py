@@ -197,3 +197,35 @@ def test_infinite_values_and_masked_runs_of_keys(dtype, d, splits, waves, halves
                 else:
                     assert not np.isfinite(x).any()
     ac.close()
+
+
+@pytest.mark.parametrize("dtype,d", STORAGES)
+@pytest.mark.parametrize("q0,k0", [(8.0, 37.0), (8.0, -37.0), (64.0, 47.0), (-256.0, 83.0), (1024.0, 997.0), (1024.0, -771.0)])
+def test_appended_token_weighs_what_a_cached_key_of_the_same_logit_does(dtype, d, q0, k0):
+    # every key the same: the weights are equal however large the logit (up to 1e6 before the scale), so that with values of 0
+    # and 1 the output is the appended token's share of the cache
+    import numpy as np
+    import torch
+
+    import paper_2503_23956_amd as A
+    from paper_2503_23956_amd.device_inputs import config_for, to_device, to_host
+
+    dev = torch.device("cuda:0")
+    w = _workload(dtype, d, n_layers=1, n_sys=5, n_vis=90, n_text=11, decode_steps=1)
+    seqs = w.seqs()
+    q, k, v = (torch.zeros_like(to_device(x, dev)) for x in (lambda li: (li.q_text, li.k, li.v))(synth.layer_inputs(w, 0, seqs)))
+    k[..., 0] = k0
+    qn, kn, vn = (torch.zeros_like(to_device(x, dev)[None]) for x in synth.decode_inputs(w, 0, 0))
+    qn[..., 0], kn[..., 0], vn[:] = q0, k0, 1.0
+    for splits, waves, halves in [(1, 1, 1), (1, 4, 1), (4, 4, 1), (1, 4, 2)]:
+        ac = A.AirCache(config_for(w, 1.0, seqs=seqs, max_decode_steps=1), dev)
+        ac.air_set_tuning(decode_splits=splits, decode_waves=waves, decode_halves=halves)
+        ac.air_score(0, 1, [q], [k], [v], seqs)
+        ac.air_budget()
+        ac.air_select_compact(0, 1, [k], [v])
+        out = torch.empty((1, 1, w.n_q_heads, d), dtype=q.dtype, device=dev)
+        ac.air_decode_attn(0, 1, qn, kn, vn, out)
+        share = synth.storage_to_f64(to_host(out)) * (seqs[0].seq_len + 1)
+        # fp32: 107 equal addends, each partial sum rounded; bf16: the output's rounding
+        assert np.abs(share - 1.0).max() <= (2e-6 if dtype == "f32" else 2.0 ** -8), (splits, waves, halves, share.min(), share.max())
+        ac.close()
