@@ -458,13 +458,19 @@ __global__ __launch_bounds__(256, 4) void score_finish_kernel(Dims dm, DevTables
 //   phase 1: raw last-row logits of the G heads against every candidate text key on MFMA
 //            (fp32 accumulation), into LDS.
 //   phase 2: one wave per head.  Eq.5 is decided as the fp64 test exp((a_j - a_max)/sqrt(d)) >= alpha.
-//            The fp32 logits settle every candidate that is not within kEliteMargin of the
+//            The fp32 logits settle every candidate that is not within a margin of the
 //            threshold; the maximum and the few candidates inside the margin are recomputed as
 //            exact fp64 dot products (bf16 products are exact, the sum is fp64) before deciding.
+//            The margin is what an fp32 sum of D products can be off by, D 2^-23 of the sum of their
+//            magnitudes (the largest over the head's candidates, formed on MFMA from the operands without
+//            their signs), and kEliteMargin at least.
 //            Then the ordered compaction of the elite positions and the elite-text columns of Eq.7.
 // ---------------------------------------------------------------------------------------
 constexpr int kEliteWaves = 8;      // phase 2 takes one head per wave
-constexpr float kEliteMargin = 4e-3f;  // raw-logit units; fp32 accumulation of 128 bf16 products of this size errs by < 1e-3
+constexpr float kEliteMargin = 4e-3f;  // raw-logit units
+__device__ __forceinline__ uint4 magnitudes(const uint4 &x) {  // of eight bf16 elements
+    return make_uint4(x.x & 0x7fff7fffu, x.y & 0x7fff7fffu, x.z & 0x7fff7fffu, x.w & 0x7fff7fffu);
+}
 
 template <int D>
 __device__ __forceinline__ double dot64_wave(const bf16_t *a, const bf16_t *b, int lane) {
@@ -497,6 +503,7 @@ __global__ __launch_bounds__(64 * kEliteWaves) void elite_mfma_kernel(Dims dm, D
     constexpr int NS = D / 32;
     constexpr double inv_sqrt_d = D == 128 ? 0.08838834764831845 : 0.125;  // 1 / sqrt(d), correctly rounded
     constexpr float scale = (float)inv_sqrt_d;
+    __shared__ float s_size[16][kEliteWaves];  // per head of the round: a wave's largest sum of magnitudes
 
     for (int g0 = 0; g0 < G; g0 += gb) {
         const int ng = min(gb, G - g0);
@@ -510,6 +517,7 @@ __global__ __launch_bounds__(64 * kEliteWaves) void elite_mfma_kernel(Dims dm, D
                 if (n < ng) qa[sl] = *reinterpret_cast<const uint4 *>(qr + 32 * sl + 8 * c);
             }
         }
+        f32x4 size = (f32x4){0.f, 0.f, 0.f, 0.f};
         for (int j0 = wave * 16; j0 < wl; j0 += 16 * kEliteWaves) {
             const int j = j0 + n;
             uint4 kb[NS];
@@ -522,9 +530,20 @@ __global__ __launch_bounds__(64 * kEliteWaves) void elite_mfma_kernel(Dims dm, D
 #pragma unroll
             for (int sl = 0; sl < NS; ++sl)
                 s4 = mma<bf16_t>(qa[sl], kb[sl], s4);
+            f32x4 a4 = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+            for (int sl = 0; sl < NS; ++sl)
+                a4 = mma<bf16_t>(magnitudes(qa[sl]), magnitudes(kb[sl]), a4);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
                 if (4 * c + i < ng && j < wl) s_logit[(size_t)(4 * c + i) * W + j] = s4[i];
+                size[i] = fmaxf(size[i], a4[i]);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float x = max16(size[i]);
+            if (n == 0) s_size[4 * c + i][wave] = x;
         }
         __syncthreads();
         // ---- phase 2
@@ -535,14 +554,21 @@ __global__ __launch_bounds__(64 * kEliteWaves) void elite_mfma_kernel(Dims dm, D
             int *elite = s_elite + (size_t)hh * W;
             const bf16_t *q = qb + (int64_t)h * st.q_h;
             const bf16_t *qref = q + (int64_t)(ref - t0) * st.q_t;
+            // What an fp32 logit of this head can be off by: infinite where operands overflow, every candidate is then decided in
+            // fp64; a logit that is no number is whatever the margin (the comparisons below are negated).
+            float err = 0.f;
+#pragma unroll
+            for (int w = 0; w < kEliteWaves; ++w) err = fmaxf(err, s_size[hh][w]);
+            err *= D * 0x1p-23f;
+            const float margin = fmaxf(kEliteMargin, err), near_max = fmaxf(kEliteMargin, 2.f * err);
             float m32 = -INFINITY;
             for (int j = lane; j < wl; j += 64) m32 = fmaxf(m32, logit[j]);
             m32 = wave_max(m32);
-            // exact maximum: every candidate within the margin of the fp32 maximum is recomputed
+            // exact maximum: every candidate within both logits' errors of the fp32 maximum is recomputed
             double amax = -INFINITY;
             for (int j0 = 0; j0 < wl; j0 += 64) {
                 const int j = j0 + lane;
-                unsigned long long near = __ballot(j < wl && logit[j] >= m32 - kEliteMargin);
+                unsigned long long near = __ballot(j < wl && !(logit[j] < m32 - near_max));
                 while (near) {
                     const int src = __ffsll(near) - 1;
                     near &= near - 1;
@@ -555,7 +581,7 @@ __global__ __launch_bounds__(64 * kEliteWaves) void elite_mfma_kernel(Dims dm, D
                 // x > 0 <=> exp((a_j - a_max) / sqrt(d)) > alpha
                 const double x = j < wl ? ((double)logit[j] - amax) * inv_sqrt_d - ln_alpha : -1.0;
                 bool flag = j < wl && x > 0.0;
-                unsigned long long unsure = __ballot(j < wl && fabs(x) <= (double)(kEliteMargin * scale));
+                unsigned long long unsure = __ballot(j < wl && !(fabs(x) > (double)(margin * scale)));
                 while (unsure) {
                     const int src = __ffsll(unsure) - 1;
                     unsure &= unsure - 1;

@@ -1,0 +1,86 @@
+"""Eq.5 on bf16 tensors far from the usual magnitudes: the fp32 logits of the matrix unit settle what lies outside their own
+error, everything else is decided in fp64, so the elite sets are the oracle's at any size of the operands."""
+import numpy as np
+import pytest
+
+import synth
+from oracle import aircache_oracle as O
+from tests import parity_util as P
+
+pytestmark = pytest.mark.gpu
+
+
+def _bf16(x):
+    from synth.generate import f32_to_bf16_bits
+
+    return f32_to_bf16_bits(x.astype(np.float32))
+
+
+def _elite_sets(w, q, k, alpha):
+    import torch
+
+    import paper_2503_23956_amd as A
+    from paper_2503_23956_amd.device_inputs import config_for, to_device
+
+    dev = torch.device("cuda:0")
+    seqs = w.seqs()
+    ac = A.AirCache(config_for(w, 0.1, alpha=alpha, seqs=seqs, max_decode_steps=1), dev)
+    qd, kd = to_device(q, dev), to_device(k, dev)
+    ac.air_score(0, 1, [qd], [kd], [kd], seqs)
+    cnt, idx = ac.air_get_elite(0)
+    ac.close()
+    return seqs, cnt, idx
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("big", [1.0, 64.0, 2048.0, 2.0 ** 17])
+def test_elite_sets_of_large_operands_match_the_oracle(d, big):
+    # half of the elements cancel: products of size `big`^2 that fp32 sums with errors far above the spacing of the logits,
+    # which the other half spreads around the threshold
+    w = synth.get_workload(2).scaled(head_dim=d, n_layers=1, n_vis=40, n_text=300, decode_steps=1)
+    rng = np.random.default_rng(17)
+    li = synth.layer_inputs(w, 0, w.seqs())
+    q, k = (synth.storage_to_f64(x).copy() for x in (li.q_text, li.k))
+    h, m = d // 4, d // 2  # elements [0, h) cancel against [m, m + h): in different slices of the contraction
+    q[..., :h] = rng.integers(1, 4, q[..., :h].shape) * big
+    q[..., m:m + h] = q[..., :h]
+    k[..., :h] = rng.integers(-4, 5, k[..., :h].shape) * big
+    k[..., m:m + h] = -k[..., :h]
+    for lo in (h, m + h):
+        q[..., lo:lo + h] = rng.integers(-3, 4, q[..., lo:lo + h].shape) * 0.25
+        k[..., lo:lo + h] = rng.integers(-3, 4, k[..., lo:lo + h].shape) * 0.0625
+    q, k = (_bf16(x) for x in (q, k))
+    alpha = 0.9
+    seqs, cnt, idx = _elite_sets(w, q, k, alpha)
+    q64, k64 = synth.storage_to_f64(q), synth.storage_to_f64(k)
+    s = seqs[0]
+    ref, cand = s.win_start + s.win_len - 1, np.arange(s.win_start, s.win_start + s.win_len)
+    t0 = s.vis_start + s.vis_len
+    want = []
+    for hq in range(w.n_q_heads):
+        logits = O.last_row_logits(q64[0, hq, ref - t0], k64[0, hq // w.group][cand])  # every partial sum is exact in fp64
+        want.append(cand[O.elite_set(logits, alpha)])
+    P.check_elite(cnt, idx, [want], f"d={d} big={big}")
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("alpha", [0.0, 0.5])
+def test_infinite_logits(d, alpha):
+    # a candidate with a logit of -inf is in the set exactly if the threshold is 0, one that is no number never is
+    w = synth.get_workload(2).scaled(head_dim=d, n_layers=1, n_vis=40, n_text=70, decode_steps=1)
+    s = w.seqs()[0]
+    t0 = s.vis_start + s.vis_len
+    li = synth.layer_inputs(w, 0, w.seqs())
+    q, k = (synth.storage_to_f64(x).copy() for x in (li.q_text, li.k))
+    q[..., 0] = 1.0
+    k[:, :, t0 + 5, 0] = -np.inf
+    k[:, :, t0 + 33, 0] = np.nan
+    seqs, cnt, idx = _elite_sets(w, _bf16(q), _bf16(k), alpha)
+    q64, k64 = synth.storage_to_f64(_bf16(q)), synth.storage_to_f64(_bf16(k))
+    for hq in range(w.n_q_heads):
+        with np.errstate(invalid="ignore"):
+            logits = k64[0, hq // w.group, t0:] @ q64[0, hq, -1] / np.sqrt(d)
+            want = t0 + np.nonzero(np.exp(logits - np.nanmax(logits)) >= alpha)[0]
+        got = idx[0, hq, : cnt[0, hq]]
+        assert np.array_equal(got, want), (hq, got, want)
+        assert (t0 + 5 in got) == (alpha == 0.0) and t0 + 33 not in got
