@@ -319,17 +319,19 @@ __global__ __launch_bounds__(kThreads, 2) void window_kernel(Dims dm, DevTables 
     leave_moments(dm, t, u.unit, u.b, u.sq, n_wg, (nch + kFinishChunks - 1) / kFinishChunks, xs, ok, s_mom);
 }
 
-// Chunks of 256 keys per workgroup of pass 1: as many as leave the launch 1536 workgroups (two rounds of three per CU), so
-// that the rows a workgroup loads (57 KB at 224 rows) serve many keys; pass 2 takes the four chunks of a moment entry.
-static int window_seg_chunks(const Dims &dm, int nl) {
+// Chunks of 256 keys per workgroup of pass 1: as many as leave a launch over all layers 1536 workgroups (three rounds of two per
+// CU), so that the rows a workgroup loads (57 KB at 224 rows) serve many keys; pass 2 takes the four chunks of a
+// moment entry.  The run decides references and partial sums, so it follows from the context alone, not from the layers of
+// the call: the scores are the same bits however the layers are cut into calls and launches.
+static int window_seg_chunks(const Dims &dm) {
     int seg = kFinishChunks;
-    while (seg > 1 && (int64_t)((dm.n_chunks + seg - 1) / seg) * dm.Hkv * dm.B * nl < 1536) seg >>= 1;
+    while (seg > 1 && (int64_t)((dm.n_chunks + seg - 1) / seg) * dm.Hkv * dm.B * dm.L < 1536) seg >>= 1;
     return seg;
 }
 
 hipError_t launch_score_window(hipStream_t s, const Dims &dm, const DevTables &t, int pass, int l0, int nl, const LaunchLayers &ll,
                                const air_strides &st, const SeqArgs &seqs) {
-    const int seg = window_seg_chunks(dm, nl);
+    const int seg = window_seg_chunks(dm);
     const int per = pass == 1 ? seg : kFinishChunks;
     const dim3 grid((dm.n_chunks + per - 1) / per, dm.Hkv, nl * dm.B), block(kThreads);
     if (dm.D == 128) {
