@@ -3,15 +3,20 @@
 //
 // A workgroup of four waves owns a run of a unit's keys.  Every wave holds up to 64 window rows (four MFMA A operands of 16
 // rows) and all waves take the same 64 keys at a time from LDS (double-buffered, one barrier per 64 keys, the next keys
-// in flight meanwhile).  The accumulator of a logit starts at minus the row's reference, so that what comes out of the
-// matrix unit is already s - M:
-//   pass 1  leaves (reference, sum-exp) per (row, run of keys).  The reference is the lane's own: the first logit it
-//           sees, raised only when a sum stands above 2^100 (fp32 holds that without loss), so there is no
-//           maximum to find across lanes until the run is over: per element one multiplication, one exponential and
-//           one addition.
+// in flight meanwhile).  Exponentials are 2^(s kC - m): one fused multiply-add and one exponential per element, with a
+// reference m that is a whole number, so that references are moved and partial sums merged exactly.
+//   pass 1  leaves (reference, sum) per (row, run of keys).  The reference starts at the maximum over the first 64 keys of
+//           the run; a lane raises its own, and scales its sum down, after a step that left the sum above its limit: one
+//           addition per element, no maximum.
 //   pass 2  forms maximum, fp64 normaliser and weight of the unit's rows from the partials, a thread per row, then
-//           I[key] = sum over the rows of w exp(s - M): one multiplication, exponential and fused add per element, the sum over the
+//           I[key] = sum over the rows of w 2^(s kC - m): one fused add per element, the sum over the
 //           lanes and waves once per 64 keys.
+// Precision: the argument of an exponential is rounded, to 2^-24 of itself, and the largest terms are the ones that count, so a
+// reference has to stay near the maximum; and a logit keeps its bits only if its sum starts at zero.  (With sums that
+// started at minus the reference, and the lane's first logit as reference up to 2^100, the scores were 9.7e-7 off fp64 in
+// place of 4.3e-7 for logits of a spread of 5, 4.0e-6 in place of 8.7e-7 for a spread of 18, heads of 128.  The limit on a sum
+// weighs the error of the step that finds a logit far above the reference against doing it again: 2^12 / 2^16 / 2^24 / 2^100,
+// us for 224 rows at a spread of 5: 271 / 250 / 220 / 226, at a spread of 2: 222 / 220 / 218 / 224.)
 // Bound: the vector unit (16 clocks of a SIMD for 64 exponentials, 4 for each of the other instructions, counters: 83 % of
 // the clocks) with the matrix unit busy for a quarter of the time.
 // 224 rows per unit (7 heads x 32), 28 layers x 4 KV heads x 7290 keys, us for the two passes: 208 (104 each).  Before, a
@@ -29,7 +34,6 @@ constexpr int kStepKeys = 64;                 // keys in LDS at a time
 constexpr int kWaves = 4, kThreads = 64 * kWaves;
 constexpr int kWaveBlocks = 4;                 // blocks of 16 rows per wave
 constexpr int kWinRows = kWaves * kWaveBlocks * 16;  // rows of a workgroup at a time
-constexpr float kUnset = -3.0e38f;            // reference of a lane that has seen no key of its row
 
 // Keys in LDS: place p of key k holds its 16-byte piece p ^ swizzle(k), so that the sixteen keys that a read of one piece
 // touches lie in different banks.  They pass through registers: with loads straight into LDS the compiler waits for all of
@@ -39,6 +43,8 @@ __device__ __forceinline__ int key_swizzle(int key) {
     return D == 128 ? key & 15 : (key >> 1) & 7;
 }
 
+__device__ __forceinline__ int ilogb_of(float x) { return (int)(__float_as_uint(x) >> 23) - 127; }  // of a normal number above 0
+
 template <int D, int PASS>
 __global__ __launch_bounds__(kThreads, 2) void window_kernel(Dims dm, DevTables t, int l0, LaunchLayers ll, air_strides st, SeqArgs seqs,
                                                         int seg_chunks) {
@@ -46,7 +52,9 @@ __global__ __launch_bounds__(kThreads, 2) void window_kernel(Dims dm, DevTables 
     constexpr int kPieces = D / 8;               // 16-byte pieces of a key
     constexpr int kIt = kStepKeys * kPieces / kThreads;
     constexpr float kC = Log2Scale<D>::kHi;
-    constexpr float kSlackRaw = 64.0f / kC;
+    constexpr float kSumLimit = 64.0f;   // of a lane's sum in front of a step: it has at most 64 keys of a row
+    constexpr float kSumMost = 0x1p24f;  // a step that leaves a sum above this is done again
+    constexpr float kHigh = 4.0f;        // then with the reference raised in front of exponentials above 2^kHigh
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, n = lane & 15, c = lane >> 4;
     const int wg_chunks = PASS == 1 ? seg_chunks : kFinishChunks;
     UnitCtx u;
@@ -111,9 +119,9 @@ __global__ __launch_bounds__(kThreads, 2) void window_kernel(Dims dm, DevTables 
             s_query[tid] = (int64_t)(u.kvh * u.G + g) * st.q_h + (int64_t)(tok - u.qbase) * st.q_t;
             if (PASS == 2) {
                 const float2 *p = t.part + slot * dm.n_chunks;
-                const float mt = t.row_mtext[slot], zt = t.row_ztext[slot];
+                const float mt = t.row_mtext[slot], zt = t.row_ztext[slot];  // of raw logits
                 constexpr int kAtOnce = 16;  // partials requested together; a run of them past the end repeats the last one
-                float M = mt;
+                float M = rintf(mt * kC);
                 double Z = 0.0;
                 for (int pass = n_seg <= kAtOnce ? 1 : 0; pass < 2; ++pass) {
                     for (int s0 = 0; s0 < n_seg; s0 += kAtOnce) {
@@ -127,11 +135,11 @@ __global__ __launch_bounds__(kThreads, 2) void window_kernel(Dims dm, DevTables 
                         if (pass == 1) {
 #pragma unroll
                             for (int s = 0; s < kAtOnce; ++s)
-                                if (s0 + s < n_seg && x[s].y > 0.f) Z += (double)(x[s].y * exp_raw<D>(x[s].x - M));
+                                if (s0 + s < n_seg && x[s].y > 0.f) Z += (double)ldexpf(x[s].y, (int)(x[s].x - M));
                         }
                     }
                 }
-                if (zt > 0.f) Z += (double)(zt * exp_raw<D>(mt - M));
+                if (zt > 0.f) Z += (double)(zt * __builtin_amdgcn_exp2f(fmaf(mt, kC, -M)));
                 s_M[tid] = have ? M : 0.f;  // rows past the list weigh nothing
                 s_w[tid] = have ? (float)(1.0 / ((double)(s_pref[g + 1] - s_pref[g]) * (double)u.G * Z)) : 0.f;
             }
@@ -151,12 +159,12 @@ __global__ __launch_bounds__(kThreads, 2) void window_kernel(Dims dm, DevTables 
                 if (row >= rows_here) qa[b][sl] = make_uint4(0, 0, 0, 0);
             }
         }
-        // ref: what the accumulators start from (minus the row's reference); sum: pass 1 the sum-exp, pass 2 the row's weight
+        // ref: minus the row's reference; sum: pass 1 the sum of the exponentials, pass 2 the row's weight
         f32x4 ref[kWaveBlocks], sum[kWaveBlocks];
         if (PASS == 1) {
 #pragma unroll
             for (int b = 0; b < kWaveBlocks; ++b) {
-                ref[b] = (f32x4){-kUnset, -kUnset, -kUnset, -kUnset};
+                ref[b] = (f32x4){0.f, 0.f, 0.f, 0.f};
                 sum[b] = (f32x4){0.f, 0.f, 0.f, 0.f};
             }
         } else {
@@ -174,8 +182,8 @@ __global__ __launch_bounds__(kThreads, 2) void window_kernel(Dims dm, DevTables 
         // wave passes the same number of barriers, whichever instance it runs.
         auto stream = [&](auto nb_const) __attribute__((always_inline)) {
             constexpr int NB = decltype(nb_const)::value;
-            // one step over the 64 keys of a buffer.  CHECKED (pass 1): references are raised where a logit asks for it;
-            // MASKED: some keys of the step do not exist or lie behind a row.
+            // one step over the 64 keys of a buffer.  CHECKED (pass 1): the reference is raised in front of an exponential above
+            // 2^kHigh; MASKED: some keys of the step do not exist or lie behind a row.
             auto keys_of_step = [&](const bf16_t *buf, int key0, f32x4(&acc), auto checked, auto masked) __attribute__((always_inline)) {
                 int lim[NB > 0 ? NB : 1][4];  // last key that a row sees
                 if constexpr (decltype(masked)::value) {
@@ -193,7 +201,7 @@ __global__ __launch_bounds__(kThreads, 2) void window_kernel(Dims dm, DevTables 
                     f32x4 s[NB > 0 ? NB : 1];
 #pragma unroll
                     for (int b = 0; b < NB; ++b) {
-                        s[b] = ref[b];
+                        s[b] = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                         for (int sl = 0; sl < NS; ++sl) s[b] = mma<bf16_t>(qa[b][sl], kb[sl], s[b]);
                     }
@@ -207,59 +215,103 @@ __global__ __launch_bounds__(kThreads, 2) void window_kernel(Dims dm, DevTables 
                     if constexpr (decltype(checked)::value) {
 #pragma unroll
                         for (int b = 0; b < NB; ++b) {
-                            const float top = fmaxf(fmaxf(s[b][0], s[b][1]), fmaxf(s[b][2], s[b][3]));
-                            if (__ballot(top > kSlackRaw) == 0ull) continue;
-                            // some lane's reference is unset or far too low: the logit is the new one
-                            f32x4 full = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                            for (int sl = 0; sl < NS; ++sl) full = mma<bf16_t>(qa[b][sl], kb[sl], full);
-#pragma unroll
-                            for (int i = 0; i < 4; ++i)
-                                if (s[b][i] > kSlackRaw) {
-                                    sum[b][i] *= exp_key<D>(-ref[b][i] - full[i]);
-                                    ref[b][i] = -full[i];
-                                    s[b][i] = 0.f;
+                            for (int i = 0; i < 4; ++i) {
+                                const bool high = fmaf(s[b][i], kC, ref[b][i]) > kHigh;
+                                if (__ballot(high) == 0ull) continue;
+                                const float m = rintf(s[b][i] * kC);
+                                if (high) {
+                                    sum[b][i] = ldexpf(sum[b][i], (int)(-ref[b][i] - m));
+                                    ref[b][i] = -m;
                                 }
+                            }
                         }
                     }
 #pragma unroll
                     for (int b = 0; b < NB; ++b)
 #pragma unroll
                         for (int i = 0; i < 4; ++i) {
-                            const float e = exp_key<D>(s[b][i]);
+                            const float e = __builtin_amdgcn_exp2f(fmaf(s[b][i], kC, ref[b][i]));
                             if (PASS == 1) sum[b][i] += e;
                             else acc[tile] = fmaf(sum[b][i], e, acc[tile]);
                         }
                 }
             };
+            auto masked_from = [&](int key0) { return key0 + kStepKeys > u.sq.vis_len || (dm.vis_window && key0 + kStepKeys > prow0 + 1); };
+            constexpr int kFirst = 4;  // tiles of 16 keys
+            if (PASS == 1 && steps > 0) {  // the rows' first references: the maximum over the first keys
+                const bool masked = masked_from(key_lo);
+                f32x4 top[NB > 0 ? NB : 1];
+#pragma unroll
+                for (int b = 0; b < NB; ++b) top[b] = (f32x4){-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+#pragma unroll
+                for (int tile = 0; tile < kFirst; ++tile) {
+                    const int key = key_lo + 16 * tile + n;
+                    uint4 kb[NS];
+#pragma unroll
+                    for (int sl = 0; sl < NS; ++sl) kb[sl] = *reinterpret_cast<const uint4 *>(s_k[0] + key_at[sl] + 16 * tile * D);
+#pragma unroll
+                    for (int b = 0; b < NB; ++b) {
+                        f32x4 s = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                        for (int sl = 0; sl < NS; ++sl) s = mma<bf16_t>(qa[b][sl], kb[sl], s);
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            if (masked) {
+                                const int lim = dm.vis_window ? prow0 + (r0 + 16 * (blk0 + b) + 4 * i + c) % u.sq.win_len : u.sq.vis_len - 1;
+                                s[i] = key > lim ? -INFINITY : s[i];
+                            }
+                            top[b][i] = fmaxf(top[b][i], s[i]);
+                        }
+                    }
+                }
+#pragma unroll
+                for (int b = 0; b < NB; ++b)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const float m = max16(top[b][i]);
+                        if (m > -INFINITY) ref[b][i] = -rintf(m * kC);  // else the row sees none of these keys, or logits of -inf
+                    }
+            }
             for (int step = 0; step < steps; ++step) {
                 const bf16_t *buf = s_k[step & 1];
                 const int key0 = key_lo + kStepKeys * step;
                 u32x4 kx[kIt];
                 fetch(kx, min(step + 1, steps - 1));
-                const bool masked = key0 + kStepKeys > u.sq.vis_len || (dm.vis_window && key0 + kStepKeys > prow0 + 1);
+                const bool masked = masked_from(key0);
                 f32x4 acc = (f32x4){0.f, 0.f, 0.f, 0.f};
                 if (PASS == 1) {
-                    // Steps are taken without looking at single logits; where a sum then stands above 2^100 (or is no number)
-                    // the step is done again from the sums before it, with the check.  The first step sets the references.
-                    bool again = masked || step == 0;
+                    // Steps are taken without looking at single logits; where some logit stands far above its reference the step is
+                    // done again from the sums before it, with the check.
+                    auto largest_sum = [&]() __attribute__((always_inline)) {
+                        float x = 0.f;
+#pragma unroll
+                        for (int b = 0; b < NB; ++b) x = fmaxf(fmaxf(x, fmaxf(sum[b][0], sum[b][1])), fmaxf(sum[b][2], sum[b][3]));
+                        return x;
+                    };
+                    bool again = masked;
                     if (!again) {
                         f32x4 before[NB > 0 ? NB : 1];
 #pragma unroll
                         for (int b = 0; b < NB; ++b) before[b] = sum[b];
                         keys_of_step(buf, key0, acc, std::false_type(), std::false_type());
-                        bool fine = true;
-#pragma unroll
-                        for (int b = 0; b < NB; ++b)
-#pragma unroll
-                            for (int i = 0; i < 4; ++i) fine = fine && sum[b][i] < 0x1p100f;
-                        again = __ballot(!fine) != 0ull;
+                        again = __ballot(largest_sum() >= kSumMost) != 0ull;
                         if (again) {
 #pragma unroll
                             for (int b = 0; b < NB; ++b) sum[b] = before[b];
                         }
                     }
                     if (again) keys_of_step(buf, key0, acc, std::true_type(), std::true_type());
+                    if (__ballot(largest_sum() >= kSumLimit) != 0ull) {  // the next steps' exponentials start from a reference that fits
+#pragma unroll
+                        for (int b = 0; b < NB; ++b)
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) {
+                                const int up = sum[b][i] >= kSumLimit && sum[b][i] < INFINITY ? ilogb_of(sum[b][i]) : 0;
+                                sum[b][i] = ldexpf(sum[b][i], -up);
+                                ref[b][i] -= (float)up;
+                            }
+                    }
                 } else {
                     if (masked) keys_of_step(buf, key0, acc, std::false_type(), std::true_type());
                     else keys_of_step(buf, key0, acc, std::false_type(), std::false_type());
@@ -290,13 +342,16 @@ __global__ __launch_bounds__(kThreads, 2) void window_kernel(Dims dm, DevTables 
                 if (b >= nb) continue;
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const float m = -ref[b][i];
+                    const float m = sum[b][i] > 0.f ? -ref[b][i] : -INFINITY;
                     const float M = max16(m);
-                    const float z = sum16(sum[b][i] > 0.f ? sum[b][i] * exp_raw<D>(m - M) : 0.f);
+                    float z = sum16(m > -INFINITY ? ldexpf(sum[b][i], (int)(m - M)) : sum[b][i]);
+                    // (the sum goes out as a fraction of 1 to 2: pass 2 takes the largest reference of a row, which its terms then stay below)
+                    const int up = z > 0.f && z < INFINITY ? ilogb_of(z) : 0;
+                    z = ldexpf(z, -up);
                     const int rho = r0 + 16 * (blk0 + b) + 4 * i + c;
                     if (n == 0 && rho < u.R_total) {
                         const int64_t slot = u.hrow0 * u.W + s_slot[rho - r0];
-                        t.part[slot * dm.n_chunks + (int)blockIdx.x] = make_float2(z > 0.f ? M : -INFINITY, z);
+                        t.part[slot * dm.n_chunks + (int)blockIdx.x] = make_float2(z > 0.f ? M + (float)up : -INFINITY, z);
                     }
                 }
             }

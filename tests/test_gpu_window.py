@@ -1,5 +1,7 @@
-"""Windows of many rows (bf16, no threshold): runs of one, two and four chunks of keys per workgroup, scores that do not depend
-on how the layers are cut into calls."""
+"""Windows of many rows (bf16, no threshold): runs of one, two and four chunks of keys per workgroup, logits that outrun their
+reference, scores that do not depend on how the layers are cut into calls, and their error against fp64."""
+import math
+
 import numpy as np
 import pytest
 
@@ -68,3 +70,50 @@ def test_scores_are_the_same_bits_however_the_layers_are_cut(L, d, visual):
     ac = p.context(score_block_mb=2)
     assert all(np.array_equal(x, y) for x, y in zip(want, p.score(ac)))
     ac.close()
+
+
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("visual", [False, True])
+@pytest.mark.parametrize("shape", ["rising", "falling", "peaks"])
+@pytest.mark.parametrize("L", [1, 34])
+def test_logits_that_outrun_their_reference(d, visual, shape, L):
+    # raw logits that step by 240 (30 or 43 bits) every 64 keys, or stand 1600 above everything at single keys: a step's sums
+    # pass their limit, references are raised and sums scaled, in runs of one and of four chunks.  Small whole numbers, so that
+    # every logit is exact in fp32.
+    import torch
+
+    p = _Prompt(L, 6 if L > 1 else 1, 8 if L > 1 else 2, 2, d, 1000, 24, 20, visual)
+    n0 = p.seqs[0].vis_start
+    step = torch.arange(1000, device="cuda:0")
+    lead = {"rising": 30 * (step // 64), "falling": 30 * (15 - step // 64), "peaks": torch.where(step % 97 == 90, 200, 0)}[shape]
+    for x in (*p.k, *p.q):
+        x.copy_(x.clamp(-2, 2).round())
+    for l in range(L):
+        p.k[l][..., 0] = 0.0
+        p.k[l][:, :, n0:n0 + 1000, 0] = lead.to(torch.bfloat16)
+        p.q[l][..., 0] = 8.0
+    ac = p.context()
+    got = p.score(ac)
+    for (l, b, h) in [(0, 0, 0), (L - 1, p.B - 1, p.hkv - 1)]:
+        np.testing.assert_allclose(got[l][b, h], p.oracle(l, b, h), rtol=P.SCORE_RTOL, atol=P.SCORE_ATOL)
+    ac.close()
+
+
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("visual", [False, True])
+@pytest.mark.parametrize("spread,bound", [(1.0, 1e-7), (5.0, 6e-7), (18.0, 1.5e-6)])
+def test_error_against_fp64(d, visual, spread, bound):
+    # Relative 2-norm.  A logit near the maximum is about 4 spreads in size; its fp32 sum is rounded at partial sums of that size,
+    # 4 spread 2^-24 = 2.4e-7 spread at the most for one row, and averages over the rows that share a key.  Sums from zero
+    # with references near the maximum: 0.6e-7, 4.3e-7 and 8.7e-7 measured (with the logits of this kernel as with those of
+    # the one before it); sums that start at minus the reference: 0.7e-7, 9.7e-7 and 4.0e-6.
+    p = _Prompt(2, 1, 2, 7, d, 2304, 64, 32, visual, spread)
+    ac = p.context()
+    got = p.score(ac)
+    ac.close()
+    errs = []
+    for l in range(2):
+        for h in range(2):
+            want = p.oracle(l, 0, h)
+            errs.append(np.linalg.norm(got[l][0, h] - want) / np.linalg.norm(want))
+    assert math.sqrt(np.mean(np.square(errs))) <= bound, errs
