@@ -142,8 +142,10 @@ __device__ __forceinline__ double block_sum(double v, double *scratch) {
 
 // exp(d * c / log2(e)) = 2^(d * c) for d <= 0 and a constant c given as a hi/lo pair (c_hi + c_lo = c to
 // ~48 bits): the product is split exactly, its integer part goes through ldexp and only the
-// fraction through the hardware exp2, so that the result is good to about 2 ulp for any d.
+// fraction through the hardware exp2, so that the result is good to about 2 ulp for any d.  (Far below the smallest number the
+// split product's lower part is no fraction any more: there the result is 0 from a bound of its own, c >= 1/8.)
 __device__ __forceinline__ float exp2_scaled(float d, float c_hi, float c_lo) {
+    d = d < -4096.0f ? -4096.0f : d;
     const float t = d * c_hi;
     const float lo = fmaf(d, c_hi, -t) + d * c_lo;
     const float nf = rintf(t);

@@ -55,6 +55,11 @@ __global__ __launch_bounds__(kThreads, 2) void window_kernel(Dims dm, DevTables 
     constexpr float kSumLimit = 64.0f;   // of a lane's sum in front of a step: it has at most 64 keys of a row
     constexpr float kSumMost = 0x1p24f;  // a step that leaves a sum above this is done again
     constexpr float kHigh = 4.0f;        // then with the reference raised in front of exponentials above 2^kHigh
+    // Beyond 2^22 a reference and a logit no longer differ by what fp32 says they do (raw logits of 3e7: keys masked by a large
+    // negative number, operands in the thousands).  References stop there; logits below weigh nothing, logits above are
+    // held at the bound: in pass 1 when their step is done again, in pass 2 by a plain loop over the rows that have such a reference.
+    constexpr float kFar = 0x1p22f, kFarRaw = kFar / kC;
+    auto held = [](float s) __attribute__((always_inline)) { return s > kFarRaw ? kFarRaw : (s < -kFarRaw ? -kFarRaw : s); };
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, n = lane & 15, c = lane >> 4;
     const int wg_chunks = PASS == 1 ? seg_chunks : kFinishChunks;
     UnitCtx u;
@@ -62,6 +67,7 @@ __global__ __launch_bounds__(kThreads, 2) void window_kernel(Dims dm, DevTables 
     __shared__ int s_pref[17];
     __shared__ __align__(16) bf16_t s_k[2][kStepKeys * D];
     __shared__ float s_M[kWinRows], s_w[kWinRows];
+    __shared__ int s_any_far;             // pass 2: some row has its reference at the bound
     __shared__ int s_slot[kWinRows];      // a row's place in the unit's row tables
     __shared__ int64_t s_query[kWinRows]; // and in the query tensor
     __shared__ __align__(16) float s_part[PASS == 2 ? 2 : 1][kWaves][PASS == 2 ? 4 * kStepKeys : 4];  // [lane][tile]
@@ -75,6 +81,7 @@ __global__ __launch_bounds__(kThreads, 2) void window_kernel(Dims dm, DevTables 
     const int prow0 = u.sq.win_start - u.sq.vis_start;
     const int key_end = min(last * kChunkKeys, dm.vis_window ? prow0 + u.sq.win_len : u.sq.vis_len);
     const int steps = max(0, (key_end - key_lo + kStepKeys - 1) / kStepKeys);
+    if (PASS == 2 && tid == 0) s_any_far = 0;
     head_prefix(t, u.hrow0, u.G, s_pref);
     u.R_total = s_pref[u.G];
     if (PASS == 2)
@@ -121,7 +128,7 @@ __global__ __launch_bounds__(kThreads, 2) void window_kernel(Dims dm, DevTables 
                 const float2 *p = t.part + slot * dm.n_chunks;
                 const float mt = t.row_mtext[slot], zt = t.row_ztext[slot];  // of raw logits
                 constexpr int kAtOnce = 16;  // partials requested together; a run of them past the end repeats the last one
-                float M = rintf(mt * kC);
+                float M = mt > -INFINITY ? rintf(held(mt) * kC) : -INFINITY;
                 double Z = 0.0;
                 for (int pass = n_seg <= kAtOnce ? 1 : 0; pass < 2; ++pass) {
                     for (int s0 = 0; s0 < n_seg; s0 += kAtOnce) {
@@ -139,9 +146,10 @@ __global__ __launch_bounds__(kThreads, 2) void window_kernel(Dims dm, DevTables 
                         }
                     }
                 }
-                if (zt > 0.f) Z += (double)(zt * __builtin_amdgcn_exp2f(fmaf(mt, kC, -M)));
-                s_M[tid] = have ? M : 0.f;  // rows past the list weigh nothing
-                s_w[tid] = have ? (float)(1.0 / ((double)(s_pref[g + 1] - s_pref[g]) * (double)u.G * Z)) : 0.f;
+                if (zt > 0.f) Z += (double)(zt * __builtin_amdgcn_exp2f(fmaf(held(mt), kC, -M)));
+                if (fabsf(M) > 0.5f * kFar && M > -INFINITY) s_any_far = 1;
+                s_M[tid] = have && Z > 0.0 ? M : 0.f;  // rows past the list weigh nothing, nor do rows that see no key but far ones
+                s_w[tid] = have && !(Z <= 0.0) ? (float)(1.0 / ((double)(s_pref[g + 1] - s_pref[g]) * (double)u.G * Z)) : 0.f;
             }
         }
         put(kx0, 0);
@@ -173,7 +181,8 @@ __global__ __launch_bounds__(kThreads, 2) void window_kernel(Dims dm, DevTables 
                 if (b < nb) {
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
-                        ref[b][i] = -s_M[16 * (blk0 + b) + 4 * i + c];
+                        const float M = s_M[16 * (blk0 + b) + 4 * i + c];
+                        ref[b][i] = fabsf(M) > 0.5f * kFar ? -INFINITY : -M;  // the plain loop below takes that row
                         sum[b][i] = s_w[16 * (blk0 + b) + 4 * i + c];
                     }
                 }
@@ -182,8 +191,8 @@ __global__ __launch_bounds__(kThreads, 2) void window_kernel(Dims dm, DevTables 
         // wave passes the same number of barriers, whichever instance it runs.
         auto stream = [&](auto nb_const) __attribute__((always_inline)) {
             constexpr int NB = decltype(nb_const)::value;
-            // one step over the 64 keys of a buffer.  CHECKED (pass 1): the reference is raised in front of an exponential above
-            // 2^kHigh; MASKED: some keys of the step do not exist or lie behind a row.
+            // one step over the 64 keys of a buffer.  CHECKED (pass 1): far logits are held at the bound, and the reference is
+            // raised in front of an exponential above 2^kHigh; MASKED: some keys of the step do not exist or lie behind a row.
             auto keys_of_step = [&](const bf16_t *buf, int key0, f32x4(&acc), auto checked, auto masked) __attribute__((always_inline)) {
                 int lim[NB > 0 ? NB : 1][4];  // last key that a row sees
                 if constexpr (decltype(masked)::value) {
@@ -204,6 +213,12 @@ __global__ __launch_bounds__(kThreads, 2) void window_kernel(Dims dm, DevTables 
                         s[b] = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                         for (int sl = 0; sl < NS; ++sl) s[b] = mma<bf16_t>(qa[b][sl], kb[sl], s[b]);
+                    }
+                    if constexpr (decltype(checked)::value) {
+#pragma unroll
+                        for (int b = 0; b < NB; ++b)
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) s[b][i] = held(s[b][i]);
                     }
                     if constexpr (decltype(masked)::value) {
                         const int key = key0 + 16 * tile + n;
@@ -238,14 +253,13 @@ __global__ __launch_bounds__(kThreads, 2) void window_kernel(Dims dm, DevTables 
                 }
             };
             auto masked_from = [&](int key0) { return key0 + kStepKeys > u.sq.vis_len || (dm.vis_window && key0 + kStepKeys > prow0 + 1); };
-            constexpr int kFirst = 4;  // tiles of 16 keys
             if (PASS == 1 && steps > 0) {  // the rows' first references: the maximum over the first keys
                 const bool masked = masked_from(key_lo);
                 f32x4 top[NB > 0 ? NB : 1];
 #pragma unroll
                 for (int b = 0; b < NB; ++b) top[b] = (f32x4){-INFINITY, -INFINITY, -INFINITY, -INFINITY};
 #pragma unroll
-                for (int tile = 0; tile < kFirst; ++tile) {
+                for (int tile = 0; tile < 4; ++tile) {
                     const int key = key_lo + 16 * tile + n;
                     uint4 kb[NS];
 #pragma unroll
@@ -270,7 +284,7 @@ __global__ __launch_bounds__(kThreads, 2) void window_kernel(Dims dm, DevTables 
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
                         const float m = max16(top[b][i]);
-                        if (m > -INFINITY) ref[b][i] = -rintf(m * kC);  // else the row sees none of these keys, or logits of -inf
+                        if (m > -INFINITY) ref[b][i] = -rintf(held(m) * kC);  // else the row sees none of these keys, or logits of -inf
                     }
             }
             for (int step = 0; step < steps; ++step) {
@@ -336,6 +350,22 @@ __global__ __launch_bounds__(kThreads, 2) void window_kernel(Dims dm, DevTables 
         else if (nb == 2) stream(std::integral_constant<int, 2>());
         else if (nb == 1) stream(std::integral_constant<int, 1>());
         else stream(std::integral_constant<int, 0>());
+        if (PASS == 2 && s_any_far) {
+            lds_barrier();  // the last step's sums are in place
+            for (int r = 0; r < rows_here; ++r) {
+                const float M = s_M[r], w = s_w[r];
+                if (fabsf(M) <= 0.5f * kFar) continue;
+                const int last_key = dm.vis_window ? prow0 + (r0 + r) % u.sq.win_len : u.sq.vis_len - 1;
+                for (int i = tid; i < kFinishChunks * kChunkKeys && key_lo + i <= last_key; i += kThreads) {
+                    const bf16_t *kr = u.k + (int64_t)(u.sq.vis_start + key_lo + i) * st.kv_t, *qr = u.q + s_query[r];
+                    float s = 0.f;
+#pragma unroll 1
+                    for (int e = 0; e < D; e += 8)
+                        s = dot_piece<bf16_t>(*reinterpret_cast<const uint4 *>(qr + e), *reinterpret_cast<const uint4 *>(kr + e), s);
+                    s_imp[i] += w * __builtin_amdgcn_exp2f(fmaf(held(s), kC, -M));
+                }
+            }
+        }
         if (PASS == 1) {  // one (maximum, sum-exp) per row from the sixteen lanes that share it
 #pragma unroll
             for (int b = 0; b < kWaveBlocks; ++b) {

@@ -84,3 +84,70 @@ def test_infinite_logits(d, alpha):
         got = idx[0, hq, : cnt[0, hq]]
         assert np.array_equal(got, want), (hq, got, want)
         assert (t0 + 5 in got) == (alpha == 0.0) and t0 + 33 not in got
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("low", [-3000.0, -1e5, -3e7, -3e9, -1e20, -7e25, -3e30, -1e36])
+@pytest.mark.parametrize("alpha,n_text", [(0.9, 40), (0.0, 4), (0.0, 40)])  # the elite window, 28 rows, 280 rows
+def test_visual_keys_masked_by_a_large_negative_logit(d, low, alpha, n_text):
+    # whole chunks of visual keys with logits far below all others weigh nothing and leave the rest as it is without them
+    import torch
+
+    import paper_2503_23956_amd as A
+    from paper_2503_23956_amd.device_inputs import config_for, to_device
+
+    dev = torch.device("cuda:0")
+    w = synth.get_workload(2).scaled(head_dim=d, n_layers=1, n_vis=1100, n_text=n_text, decode_steps=1)
+    seqs = w.seqs()
+    li = synth.layer_inputs(w, 0, seqs)
+    q, k = (synth.storage_to_f64(x).copy() for x in (li.q_text, li.k))
+    v0 = seqs[0].vis_start
+    masked = np.zeros(1100, dtype=bool)
+    masked[:256] = masked[600:1040] = True
+    q[..., 0], k[..., 0] = 1.0, 0.0
+    k[:, :, v0:v0 + 1100][:, :, masked, 0] = low
+    q, k = _bf16(q), _bf16(k)
+    ac = A.AirCache(config_for(w, 0.1, alpha=alpha, seqs=seqs, max_decode_steps=1), dev)
+    qd, kd = to_device(q, dev), to_device(k, dev)
+    ac.air_score(0, 1, [qd], [kd], [kd], seqs)
+    got = ac.air_get_scores(0)
+    ac.close()
+    want, _ = O.layer_importance(synth.storage_to_f64(q)[0], synth.storage_to_f64(k)[0], P.seg_of(seqs[0]), alpha)
+    P.check_scores(got, [want], seqs, f"low={low}")
+    assert (got[0][:, masked] < 1e-30).all()
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("high", [3000.0, 1e6, 3e7, 3e9, 1e20, 1e36])
+@pytest.mark.parametrize("alpha,n_text,visual", [(0.9, 40, False), (0.0, 4, False), (0.0, 40, False), (0.0, 40, True)])
+def test_visual_keys_of_a_large_positive_logit(d, high, alpha, n_text, visual):
+    # two equal keys far above all others share the weight of every row that sees both
+    import dataclasses
+
+    import torch
+
+    import paper_2503_23956_amd as A
+    from paper_2503_23956_amd.device_inputs import config_for, to_device
+
+    dev = torch.device("cuda:0")
+    w = synth.get_workload(2).scaled(head_dim=d, n_layers=1, n_vis=1100, n_text=n_text, decode_steps=1)
+    seqs = w.seqs()
+    if visual:
+        seqs = [dataclasses.replace(s, win_start=s.vis_start + 690, win_len=n_text) for s in seqs]  # the second key is inside the window
+    li = synth.layer_inputs(w, 0, w.seqs())
+    q, k = (synth.storage_to_f64(x).copy() for x in (li.q_text, li.k))
+    v0 = seqs[0].vis_start
+    q[..., 0], k[..., 0] = 1.0, 0.0
+    for key in (300, 700):
+        k[:, :, v0 + key] = 0.0
+        k[:, :, v0 + key, 0] = high
+    q, k = _bf16(q), _bf16(k)
+    ac = A.AirCache(config_for(w, 0.1, alpha=alpha, seqs=seqs, max_decode_steps=1, window_kind=int(visual)), dev)
+    qd, kd = to_device(q, dev), to_device(k, dev)
+    ac.air_score(0, 1, [qd], [kd], [kd], seqs)
+    got = ac.air_get_scores(0)
+    ac.close()
+    q64, k64 = synth.storage_to_f64(q)[0], synth.storage_to_f64(k)[0]
+    want = (O.layer_importance_visual_window(q64, k64, P.seg_of(seqs[0])) if visual else O.layer_importance(q64, k64, P.seg_of(seqs[0]), alpha))[0]
+    P.check_scores(got, [want], seqs, f"high={high}")
+    assert visual or np.allclose(got[0][:, [300, 700]], 0.5)
