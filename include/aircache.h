@@ -130,7 +130,10 @@ typedef struct {
     int64_t kv_b, kv_h, kv_t; /* k and v: batch, head, token */
 } air_strides;
 
-/* Bytes of device workspace a context with this config needs (0 on invalid config). */
+/* Bytes of device workspace a context with this config needs (0 on invalid config).  At most the last
+ * n_layers * batch * n_kv_heads * ceil(max_vis_len / 256) * 32 KB of them (and, with bf16, 1/256 of that) are a stash that saves
+ * air_score a second read of the visual keys; windows without a threshold of more than 32 rows per KV head have none.  fp32
+ * contexts and contexts with heads of 64 elements are also created in a workspace that ends before the stash. */
 size_t air_workspace_bytes(const air_config *cfg);
 
 /* Create a context over a caller-allocated device workspace (256-byte aligned, at least

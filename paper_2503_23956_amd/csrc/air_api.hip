@@ -49,6 +49,12 @@ static int64_t total_budget(const air_config &c, int n_vis) {
     return k < lo ? lo : (k > hi ? hi : k);
 }
 
+// Units of at most kStashRows window rows stash their logits or exponentials; a window without a threshold that makes
+// more rows of every unit of max_window tokens has no use for it (shorter windows of such a context read K_v twice).
+static bool has_stash(const air_config &c) {
+    return !(c.alpha == 0.0 && (int64_t)(c.n_q_heads / c.n_kv_heads) * c.max_window > kStashRows);
+}
+
 WsLayout make_layout(const air_config &c) {
     WsLayout w;
     memset(&w, 0, sizeof(w));
@@ -94,12 +100,15 @@ WsLayout make_layout(const air_config &c) {
     w.cache_ptrs = take(L * sizeof(CachePtrs));
     w.dec_o = take(L * B * Hkv * kMaxSplits * 16 * D * 4);  // per (unit, split): 16 head rows x D
     w.dec_ml = take(L * B * Hq * kMaxSplits * 8);
-    w.stash = take(L * B * Hkv * (size_t)w.n_chunks * kStashRows * kChunkKeys * 4);
-    w.row_f = take(L * B * Hkv * (size_t)kStashRows * w.n_chunks * 4);
     w.unit_R = take(L * B * Hkv * 4);
     w.len_off = take(B * L * 8);
     w.by_length = take(B * L * 16);
+    // The stash comes last: fp32 and heads of 64 elements do without it in a workspace that ends here
+    w.least = off;
+    w.stash = take(has_stash(c) ? L * B * Hkv * (size_t)w.n_chunks * kStashRows * kChunkKeys * 4 : 0);
+    w.row_f = take(has_stash(c) && c.dtype == AIR_BF16 ? L * B * Hkv * (size_t)kStashRows * w.n_chunks * 4 : 0);
     w.total = off;
+    if (v_transposed(c.dtype, c.head_dim)) w.least = off;
     return w;
 }
 
@@ -169,7 +178,7 @@ air_status air_create(const air_config *cfg, void *workspace, size_t workspace_b
     *out = nullptr;
     if (!config_ok(*cfg)) return AIR_ERR_SHAPE;
     WsLayout lay = make_layout(*cfg);
-    if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < lay.total) return AIR_ERR_WORKSPACE;
+    if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < lay.least) return AIR_ERR_WORKSPACE;
     air_ctx *c = new air_ctx();
     c->cfg = *cfg;
     c->lay = lay;
@@ -190,6 +199,7 @@ air_status air_create(const air_config *cfg, void *workspace, size_t workspace_b
     d.causal_text = cfg->causal_text;
     d.inv_B = cfg->batch > 1 ? (uint32_t)(0x100000000ull / (uint64_t)cfg->batch) + 1u : 0u;
     d.pool_rows = lay.pool_rows;
+    d.stash_rows = has_stash(*cfg) && workspace_bytes >= lay.total ? kStashRows : 0;
     d.fuse_budget = can_fuse_budget(*cfg) ? 1 : 0;
     d.budget_mode = cfg->budget_mode;
     d.min_keep = cfg->min_keep;
@@ -357,7 +367,8 @@ air_status air_score(air_ctx *ctx, void *stream, int32_t l0, int32_t l1, const a
     // kernels that are bound by their exponentials: all layers in one pair of passes (224 rows, 28 x 4 x 7290 keys: one pair
     // beats two of 14 layers, whose second read would come from the memory-side cache, by a quarter: fewer half-filled
     // rounds of workgroups).  air_tuning.score_block_mb cuts the layers into groups.
-    const int many_rows = ctx->cfg.alpha == 0.0 && (int64_t)ctx->dm.G * ctx->cfg.max_window > kStashRows;
+    // (So do bf16 contexts whose workspace holds no stash, whatever their windows.)
+    const int many_rows = ctx->dm.stash_rows == 0;
     if (many_rows && ctx->tune.score_block_mb > 0) {
         double layer_bytes = 0.0;
         for (int b = 0; b < ctx->cfg.batch; ++b)

@@ -41,7 +41,7 @@ struct WsLayout {
     size_t seq_tab, elite_cnt, elite_idx, row_mtext, row_ztext, row_M, row_w, part, scores;
     size_t unit_st, unit_sk, s_t, s_k, budgets, base_len, layer_off, dec_cnt, unit_cnt, seq_cnt, moments, indices;
     size_t kcache, vcache, dec_o, dec_ml, stash, row_f, unit_R, len_off, dec_steps, cache_ptrs, by_length;
-    size_t total;
+    size_t least, total;  // bytes without and with the stash (the same where a context cannot do without)
     int32_t n_chunks;     // ceil(max_vis_len / kChunkKeys)
     int64_t pool_rows;    // rows of one (sequence, KV head) cache pool
 };
@@ -57,6 +57,7 @@ struct Dims {
     int64_t pool_rows;
     // Eq.11 inside air_score: the last workgroup of a sequence to finish its unit does the allocation (the layers fit one wave)
     int32_t fuse_budget, budget_mode, min_keep;
+    int32_t stash_rows;  // kStashRows, or 0: the workspace has no stash
     double retention;
 };
 

@@ -158,7 +158,7 @@ __global__ __launch_bounds__(256) void score_stream_f32(Dims dm, DevTables t, in
     __shared__ float s_red[kGroupRows][4];
     row_prefix(t, u.hrow0, dm.G, s.pref);
     const int R_total = s.pref[dm.G];
-    const bool stash = R_total <= kStashRows;
+    const bool stash = R_total <= dm.stash_rows;
     const int i = chunk * kChunkKeys + tid;
     const bool valid = i < u.sq.vis_len;
     float *stash_base = t.stash + ((u.unit * dm.n_chunks + chunk) * (int64_t)kStashRows) * kChunkKeys;
@@ -214,7 +214,7 @@ __global__ __launch_bounds__(256) void score_finish_f32(Dims dm, DevTables t, in
     __shared__ double s_mom[4][3];
     row_prefix(t, u.hrow0, dm.G, s.pref);
     const int R_total = s.pref[dm.G];
-    const bool stash = R_total <= kStashRows;
+    const bool stash = R_total <= dm.stash_rows;
     float imp[kFinishChunks] = {0.f, 0.f, 0.f, 0.f};
     for (int r0 = 0; r0 < R_total; r0 += kGroupRows) {
         const int nb = min(kGroupRows, R_total - r0);

@@ -122,3 +122,20 @@ def test_binding_structs_follow_the_header_field_by_field():
                 fields.append((var.lstrip("*").strip(), C.c_void_p if var.startswith("*") else ctype[base]))
         got = [(n, t) for n, t in getattr(binding, name)._fields_]
         assert got == fields, (name, got, fields)
+
+
+def test_workspace_holds_a_stash_only_where_scoring_can_use_it():
+    """The stash of air_score is 128 bytes per visual key (whole chunks of 256) and unit; a window without a threshold of more
+    than 32 rows per KV head has none."""
+    import paper_2503_23956_amd as A
+
+    lib = A.load_library()
+    shape = dict(n_layers=3, n_q_heads=14, n_kv_heads=2, batch=2, max_vis_len=1000, max_nonvis_len=80, max_decode_steps=4)
+    for dtype, d in ((A.AIR_F32, 64), (A.AIR_F32, 128), (A.AIR_BF16, 64), (A.AIR_BF16, 128)):
+        def size(window, alpha):
+            return lib.air_workspace_bytes(C.byref(A.make_config(**shape, dtype=dtype, head_dim=d, max_window=window, alpha=alpha)))
+
+        stash = 3 * 2 * 2 * 4 * 32 * 256 * 4
+        factors = stash // 256 if dtype == A.AIR_BF16 else 0
+        assert size(5, 0.9) - size(5, 0.0) == stash + factors  # 35 rows
+        assert size(4, 0.9) == size(4, 0.0)  # 28 rows
