@@ -468,9 +468,7 @@ __global__ __launch_bounds__(256, 4) void score_finish_kernel(Dims dm, DevTables
 // ---------------------------------------------------------------------------------------
 constexpr int kEliteWaves = 8;      // phase 2 takes one head per wave
 constexpr float kEliteMargin = 4e-3f;  // raw-logit units
-__device__ __forceinline__ uint4 magnitudes(const uint4 &x) {  // of eight bf16 elements
-    return make_uint4(x.x & 0x7fff7fffu, x.y & 0x7fff7fffu, x.z & 0x7fff7fffu, x.w & 0x7fff7fffu);
-}
+__device__ __forceinline__ uint4 masked(const uint4 &x, uint32_t keep) { return make_uint4(x.x & keep, x.y & keep, x.z & keep, x.w & keep); }
 
 template <int D>
 __device__ __forceinline__ double dot64_wave(const bf16_t *a, const bf16_t *b, int lane) {
@@ -503,7 +501,7 @@ __global__ __launch_bounds__(64 * kEliteWaves) void elite_mfma_kernel(Dims dm, D
     constexpr int NS = D / 32;
     constexpr double inv_sqrt_d = D == 128 ? 0.08838834764831845 : 0.125;  // 1 / sqrt(d), correctly rounded
     constexpr float scale = (float)inv_sqrt_d;
-    __shared__ float s_size[16][kEliteWaves];  // per head of the round: a wave's largest sum of magnitudes
+    __shared__ float s_size[16][16 * kEliteWaves];  // per head of the round: the largest sum of magnitudes that a lane has seen
 
     for (int g0 = 0; g0 < G; g0 += gb) {
         const int ng = min(gb, G - g0);
@@ -526,25 +524,27 @@ __global__ __launch_bounds__(64 * kEliteWaves) void elite_mfma_kernel(Dims dm, D
                 kb[sl] = make_uint4(0, 0, 0, 0);
                 if (j < wl) kb[sl] = *reinterpret_cast<const uint4 *>(k + (int64_t)(sq.win_start + j) * st.kv_t + 32 * sl + 8 * c);
             }
-            f32x4 s4 = (f32x4){0.f, 0.f, 0.f, 0.f};
+            // the logits, then the sums of magnitudes: one copy of the code, the operands with and without their signs (a
+            // kernel this short waits for its instructions)
+#pragma unroll 1
+            for (int turn = 0; turn < 2; ++turn) {
+                const uint32_t keep = turn == 0 ? 0xffffffffu : 0x7fff7fffu;
+                f32x4 s4 = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int sl = 0; sl < NS; ++sl)
-                s4 = mma<bf16_t>(qa[sl], kb[sl], s4);
-            f32x4 a4 = (f32x4){0.f, 0.f, 0.f, 0.f};
+                for (int sl = 0; sl < NS; ++sl) s4 = mma<bf16_t>(masked(qa[sl], keep), masked(kb[sl], keep), s4);
+                if (turn == 0) {
 #pragma unroll
-            for (int sl = 0; sl < NS; ++sl)
-                a4 = mma<bf16_t>(magnitudes(qa[sl]), magnitudes(kb[sl]), a4);
+                    for (int i = 0; i < 4; ++i)
+                        if (4 * c + i < ng && j < wl) s_logit[(size_t)(4 * c + i) * W + j] = s4[i];
+                } else {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                if (4 * c + i < ng && j < wl) s_logit[(size_t)(4 * c + i) * W + j] = s4[i];
-                size[i] = fmaxf(size[i], a4[i]);
+                    for (int i = 0; i < 4; ++i) size[i] = fmaxf(size[i], s4[i]);
+                }
             }
         }
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const float x = max16(size[i]);
-            if (n == 0) s_size[4 * c + i][wave] = x;
-        }
+        for (int i = 0; i < 4; ++i)
+            if (4 * c + i < ng) s_size[4 * c + i][16 * wave + n] = size[i];
         __syncthreads();
         // ---- phase 2
         for (int hh = wave; hh < ng; hh += kEliteWaves) {
@@ -556,10 +556,8 @@ __global__ __launch_bounds__(64 * kEliteWaves) void elite_mfma_kernel(Dims dm, D
             const bf16_t *qref = q + (int64_t)(ref - t0) * st.q_t;
             // What an fp32 logit of this head can be off by: infinite where operands overflow, every candidate is then decided in
             // fp64; a logit that is no number is whatever the margin (the comparisons below are negated).
-            float err = 0.f;
-#pragma unroll
-            for (int w = 0; w < kEliteWaves; ++w) err = fmaxf(err, s_size[hh][w]);
-            err *= D * 0x1p-23f;
+            static_assert(16 * kEliteWaves == 128, "two entries a lane");
+            const float err = wave_max(fmaxf(s_size[hh][lane], s_size[hh][lane + 64])) * (D * 0x1p-23f);
             const float margin = fmaxf(kEliteMargin, err), near_max = fmaxf(kEliteMargin, 2.f * err);
             float m32 = -INFINITY;
             for (int j = lane; j < wl; j += 64) m32 = fmaxf(m32, logit[j]);
