@@ -555,7 +555,7 @@ static void decode_shape(const air_ctx *ctx, int n_layers_in_launch, int appende
     // fp32 d = 64 225 KB 8.1 / 8.4, 530 KB 13.1 / 8.9; fp32 d = 128 450 KB 13.9 (two parts 11.1) / 9.6.
     const double unit_bytes = avg_len * 2.0 * c.head_dim * (c.dtype == AIR_BF16 ? 2.0 : 4.0);
     const bool other = !v_transposed(c.dtype, c.head_dim);
-    const bool short_unit = other && unit_bytes < 288.0 * 1024.0;
+    const bool short_unit = other && unit_bytes * ((avg_len - appended) / avg_len) < 288.0 * 1024.0;
     const bool short_halves = units <= 16 && halves_ok && (other ? short_unit : avg_len - appended < 1750.0);
     const bool tiny_launch = units <= 16 && !short_halves;
     // 64 keys a wave and iteration (32 of the 512-byte fp32 rows); bf16 with heads of 128 elements has other sizes compiled too

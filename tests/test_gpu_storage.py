@@ -275,3 +275,35 @@ def test_scoring_in_a_workspace_without_the_stash(dtype, d, alpha, n_text, visua
         else:
             np.testing.assert_allclose(x, y, rtol=1e-5, atol=1e-30)
     assert np.abs(seen[0][1] - seen[1][1]).max() <= (0 if dtype == "f32" else 1)
+
+
+@pytest.mark.parametrize("dtype,d,rows", [("f32", 64, 570), ("bf16", 64, 1140), ("f32", 128, 283)])
+def test_decode_keeps_its_launch_shape_while_the_cache_grows(dtype, d, rows):
+    # 285 KB a unit by the prompt, 288 KB passed after a few steps: the shape goes by the prompt, so every step has the bits of
+    # the first step's shape (one workgroup of four waves, or its column parts)
+    import numpy as np
+    import torch
+
+    import paper_2503_23956_amd as A
+    from paper_2503_23956_amd.device_inputs import config_for, to_device
+
+    dev = torch.device("cuda:0")
+    steps = 24
+    w = _workload(dtype, d, n_layers=1, n_sys=4, n_vis=rows - 24, n_text=20, decode_steps=steps)
+    seqs = w.seqs()
+    li = synth.layer_inputs(w, 0, seqs)
+    q, k, v = ([to_device(x, dev)] for x in (li.q_text, li.k, li.v))
+    outs = []
+    for tuning in ({}, dict(decode_splits=1, decode_waves=4)):
+        ac = A.AirCache(config_for(w, 1.0, seqs=seqs, max_decode_steps=steps), dev)
+        ac.air_set_tuning(**tuning)
+        ac.air_score(0, 1, q, k, v, seqs)
+        ac.air_budget()
+        ac.air_select_compact(0, 1, k, v)
+        out = torch.empty((steps, 1, 1, w.n_q_heads, d), dtype=q[0].dtype, device=dev)
+        for t in range(steps):
+            ac.air_decode_attn(0, 1, *(to_device(x[None], dev) for x in synth.decode_inputs(w, 0, t)), out[t])
+        outs.append(out)
+        ac.close()
+    for t in range(steps):
+        assert torch.equal(outs[0][t], outs[1][t]), t
