@@ -307,3 +307,30 @@ def test_decode_keeps_its_launch_shape_while_the_cache_grows(dtype, d, rows):
         ac.close()
     for t in range(steps):
         assert torch.equal(outs[0][t], outs[1][t]), t
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("f32", 64)])
+@pytest.mark.parametrize("tuning", [{}, dict(score_rows_kernel=1)])
+def test_a_low_threshold_that_leaves_more_rows_than_one_staging_round(dtype, d, tuning):
+    # several hundred rows a unit with a threshold: the finish kernel's own passes over K_v, 512 rows staged at a time
+    w = _workload(dtype, d, n_layers=1, n_q_heads=14, n_kv_heads=2, n_vis=560, n_text=160, decode_steps=1)
+    import numpy as np
+    import torch
+
+    import paper_2503_23956_amd as A
+    from paper_2503_23956_amd.device_inputs import config_for, to_device
+    from tests import parity_util as P
+
+    dev = torch.device("cuda:0")
+    seqs = w.seqs()
+    li = synth.layer_inputs(w, 0, seqs)
+    alpha = 1e-6
+    scores, elites, _, _ = P.oracle_score_layer(w, li, seqs, alpha)
+    assert sum(len(e) for e in elites[0][:7]) > 512
+    ac = A.AirCache(config_for(w, 0.1, alpha=alpha, seqs=seqs, max_decode_steps=1), dev)
+    ac.air_set_tuning(**tuning)
+    ac.air_score(0, 1, [to_device(li.q_text, dev)], [to_device(li.k, dev)], [to_device(li.v, dev)], seqs)
+    cnt, idx = ac.air_get_elite(0)
+    P.check_elite(cnt, idx, elites)
+    P.check_scores(ac.air_get_scores(0), scores, seqs)
+    ac.close()
