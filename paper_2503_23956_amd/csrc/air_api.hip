@@ -688,7 +688,8 @@ static air_status decode_attn(air_ctx *ctx, void *stream, int32_t l0, int32_t l1
             e = launch_zero_counters(s, xch.cnt, (int)(nl * units_per_layer));
         if (e == hipSuccess)
             e = launch_decode(s, ctx->dm, ctx->tab, xch, ctx->cfg.dtype, c0, nl, c0 - l0, ll, q_new, k_new, v_new, out,
-                              splits, waves, tiles, in_step ? ctx->appended[l0] : -1, longest_first, column_parts, cache_bytes(ctx) > kDecodeStreamBytes);
+                              splits, waves, tiles, in_step ? ctx->appended[l0] : -1, longest_first, column_parts,
+                              cache_bytes(ctx) > kDecodeStreamBytes);
         if (e != hipSuccess) return hip_fail(ctx, e, "air_decode_attn launch");
     }
     for (int l = l0; l < l1; ++l) {
@@ -717,7 +718,8 @@ air_status air_set_tuning(air_ctx *ctx, const air_tuning *tn) {
     };
     if (!one_of(tn->decode_splits, {0, 1, 2, 4, 8, 16}) || !one_of(tn->decode_waves, {0, 1, 2, 4, 8}) ||
         !one_of(tn->decode_tiles, {0, 2, 4, 8}) || tn->score_block_mb < 0 || tn->score_block_mb > 65536 ||
-        !one_of(tn->score_rows_kernel, {0, 1}) || !one_of(tn->decode_order, {0, 1, 2}) || !one_of(tn->decode_halves, {0, 1, 2}) || !one_of(tn->budget_in_score, {0, 1}) || !one_of(tn->select_threads, {0, 256, 512}) ||
+        !one_of(tn->score_rows_kernel, {0, 1}) || !one_of(tn->decode_order, {0, 1, 2}) ||
+        !one_of(tn->decode_halves, {0, 1, 2}) || !one_of(tn->budget_in_score, {0, 1}) || !one_of(tn->select_threads, {0, 256, 512}) ||
         tn->select_direct_max < -1 || tn->select_direct_max > 1024 || tn->gather_wgs < 0 || tn->gather_wgs > 64)
         return fail(ctx, AIR_ERR_INVALID_ARG, "air_set_tuning: a field holds a value outside its list");
     ctx->tune = *tn;

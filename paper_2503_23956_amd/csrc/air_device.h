@@ -126,20 +126,6 @@ __device__ __forceinline__ void seq_layer_of(const DimsT &dm, int z, int &b, int
     b = z - li * dm.B;
 }
 
-// Sum over a workgroup of NW waves in a fixed order; every thread gets the result.
-// `scratch` holds NW doubles; the call contains two barriers.
-template <int NW>
-__device__ __forceinline__ double block_sum(double v, double *scratch) {
-    v = wave_sum(v);
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) scratch[threadIdx.x >> 6] = v;
-    __syncthreads();
-    double r = 0.0;
-#pragma unroll
-    for (int w = 0; w < NW; ++w) r += scratch[w];
-    return r;
-}
-
 // exp(d * c / log2(e)) = 2^(d * c) for d <= 0 and a constant c given as a hi/lo pair (c_hi + c_lo = c to
 // ~48 bits): the product is split exactly, its integer part goes through ldexp and only the
 // fraction through the hardware exp2, so that the result is good to about 2 ulp for any d.  (Far below the smallest number the

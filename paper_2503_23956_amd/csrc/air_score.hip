@@ -18,23 +18,6 @@ namespace air {
 //           then the elite-text columns of Eq.7 for that head's elite rows.
 // Heads are processed in batches of `gb` so that gb * max_window logits fit the LDS.
 // ---------------------------------------------------------------------------------------
-__device__ __forceinline__ double sum16_f64(double v) {
-    // all-reduce over 16 consecutive lanes, DPP on the two halves of the double
-#define AIR_DPP_F64(ctrl)                                                                                  \
-    {                                                                                                      \
-        const unsigned long long u = __builtin_bit_cast(unsigned long long, v);                            \
-        const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)u, (ctrl), 0xf, 0xf, false);           \
-        const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(u >> 32), (ctrl), 0xf, 0xf, false);   \
-        v += __builtin_bit_cast(double, ((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);           \
-    }
-    AIR_DPP_F64(0xB1)
-    AIR_DPP_F64(0x4E)
-    AIR_DPP_F64(0x141)
-    AIR_DPP_F64(0x140)
-#undef AIR_DPP_F64
-    return v;
-}
-
 template <typename T, int D>
 __global__ __launch_bounds__(256) void elite_kernel(Dims dm, DevTables t, int l0, LaunchLayers ll, air_strides st,
                                                     SeqArgs seqs, double alpha, int gb) {
@@ -94,7 +77,7 @@ __global__ __launch_bounds__(256) void elite_kernel(Dims dm, DevTables t, int l0
                         double acc = 0.0;
 #pragma unroll
                         for (int e = 0; e < E; ++e) acc += qd[hh][e] * kd[e];
-                        acc = sum16_f64(acc);
+                        acc = sum16(acc);
                         if (sub == 0 && j < wl) s_logit[(size_t)(hb + hh) * W + j] = acc / sqrt_d;
                     }
                 }

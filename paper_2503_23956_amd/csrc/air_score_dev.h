@@ -90,88 +90,88 @@ __device__ __forceinline__ void leave_moments(const Dims &dm, const DevTables &t
         lds_barrier();
         return over_waves(slot);
     };
-                    double s1 = 0.0;
-    #pragma unroll
-            for (int i = 0; i < NX; ++i) s1 += ok[i] ? (double)x[i] : 0.0;
-            const double S1 = wg_sum(s1, 0);
-            const double mean = S1 / (double)n_wg;
-            double m2 = 0.0, m3 = 0.0;
-    #pragma unroll
-            for (int i = 0; i < NX; ++i) {
-                const double dlt = ok[i] ? (double)x[i] - mean : 0.0;
-                m2 += dlt * dlt;
-                m3 += dlt * dlt * dlt;
-            }
-            m2 = wave_sum(m2);
-            m3 = wave_sum(m3);
-            if (lane == 0) {
-                s_mom[wave][1] = m2;
-                s_mom[wave][2] = m3;
-            }
-            lds_barrier();
-            if (wave != 0) return;
-            // The entry goes out written through to memory, and the workgroup then counts itself at the unit's arrival
-            // counter; the one that counts last (every entry of the unit is in memory by then: each writer waited for its
-            // stores before it counted) turns the entries into the unit's strength and skewness.  The ordering is that of
-            // the decode kernel's exchange of partials: write-through stores, s_waitcnt, a relaxed device-scope
-            // read-modify-write, loads that bypass the caches.
-            double *mo_unit = t.moments + unit * dm.n_entries * 4;
-            const __amdgpu_buffer_rsrc_t ers = __builtin_amdgcn_make_buffer_rsrc(mo_unit, 0, dm.n_entries * 32, 0x00020000);
-            if (lane < 4) {
-                const double r = lane == 0 ? S1 : (lane == 1 ? mean : over_waves(lane - 1));
-                __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, r), ers, (int)blockIdx.x * 32 + lane * 8, 0, kSysScope);
-            }
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            int prev = 0;
-            if (lane == 0) prev = __hip_atomic_fetch_add(&t.unit_cnt[unit], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            prev = __builtin_amdgcn_readfirstlane(prev);
-                    if (prev != n_ent - 1) return;
-            if (lane == 0) __hip_atomic_store(&t.unit_cnt[unit], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // next launch
-            double unit_st, unit_sk;
-            unit_statistics(ers, n_ent, sq.vis_len, lane, unit_st, unit_sk);
-            if (!dm.fuse_budget) {
-                if (lane == 0) {
-                    t.unit_st[unit] = unit_st;
-                    t.unit_sk[unit] = unit_sk;
-                }
-                return;
-            }
-            // The same once more, one level up: the unit's statistics go out written through, the wave counts the unit at
-            // its sequence's arrival counter, and the wave that counts the last of the L * H_kv units does Eq.11 and the
-            // cache layout of the sequence (the layers fit one wave): air_budget has nothing left to launch.
-            const int64_t all_units = (int64_t)dm.L * dm.B * dm.Hkv;
-            const __amdgpu_buffer_rsrc_t srs = __builtin_amdgcn_make_buffer_rsrc(t.unit_st, 0, (int)(all_units * 8), 0x00020000);
-            const __amdgpu_buffer_rsrc_t krs = __builtin_amdgcn_make_buffer_rsrc(t.unit_sk, 0, (int)(all_units * 8), 0x00020000);
-            if (lane == 0) {
-                __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, unit_st), srs, (int)unit * 8, 0, kSysScope);
-                __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, unit_sk), krs, (int)unit * 8, 0, kSysScope);
-            }
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            prev = 0;
-            if (lane == 0) prev = __hip_atomic_fetch_add(&t.seq_cnt[b], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            prev = __builtin_amdgcn_readfirstlane(prev);
-            if (prev != dm.L * dm.Hkv - 1) return;
-            if (lane == 0) __hip_atomic_store(&t.seq_cnt[b], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // next prompt
-            __shared__ double s_a0[64], s_a1[64], s_frac[64];
-            __shared__ int s_i0[64], s_i1[64];
-            allocate_and_lay_out<true>(dm, t, b, sq, dm.retention, dm.budget_mode, dm.min_keep, false, lane, s_a0, s_a1, s_frac,
-                                       s_i0, s_i1, [&](int l, double &a, double &c) __attribute__((always_inline)) {
-                                           // all heads' loads go out together; the sums run left to right over the live ones
-                                           u32x2 vs[16], vk[16];
-    #pragma unroll
-                                           for (int h = 0; h < 16; ++h) {
-                                               const int off = (int)((((int64_t)l * dm.B + b) * dm.Hkv + min(h, dm.Hkv - 1)) * 8);
-                                               vs[h] = __builtin_amdgcn_raw_buffer_load_b64(srs, off, 0, kSysScope);
-                                               vk[h] = __builtin_amdgcn_raw_buffer_load_b64(krs, off, 0, kSysScope);
-                                           }
-    #pragma unroll
-                                           for (int h = 0; h < 16; ++h) {
-                                               if (h < dm.Hkv) {
-                                                   a += __builtin_bit_cast(double, vs[h]);
-                                                   c += __builtin_bit_cast(double, vk[h]);
-                                               }
-                                           }
-                                       });
+    double s1 = 0.0;
+#pragma unroll
+    for (int i = 0; i < NX; ++i) s1 += ok[i] ? (double)x[i] : 0.0;
+    const double S1 = wg_sum(s1, 0);
+    const double mean = S1 / (double)n_wg;
+    double m2 = 0.0, m3 = 0.0;
+#pragma unroll
+    for (int i = 0; i < NX; ++i) {
+        const double dlt = ok[i] ? (double)x[i] - mean : 0.0;
+        m2 += dlt * dlt;
+        m3 += dlt * dlt * dlt;
+    }
+    m2 = wave_sum(m2);
+    m3 = wave_sum(m3);
+    if (lane == 0) {
+        s_mom[wave][1] = m2;
+        s_mom[wave][2] = m3;
+    }
+    lds_barrier();
+    if (wave != 0) return;
+    // The entry goes out written through to memory, and the workgroup then counts itself at the unit's arrival
+    // counter; the one that counts last (every entry of the unit is in memory by then: each writer waited for its
+    // stores before it counted) turns the entries into the unit's strength and skewness.  The ordering is that of
+    // the decode kernel's exchange of partials: write-through stores, s_waitcnt, a relaxed device-scope
+    // read-modify-write, loads that bypass the caches.
+    double *mo_unit = t.moments + unit * dm.n_entries * 4;
+    const __amdgpu_buffer_rsrc_t ers = __builtin_amdgcn_make_buffer_rsrc(mo_unit, 0, dm.n_entries * 32, 0x00020000);
+    if (lane < 4) {
+        const double r = lane == 0 ? S1 : (lane == 1 ? mean : over_waves(lane - 1));
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, r), ers, (int)blockIdx.x * 32 + lane * 8, 0, kSysScope);
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    int prev = 0;
+    if (lane == 0) prev = __hip_atomic_fetch_add(&t.unit_cnt[unit], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    prev = __builtin_amdgcn_readfirstlane(prev);
+    if (prev != n_ent - 1) return;
+    if (lane == 0) __hip_atomic_store(&t.unit_cnt[unit], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // next launch
+    double unit_st, unit_sk;
+    unit_statistics(ers, n_ent, sq.vis_len, lane, unit_st, unit_sk);
+    if (!dm.fuse_budget) {
+        if (lane == 0) {
+            t.unit_st[unit] = unit_st;
+            t.unit_sk[unit] = unit_sk;
+        }
+        return;
+    }
+    // The same once more, one level up: the unit's statistics go out written through, the wave counts the unit at
+    // its sequence's arrival counter, and the wave that counts the last of the L * H_kv units does Eq.11 and the
+    // cache layout of the sequence (the layers fit one wave): air_budget has nothing left to launch.
+    const int64_t all_units = (int64_t)dm.L * dm.B * dm.Hkv;
+    const __amdgpu_buffer_rsrc_t srs = __builtin_amdgcn_make_buffer_rsrc(t.unit_st, 0, (int)(all_units * 8), 0x00020000);
+    const __amdgpu_buffer_rsrc_t krs = __builtin_amdgcn_make_buffer_rsrc(t.unit_sk, 0, (int)(all_units * 8), 0x00020000);
+    if (lane == 0) {
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, unit_st), srs, (int)unit * 8, 0, kSysScope);
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, unit_sk), krs, (int)unit * 8, 0, kSysScope);
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    prev = 0;
+    if (lane == 0) prev = __hip_atomic_fetch_add(&t.seq_cnt[b], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    prev = __builtin_amdgcn_readfirstlane(prev);
+    if (prev != dm.L * dm.Hkv - 1) return;
+    if (lane == 0) __hip_atomic_store(&t.seq_cnt[b], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // next prompt
+    __shared__ double s_a0[64], s_a1[64], s_frac[64];
+    __shared__ int s_i0[64], s_i1[64];
+    allocate_and_lay_out<true>(dm, t, b, sq, dm.retention, dm.budget_mode, dm.min_keep, false, lane, s_a0, s_a1, s_frac,
+                               s_i0, s_i1, [&](int l, double &a, double &c) __attribute__((always_inline)) {
+                                   // all heads' loads go out together; the sums run left to right over the live ones
+                                   u32x2 vs[16], vk[16];
+#pragma unroll
+                                   for (int h = 0; h < 16; ++h) {
+                                       const int off = (int)((((int64_t)l * dm.B + b) * dm.Hkv + min(h, dm.Hkv - 1)) * 8);
+                                       vs[h] = __builtin_amdgcn_raw_buffer_load_b64(srs, off, 0, kSysScope);
+                                       vk[h] = __builtin_amdgcn_raw_buffer_load_b64(krs, off, 0, kSysScope);
+                                   }
+#pragma unroll
+                                   for (int h = 0; h < 16; ++h) {
+                                       if (h < dm.Hkv) {
+                                           a += __builtin_bit_cast(double, vs[h]);
+                                           c += __builtin_bit_cast(double, vk[h]);
+                                       }
+                                   }
+                               });
 }
 
 }  // namespace air

@@ -16,11 +16,11 @@
 //       rows per head) it also stashes e = exp(s - m) per (row, key) in fp32, 4 bytes per row
 //       and key against the 256 bytes of the key itself.
 //   score_rows_mfma_kernel  per row: M = max over chunks (and over the elite-text columns),
-//       Z = sum z exp(m - M), weight w = 1 / (R_h G Z).  Launched for the windows that turn their
-//       whole span into rows; the elite window's few rows are done inside the finish kernel.
+//       Z = sum z exp(m - M), weight w = 1 / (R_h G Z).  Launched for windows that turn their
+//       whole span into rows (up to 32 of them); the elite window's rows are done inside the finish kernel.
 //   score_finish_kernel  units with a stash never touch K again:
-//       I[key] = sum_rows e[row][key] * (w exp(m_chunk - M)).  Units with more rows (continuous
-//       or all-text windows) recompute their logits from K_v: I[key] = sum_rows w exp(s - M).
+//       I[key] = sum_rows e[row][key] * (w exp(m_chunk - M)).  Units with more rows (a low threshold; windows without one
+//       have a kernel of their own, air_score_window.hip) recompute their logits from K_v: I[key] = sum_rows w exp(s - M).
 //       Epilogue: the workgroup's sum of I and its second and third moments about the workgroup's own
 //       mean (fp64); the unit's last workgroup to finish shifts the entries to the row mean and adds them
 //       up for Eq.9-10 (raw power sums would cancel on rows of little spread: S2 - S1 mu loses
@@ -374,6 +374,7 @@ __global__ __launch_bounds__(256, 4) void score_finish_kernel(Dims dm, DevTables
         put_moments(xs, ok);
         return;
     }
+    if constexpr (VIS) return;  // not reached: visual windows of more rows go to the kernel for many rows
     // recompute path: (M, w) of a block of rows staged from the row tables
     auto stage_rows = [&](int rs, int rows) {
         __syncthreads();
@@ -421,13 +422,8 @@ __global__ __launch_bounds__(256, 4) void score_finish_kernel(Dims dm, DevTables
                     const bool have = rr < rows_here;
                     const float M = have ? s_M[rr] : 0.f;
                     const float w = have ? s_w[rr] : 0.f;
-                    // visual window: the row sees the keys up to its own visual index
-                    const int lim = VIS ? (u.sq.win_start - u.sq.vis_start) + (rs + rr) % u.sq.win_len - (key0 + n) : 0;
 #pragma unroll
-                    for (int tile = 0; tile < 4; ++tile) {
-                        const float e = exp_key<D>(s[tile][i] - M);
-                        acc[tile] = fmaf(w, VIS && 16 * tile > lim ? 0.f : e, acc[tile]);
-                    }
+                    for (int tile = 0; tile < 4; ++tile) acc[tile] = fmaf(w, exp_key<D>(s[tile][i] - M), acc[tile]);
                 }
             }
         }
