@@ -100,13 +100,17 @@ WsLayout make_layout(const air_config &c) {
     w.cache_ptrs = take(L * sizeof(CachePtrs));
     w.dec_o = take(L * B * Hkv * kMaxSplits * 16 * D * 4);  // per (unit, split): 16 head rows x D
     w.dec_ml = take(L * B * Hq * kMaxSplits * 8);
+    auto take_stash = [&]() {
+        w.stash = take(has_stash(c) ? L * B * Hkv * (size_t)w.n_chunks * kStashRows * kChunkKeys * 4 : 0);
+        w.row_f = take(has_stash(c) && c.dtype == AIR_BF16 ? L * B * Hkv * (size_t)kStashRows * w.n_chunks * 4 : 0);
+    };
+    if (v_transposed(c.dtype, c.head_dim)) take_stash();
     w.unit_R = take(L * B * Hkv * 4);
     w.len_off = take(B * L * 8);
     w.by_length = take(B * L * 16);
-    // The stash comes last: fp32 and heads of 64 elements do without it in a workspace that ends here
+    // fp32 and heads of 64 elements have the stash last and do without it in a workspace that ends here
     w.least = off;
-    w.stash = take(has_stash(c) ? L * B * Hkv * (size_t)w.n_chunks * kStashRows * kChunkKeys * 4 : 0);
-    w.row_f = take(has_stash(c) && c.dtype == AIR_BF16 ? L * B * Hkv * (size_t)kStashRows * w.n_chunks * 4 : 0);
+    if (!v_transposed(c.dtype, c.head_dim)) take_stash();
     w.total = off;
     if (v_transposed(c.dtype, c.head_dim)) w.least = off;
     return w;
@@ -549,7 +553,8 @@ static void decode_shape(const air_ctx *ctx, int n_layers_in_launch, int appende
     // Short units of such a launch do better still as eight (four) workgroups each with its part of V' and no exchange (the
     // column parts: four waves, 64-key chunks): 4 units, us per launch against the splits, 642 keys 6.5 / 7.7, 1242 keys
     // 7.8 / 9.5, 1642 keys 9.1 / 9.7, 2442 keys 12.1 / 10.2.
-    // (The rule goes by the prompt's own length, so that a decode run keeps one shape from its first step to its last.)
+    // (Whether a unit is short goes by the prompt's own length, for every storage, so that a decode run does not change
+    // between parts and splits on the way.)
     // The other storages (bf16 with heads of 64 elements, fp32) split from 288 KB a unit on: 4 units, us per launch as one
     // workgroup of eight waves against the best split, bf16 d = 64 112 KB 5.9 / 7.0, 266 KB 7.2 / 7.5, 770 KB 12.8 / 8.4;
     // fp32 d = 64 225 KB 8.1 / 8.4, 530 KB 13.1 / 8.9; fp32 d = 128 450 KB 13.9 (two parts 11.1) / 9.6.
@@ -644,8 +649,12 @@ static air_status decode_attn(air_ctx *ctx, void *stream, int32_t l0, int32_t l1
         const bool can = in_step && (hkv & (hkv - 1)) == 0 && splits == 1 && waves == 4 && tiles == decode_tiles_of(ctx->cfg);
         const int64_t units = (nl * units_per_layer + 7) & ~7;
         if (!can || ctx->tune.decode_halves == 1 || (units > 128 && ctx->tune.decode_halves != 2)) return 1;
-        // more than two parts only for caches of 640 keys on (by the prompt's own length): at 60-340 keys a unit the launch is all
-        // latency and more workgroups cost 0.4-1.4 us of it
+        // More than two parts only for caches of 640 keys on (by the prompt's own length, whatever a key's bytes).  Requests of four
+        // steps, 32 units (heads of 128 in bf16), us with 2 / 4 / 8 parts: 60 keys 48.9 / 53.8 / 52.6, 200 keys 50.3 / 52.8 / 52.0,
+        // 400 keys 56.0 / 55.4 / 54.7, 640 keys 63.4 / 61.4 / 60.7, 900 keys 66.4 / 64.7 / 63.8: the line is on the safe side of
+        // the crossing.  Steps alone, cache warm, us a launch of 4 units at 100 / 300 / 640 / 1000 keys: bf16 d = 128 4.1 / 5.0 / 6.5 /
+        // 8.0 with two parts, 3.8 / 4.6 / 5.9 / 7.3 with four; bf16 d = 64 3.8 / 4.8 / 5.5 / 6.9 and 3.5 / 4.4 / 5.1 / 6.4; fp32 at 100
+        // keys, d = 64 5.2 and 4.7, d = 128 6.7 and 6.1 (longer ones are split).
         const double keys = cache_bytes(ctx) / ((double)ctx->cfg.n_layers * ctx->cfg.batch * hkv * 2.0 * ctx->cfg.head_dim *
                                                 (ctx->cfg.dtype == AIR_BF16 ? 2.0 : 4.0));
         int parts = keys < 640.0 ? 2 : (ctx->cfg.head_dim == 128 ? 8 : 4);

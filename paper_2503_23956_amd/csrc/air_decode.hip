@@ -208,11 +208,12 @@ __global__ __launch_bounds__(64 * NW) void decode_mfma_kernel(Dims dm, DecodeTab
     // that is replayed): the workgroup that finishes the unit advances the count, after every workgroup
     // of the unit has read it
     int appended = ll.uniform >= 0 ? ll.uniform : ll.appended[li];
-    if (t.dec_steps) {
-        // a workgroup past the last unit is not counted at the unit's arrival counter: the count it would read may already be the
-        // next step's, and with it a cache that only looks full
-        if (VH > 1 && !live) return;
-        appended = t.dec_steps[unit];
+    // A workgroup past the last unit does not look at the device's count: it is not counted at the unit's arrival counter, so
+    // that the count may already be the next step's, and with it a cache that only looks full.  (A pointer it does not have, not
+    // a return in front of it: behind a branch the argument is fetched late, 0.15 us a launch.)
+    const int32_t *const steps = VH > 1 && !live ? nullptr : t.dec_steps;
+    if (steps) {
+        appended = steps[unit];
         if (appended >= dm.max_steps) {  // cache full: nothing is appended or written
             if (threadIdx.x == 0) t.dec_steps[t.n_units] = 1;
             return;
@@ -243,8 +244,8 @@ __global__ __launch_bounds__(64 * NW) void decode_mfma_kernel(Dims dm, DecodeTab
         for (int s = 0; s < NS; ++s) qb[s] = *reinterpret_cast<const uint4 *>(q + Elem<T>::kSlice * s + kVec * c);
     }
     constexpr double kScale2D = (D == 128 ? 0.08838834764831845 : 0.125) * 1.4426950408889634;  // log2(e) / sqrt(d)
-    // fp32 and heads of 64 elements take it to 46 bits; the second term is positive, so that a masked score stays -inf
-    constexpr bool kTwoTerm = sizeof(T) == 4 || D == 64;
+    // fp32 takes it to 46 bits; the second term is positive, so that a masked score stays -inf
+    constexpr bool kTwoTerm = sizeof(T) == 4;
     constexpr float kScale2 = (float)(kTwoTerm ? kScale2D * (1.0 - 1.2e-7) : kScale2D);
     constexpr float kScale2Lo = (float)(kScale2D - (double)kScale2);
     static_assert(!kTwoTerm || kScale2Lo > 0.f, "sign of the second term");
@@ -288,8 +289,9 @@ __global__ __launch_bounds__(64 * NW) void decode_mfma_kernel(Dims dm, DecodeTab
         sn += __shfl_xor(sn, 32, 64);
         m_run = sn * kScale2;
         float p = 1.f;
-        if constexpr (kTwoTerm) {
-            p = __builtin_amdgcn_exp2f(fmaf(sn, kScale2Lo, fmaf(sn, kScale2, -m_run)));
+        if constexpr (sizeof(T) == 4 || D == 64) {
+            const float x = fmaf(sn, kScale2, -m_run);
+            p = __builtin_amdgcn_exp2f(kTwoTerm ? fmaf(sn, kScale2Lo, x) : x);
             if (m_run == -INFINITY) p = 0.f;
         }
         l_run = c == 0 ? p : 0.f;  // l_run is a per-lane partial of the head's sum: the token counts once
@@ -297,7 +299,7 @@ __global__ __launch_bounds__(64 * NW) void decode_mfma_kernel(Dims dm, DecodeTab
         for (int j = 0; j < NJ; ++j) {
             const float v = ldf(&vnew[j]);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) acc[j][i] = kTwoTerm ? v * __shfl(p, 4 * c + i, 64) : v;  // rows are heads 4c..4c+3
+            for (int i = 0; i < 4; ++i) acc[j][i] = sizeof(T) == 4 || D == 64 ? v * __shfl(p, 4 * c + i, 64) : v;  // rows are heads 4c..4c+3
         }
     }
 
@@ -388,7 +390,7 @@ __global__ __launch_bounds__(64 * NW) void decode_mfma_kernel(Dims dm, DecodeTab
                 float x = fmaf(s[tile][i], kScale2, -m_ref);
                 if (kTwoTerm) x = fmaf(s[tile][i], kScale2Lo, x);
                 const float p = __builtin_amdgcn_exp2f(x);
-                s[tile][i] = kNonFinite ? fmaxf(p, kLeast) : p;
+                s[tile][i] = sizeof(T) == 4 ? fmaxf(p, kLeast) : p;
                 lb += p;
             }
         l_run += lb;
@@ -408,6 +410,8 @@ __global__ __launch_bounds__(64 * NW) void decode_mfma_kernel(Dims dm, DecodeTab
 #pragma unroll
                     for (int i = 0; i < 8; ++i) pa[0][i] = (__bf16)s[2 * tb + (i >> 2)][i & 3];
                 } else {
+                    typedef __attribute__((ext_vector_type(2))) unsigned short u16x2;
+                    constexpr uint32_t kLeast2 = 0x00800080u;  // twice kLeast in bf16; positive values order as their bits do
                     u32x4 term[kTerms];
 #pragma unroll
                     for (int w = 0; w < 4; ++w) {
@@ -415,9 +419,10 @@ __global__ __launch_bounds__(64 * NW) void decode_mfma_kernel(Dims dm, DecodeTab
 #pragma unroll
                         for (int k = 0; k < kTerms; ++k) {
                             const uint32_t t0 = __float_as_uint(p0) & 0xffff0000u, t1 = __float_as_uint(p1) & 0xffff0000u;
-                            term[k][w] = (t0 >> 16) | t1;
-                            p0 = fmaxf(p0 - __uint_as_float(t0), kLeast);
-                            p1 = fmaxf(p1 - __uint_as_float(t1), kLeast);
+                            term[k][w] = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, (t0 >> 16) | t1),
+                                                                                                __builtin_bit_cast(u16x2, kLeast2)));
+                            p0 -= __uint_as_float(t0);
+                            p1 -= __uint_as_float(t1);
                         }
                     }
 #pragma unroll

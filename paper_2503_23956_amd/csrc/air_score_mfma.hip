@@ -142,8 +142,10 @@ __global__ __launch_bounds__(256, 4) void score_stream_kernel(Dims dm, DevTables
                 for (int tile = 0; tile < 4; ++tile) e[tile] = live(tile, i) ? exp_key<D>(s[tile][i] - M) : 0.f;
                 float zz = (e[0] + e[1]) + (e[2] + e[3]);
                 if (stash && rb + r < u.R_total)
-                    // read once, by the next kernel: marked so (scoring, 16 prompts of ~2304 tokens 341 -> 335 us, two of 16384
-                    // with 80 layers 1441 -> 1385, one of 7290 unchanged; marking the key loads costs 1-11 %)
+                    // read once, by the next kernel: marked so.  us for air_score marked / plain: one layer of 576 ... 16384 tokens and
+                    // one prompt of them in 28 layers no difference (29.7 / 29.7, 65.5 / 65.4, 135.0 / 134.9), four of 2304 81.2 / 81.5,
+                    // eight 157 / 161, sixteen 302 / 310, four of 6272 201 / 204, two of 16384 in 32 layers of 8 KV heads
+                    // 552 / 571.  Marking the key loads costs 1-11 %.
                     __builtin_nontemporal_store(e, reinterpret_cast<f32x4 *>(stash_base + (int64_t)(rb + r) * kChunkKeys + wave * 64 + 4 * n));
                 z[i] = sum16(zz);
                 if (wave == 0 && n == 0) s_mw[r] = M;
