@@ -180,7 +180,7 @@ air_status air_score(air_ctx *ctx, void *stream, int32_t l0, int32_t l1, const a
                      const air_strides *strides, const air_seq *seqs);
 
 /* Eq.11 for every sequence.  All layers must have been scored (else AIR_ERR_STATE).  Where every layer went
- * through air_score exactly once since the reset, with at most 64 layers and 16 KV
+ * through air_score exactly once since the reset and no budgets were set by the caller, with at most 64 layers and 16 KV
  * heads, the last kernel of air_score has done the allocation in its tail and this call launches nothing; it is
  * still the call that makes the budgets available to air_select_compact.  Call it on the stream air_score ran on
  * (or one ordered behind it). */
@@ -200,6 +200,8 @@ air_status air_select_compact(air_ctx *ctx, void *stream, int32_t l0, int32_t l1
  * cache (Eq.2), then out[h] = softmax(q_h K'^T / sqrt(d)) V' over the whole cache
  * including the new token.  All tensors dense: q_new, out [l1-l0][B][H_q][d];
  * k_new, v_new [l1-l0][B][H_kv][d].  At most max_decode_steps calls per layer.
+ * A logit of -inf weighs nothing and an infinite element of V makes its output column infinite, except in bf16 with
+ * head_dim 128, where 64 keys in a row that have no other logit, and infinities in the last 32 rows, may give NaN.
  * The call enqueues kernel launches only (no copy, no memset, no allocation, no host wait), so it
  * can be recorded into a HIP graph.  With cfg.device_steps the recorded step advances the cache by
  * itself on every replay; the host then cannot check the capacity: a step that runs with the cache

@@ -17,9 +17,11 @@
 // place of 4.3e-7 for logits of a spread of 5, 4.0e-6 in place of 8.7e-7 for a spread of 18, heads of 128.  The limit on a sum
 // weighs the error of the step that finds a logit far above the reference against doing it again: 2^12 / 2^16 / 2^24 / 2^100,
 // us for 224 rows at a spread of 5: 271 / 250 / 220 / 226, at a spread of 2: 222 / 220 / 218 / 224.)
-// Bound: the vector unit (16 clocks of a SIMD for 64 exponentials, 4 for each of the other instructions, counters: 83 % of
-// the clocks) with the matrix unit busy for a quarter of the time.
-// 224 rows per unit (7 heads x 32), 28 layers x 4 KV heads x 7290 keys, us for the two passes: 208 (104 each).  Before, a
+// Bound: nothing alone.  The exponentials are 19 us a pass (2.86 M of a wave, 16 clocks of a SIMD each), 33 with the three
+// instructions beside each; counters: vector issue 55 % of the clocks in pass 1 and 40 % in pass 2, matrix unit 20 and 18 %.  The
+// rest is waiting: a barrier per 64 keys, 57 KB of query rows and (pass 2) the rows' parameters in front of 8-16 steps, 14
+// blocks dealt 3 / 4 / 3 / 4, two workgroups a CU in 3.3 rounds (pass 1, 1680 workgroups) and 1.75 (pass 2, 896).
+// 224 rows per unit (7 heads x 32), 28 layers x 4 KV heads x 7290 keys, us for the two passes: 207 (102 + 105).  Before, a
 // workgroup kept 256 keys and walked the rows with three barriers and two reductions over sixteen lanes per 16 rows, plus a
 // kernel for the row parameters, layers in two groups: 478 (195 + 40 + 243).
 #include "air_score_mfma_dev.h"
