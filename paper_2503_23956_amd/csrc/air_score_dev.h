@@ -8,6 +8,19 @@
 
 namespace air {
 
+// Eq.10 from the central sums of second and third powers
+__device__ __forceinline__ double skewness(int n_vis, double mu, double c2, double c3) {
+#pragma clang fp contract(off)
+    const double n = (double)n_vis;
+    double sk = 0.0;
+    if (n_vis >= 3) {
+        const double sigma = sqrt(c2 / (n - 1.0));
+        // zero spread (Eq.10 undefined; taken as 0): a standard deviation at most 1e-6 of the mean
+        if (sigma > 1e-6 * fabs(mu)) sk = n / ((n - 1.0) * (n - 2.0)) * (c3 / (sigma * sigma * sigma));
+    }
+    return sk;
+}
+
 // Eq.9-10 of one (layer, sequence, KV head) from the moment entries of its importance row, by one wave.  Entry c holds
 // the sum S1_c, the mean m_c and the moments M2_c, M3_c about m_c of the n_c scores of kFinishChunks chunks.  With
 // d_c = m_c - mu the central moments of the row are
@@ -61,14 +74,56 @@ __device__ __forceinline__ void unit_statistics(__amdgpu_buffer_rsrc_t ers, int 
     }
     c2 = sum16(c2);
     c3 = sum16(c3);
-    double sk = 0.0;
-    if (n_vis >= 3) {
-        const double sigma = sqrt(c2 / (n - 1.0));
-        // zero spread (Eq.10 undefined; taken as 0): a standard deviation at most 1e-6 of the mean
-        if (sigma > 1e-6 * fabs(mu)) sk = n / ((n - 1.0) * (n - 2.0)) * (c3 / (sigma * sigma * sigma));
-    }
     st_out = S1;
-    sk_out = sk;
+    sk_out = skewness(n_vis, mu, c2, c3);
+}
+
+// The statistics of a unit that is complete, by one wave; the last unit of a sequence goes on to Eq.11 (dm.fuse_budget).
+__device__ __forceinline__ void leave_unit(const Dims &dm, const DevTables &t, int64_t unit, int b, const air_seq &sq, int lane,
+                                           double unit_st, double unit_sk) {
+    if (!dm.fuse_budget) {
+        if (lane == 0) {
+            t.unit_st[unit] = unit_st;
+            t.unit_sk[unit] = unit_sk;
+        }
+        return;
+    }
+    // The same once more, one level up: the unit's statistics go out written through, the wave counts the unit at
+    // its sequence's arrival counter, and the wave that counts the last of the L * H_kv units does Eq.11 and the
+    // cache layout of the sequence (the layers fit one wave): air_budget has nothing left to launch.
+    const int64_t all_units = (int64_t)dm.L * dm.B * dm.Hkv;
+    const __amdgpu_buffer_rsrc_t srs = __builtin_amdgcn_make_buffer_rsrc(t.unit_st, 0, (int)(all_units * 8), 0x00020000);
+    const __amdgpu_buffer_rsrc_t krs = __builtin_amdgcn_make_buffer_rsrc(t.unit_sk, 0, (int)(all_units * 8), 0x00020000);
+    if (lane == 0) {
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, unit_st), srs, (int)unit * 8, 0, kSysScope);
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, unit_sk), krs, (int)unit * 8, 0, kSysScope);
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    int prev = 0;
+    if (lane == 0) prev = __hip_atomic_fetch_add(&t.seq_cnt[b], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    prev = __builtin_amdgcn_readfirstlane(prev);
+    if (prev != dm.L * dm.Hkv - 1) return;
+    if (lane == 0) __hip_atomic_store(&t.seq_cnt[b], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // next prompt
+    __shared__ double s_a0[64], s_a1[64], s_frac[64];
+    __shared__ int s_i0[64], s_i1[64];
+    allocate_and_lay_out<true>(dm, t, b, sq, dm.retention, dm.budget_mode, dm.min_keep, false, lane, s_a0, s_a1, s_frac,
+                               s_i0, s_i1, [&](int l, double &a, double &c) __attribute__((always_inline)) {
+                                   // all heads' loads go out together; the sums run left to right over the live ones
+                                   u32x2 vs[16], vk[16];
+#pragma unroll
+                                   for (int h = 0; h < 16; ++h) {
+                                       const int off = (int)((((int64_t)l * dm.B + b) * dm.Hkv + min(h, dm.Hkv - 1)) * 8);
+                                       vs[h] = __builtin_amdgcn_raw_buffer_load_b64(srs, off, 0, kSysScope);
+                                       vk[h] = __builtin_amdgcn_raw_buffer_load_b64(krs, off, 0, kSysScope);
+                                   }
+#pragma unroll
+                                   for (int h = 0; h < 16; ++h) {
+                                       if (h < dm.Hkv) {
+                                           a += __builtin_bit_cast(double, vs[h]);
+                                           c += __builtin_bit_cast(double, vk[h]);
+                                       }
+                                   }
+                               });
 }
 
 // Moments of a workgroup's scores, every sum in a fixed order: S1 = sum x, the workgroup mean S1 / n, then
@@ -129,49 +184,65 @@ __device__ __forceinline__ void leave_moments(const Dims &dm, const DevTables &t
     if (lane == 0) __hip_atomic_store(&t.unit_cnt[unit], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // next launch
     double unit_st, unit_sk;
     unit_statistics(ers, n_ent, sq.vis_len, lane, unit_st, unit_sk);
-    if (!dm.fuse_budget) {
-        if (lane == 0) {
-            t.unit_st[unit] = unit_st;
-            t.unit_sk[unit] = unit_sk;
-        }
-        return;
-    }
-    // The same once more, one level up: the unit's statistics go out written through, the wave counts the unit at
-    // its sequence's arrival counter, and the wave that counts the last of the L * H_kv units does Eq.11 and the
-    // cache layout of the sequence (the layers fit one wave): air_budget has nothing left to launch.
-    const int64_t all_units = (int64_t)dm.L * dm.B * dm.Hkv;
-    const __amdgpu_buffer_rsrc_t srs = __builtin_amdgcn_make_buffer_rsrc(t.unit_st, 0, (int)(all_units * 8), 0x00020000);
-    const __amdgpu_buffer_rsrc_t krs = __builtin_amdgcn_make_buffer_rsrc(t.unit_sk, 0, (int)(all_units * 8), 0x00020000);
-    if (lane == 0) {
-        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, unit_st), srs, (int)unit * 8, 0, kSysScope);
-        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, unit_sk), krs, (int)unit * 8, 0, kSysScope);
-    }
+    leave_unit(dm, t, unit, b, sq, lane, unit_st, unit_sk);
+}
+
+// The same for a workgroup of NW waves that has written scores of its unit, through to memory (all of its waves; n_parts
+// workgroups share the unit): the last of them reads the unit's scores back past the caches and forms S1, the mean and the central
+// sums from them, in a fixed order, whatever the workgroups' parts were.  s_mom: as above; s_last: an int in LDS.
+template <int NW>
+__device__ __forceinline__ void leave_scores(const Dims &dm, const DevTables &t, int64_t unit, int b, const air_seq &sq, int n_parts,
+                                             double (&s_mom)[NW][3], int &s_last) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    prev = 0;
-    if (lane == 0) prev = __hip_atomic_fetch_add(&t.seq_cnt[b], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    prev = __builtin_amdgcn_readfirstlane(prev);
-    if (prev != dm.L * dm.Hkv - 1) return;
-    if (lane == 0) __hip_atomic_store(&t.seq_cnt[b], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // next prompt
-    __shared__ double s_a0[64], s_a1[64], s_frac[64];
-    __shared__ int s_i0[64], s_i1[64];
-    allocate_and_lay_out<true>(dm, t, b, sq, dm.retention, dm.budget_mode, dm.min_keep, false, lane, s_a0, s_a1, s_frac,
-                               s_i0, s_i1, [&](int l, double &a, double &c) __attribute__((always_inline)) {
-                                   // all heads' loads go out together; the sums run left to right over the live ones
-                                   u32x2 vs[16], vk[16];
+    lds_barrier();
+    if (tid == 0) s_last = __hip_atomic_fetch_add(&t.unit_cnt[unit], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n_parts - 1;
+    lds_barrier();
+    if (!s_last) return;
+    if (tid == 0) __hip_atomic_store(&t.unit_cnt[unit], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // next launch
+    const int n_vis = sq.vis_len;
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(t.scores + unit * dm.max_vis, 0, n_vis * 4, 0x00020000);
+    constexpr int kAtOnce = 16, kStep = 64 * NW;  // reads past the scores give zero
+    auto over_waves = [&](int slot) {
+        double v = s_mom[0][slot];
 #pragma unroll
-                                   for (int h = 0; h < 16; ++h) {
-                                       const int off = (int)((((int64_t)l * dm.B + b) * dm.Hkv + min(h, dm.Hkv - 1)) * 8);
-                                       vs[h] = __builtin_amdgcn_raw_buffer_load_b64(srs, off, 0, kSysScope);
-                                       vk[h] = __builtin_amdgcn_raw_buffer_load_b64(krs, off, 0, kSysScope);
-                                   }
+        for (int w = 1; w < NW; ++w) v += s_mom[w][slot];
+        return v;
+    };
+    float x[kAtOnce];
+    auto read = [&](int i0) {
 #pragma unroll
-                                   for (int h = 0; h < 16; ++h) {
-                                       if (h < dm.Hkv) {
-                                           a += __builtin_bit_cast(double, vs[h]);
-                                           c += __builtin_bit_cast(double, vk[h]);
-                                       }
-                                   }
-                               });
+        for (int j = 0; j < kAtOnce; ++j)
+            x[j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, (i0 + kStep * j + tid) * 4, 0, kSysScope));
+    };
+    double s1 = 0.0;
+    for (int i0 = 0; i0 < n_vis; i0 += kStep * kAtOnce) {
+        read(i0);
+#pragma unroll
+        for (int j = 0; j < kAtOnce; ++j) s1 += (double)x[j];
+    }
+    s1 = wave_sum(s1);
+    if (lane == 0) s_mom[wave][0] = s1;
+    lds_barrier();
+    const double S1 = over_waves(0), mu = S1 / (double)n_vis;
+    double m2 = 0.0, m3 = 0.0;
+    for (int i0 = 0; i0 < n_vis; i0 += kStep * kAtOnce) {
+        if (n_vis > kStep * kAtOnce) read(i0);  // (else they are still there)
+#pragma unroll
+        for (int j = 0; j < kAtOnce; ++j) {
+            const double dlt = i0 + kStep * j + tid < n_vis ? (double)x[j] - mu : 0.0;
+            m2 += dlt * dlt;
+            m3 += dlt * dlt * dlt;
+        }
+    }
+    m2 = wave_sum(m2);
+    m3 = wave_sum(m3);
+    if (lane == 0) {
+        s_mom[wave][1] = m2;
+        s_mom[wave][2] = m3;
+    }
+    lds_barrier();
+    if (wave == 0) leave_unit(dm, t, unit, b, sq, lane, S1, skewness(n_vis, mu, over_waves(1), over_waves(2)));
 }
 
 }  // namespace air

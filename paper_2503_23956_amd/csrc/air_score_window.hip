@@ -1,432 +1,442 @@
 // air_score, bf16, windows that turn their whole span into rows (a continuous, all-text or visual window of dozens to
-// hundreds of rows per unit): Eq.6-8 with the ROWS kept in registers and the keys streamed past them, twice.
+// hundreds of rows per unit): Eq.6-8 with the ROWS in LDS, once per workgroup, and the keys of a wave in its registers, twice.
 //
-// A workgroup of four waves owns a run of a unit's keys.  Every wave holds up to 64 window rows (four MFMA A operands of 16
-// rows) and all waves take the same 64 keys at a time from LDS (double-buffered, one barrier per 64 keys, the next keys
-// in flight meanwhile).  Exponentials are 2^(s kC - m): one fused multiply-add and one exponential per element, with a
-// reference m that is a whole number, so that references are moved and partial sums merged exactly.
-//   pass 1  leaves (reference, sum) per (row, run of keys).  The reference starts at the maximum over the first 64 keys of
-//           the run; a lane raises its own, and scales its sum down, after a step that left the sum above its limit: one
-//           addition per element, no maximum.
+// A workgroup of eight waves takes a part of a unit's keys; its waves share up to 256 window rows in LDS (loaded straight into
+// it) and go their own ways: a wave loads 64 (pass 1: 32) keys from memory as MFMA operands, walks the row blocks over them and
+// takes its next keys, without a barrier.  Exponentials are 2^(s kC - m): one fused multiply-add and one exponential per
+// element, with a reference m that is a whole number, so that references are moved and partial sums merged exactly.
+//   pass 1  products of 32 keys x 32 rows: a lane holds 16 logits of ONE window row per block, so that it needs one sum and one
+//           reference per block.  Leaves (reference, sum) per (row, run of keys).  A lane whose 16 exponentials add up
+//           to more than its limit raises its reference to their maximum and forms them again.
 //   pass 2  forms maximum, fp64 normaliser and weight of the unit's rows from the partials, a thread per row, then
-//           I[key] = sum over the rows of w 2^(s kC - m): one fused add per element, the sum over the
-//           lanes and waves once per 64 keys.
+//           I[key] = sum over the rows of w 2^(s kC - m): the keys of a wave are complete after the last row block (two steps
+//           across the lanes).  The unit's last workgroup forms its statistics from the scores.
+// Bound: instruction issue, of which the exponentials are half: 484 clocks per 64 keys and 16 rows in pass 2, 256 of them
+// exponentials, 64 products, 128 the multiply-adds; 43 us for 224 rows x 112 units x 7290 keys at the 1.97 GHz that the chip holds
+// under this load.  The rest: about 9 us in front (row lists, 57 KB of rows, parameters: chains of dependent accesses) and a
+// last round that is not full.  Four waves a SIMD need 128 registers: everything in front of the loops is kept out of
+// registers across them (`here`), because a spill in the prologue cost 15-30 us (its scratch is touched for the first time).
+// 224 rows per unit (7 heads x 32), 28 layers x 4 KV heads x 7290 keys, us for air_score with the elite kernel (16): 172.  Before, the
+// rows in registers, the keys through LDS with a barrier per 64 keys, four waves of 3 and 4 row blocks: 203.  10 rows a head 128 ->
+// 108, 48 rows of 8 heads 335 -> 280, four layers 79 -> 66, heads of 64 165 -> 134, 28 layers one by one 2080 -> 1740.
 // Precision: the argument of an exponential is rounded, to 2^-24 of itself, and the largest terms are the ones that count, so a
 // reference has to stay near the maximum; and a logit keeps its bits only if its sum starts at zero.  (With sums that
 // started at minus the reference, and the lane's first logit as reference up to 2^100, the scores were 9.7e-7 off fp64 in
-// place of 4.3e-7 for logits of a spread of 5, 4.0e-6 in place of 8.7e-7 for a spread of 18, heads of 128.  The limit on a sum
-// weighs the error of the step that finds a logit far above the reference against doing it again: 2^12 / 2^16 / 2^24 / 2^100,
-// us for 224 rows at a spread of 5: 271 / 250 / 220 / 226, at a spread of 2: 222 / 220 / 218 / 224.)
-// Bound: nothing alone.  The exponentials are 19 us a pass (2.86 M of a wave, 16 clocks of a SIMD each), 33 with the three
-// instructions beside each; counters: vector issue 55 % of the clocks in pass 1 and 40 % in pass 2, matrix unit 20 and 18 %.  The
-// rest is waiting: a barrier per 64 keys, 57 KB of query rows and (pass 2) the rows' parameters in front of 8-16 steps, 14
-// blocks dealt 3 / 4 / 3 / 4, two workgroups a CU in 3.3 rounds (pass 1, 1680 workgroups) and 1.75 (pass 2, 896).
-// 224 rows per unit (7 heads x 32), 28 layers x 4 KV heads x 7290 keys, us for the two passes: 207 (102 + 105).  Before, a
-// workgroup kept 256 keys and walked the rows with three barriers and two reductions over sixteen lanes per 16 rows, plus a
-// kernel for the row parameters, layers in two groups: 478 (195 + 40 + 243).
+// place of 4.3e-7 for logits of a spread of 5, 4.0e-6 in place of 8.7e-7 for a spread of 18, heads of 128.)
 #include "air_score_mfma_dev.h"
 
 #include <type_traits>
 
 namespace air {
 
-constexpr int kStepKeys = 64;                 // keys in LDS at a time
-// Four waves with four blocks each and two waves a SIMD: eight with two blocks, at three or four a SIMD, measured 240-277 us
-// against 230 for 224 rows (a key operand read from LDS then serves half as many rows, or registers spill).
-constexpr int kWaves = 4, kThreads = 64 * kWaves;
-constexpr int kWaveBlocks = 4;                 // blocks of 16 rows per wave
-constexpr int kWinRows = kWaves * kWaveBlocks * 16;  // rows of a workgroup at a time
+typedef __attribute__((ext_vector_type(16))) float f32x16;
 
-// Keys in LDS: place p of key k holds its 16-byte piece p ^ swizzle(k), so that the sixteen keys that a read of one piece
-// touches lie in different banks.  They pass through registers: with loads straight into LDS the compiler waits for all of
-// them in front of the first LDS read behind them, the other buffer's keys or not.
+constexpr int kWaves = 8, kThreads = 64 * kWaves;
+constexpr int kWinRows = 256;                  // rows in LDS at a time
+constexpr int kPartLeast = 512, kPartMost = 2048;  // keys of a workgroup
+constexpr int kTiles = 4;                      // pass 2: tiles of 16 keys in a wave's registers
+// Beyond 2^22 a reference and a logit no longer differ by what fp32 says they do (raw logits of 3e7: keys masked by a large
+// negative number, operands in the thousands).  References stop there; logits below weigh nothing, logits above are
+// held at the bound: in pass 1 where exponentials are formed again, in pass 2 by a plain loop over the rows that have such a
+// reference.  -2^22 is also where a reference starts: the first logits above it raise it.
+constexpr float kFar = 0x1p22f;
 template <int D>
-__device__ __forceinline__ int key_swizzle(int key) {
-    return D == 128 ? key & 15 : (key >> 1) & 7;
+__device__ __forceinline__ float held(float s) {
+    constexpr float kFarRaw = kFar / Log2Scale<D>::kHi;
+    return s > kFarRaw ? kFarRaw : (s < -kFarRaw ? -kFarRaw : s);
+}
+
+// Rows in LDS: place p of row r holds its 16-byte piece p ^ swizzle(r), so that the sixteen rows that a read of one piece
+// touches lie in different banks.
+template <int D>
+__device__ __forceinline__ int row_swizzle(int row) {
+    return D == 128 ? row & 15 : (row >> 1) & 7;
 }
 
 __device__ __forceinline__ int ilogb_of(float x) { return (int)(__float_as_uint(x) >> 23) - 127; }  // of a normal number above 0
 
-template <int D, int PASS>
-__global__ __launch_bounds__(kThreads, 2) void window_kernel(Dims dm, DevTables t, int l0, LaunchLayers ll, air_strides st, SeqArgs seqs,
-                                                        int seg_chunks) {
-    constexpr int NS = D / 32;
-    constexpr int kPieces = D / 8;               // 16-byte pieces of a key
-    constexpr int kIt = kStepKeys * kPieces / kThreads;
+// the lane's 16 bytes of row n of a block in LDS, slice by slice
+template <int D>
+__device__ __forceinline__ void row_places(int n, int c, int (&row_at)[D / 32]) {
+#pragma unroll
+    for (int sl = 0; sl < D / 32; ++sl) row_at[sl] = n * D + 8 * ((4 * sl + c) ^ row_swizzle<D>(n));
+}
+
+// A value that the compiler takes as new: what follows from it is formed where it is used, not in front of the loop around
+// (held in registers there it was spilled, and a spill in the prologue costs microseconds).
+__device__ __forceinline__ int here(int x) {
+    asm volatile("" : "+v"(x));
+    return x;
+}
+
+// the keys of a wave's group as MFMA operands; keys past the end of the span repeat the last one
+template <int TILES, int NS>
+__device__ __forceinline__ void group_keys(const UnitCtx &u, const air_strides &st, int key0, uint4 (&kreg)[TILES][NS]) {
+    const int lane = here(threadIdx.x & 63), n = lane & 15, c = lane >> 4;
+#pragma unroll
+    for (int tile = 0; tile < TILES; ++tile) {
+        const bf16_t *src = u.k + (int64_t)(u.sq.vis_start + min(key0 + 16 * tile + n, u.sq.vis_len - 1)) * st.kv_t + 8 * c;
+#pragma unroll
+        for (int sl = 0; sl < NS; ++sl) kreg[tile][sl] = *reinterpret_cast<const uint4 *>(src + 32 * sl);
+    }
+}
+
+// a row's query: head of the group and place in the query tensor (below 2^27), as one word in LDS
+__device__ __forceinline__ const bf16_t *query_of(const UnitCtx &u, const air_strides &st, int word) {
+    return u.q + (int64_t)(u.kvh * u.G + (int)((unsigned)word >> 27)) * st.q_h + (int64_t)(word & 0x7ffffff) * st.q_t;
+}
+
+// The rows of a workgroup straight into LDS, n_load of them (whole blocks; those past the list repeat the last one); the
+// caller waits for them.
+template <int D>
+__device__ __forceinline__ void load_rows_lds(const UnitCtx &u, const air_strides &st, const int *s_query, bf16_t *s_rows, int n_rows, int n_load, int wave) {
+    typedef __attribute__((address_space(1))) void gptr_t;
+    typedef __attribute__((address_space(3))) void lptr_t;
+    constexpr int kPieces = D / 8, kRowsOfWave = 64 / kPieces;
+    const int lane = here(threadIdx.x & 63);
+    for (int row0 = kRowsOfWave * wave; row0 < n_load; row0 += kRowsOfWave * kWaves) {
+        const int row = row0 + lane / kPieces;  // lane i's 16 bytes land at the place of lane 0's + 16 i
+        const bf16_t *src = query_of(u, st, s_query[min(row, n_rows - 1)]) + 8 * ((lane % kPieces) ^ row_swizzle<D>(row));
+        __builtin_amdgcn_global_load_lds((gptr_t *)src, (lptr_t *)(s_rows + row0 * D), 16, 0, 0);
+    }
+}
+__device__ __forceinline__ void rows_wait_barrier() {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    lds_barrier();
+}
+
+// ---------------------------------------------------------------------------------------
+// Pass 1.  A workgroup takes a run of run_keys keys of a unit.  Products of 32 keys x 32 rows: lane (n, c),
+// n = lane % 32, holds sixteen logits of row n.
+constexpr int kBlocks1 = kWinRows / 32;
+template <int D>
+__global__ __launch_bounds__(kThreads, 4) void window_sums_kernel(Dims dm, DevTables t, int l0, LaunchLayers ll, air_strides st, SeqArgs seqs,
+                                                               int run_keys) {
+    constexpr int NS = D / 16, kGroup = 32;
     constexpr float kC = Log2Scale<D>::kHi;
-    constexpr float kSumLimit = 64.0f;   // of a lane's sum in front of a step: it has at most 64 keys of a row
-    constexpr float kSumMost = 0x1p24f;  // a step that leaves a sum above this is done again
-    constexpr float kHigh = 4.0f;        // then with the reference raised in front of exponentials above 2^kHigh
-    // Beyond 2^22 a reference and a logit no longer differ by what fp32 says they do (raw logits of 3e7: keys masked by a large
-    // negative number, operands in the thousands).  References stop there; logits below weigh nothing, logits above are
-    // held at the bound: in pass 1 when their step is done again, in pass 2 by a plain loop over the rows that have such a reference.
-    constexpr float kFar = 0x1p22f, kFarRaw = kFar / kC;
-    auto held = [](float s) __attribute__((always_inline)) { return s > kFarRaw ? kFarRaw : (s < -kFarRaw ? -kFarRaw : s); };
-    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, n = lane & 15, c = lane >> 4;
-    const int wg_chunks = PASS == 1 ? seg_chunks : kFinishChunks;
+    constexpr float kSumLimit = 64.0f;  // of a lane's exponentials of a block
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     UnitCtx u;
-    if (!unit_setup(dm, seqs, l0, ll, st, u, wg_chunks)) return;
+    if (!unit_setup(dm, seqs, l0, ll, st, u, 0) || (int)blockIdx.x * run_keys >= u.sq.vis_len) return;
     __shared__ int s_pref[17];
-    __shared__ __align__(16) bf16_t s_k[2][kStepKeys * D];
-    __shared__ float s_M[kWinRows], s_w[kWinRows];
-    __shared__ int s_any_far;             // pass 2: some row has its reference at the bound
-    __shared__ int s_slot[kWinRows];      // a row's place in the unit's row tables
-    __shared__ int64_t s_query[kWinRows]; // and in the query tensor
-    __shared__ __align__(16) float s_part[PASS == 2 ? 2 : 1][kWaves][PASS == 2 ? 4 * kStepKeys : 4];  // [lane][tile]
-    __shared__ float s_imp[PASS == 2 ? kFinishChunks * kChunkKeys : 1];
-    __shared__ double s_mom[kWaves][3];
-    const int nch = (u.sq.vis_len + kChunkKeys - 1) / kChunkKeys;
-    const int first = u.chunk, last = min(nch, first + wg_chunks);
-    const int n_seg = (nch + seg_chunks - 1) / seg_chunks;
-    const int key_lo = first * kChunkKeys;
+    __shared__ __align__(16) bf16_t s_rows[kWinRows * D];
+    __shared__ int s_slot[kWinRows];  // a row's place in the unit's row tables
+    __shared__ int s_query[kWinRows];
+    __shared__ int s_last[kWinRows];  // last key that a row sees
+    __shared__ float2 s_part[kWaves / 2][kWinRows];
     // a visual-window row at visual index p sees the keys up to p: keys behind the last row are never looked at
     const int prow0 = u.sq.win_start - u.sq.vis_start;
-    const int key_end = min(last * kChunkKeys, dm.vis_window ? prow0 + u.sq.win_len : u.sq.vis_len);
-    const int steps = max(0, (key_end - key_lo + kStepKeys - 1) / kStepKeys);
-    if (PASS == 2 && tid == 0) s_any_far = 0;
+    const int run = blockIdx.x, key_first = run * run_keys + 32 * wave;
+    const int key_hi = min((run + 1) * run_keys, dm.vis_window ? prow0 + u.sq.win_len : u.sq.vis_len);
+    // the keys of the wave's next group, 16 elements a slice, eight of them in either half of the wave; requested at the end of
+    // the group before
+    uint4 kreg[NS];
+    auto load_keys = [&](int key0) __attribute__((always_inline)) {
+        const int lane = here(threadIdx.x & 63);
+        const bf16_t *src = u.k + (int64_t)(u.sq.vis_start + min(key0 + (lane & 31), u.sq.vis_len - 1)) * st.kv_t + 8 * (lane >> 5);
+#pragma unroll
+        for (int sl = 0; sl < NS; ++sl) kreg[sl] = *reinterpret_cast<const uint4 *>(src + 16 * sl);
+    };
     head_prefix(t, u.hrow0, u.G, s_pref);
     u.R_total = s_pref[u.G];
-    if (PASS == 2)
-        for (int i = tid; i < kFinishChunks * kChunkKeys; i += kThreads) s_imp[i] = 0.f;
-
-    // the keys of a step; keys past the end of the span repeat the last one
-    auto fetch = [&](u32x4(&kx)[kIt], int step) __attribute__((always_inline)) {
-#pragma unroll
-        for (int it = 0; it < kIt; ++it) {
-            const int p = tid + kThreads * it;
-            const int key = min(key_lo + kStepKeys * step + p / kPieces, u.sq.vis_len - 1);
-            kx[it] = *reinterpret_cast<const u32x4 *>(u.k + (int64_t)(u.sq.vis_start + key) * st.kv_t + 8 * (p % kPieces));
-        }
-    };
-    int key_at[NS];  // the lane's 16 bytes of key n of a tile, slice by slice
-#pragma unroll
-    for (int sl = 0; sl < NS; ++sl) key_at[sl] = n * D + 8 * ((4 * sl + c) ^ key_swizzle<D>(n));
-    auto put = [&](const u32x4(&kx)[kIt], int buf) __attribute__((always_inline)) {
-#pragma unroll
-        for (int it = 0; it < kIt; ++it) {
-            const int p = tid + kThreads * it, k = p / kPieces;
-            *reinterpret_cast<u32x4 *>(&s_k[buf][k * D + 8 * ((p % kPieces) ^ key_swizzle<D>(k))]) = kx[it];
-        }
-    };
 
     for (int r0 = 0; r0 < u.R_total; r0 += kWinRows) {
         const int rows_here = min(kWinRows, u.R_total - r0);
-        const int n_blk = (rows_here + 15) >> 4;
-        // the blocks are dealt evenly: 14 blocks as 3, 4, 3, 4
-        const int blk0 = wave * n_blk / kWaves, nb = (wave + 1) * n_blk / kWaves - blk0;
-        u32x4 kx0[kIt];
-        fetch(kx0, 0);
-        // a thread per row of the group: where it lives and (pass 2) its maximum, normaliser and weight
-        if (tid < ((rows_here + 15) & ~15)) {
-            const bool have = tid < rows_here;
-            const int rho = r0 + min(tid, rows_here - 1);
+        const int n_blk = (rows_here + 31) >> 5, tid = here(threadIdx.x);
+        if (tid < rows_here) {
+            const int rho = r0 + tid;
             const int g = head_of_row(s_pref, u.G, rho);
             const int place = g * u.W + (rho - s_pref[g]);
-            const int64_t slot = u.hrow0 * u.W + place;
-            const int tok = t.elite_idx[slot];
+            const int tok = t.elite_idx[u.hrow0 * u.W + place];
             s_slot[tid] = place;
-            s_query[tid] = (int64_t)(u.kvh * u.G + g) * st.q_h + (int64_t)(tok - u.qbase) * st.q_t;
-            if (PASS == 2) {
-                const float2 *p = t.part + slot * dm.n_chunks;
-                const float mt = t.row_mtext[slot], zt = t.row_ztext[slot];  // of raw logits
-                constexpr int kAtOnce = 16;  // partials requested together; a run of them past the end repeats the last one
-                float M = mt > -INFINITY ? rintf(held(mt) * kC) : -INFINITY;
-                double Z = 0.0;
-                for (int pass = n_seg <= kAtOnce ? 1 : 0; pass < 2; ++pass) {
-                    for (int s0 = 0; s0 < n_seg; s0 += kAtOnce) {
-                        float2 x[kAtOnce];
-#pragma unroll
-                        for (int s = 0; s < kAtOnce; ++s) x[s] = p[min(s0 + s, n_seg - 1)];
-                        if (pass == 0 || n_seg <= kAtOnce) {
-#pragma unroll
-                            for (int s = 0; s < kAtOnce; ++s) M = fmaxf(M, x[s].x);
-                        }
-                        if (pass == 1) {
-#pragma unroll
-                            for (int s = 0; s < kAtOnce; ++s)
-                                if (s0 + s < n_seg && x[s].y > 0.f) Z += (double)ldexpf(x[s].y, (int)(x[s].x - M));
-                        }
-                    }
-                }
-                if (zt > 0.f) Z += (double)(zt * __builtin_amdgcn_exp2f(fmaf(held(mt), kC, -M)));
-                if (fabsf(M) > 0.5f * kFar && M > -INFINITY) s_any_far = 1;
-                s_M[tid] = have && Z > 0.0 ? M : 0.f;  // rows past the list weigh nothing, nor do rows that see no key but far ones
-                s_w[tid] = have && !(Z <= 0.0) ? (float)(1.0 / ((double)(s_pref[g + 1] - s_pref[g]) * (double)u.G * Z)) : 0.f;
-            }
+            s_last[tid] = dm.vis_window ? prow0 + (rho - s_pref[g]) : u.sq.vis_len - 1;
+            s_query[tid] = (int)((unsigned)g << 27 | (unsigned)(tok - u.qbase));
         }
-        put(kx0, 0);
         lds_barrier();
-        // A operands; list row rb + 4 i + c of a block sits where the accumulator of lane group c, element i, expects it
-        uint4 qa[kWaveBlocks][NS];
+        load_rows_lds<D>(u, st, s_query, s_rows, rows_here, 32 * n_blk, wave);
+        rows_wait_barrier();
+        float ref[kBlocks1], sum[kBlocks1];  // of row 32 b + n
 #pragma unroll
-        for (int b = 0; b < kWaveBlocks; ++b) {
-            if (b >= nb) continue;
-            const int row = 16 * (blk0 + b) + 4 * (n & 3) + (n >> 2);
-            const bf16_t *qr = u.q + s_query[row] + 8 * c;
+        for (int b = 0; b < kBlocks1; ++b) {
+            ref[b] = -kFar;
+            sum[b] = 0.f;
+        }
+        auto group = [&](int key0, auto masked) __attribute__((always_inline)) {
+            asm volatile("" ::: "memory");  // the rows are read from LDS for every group: as values of the loop they would be spilled
+            const int lane = here(threadIdx.x & 63), n = lane & 31, c = lane >> 5;
+            int row_at[NS];  // the lane's 16 bytes of row n of a block
 #pragma unroll
-            for (int sl = 0; sl < NS; ++sl) {
-                qa[b][sl] = *reinterpret_cast<const uint4 *>(qr + 32 * sl);
-                if (row >= rows_here) qa[b][sl] = make_uint4(0, 0, 0, 0);
+            for (int sl = 0; sl < NS; ++sl) row_at[sl] = n * D + 8 * ((2 * sl + c) ^ row_swizzle<D>(n));
+#pragma unroll
+            for (int b = 0; b < kBlocks1; ++b) {
+                if (b >= n_blk) break;
+                f32x16 s = (f32x16){0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int sl = 0; sl < NS; ++sl) {
+                    const uint4 qb = *reinterpret_cast<const uint4 *>(s_rows + 32 * b * D + row_at[sl]);
+                    s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kreg[sl]), __builtin_bit_cast(bf16x8, qb), s, 0, 0, 0);
+                }
+                if constexpr (decltype(masked)::value) {  // some keys do not exist or lie behind the row
+                    const int lim = s_last[min(32 * b + n, rows_here - 1)] - key0 - 4 * c;
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) s[i] = 8 * (i >> 2) + (i & 3) > lim ? -INFINITY : s[i];  // key 8 (i / 4) + 4 c + i % 4
+                }
+                auto exps = [&](float r) __attribute__((always_inline)) {
+                    f32x4 z;
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) {
+                        const float e = __builtin_amdgcn_exp2f(fmaf(s[i], kC, -r));
+                        z[i & 3] = i < 4 ? e : z[i & 3] + e;
+                    }
+                    return (z[0] + z[1]) + (z[2] + z[3]);
+                };
+                float z = exps(ref[b]);
+                if (__ballot(z >= kSumLimit) != 0ull) {
+                    // the lane's reference becomes its largest logit, if that lies above; logits above the bound are held at it
+                    constexpr float kFarRaw = kFar / kC;
+                    float m = -kFarRaw;
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) {
+                        m = fmaxf(m, s[i]);
+                        s[i] = s[i] > kFarRaw ? kFarRaw : s[i];
+                    }
+                    const float up = fmaxf(ref[b], rintf(fminf(m, kFarRaw) * kC));
+                    sum[b] = ldexpf(sum[b], (int)(ref[b] - up));
+                    ref[b] = up;
+                    z = exps(up);
+                }
+                sum[b] += z;
+            }
+            if (key0 + kGroup * kWaves < key_hi) load_keys(key0 + kGroup * kWaves);
+        };
+        load_keys(key_first);
+        for (int key0 = key_first; key0 < key_hi; key0 += kGroup * kWaves) {
+            if (key0 + kGroup > u.sq.vis_len || (dm.vis_window && key0 + kGroup > prow0 + 1)) group(key0, std::true_type());
+            else group(key0, std::false_type());
+        }
+        // one (reference, sum) per row: over the two lanes that share it, then over the waves (waves 4-7 leave theirs,
+        // waves 0-3 add their own, a thread per row adds the four).  (A lane or wave without a term has the lowest reference.)
+        auto merge = [](float &M, float &z, float m2, float z2) __attribute__((always_inline)) {
+            const float top = fmaxf(M, m2);
+            z = ldexpf(z, (int)(M - top)) + ldexpf(z2, (int)(m2 - top));
+            M = top;
+        };
+        const int lane = tid & 63;
+#pragma unroll
+        for (int b = 0; b < kBlocks1; ++b) {
+            if (b >= n_blk) break;
+            merge(ref[b], sum[b], __shfl_xor(ref[b], 32, 64), __shfl_xor(sum[b], 32, 64));
+            if (wave >= kWaves / 2 && lane < 32) s_part[wave - kWaves / 2][32 * b + lane] = make_float2(ref[b], sum[b]);
+        }
+        lds_barrier();
+        if (wave < kWaves / 2 && lane < 32) {
+#pragma unroll
+            for (int b = 0; b < kBlocks1; ++b) {
+                if (b >= n_blk) break;
+                const float2 x = s_part[wave][32 * b + lane];
+                merge(ref[b], sum[b], x.x, x.y);
+                s_part[wave][32 * b + lane] = make_float2(ref[b], sum[b]);
             }
         }
-        // ref: minus the row's reference; sum: pass 1 the sum of the exponentials, pass 2 the row's weight
-        f32x4 ref[kWaveBlocks], sum[kWaveBlocks];
-        if (PASS == 1) {
+        lds_barrier();
+        if (tid < rows_here) {
+            float2 x = s_part[0][tid];
 #pragma unroll
-            for (int b = 0; b < kWaveBlocks; ++b) {
-                ref[b] = (f32x4){0.f, 0.f, 0.f, 0.f};
-                sum[b] = (f32x4){0.f, 0.f, 0.f, 0.f};
+            for (int w = 1; w < kWaves / 2; ++w) merge(x.x, x.y, s_part[w][tid].x, s_part[w][tid].y);
+            // (the sum goes out as a fraction of 1 to 2: pass 2 takes the largest reference of a row, which its terms then stay below)
+            const int up = x.y > 0.f && x.y < INFINITY ? ilogb_of(x.y) : 0;
+            t.part[(u.hrow0 * u.W + s_slot[tid]) * dm.n_chunks + run] =
+                make_float2(x.y > 0.f ? x.x + (float)up : -INFINITY, ldexpf(x.y, -up));
+        }
+        lds_barrier();  // the partials have been read: the next group of rows may come
+    }
+}
+
+// ---------------------------------------------------------------------------------------
+// Pass 2.  A workgroup takes part_keys keys of a unit.
+template <int D>
+__global__ __launch_bounds__(kThreads, 4) void window_scores_kernel(Dims dm, DevTables t, int l0, LaunchLayers ll, air_strides st, SeqArgs seqs,
+                                                                 int run_keys, int part_keys) {
+    constexpr int NS = D / 32, T = kTiles, kGroup = 16 * T;
+    constexpr float kC = Log2Scale<D>::kHi;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, n = lane & 15, c = lane >> 4;
+    UnitCtx u;
+    if (!unit_setup(dm, seqs, l0, ll, st, u, 0) || (int)blockIdx.x * part_keys >= u.sq.vis_len) return;
+    __shared__ int s_pref[17];
+    __shared__ __align__(16) bf16_t s_rows[kWinRows * D];
+    __shared__ __align__(16) float s_M[kWinRows], s_w[kWinRows];
+    __shared__ __align__(16) float s_ref[kWinRows];  // minus s_M; -inf for a row that the plain loop takes
+    __shared__ __align__(16) int s_last[kWinRows];   // last key that a row sees
+    __shared__ int s_query[kWinRows];
+    __shared__ float s_imp[kPartMost];
+    __shared__ int s_any_far;  // some row has its reference at the bound
+    __shared__ double s_mom[kWaves][3];
+    __shared__ int s_is_last;
+    const int n_seg = (u.sq.vis_len + run_keys - 1) / run_keys;
+    const int prow0 = u.sq.win_start - u.sq.vis_start;
+    const int key_lo = (int)blockIdx.x * part_keys;
+    const int key_hi = min(key_lo + part_keys, dm.vis_window ? prow0 + u.sq.win_len : u.sq.vis_len);
+    uint4 kreg[T][NS];  // the keys of the wave's next group
+    if (tid == 0) s_any_far = 0;
+    head_prefix(t, u.hrow0, u.G, s_pref);
+    u.R_total = s_pref[u.G];
+    for (int i = tid; i < part_keys; i += kThreads) s_imp[i] = 0.f;
+    for (int r0 = 0; r0 < u.R_total; r0 += kWinRows) {
+        const int rows_here = min(kWinRows, u.R_total - r0);
+        const int n_blk = (rows_here + 15) >> 4, tid = here(threadIdx.x);
+        if (tid < rows_here) {
+            const int rho = r0 + tid, g = head_of_row(s_pref, u.G, rho);
+            const int tok = t.elite_idx[(u.hrow0 + g) * u.W + (rho - s_pref[g])];
+            s_query[tid] = (int)((unsigned)g << 27 | (unsigned)(tok - u.qbase));
+        }
+        lds_barrier();
+        load_rows_lds<D>(u, st, s_query, s_rows, rows_here, 16 * n_blk, wave);
+        if (tid < 16 * n_blk) {  // maximum, normaliser, weight
+            float M = -INFINITY, w = 0.f;
+            const int tid = here(threadIdx.x), rho = r0 + min(tid, rows_here - 1), g = head_of_row(s_pref, u.G, rho);
+            if (tid < rows_here) {
+                const int64_t slot = (u.hrow0 + g) * u.W + (rho - s_pref[g]);
+                const float2 *part = t.part + slot * dm.n_chunks;
+                const float mt = t.row_mtext[slot], zt = t.row_ztext[slot];  // of raw logits
+                constexpr int kAtOnce = 16;  // partials requested together; those past the end repeat the last one
+                float2 x[kAtOnce];
+#pragma unroll
+                for (int s = 0; s < kAtOnce; ++s) x[s] = part[min(s, n_seg - 1)];
+                M = mt > -INFINITY ? rintf(held<D>(mt) * kC) : -INFINITY;
+#pragma unroll
+                for (int s = 0; s < kAtOnce; ++s) M = fmaxf(M, x[s].x);
+                for (int s = kAtOnce; s < n_seg; ++s) M = fmaxf(M, part[s].x);
+                double Z = 0.0;
+#pragma unroll
+                for (int s = 0; s < kAtOnce; ++s) Z += s < n_seg && x[s].y > 0.f ? (double)ldexpf(x[s].y, (int)(x[s].x - M)) : 0.0;
+                for (int s = kAtOnce; s < n_seg; ++s) {
+                    const float2 y = part[s];
+                    if (y.y > 0.f) Z += (double)ldexpf(y.y, (int)(y.x - M));
+                }
+                if (zt > 0.f) Z += (double)(zt * __builtin_amdgcn_exp2f(fmaf(held<D>(mt), kC, -M)));
+                if (fabsf(M) > 0.5f * kFar && M > -INFINITY) s_any_far = 1;
+                w = !(Z <= 0.0) ? (float)(1.0 / ((double)(s_pref[g + 1] - s_pref[g]) * (double)u.G * Z)) : 0.f;
+                if (!(Z > 0.0)) M = 0.f;  // a row that sees no key but far ones weighs nothing
             }
-        } else {
+            s_M[tid] = tid < rows_here ? M : 0.f;
+            s_ref[tid] = fabsf(M) > 0.5f * kFar ? -INFINITY : -M;  // (so does a row past the list)
+            s_w[tid] = w;
+            s_last[tid] = dm.vis_window ? prow0 + (rho - s_pref[g]) : u.sq.vis_len - 1;
+        }
+        rows_wait_barrier();
+        group_keys<T, NS>(u, st, key_lo + kGroup * wave, kreg);
+        auto group = [&](int key0, auto masked) __attribute__((always_inline)) {
+            asm volatile("" ::: "memory");
+            const int lane = here(threadIdx.x & 63), n = lane & 15, c = lane >> 4;
+            int row_at[NS];
+            row_places<D>(n, c, row_at);
+            f32x4 acc = (f32x4){0.f, 0.f, 0.f, 0.f};  // key 16 tile + n, the rows of lane group c
+            auto block = [&](int b, auto last_block) __attribute__((always_inline)) {
+                uint4 qa[NS];
 #pragma unroll
-            for (int b = 0; b < kWaveBlocks; ++b)
-                if (b < nb) {
+                for (int sl = 0; sl < NS; ++sl) qa[sl] = *reinterpret_cast<const uint4 *>(s_rows + 16 * b * D + row_at[sl]);
+                f32x4 s[T];
+#pragma unroll
+                for (int tile = 0; tile < T; ++tile) {
+                    s[tile] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int sl = 0; sl < NS; ++sl) s[tile] = mma<bf16_t>(qa[sl], kreg[tile][sl], s[tile]);
+                }
+                // the next group's keys (or the first's again, for the next group of rows) behind the last products of this one
+                if constexpr (decltype(last_block)::value)
+                    group_keys<T, NS>(u, st, key0 + kGroup * kWaves < key_hi ? key0 + kGroup * kWaves : key_lo + kGroup * wave, kreg);
+                const f32x4 ref = *reinterpret_cast<const f32x4 *>(s_ref + 16 * b + 4 * c);
+                const f32x4 w = *reinterpret_cast<const f32x4 *>(s_w + 16 * b + 4 * c);
+                typedef __attribute__((ext_vector_type(4))) int i32x4;
+                i32x4 last;
+                if constexpr (decltype(masked)::value) last = *reinterpret_cast<const i32x4 *>(s_last + 16 * b + 4 * c);
+#pragma unroll
+                for (int tile = 0; tile < T; ++tile) {
+                    float sum = 0.f;  // of the block: one long chain of additions would be 5 % further off fp64 where all keys weigh alike
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
-                        const float M = s_M[16 * (blk0 + b) + 4 * i + c];
-                        ref[b][i] = fabsf(M) > 0.5f * kFar ? -INFINITY : -M;  // the plain loop below takes that row
-                        sum[b][i] = s_w[16 * (blk0 + b) + 4 * i + c];
+                        if constexpr (decltype(masked)::value)
+                            if (key0 + 16 * tile + n > last[i]) s[tile][i] = -INFINITY;
+                        const float e = __builtin_amdgcn_exp2f(fmaf(s[tile][i], kC, ref[i]));
+                        sum = i == 0 ? w[0] * e : fmaf(w[i], e, sum);
                     }
-                }
-        }
-        // NB: blocks of the wave, a constant (the products of its blocks interleave, rows it does not have cost nothing).  Every
-        // wave passes the same number of barriers, whichever instance it runs.
-        auto stream = [&](auto nb_const) __attribute__((always_inline)) {
-            constexpr int NB = decltype(nb_const)::value;
-            // one step over the 64 keys of a buffer.  CHECKED (pass 1): far logits are held at the bound, and the reference is
-            // raised in front of an exponential above 2^kHigh; MASKED: some keys of the step do not exist or lie behind a row.
-            auto keys_of_step = [&](const bf16_t *buf, int key0, f32x4(&acc), auto checked, auto masked) __attribute__((always_inline)) {
-                int lim[NB > 0 ? NB : 1][4];  // last key that a row sees
-                if constexpr (decltype(masked)::value) {
-#pragma unroll
-                    for (int b = 0; b < NB; ++b)
-#pragma unroll
-                        for (int i = 0; i < 4; ++i)
-                            lim[b][i] = dm.vis_window ? prow0 + (r0 + 16 * (blk0 + b) + 4 * i + c) % u.sq.win_len : u.sq.vis_len - 1;
-                }
-#pragma unroll
-                for (int tile = 0; tile < 4; ++tile) {
-                    uint4 kb[NS];
-#pragma unroll
-                    for (int sl = 0; sl < NS; ++sl) kb[sl] = *reinterpret_cast<const uint4 *>(buf + key_at[sl] + 16 * tile * D);
-                    f32x4 s[NB > 0 ? NB : 1];
-#pragma unroll
-                    for (int b = 0; b < NB; ++b) {
-                        s[b] = (f32x4){0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                        for (int sl = 0; sl < NS; ++sl) s[b] = mma<bf16_t>(qa[b][sl], kb[sl], s[b]);
-                    }
-                    if constexpr (decltype(checked)::value) {
-#pragma unroll
-                        for (int b = 0; b < NB; ++b)
-#pragma unroll
-                            for (int i = 0; i < 4; ++i) s[b][i] = held(s[b][i]);
-                    }
-                    if constexpr (decltype(masked)::value) {
-                        const int key = key0 + 16 * tile + n;
-#pragma unroll
-                        for (int b = 0; b < NB; ++b)
-#pragma unroll
-                            for (int i = 0; i < 4; ++i) s[b][i] = key > lim[b][i] ? -INFINITY : s[b][i];
-                    }
-                    if constexpr (decltype(checked)::value) {
-#pragma unroll
-                        for (int b = 0; b < NB; ++b) {
-#pragma unroll
-                            for (int i = 0; i < 4; ++i) {
-                                const bool high = fmaf(s[b][i], kC, ref[b][i]) > kHigh;
-                                if (__ballot(high) == 0ull) continue;
-                                const float m = rintf(s[b][i] * kC);
-                                if (high) {
-                                    sum[b][i] = ldexpf(sum[b][i], (int)(-ref[b][i] - m));
-                                    ref[b][i] = -m;
-                                }
-                            }
-                        }
-                    }
-#pragma unroll
-                    for (int b = 0; b < NB; ++b)
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) {
-                            const float e = __builtin_amdgcn_exp2f(fmaf(s[b][i], kC, ref[b][i]));
-                            if (PASS == 1) sum[b][i] += e;
-                            else acc[tile] = fmaf(sum[b][i], e, acc[tile]);
-                        }
+                    acc[tile] += sum;
                 }
             };
-            auto masked_from = [&](int key0) { return key0 + kStepKeys > u.sq.vis_len || (dm.vis_window && key0 + kStepKeys > prow0 + 1); };
-            if (PASS == 1 && steps > 0) {  // the rows' first references: the maximum over the first keys
-                const bool masked = masked_from(key_lo);
-                f32x4 top[NB > 0 ? NB : 1];
+#pragma unroll 1
+            for (int b = 0; b < n_blk - 1; ++b) block(b, std::false_type());
+            block(n_blk - 1, std::true_type());
+            // over the lane groups; lane (n, c) stores key 16 c + n
+            float v = 0.f;
 #pragma unroll
-                for (int b = 0; b < NB; ++b) top[b] = (f32x4){-INFINITY, -INFINITY, -INFINITY, -INFINITY};
-#pragma unroll
-                for (int tile = 0; tile < 4; ++tile) {
-                    const int key = key_lo + 16 * tile + n;
-                    uint4 kb[NS];
-#pragma unroll
-                    for (int sl = 0; sl < NS; ++sl) kb[sl] = *reinterpret_cast<const uint4 *>(s_k[0] + key_at[sl] + 16 * tile * D);
-#pragma unroll
-                    for (int b = 0; b < NB; ++b) {
-                        f32x4 s = (f32x4){0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                        for (int sl = 0; sl < NS; ++sl) s = mma<bf16_t>(qa[b][sl], kb[sl], s);
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) {
-                            if (masked) {
-                                const int lim = dm.vis_window ? prow0 + (r0 + 16 * (blk0 + b) + 4 * i + c) % u.sq.win_len : u.sq.vis_len - 1;
-                                s[i] = key > lim ? -INFINITY : s[i];
-                            }
-                            top[b][i] = fmaxf(top[b][i], s[i]);
-                        }
-                    }
-                }
-#pragma unroll
-                for (int b = 0; b < NB; ++b)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const float m = max16(top[b][i]);
-                        if (m > -INFINITY) ref[b][i] = -rintf(held(m) * kC);  // else the row sees none of these keys, or logits of -inf
-                    }
+            for (int tile = 0; tile < T; ++tile) {
+                float a = acc[tile];
+                a += __shfl_xor(a, 16, 64);
+                a += __shfl_xor(a, 32, 64);
+                if (c == tile) v = a;
             }
-            for (int step = 0; step < steps; ++step) {
-                const bf16_t *buf = s_k[step & 1];
-                const int key0 = key_lo + kStepKeys * step;
-                u32x4 kx[kIt];
-                fetch(kx, min(step + 1, steps - 1));
-                const bool masked = masked_from(key0);
-                f32x4 acc = (f32x4){0.f, 0.f, 0.f, 0.f};
-                if (PASS == 1) {
-                    // Steps are taken without looking at single logits; where some logit stands far above its reference the step is
-                    // done again from the sums before it, with the check.
-                    auto largest_sum = [&]() __attribute__((always_inline)) {
-                        float x = 0.f;
-#pragma unroll
-                        for (int b = 0; b < NB; ++b) x = fmaxf(fmaxf(x, fmaxf(sum[b][0], sum[b][1])), fmaxf(sum[b][2], sum[b][3]));
-                        return x;
-                    };
-                    bool again = masked;
-                    if (!again) {
-                        f32x4 before[NB > 0 ? NB : 1];
-#pragma unroll
-                        for (int b = 0; b < NB; ++b) before[b] = sum[b];
-                        keys_of_step(buf, key0, acc, std::false_type(), std::false_type());
-                        again = __ballot(largest_sum() >= kSumMost) != 0ull;
-                        if (again) {
-#pragma unroll
-                            for (int b = 0; b < NB; ++b) sum[b] = before[b];
-                        }
-                    }
-                    if (again) keys_of_step(buf, key0, acc, std::true_type(), std::true_type());
-                    if (__ballot(largest_sum() >= kSumLimit) != 0ull) {  // the next steps' exponentials start from a reference that fits
-#pragma unroll
-                        for (int b = 0; b < NB; ++b)
-#pragma unroll
-                            for (int i = 0; i < 4; ++i) {
-                                const int up = sum[b][i] >= kSumLimit && sum[b][i] < INFINITY ? ilogb_of(sum[b][i]) : 0;
-                                sum[b][i] = ldexpf(sum[b][i], -up);
-                                ref[b][i] -= (float)up;
-                            }
-                    }
-                } else {
-                    if (masked) keys_of_step(buf, key0, acc, std::false_type(), std::true_type());
-                    else keys_of_step(buf, key0, acc, std::false_type(), std::false_type());
-                    *reinterpret_cast<f32x4 *>(&s_part[step & 1][wave][4 * lane]) = acc;
-                }
-                put(kx, (step + 1) & 1);
-                lds_barrier();
-                // keys of the step: summed over the lane groups and the waves by one of the waves
-                if (PASS == 2 && wave == (step & (kWaves - 1))) {
-                    float v = 0.f;
-#pragma unroll
-                    for (int w = 0; w < kWaves; ++w)
-#pragma unroll
-                        for (int cc = 0; cc < 4; ++cc) v += s_part[step & 1][w][4 * (16 * cc + n) + c];  // key 16 c + n
-                    s_imp[kStepKeys * step + lane] += v;
-                }
-            }
+            s_imp[key0 - key_lo + lane] += v;
         };
-        static_assert(kWaveBlocks == 4, "instances below");
-        if (nb == 4) stream(std::integral_constant<int, 4>());
-        else if (nb == 3) stream(std::integral_constant<int, 3>());
-        else if (nb == 2) stream(std::integral_constant<int, 2>());
-        else if (nb == 1) stream(std::integral_constant<int, 1>());
-        else stream(std::integral_constant<int, 0>());
-        if (PASS == 2 && s_any_far) {
-            lds_barrier();  // the last step's sums are in place
+        static_assert(T == 4, "a key per lane");
+        for (int key0 = key_lo + kGroup * wave; key0 < key_hi; key0 += kGroup * kWaves) {
+            if (key0 + kGroup > u.sq.vis_len || (dm.vis_window && key0 + kGroup > prow0 + 1)) group(key0, std::true_type());
+            else group(key0, std::false_type());
+        }
+        lds_barrier();  // the rows and their parameters have been read, the sums are in place
+        if (s_any_far) {
             for (int r = 0; r < rows_here; ++r) {
                 const float M = s_M[r], w = s_w[r];
                 if (fabsf(M) <= 0.5f * kFar) continue;
-                const int last_key = dm.vis_window ? prow0 + (r0 + r) % u.sq.win_len : u.sq.vis_len - 1;
-                for (int i = tid; i < kFinishChunks * kChunkKeys && key_lo + i <= last_key; i += kThreads) {
-                    const bf16_t *kr = u.k + (int64_t)(u.sq.vis_start + key_lo + i) * st.kv_t, *qr = u.q + s_query[r];
+                const int last_key = s_last[r];
+                for (int i = tid; i < part_keys && key_lo + i <= last_key; i += kThreads) {
+                    const bf16_t *kr = u.k + (int64_t)(u.sq.vis_start + key_lo + i) * st.kv_t, *qr = query_of(u, st, s_query[r]);
                     float s = 0.f;
 #pragma unroll 1
                     for (int e = 0; e < D; e += 8)
                         s = dot_piece<bf16_t>(*reinterpret_cast<const uint4 *>(qr + e), *reinterpret_cast<const uint4 *>(kr + e), s);
-                    s_imp[i] += w * __builtin_amdgcn_exp2f(fmaf(held(s), kC, -M));
+                    s_imp[i] += w * __builtin_amdgcn_exp2f(fmaf(held<D>(s), kC, -M));
                 }
             }
         }
-        if (PASS == 1) {  // one (maximum, sum-exp) per row from the sixteen lanes that share it
-#pragma unroll
-            for (int b = 0; b < kWaveBlocks; ++b) {
-                if (b >= nb) continue;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const float m = sum[b][i] > 0.f ? -ref[b][i] : -INFINITY;
-                    const float M = max16(m);
-                    float z = sum16(m > -INFINITY ? ldexpf(sum[b][i], (int)(m - M)) : sum[b][i]);
-                    // (the sum goes out as a fraction of 1 to 2: pass 2 takes the largest reference of a row, which its terms then stay below)
-                    const int up = z > 0.f && z < INFINITY ? ilogb_of(z) : 0;
-                    z = ldexpf(z, -up);
-                    const int rho = r0 + 16 * (blk0 + b) + 4 * i + c;
-                    if (n == 0 && rho < u.R_total) {
-                        const int64_t slot = u.hrow0 * u.W + s_slot[rho - r0];
-                        t.part[slot * dm.n_chunks + (int)blockIdx.x] = make_float2(z > 0.f ? M + (float)up : -INFINITY, z);
-                    }
-                }
-            }
-        }
-        lds_barrier();  // the buffers and the row parameters have been read: the next group of rows may come
+        lds_barrier();  // s_any_far and the parameters have been read: the next group of rows may come
     }
-    if (PASS == 1) return;
-    lds_barrier();
-    constexpr int kPer = kFinishChunks * kChunkKeys / kThreads;
-    float xs[kPer];
-    bool ok[kPer];
-#pragma unroll
-    for (int j = 0; j < kPer; ++j) {
-        const int i = kThreads * j + tid;
-        xs[j] = s_imp[i];
-        ok[j] = key_lo + i < u.sq.vis_len;  // keys of chunks past the last lie behind the span as well
-        if (ok[j]) t.scores[u.unit * dm.max_vis + key_lo + i] = xs[j];
-    }
-    const int n_wg = min(u.sq.vis_len, last * kChunkKeys) - key_lo;
-    leave_moments(dm, t, u.unit, u.b, u.sq, n_wg, (nch + kFinishChunks - 1) / kFinishChunks, xs, ok, s_mom);
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(t.scores + u.unit * dm.max_vis, 0, u.sq.vis_len * 4, 0x00020000);
+    for (int i = tid; i < min(part_keys, u.sq.vis_len - key_lo); i += kThreads)
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, s_imp[i]), rs, (key_lo + i) * 4, 0, kSysScope);
+    leave_scores(dm, t, u.unit, u.b, u.sq, (u.sq.vis_len + part_keys - 1) / part_keys, s_mom, s_is_last);
 }
 
-// Chunks of 256 keys per workgroup of pass 1: as many as leave a launch over all layers 1536 workgroups (three rounds of two per
-// CU), so that the rows a workgroup loads (57 KB at 224 rows) serve many keys; pass 2 takes the four chunks of a
-// moment entry.  The run decides references and partial sums, so it follows from the context alone, not from the layers of
-// the call: the scores are the same bits however the layers are cut into calls and launches.
-static int window_seg_chunks(const Dims &dm) {
-    int seg = kFinishChunks;
-    while (seg > 1 && (int64_t)((dm.n_chunks + seg - 1) / seg) * dm.Hkv * dm.B * dm.L < 1536) seg >>= 1;
-    return seg;
+// Keys of a workgroup, a multiple of 64 from kPartLeast to `most`.  Two workgroups share a CU, 512 the chip: as many parts of max_vis
+// as make the rounds of 512 times the work of one least.  A round costs the keys and about `extra` groups of 64 keys for what is in front
+// and behind (rows into LDS, parameters, partial sums).
+static int part_keys(const Dims &dm, int64_t units, int most, int extra) {
+    const int groups = (dm.max_vis + 63) / 64;
+    int best = most / 64;
+    int64_t best_cost = -1;
+    for (int g = most / 64; g >= kPartLeast / 64; --g) {
+        const int64_t cost = (units * ((groups + g - 1) / g) + 511) / 512 * (g + extra);
+        if (best_cost < 0 || cost < best_cost) {
+            best_cost = cost;
+            best = g;
+        }
+    }
+    return 64 * best;
 }
 
 hipError_t launch_score_window(hipStream_t s, const Dims &dm, const DevTables &t, int pass, int l0, int nl, const LaunchLayers &ll,
                                const air_strides &st, const SeqArgs &seqs) {
-    const int seg = window_seg_chunks(dm);
-    const int per = pass == 1 ? seg : kFinishChunks;
-    const dim3 grid((dm.n_chunks + per - 1) / per, dm.Hkv, nl * dm.B), block(kThreads);
+    // A run of pass 1 decides references and partial sums, so it follows from the context alone, not from the layers of the call:
+    // the scores are the same bits however the layers are cut into calls and launches.  Pass 2 leaves whole sums of a
+    // key and the unit's statistics from whole units: its parts follow the launch.
+    const int run = part_keys(dm, (int64_t)dm.L * dm.B * dm.Hkv, 1024, 4);
+    const int part = pass == 1 ? run : part_keys(dm, (int64_t)nl * dm.B * dm.Hkv, kPartMost, 8);
+    const dim3 grid((dm.max_vis + part - 1) / part, dm.Hkv, nl * dm.B), block(kThreads);
     if (dm.D == 128) {
-        if (pass == 1) hipLaunchKernelGGL((window_kernel<128, 1>), grid, block, 0, s, dm, t, l0, ll, st, seqs, seg);
-        else hipLaunchKernelGGL((window_kernel<128, 2>), grid, block, 0, s, dm, t, l0, ll, st, seqs, seg);
+        if (pass == 1) hipLaunchKernelGGL((window_sums_kernel<128>), grid, block, 0, s, dm, t, l0, ll, st, seqs, run);
+        else hipLaunchKernelGGL((window_scores_kernel<128>), grid, block, 0, s, dm, t, l0, ll, st, seqs, run, part);
     } else {
-        if (pass == 1) hipLaunchKernelGGL((window_kernel<64, 1>), grid, block, 0, s, dm, t, l0, ll, st, seqs, seg);
-        else hipLaunchKernelGGL((window_kernel<64, 2>), grid, block, 0, s, dm, t, l0, ll, st, seqs, seg);
+        if (pass == 1) hipLaunchKernelGGL((window_sums_kernel<64>), grid, block, 0, s, dm, t, l0, ll, st, seqs, run);
+        else hipLaunchKernelGGL((window_scores_kernel<64>), grid, block, 0, s, dm, t, l0, ll, st, seqs, run, part);
     }
     return hipGetLastError();
 }

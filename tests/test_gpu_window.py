@@ -117,3 +117,23 @@ def test_error_against_fp64(d, visual, spread, bound):
             want = p.oracle(l, 0, h)
             errs.append(np.linalg.norm(got[l][0, h] - want) / np.linalg.norm(want))
     assert math.sqrt(np.mean(np.square(errs))) <= bound, errs
+
+
+@pytest.mark.parametrize("d,visual", [(128, False), (64, False), (128, True), (64, True)])
+@pytest.mark.parametrize("n_vis", [63, 512, 545, 1025, 2049, 4160])  # less than a group, whole parts, parts with a remainder
+@pytest.mark.parametrize("window,G", [(9, 4), (32, 7), (33, 7), (43, 6), (32, 16)])  # 36 to 512 rows: blocks of 16 and 32, groups of 256
+def test_edges_of_parts_and_row_blocks(n_vis, window, G, d, visual):
+    p = _Prompt(3, 2, 2, G, d, n_vis, 48, window, visual)
+    ac = p.context()
+    got = p.score(ac)
+    one_by_one = p.score(ac, [(l, l + 1) for l in range(3)])  # pass 2 in parts of other sizes
+    ac.air_budget()
+    s_t, s_k = ac.air_get_stats()
+    ac.close()
+    assert all(np.array_equal(x, y) for x, y in zip(got, one_by_one))
+    for (l, b, h) in [(0, 0, 0), (2, 1, 1)]:
+        np.testing.assert_allclose(got[l][b, h], p.oracle(l, b, h), rtol=P.SCORE_RTOL, atol=P.SCORE_ATOL)
+    for b in range(2):  # strength and skewness of the scores that the call left
+        want = [O.skewness(got[2][b, h].astype(np.float64)) for h in range(2)]
+        np.testing.assert_allclose(s_t[b, 2], got[2][b].astype(np.float64).sum(axis=1).mean(), rtol=1e-12)
+        np.testing.assert_allclose(s_k[b, 2], np.mean(want), rtol=1e-9, atol=1e-12)
