@@ -18,8 +18,12 @@ namespace air {
 //           then the elite-text columns of Eq.7 for that head's elite rows.
 // Heads are processed in batches of `gb` so that gb * max_window logits fit the LDS.
 // ---------------------------------------------------------------------------------------
-template <typename T, int D>
-__global__ __launch_bounds__(256) void elite_kernel(Dims dm, DevTables t, int l0, LaunchLayers ll, air_strides st,
+// The kernel waits, for its keys and for one head after the other: NW waves are eight where the span has more than 64
+// candidates, which are two rounds of keys and, with more than four heads in the group, two of heads for four waves (28 layers
+// of 128 candidates, seven heads of 128 elements per KV head: 19.8 us with four, 15.3 with eight).  A span of at most 64 is one
+// round for four waves too (16 candidates and two heads of 64 elements: 6.2 with four, 6.4 with eight).
+template <typename T, int D, int NW>
+__global__ __launch_bounds__(64 * NW) void elite_kernel(Dims dm, DevTables t, int l0, LaunchLayers ll, air_strides st,
                                                     SeqArgs seqs, double alpha, int gb) {
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int kvh = blockIdx.x, b = blockIdx.y, li = blockIdx.z;
@@ -37,6 +41,7 @@ __global__ __launch_bounds__(256) void elite_kernel(Dims dm, DevTables t, int l0
     int *s_elite = reinterpret_cast<int *>(s_dyn + (size_t)gb * W);
 
     constexpr int E = D / 16, UN = 4, HB = 8;  // elements per lane, candidate rounds in flight, heads per register batch
+    constexpr int kGroups = 4 * NW;            // candidate keys read side by side
     const int sub = tid & 15, grp = tid >> 4;
     const double sqrt_d = sqrt((double)D);
     const float scale = 1.0f / sqrtf((float)D);
@@ -56,18 +61,18 @@ __global__ __launch_bounds__(256) void elite_kernel(Dims dm, DevTables t, int l0
 #pragma unroll
                 for (int e = 0; e < E; ++e) qd[hh][e] = (double)ldf(&tmp[e]);
             }
-            for (int j0 = 0; j0 < wl; j0 += 16 * UN) {
+            for (int j0 = 0; j0 < wl; j0 += kGroups * UN) {
                 T kv[UN][E];
 #pragma unroll
                 for (int un = 0; un < UN; ++un) {
-                    const int j = j0 + un * 16 + grp;
+                    const int j = j0 + un * kGroups + grp;
                     if (j < wl)
                         __builtin_memcpy(kv[un], __builtin_assume_aligned(k + (int64_t)(sq.win_start + j) * st.kv_t + sub * E,
                                                                           sizeof(T) * E), sizeof(kv[un]));
                 }
 #pragma unroll
                 for (int un = 0; un < UN; ++un) {
-                    const int j = j0 + un * 16 + grp;
+                    const int j = j0 + un * kGroups + grp;
                     double kd[E];
 #pragma unroll
                     for (int e = 0; e < E; ++e) kd[e] = j < wl ? (double)ldf(&kv[un][e]) : 0.0;
@@ -85,7 +90,7 @@ __global__ __launch_bounds__(256) void elite_kernel(Dims dm, DevTables t, int l0
         }
         __syncthreads();
         // ---- phase 2
-        for (int hh = wave; hh < ng; hh += 4) {
+        for (int hh = wave; hh < ng; hh += NW) {
             const int h = kvh * G + g0 + hh;
             const int64_t hrow = ((int64_t)l * dm.B + b) * dm.Hq + h;
             const double *logit = s_logit + (size_t)hh * W;
@@ -196,10 +201,11 @@ hipError_t launch_elite(hipStream_t s, const Dims &dm, const DevTables &t, int l
     int gb = (int)(49152 / per_head);  // heads whose logits share the LDS
     gb = gb < 1 ? 1 : (gb > dm.G ? dm.G : gb);
     const dim3 grid(dm.Hkv, dm.B, nl);
-    if (dm.D == 128)
-        hipLaunchKernelGGL((elite_kernel<float, 128>), grid, dim3(256), gb * per_head, s, dm, t, l0, ll, st, seqs, alpha, gb);
-    else
-        hipLaunchKernelGGL((elite_kernel<float, 64>), grid, dim3(256), gb * per_head, s, dm, t, l0, ll, st, seqs, alpha, gb);
+    auto launch = [&](auto kernel, int waves) {
+        hipLaunchKernelGGL(kernel, grid, dim3(64 * waves), gb * per_head, s, dm, t, l0, ll, st, seqs, alpha, gb);
+    };
+    if (dm.max_window > 64) dm.D == 128 ? launch(elite_kernel<float, 128, 8>, 8) : launch(elite_kernel<float, 64, 8>, 8);
+    else dm.D == 128 ? launch(elite_kernel<float, 128, 4>, 4) : launch(elite_kernel<float, 64, 4>, 4);
     return hipGetLastError();
 }
 

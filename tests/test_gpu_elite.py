@@ -1,5 +1,6 @@
 """Eq.5 on bf16 tensors far from the usual magnitudes: the fp32 logits of the matrix unit settle what lies outside their own
-error, everything else is decided in fp64, so the elite sets are the oracle's at any size of the operands."""
+error, everything else is decided in fp64, so the elite sets are the oracle's at any size of the operands.  And on fp32 tensors
+around the length of the span where the kernel takes eight waves in place of four."""
 import numpy as np
 import pytest
 
@@ -61,6 +62,27 @@ def test_elite_sets_of_large_operands_match_the_oracle(d, big):
         logits = O.last_row_logits(q64[0, hq, ref - t0], k64[0, hq // w.group][cand])  # every partial sum is exact in fp64
         want.append(cand[O.elite_set(logits, alpha)])
     P.check_elite(cnt, idx, [want], f"d={d} big={big}")
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("n_text,group", [(1, 7), (63, 9), (64, 4), (65, 9), (128, 16), (129, 1), (600, 7)])
+def test_fp32_elite_sets_on_both_sides_of_64_candidates(d, n_text, group):
+    # whole numbers: every logit is exact, in any order of its sum, and candidates of equal logit are in or out together
+    w = synth.get_workload(2).scaled(dtype="f32", head_dim=d, n_layers=1, n_q_heads=2 * group, n_kv_heads=2, n_vis=300, n_text=n_text,
+                                     decode_steps=1)
+    rng = np.random.default_rng(5)
+    li = synth.layer_inputs(w, 0, w.seqs())
+    q, k = (rng.integers(-2, 3, x.shape).astype(np.float32) for x in (li.q_text, li.k))
+    alpha = 0.5
+    seqs, cnt, idx = _elite_sets(w, q, k, alpha)
+    s = seqs[0]
+    ref, cand = s.win_start + s.win_len - 1, np.arange(s.win_start, s.win_start + s.win_len)
+    t0 = s.vis_start + s.vis_len
+    want = []
+    for hq in range(w.n_q_heads):
+        logits = O.last_row_logits(q[0, hq, ref - t0].astype(np.float64), k[0, hq // group].astype(np.float64)[cand])
+        want.append(cand[O.elite_set(logits, alpha)])
+    P.check_elite(cnt, idx, [want], f"d={d} n_text={n_text} group={group}")
 
 
 @pytest.mark.parametrize("d", [64, 128])
