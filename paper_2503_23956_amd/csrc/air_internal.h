@@ -11,6 +11,7 @@ namespace air {
 
 constexpr int kChunkKeys = 256;       // visual keys per workgroup in the score passes
 constexpr int kMaxLayersPerLaunch = 32;
+constexpr int kCUs = 256;
 constexpr int kMaxSplits = 16;        // largest split-K factor of the decode attention
 constexpr int kCacheRowAlign = 32;    // layer regions of the compacted cache start on multiples of this
 constexpr int kFinishChunks = 4;      // chunks finished (and summed into one moment entry) per workgroup of air_score's last kernel

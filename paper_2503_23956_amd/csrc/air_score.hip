@@ -18,10 +18,8 @@ namespace air {
 //           then the elite-text columns of Eq.7 for that head's elite rows.
 // Heads are processed in batches of `gb` so that gb * max_window logits fit the LDS.
 // ---------------------------------------------------------------------------------------
-// The kernel waits, for its keys and for one head after the other: NW waves are eight where the span has more than 64
-// candidates, which are two rounds of keys and, with more than four heads in the group, two of heads for four waves (28 layers
-// of 128 candidates, seven heads of 128 elements per KV head: 19.8 us with four, 15.3 with eight).  A span of at most 64 is one
-// round for four waves too (16 candidates and two heads of 64 elements: 6.2 with four, 6.4 with eight).
+// The kernel waits, for its keys and for one head after the other: eight waves (NW) take fewer rounds of keys and of heads than
+// four, but only one such workgroup fits a CU, where two of four waves do (three with heads of 64 elements).
 template <typename T, int D, int NW>
 __global__ __launch_bounds__(64 * NW) void elite_kernel(Dims dm, DevTables t, int l0, LaunchLayers ll, air_strides st,
                                                     SeqArgs seqs, double alpha, int gb) {
@@ -204,8 +202,17 @@ hipError_t launch_elite(hipStream_t s, const Dims &dm, const DevTables &t, int l
     auto launch = [&](auto kernel, int waves) {
         hipLaunchKernelGGL(kernel, grid, dim3(64 * waves), gb * per_head, s, dm, t, l0, ll, st, seqs, alpha, gb);
     };
-    if (dm.max_window > 64) dm.D == 128 ? launch(elite_kernel<float, 128, 8>, 8) : launch(elite_kernel<float, 64, 8>, 8);
-    else dm.D == 128 ? launch(elite_kernel<float, 128, 4>, 4) : launch(elite_kernel<float, 64, 4>, 4);
+    // Eight waves where the launch leaves every workgroup a CU of its own and some span has more than 64 candidates (a round of
+    // keys for four waves).  air_score, us, four waves / eight, 128 candidates, heads of 128 elements: 112 units of 7 heads 61 / 58, 256
+    // of 7 heads 68 / 64, 256 of 1 head 42.5 / 42; 448 units of 2 heads 52 / 56, 768 of 2 heads 74 / 80, 4096 of 7 heads 448 / 491;
+    // heads of 64: 256 units of 2 heads 37.5 / 37, 448 of 2 heads 45 / 48, 768 59 / 66, 4096 199 / 249.  The table entries are the
+    // same bits either way.
+    int most = 0;
+    for (int b = 0; b < dm.B; ++b) most = seqs.s[b].win_len > most ? seqs.s[b].win_len : most;
+    if (most > 64 && (int64_t)nl * dm.B * dm.Hkv <= kCUs)
+        dm.D == 128 ? launch(elite_kernel<float, 128, 8>, 8) : launch(elite_kernel<float, 64, 8>, 8);
+    else
+        dm.D == 128 ? launch(elite_kernel<float, 128, 4>, 4) : launch(elite_kernel<float, 64, 4>, 4);
     return hipGetLastError();
 }
 

@@ -1,6 +1,6 @@
 """Eq.5 on bf16 tensors far from the usual magnitudes: the fp32 logits of the matrix unit settle what lies outside their own
 error, everything else is decided in fp64, so the elite sets are the oracle's at any size of the operands.  And on fp32 tensors
-around the length of the span where the kernel takes eight waves in place of four."""
+around the length of the span and the number of units where the kernel takes eight waves in place of four."""
 import numpy as np
 import pytest
 
@@ -83,6 +83,46 @@ def test_fp32_elite_sets_on_both_sides_of_64_candidates(d, n_text, group):
         logits = O.last_row_logits(q[0, hq, ref - t0].astype(np.float64), k[0, hq // group].astype(np.float64)[cand])
         want.append(cand[O.elite_set(logits, alpha)])
     P.check_elite(cnt, idx, [want], f"d={d} n_text={n_text} group={group}")
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("group,spans", [(2, (129, 64, 20)), (7, (65, 130, 1)), (3, (64, 64, 64))])
+def test_fp32_elite_sets_are_the_same_bits_in_launches_of_many_units_and_of_few(d, group, spans):
+    # 32 layers x 3 sequences x 3 KV heads are 288 units, more than there are CUs (four waves); one layer is 9 (eight waves where a
+    # span of the call has more than 64 candidates, whatever the context could take)
+    import torch
+
+    import paper_2503_23956_amd as A
+
+    L, n_vis, n_sys, n_text, dev = 32, 100, 5, 130, torch.device("cuda:0")
+    n = n_sys + n_vis + n_text
+    seqs = [synth.configs.Seq(n, n_sys, n_vis, n - w, w) for w in spans]
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(23)
+    k = [torch.randn((3, 3, n, d), generator=gen, device=dev) for _ in range(L)]
+    q = [torch.randn((3, 3 * group, n_text, d), generator=gen, device=dev) for _ in range(L)]
+    alpha = 0.2
+    cfg = A.make_config(n_layers=L, n_q_heads=3 * group, n_kv_heads=3, head_dim=d, batch=3, max_vis_len=n_vis, max_nonvis_len=n - n_vis,
+                        max_window=n_text, max_decode_steps=1, dtype=A.AIR_F32, alpha=alpha)
+    ac = A.AirCache(cfg, dev)
+    got = []
+    for pieces in ([(0, L)], [(l, l + 1) for l in range(L)]):
+        ac.air_reset()
+        for l0, l1 in pieces:
+            ac.air_score(l0, l1, q[l0:l1], k[l0:l1], k[l0:l1], seqs)
+        got.append([(*ac.air_get_elite(l), ac.air_get_scores(l)) for l in range(L)])
+    ac.close()
+    for (cnt, idx, scores), (cnt1, idx1, scores1) in zip(*got):
+        assert np.array_equal(cnt, cnt1) and np.array_equal(scores, scores1)
+        assert all(np.array_equal(idx[b, h, :c], idx1[b, h, :c]) for (b, h), c in np.ndenumerate(cnt))
+    for l in (0, L - 1):
+        cnt, idx, _ = got[0][l]
+        for b, s in enumerate(seqs):
+            cand = np.arange(s.win_start, n)
+            for h in range(3 * group):
+                logits = O.last_row_logits(q[l][b, h, -1].double().cpu().numpy(), k[l][b, h // group].double().cpu().numpy()[cand])
+                near = np.exp(logits - logits.max()) / alpha - 1  # (random logits: none on the threshold to fp64 rounding)
+                assert np.abs(near).min() > 1e-9 and np.array_equal(idx[b, h, :cnt[b, h]], cand[near >= 0])
 
 
 @pytest.mark.parametrize("d", [64, 128])
