@@ -305,13 +305,25 @@ __global__ __launch_bounds__(kThreads, 4) void window_scores_kernel(Dims dm, Dev
                 M = mt > -INFINITY ? rintf(held<D>(mt) * kC) : -INFINITY;
 #pragma unroll
                 for (int s = 0; s < kAtOnce; ++s) M = fmaxf(M, x[s].x);
-                for (int s = kAtOnce; s < n_seg; ++s) M = fmaxf(M, part[s].x);
+                constexpr int kMore = 8;  // of those behind
+#pragma unroll 1
+                for (int s0 = kAtOnce; s0 < n_seg; s0 += kMore) {
+                    float y[kMore];
+#pragma unroll
+                    for (int s = 0; s < kMore; ++s) y[s] = part[min(s0 + s, n_seg - 1)].x;
+#pragma unroll
+                    for (int s = 0; s < kMore; ++s) M = fmaxf(M, y[s]);
+                }
                 double Z = 0.0;
 #pragma unroll
                 for (int s = 0; s < kAtOnce; ++s) Z += s < n_seg && x[s].y > 0.f ? (double)ldexpf(x[s].y, (int)(x[s].x - M)) : 0.0;
-                for (int s = kAtOnce; s < n_seg; ++s) {
-                    const float2 y = part[s];
-                    if (y.y > 0.f) Z += (double)ldexpf(y.y, (int)(y.x - M));
+#pragma unroll 1
+                for (int s0 = kAtOnce; s0 < n_seg; s0 += kMore) {
+                    float2 y[kMore];
+#pragma unroll
+                    for (int s = 0; s < kMore; ++s) y[s] = part[min(s0 + s, n_seg - 1)];
+#pragma unroll
+                    for (int s = 0; s < kMore; ++s) Z += s0 + s < n_seg && y[s].y > 0.f ? (double)ldexpf(y[s].y, (int)(y[s].x - M)) : 0.0;
                 }
                 if (zt > 0.f) Z += (double)(zt * __builtin_amdgcn_exp2f(fmaf(held<D>(mt), kC, -M)));
                 if (fabsf(M) > 0.5f * kFar && M > -INFINITY) s_any_far = 1;

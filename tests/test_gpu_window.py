@@ -137,3 +137,22 @@ def test_edges_of_parts_and_row_blocks(n_vis, window, G, d, visual):
         want = [O.skewness(got[2][b, h].astype(np.float64)) for h in range(2)]
         np.testing.assert_allclose(s_t[b, 2], got[2][b].astype(np.float64).sum(axis=1).mean(), rtol=1e-12)
         np.testing.assert_allclose(s_k[b, 2], np.mean(want), rtol=1e-9, atol=1e-12)
+
+
+@pytest.mark.parametrize("d,visual", [(128, False), (64, False), (128, True), (64, True)])
+@pytest.mark.parametrize("n_vis", [8192, 8193, 12289, 16385, 33000])  # 16, 17, 25, 33 and 65 runs
+@pytest.mark.parametrize("window,G", [(9, 4), (33, 8)])
+def test_spans_of_many_runs(n_vis, window, G, d, visual):
+    # the partial sums of a row past the first sixteen, the unit's statistics from scores that are read in several turns
+    p = _Prompt(2, 1, 1, G, d, n_vis, 48, window, visual)
+    ac = p.context()
+    got = p.score(ac)
+    ac.air_budget()
+    s_t, s_k = ac.air_get_stats()
+    one_by_one = p.score(ac, [(l, l + 1) for l in range(2)])
+    ac.close()
+    assert all(np.array_equal(x, y) for x, y in zip(got, one_by_one))
+    for l in range(2):
+        np.testing.assert_allclose(got[l][0, 0], p.oracle(l, 0, 0), rtol=P.SCORE_RTOL, atol=P.SCORE_ATOL)
+        np.testing.assert_allclose(s_t[0, l], got[l][0, 0].astype(np.float64).sum(), rtol=1e-12)
+        np.testing.assert_allclose(s_k[0, l], O.skewness(got[l][0, 0].astype(np.float64)), rtol=1e-9, atol=1e-12)
