@@ -81,7 +81,8 @@ __device__ __forceinline__ void group_keys(const UnitCtx &u, const air_strides &
     }
 }
 
-// a row's query: head of the group and place in the query tensor (below 2^27), as one word in LDS
+// a row's query: head of the group and place in the window, as one word in LDS (u.q: at the window's first token)
+static_assert(AIR_MAX_TEXT <= 1 << 27, "the places of a window and sixteen heads in a word");
 __device__ __forceinline__ const bf16_t *query_of(const UnitCtx &u, const air_strides &st, int word) {
     return u.q + (int64_t)(u.kvh * u.G + (int)((unsigned)word >> 27)) * st.q_h + (int64_t)(word & 0x7ffffff) * st.q_t;
 }
@@ -118,6 +119,7 @@ __global__ __launch_bounds__(kThreads, 4) void window_sums_kernel(Dims dm, DevTa
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     UnitCtx u;
     if (!unit_setup(dm, seqs, l0, ll, st, u, 0) || (int)blockIdx.x * run_keys >= u.sq.vis_len) return;
+    u.q += (int64_t)(u.sq.win_start - u.qbase) * st.q_t;
     __shared__ int s_pref[17];
     __shared__ __align__(16) bf16_t s_rows[kWinRows * D];
     __shared__ int s_slot[kWinRows];  // a row's place in the unit's row tables
@@ -150,7 +152,7 @@ __global__ __launch_bounds__(kThreads, 4) void window_sums_kernel(Dims dm, DevTa
             const int tok = t.elite_idx[u.hrow0 * u.W + place];
             s_slot[tid] = place;
             s_last[tid] = dm.vis_window ? prow0 + (rho - s_pref[g]) : u.sq.vis_len - 1;
-            s_query[tid] = (int)((unsigned)g << 27 | (unsigned)(tok - u.qbase));
+            s_query[tid] = (int)((unsigned)g << 27 | (unsigned)(tok - u.sq.win_start));
         }
         lds_barrier();
         load_rows_lds<D>(u, st, s_query, s_rows, rows_here, 32 * n_blk, wave);
@@ -262,6 +264,7 @@ __global__ __launch_bounds__(kThreads, 4) void window_scores_kernel(Dims dm, Dev
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, n = lane & 15, c = lane >> 4;
     UnitCtx u;
     if (!unit_setup(dm, seqs, l0, ll, st, u, 0) || (int)blockIdx.x * part_keys >= u.sq.vis_len) return;
+    u.q += (int64_t)(u.sq.win_start - u.qbase) * st.q_t;
     __shared__ int s_pref[17];
     __shared__ __align__(16) bf16_t s_rows[kWinRows * D];
     __shared__ __align__(16) float s_M[kWinRows], s_w[kWinRows];
@@ -287,7 +290,7 @@ __global__ __launch_bounds__(kThreads, 4) void window_scores_kernel(Dims dm, Dev
         if (tid < rows_here) {
             const int rho = r0 + tid, g = head_of_row(s_pref, u.G, rho);
             const int tok = t.elite_idx[(u.hrow0 + g) * u.W + (rho - s_pref[g])];
-            s_query[tid] = (int)((unsigned)g << 27 | (unsigned)(tok - u.qbase));
+            s_query[tid] = (int)((unsigned)g << 27 | (unsigned)(tok - u.sq.win_start));
         }
         lds_barrier();
         load_rows_lds<D>(u, st, s_query, s_rows, rows_here, 16 * n_blk, wave);
