@@ -201,7 +201,7 @@ __device__ __forceinline__ void leave_scores(const Dims &dm, const DevTables &t,
     if (!s_last) return;
     if (tid == 0) __hip_atomic_store(&t.unit_cnt[unit], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // next launch
     const int n_vis = sq.vis_len;
-    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(t.scores + unit * dm.max_vis, 0, n_vis * 4, 0x00020000);
+    float *scores = t.scores + unit * dm.max_vis;
     constexpr int kAtOnce = 16, kStep = 64 * NW;  // reads past the scores give zero
     auto over_waves = [&](int slot) {
         double v = s_mom[0][slot];
@@ -210,10 +210,11 @@ __device__ __forceinline__ void leave_scores(const Dims &dm, const DevTables &t,
         return v;
     };
     float x[kAtOnce];
-    auto read = [&](int i0) {
+    auto read = [&](int i0) {  // offsets from i0: those from the row's start leave 32 bits behind at 2^30 scores
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(scores + i0, 0, min(n_vis - i0, kStep * kAtOnce) * 4, 0x00020000);
 #pragma unroll
         for (int j = 0; j < kAtOnce; ++j)
-            x[j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, (i0 + kStep * j + tid) * 4, 0, kSysScope));
+            x[j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, (kStep * j + tid) * 4, 0, kSysScope));
     };
     double s1 = 0.0;
     for (int i0 = 0; i0 < n_vis; i0 += kStep * kAtOnce) {

@@ -1,5 +1,5 @@
-"""Spans that leave 32-bit offsets behind (they fit the card's memory, so they are accepted): one unit, every key and query but a
-few at zero."""
+"""Spans that leave 27 bits of a place behind (they fit the card's memory, so they are accepted): one unit, every key and query
+but a few at zero."""
 import numpy as np
 import pytest
 
