@@ -192,7 +192,8 @@ __global__ __launch_bounds__(kThreads, 4) void window_sums_kernel(Dims dm, DevTa
                     }
                     return (z[0] + z[1]) + (z[2] + z[3]);
                 };
-                float z = exps(ref[b]);
+                float z = kSumLimit;  // a wave's first keys: no reference yet, whatever the exponentials above the lowest one are
+                if (key0 != key_first) z = exps(ref[b]);
                 if (__ballot(z >= kSumLimit) != 0ull) {
                     // the lane's reference becomes its largest logit, if that lies above; logits above the bound are held at it
                     constexpr float kFarRaw = kFar / kC;
