@@ -189,17 +189,21 @@ __device__ __forceinline__ void leave_moments(const Dims &dm, const DevTables &t
 
 // The same for a workgroup of NW waves that has written scores of its unit, through to memory (all of its waves; n_parts
 // workgroups share the unit): the last of them reads the unit's scores back past the caches and forms S1, the mean and the central
-// sums from them, in a fixed order, whatever the workgroups' parts were.  s_mom: as above; s_last: an int in LDS.
+// sums from them, in a fixed order, whatever the workgroups' parts were.  A workgroup that has the unit to itself takes the scores from
+// s_scores, where its threads left them (thread i the scores i, i + 64 NW, ...): nothing to wait for, to count or to read back.
+// s_mom: as above; s_last: an int in LDS.
 template <int NW>
 __device__ __forceinline__ void leave_scores(const Dims &dm, const DevTables &t, int64_t unit, int b, const air_seq &sq, int n_parts,
-                                             double (&s_mom)[NW][3], int &s_last) {
+                                             const float *s_scores, double (&s_mom)[NW][3], int &s_last) {
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    lds_barrier();
-    if (tid == 0) s_last = __hip_atomic_fetch_add(&t.unit_cnt[unit], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n_parts - 1;
-    lds_barrier();
-    if (!s_last) return;
-    if (tid == 0) __hip_atomic_store(&t.unit_cnt[unit], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // next launch
+    if (n_parts > 1) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        lds_barrier();
+        if (tid == 0) s_last = __hip_atomic_fetch_add(&t.unit_cnt[unit], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n_parts - 1;
+        lds_barrier();
+        if (!s_last) return;
+        if (tid == 0) __hip_atomic_store(&t.unit_cnt[unit], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // next launch
+    }
     const int n_vis = sq.vis_len;
     float *scores = t.scores + unit * dm.max_vis;
     constexpr int kAtOnce = 16, kStep = 64 * NW;  // reads past the scores give zero
@@ -210,7 +214,14 @@ __device__ __forceinline__ void leave_scores(const Dims &dm, const DevTables &t,
         return v;
     };
     float x[kAtOnce];
-    auto read = [&](int i0) {  // offsets from i0: those from the row's start leave 32 bits behind at 2^30 scores
+    auto read = [&](int i0) {
+        if (n_parts == 1) {
+#pragma unroll
+            for (int j = 0; j < kAtOnce; ++j)
+                if (i0 + kStep * j < n_vis) x[j] = i0 + kStep * j + tid < n_vis ? s_scores[i0 + kStep * j + tid] : 0.f;
+            return;
+        }
+        // (offsets from i0: those from the row's start leave 32 bits behind at 2^30 scores)
         const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(scores + i0, 0, min(n_vis - i0, kStep * kAtOnce) * 4, 0x00020000);
 #pragma unroll
         for (int j = 0; j < kAtOnce; ++j)
@@ -220,7 +231,8 @@ __device__ __forceinline__ void leave_scores(const Dims &dm, const DevTables &t,
     for (int i0 = 0; i0 < n_vis; i0 += kStep * kAtOnce) {
         read(i0);
 #pragma unroll
-        for (int j = 0; j < kAtOnce; ++j) s1 += (double)x[j];
+        for (int j = 0; j < kAtOnce; ++j)
+            if (i0 + kStep * j < n_vis) s1 += (double)x[j];
     }
     s1 = wave_sum(s1);
     if (lane == 0) s_mom[wave][0] = s1;
@@ -231,6 +243,7 @@ __device__ __forceinline__ void leave_scores(const Dims &dm, const DevTables &t,
         if (n_vis > kStep * kAtOnce) read(i0);  // (else they are still there)
 #pragma unroll
         for (int j = 0; j < kAtOnce; ++j) {
+            if (i0 + kStep * j >= n_vis) continue;
             const double dlt = i0 + kStep * j + tid < n_vis ? (double)x[j] - mu : 0.0;
             m2 += dlt * dlt;
             m3 += dlt * dlt * dlt;

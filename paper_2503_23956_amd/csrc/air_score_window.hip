@@ -420,7 +420,7 @@ __global__ __launch_bounds__(kThreads, 4) void window_scores_kernel(Dims dm, Dev
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(t.scores + u.unit * dm.max_vis + key_lo, 0, n_here * 4, 0x00020000);
     for (int i = tid; i < n_here; i += kThreads)
         __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, s_imp[i]), rs, i * 4, 0, kSysScope);
-    leave_scores(dm, t, u.unit, u.b, u.sq, (u.sq.vis_len + part_keys - 1) / part_keys, s_mom, s_is_last);
+    leave_scores(dm, t, u.unit, u.b, u.sq, (u.sq.vis_len + part_keys - 1) / part_keys, s_imp, s_mom, s_is_last);
 }
 
 // Keys of a workgroup, a multiple of 64 from kPartLeast to `most`.  Two workgroups share a CU, 512 the chip: as many parts of max_vis
