@@ -302,10 +302,13 @@ __global__ __launch_bounds__(kThreads, 4) void window_scores_kernel(Dims dm, Dev
                 const int64_t slot = (u.hrow0 + g) * u.W + (rho - s_pref[g]);
                 const float2 *part = t.part + slot * dm.n_chunks;
                 const float mt = t.row_mtext[slot], zt = t.row_ztext[slot];  // of raw logits
-                constexpr int kAtOnce = 16;  // partials requested together; those past the end repeat the last one
+                constexpr int kAtOnce = 16;  // partials requested together (a load for every one of them: rows lie far apart)
                 float2 x[kAtOnce];
 #pragma unroll
-                for (int s = 0; s < kAtOnce; ++s) x[s] = part[min(s, n_seg - 1)];
+                for (int s = 0; s < kAtOnce; ++s) {
+                    x[s] = make_float2(-INFINITY, 0.f);
+                    if (s < n_seg) x[s] = part[s];
+                }
                 M = mt > -INFINITY ? rintf(held<D>(mt) * kC) : -INFINITY;
 #pragma unroll
                 for (int s = 0; s < kAtOnce; ++s) M = fmaxf(M, x[s].x);
@@ -320,7 +323,7 @@ __global__ __launch_bounds__(kThreads, 4) void window_scores_kernel(Dims dm, Dev
                 }
                 double Z = 0.0;
 #pragma unroll
-                for (int s = 0; s < kAtOnce; ++s) Z += s < n_seg && x[s].y > 0.f ? (double)ldexpf(x[s].y, (int)(x[s].x - M)) : 0.0;
+                for (int s = 0; s < kAtOnce; ++s) Z += x[s].y > 0.f ? (double)ldexpf(x[s].y, (int)(x[s].x - M)) : 0.0;
 #pragma unroll 1
                 for (int s0 = kAtOnce; s0 < n_seg; s0 += kMore) {
                     float2 y[kMore];
