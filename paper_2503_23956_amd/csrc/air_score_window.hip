@@ -2,7 +2,7 @@
 // hundreds of rows per unit): Eq.6-8 with the ROWS in LDS, once per workgroup, and the keys of a wave in its registers, twice.
 //
 // A workgroup of eight waves takes a part of a unit's keys; its waves share up to 256 window rows in LDS (loaded straight into
-// it) and go their own ways: a wave loads 64 (pass 1: 32) keys from memory as MFMA operands, walks the row blocks over them and
+// it) and go their own ways: a wave loads 32 keys from memory as MFMA operands, walks the row blocks over them and
 // takes its next keys, without a barrier.  Exponentials are 2^(s kC - m): one fused multiply-add and one exponential per
 // element, with a reference m that is a whole number, so that references are moved and partial sums merged exactly.
 //   pass 1  products of 32 keys x 32 rows: a lane holds 16 logits of ONE window row per block, so that it needs one sum and one
@@ -34,7 +34,7 @@ typedef __attribute__((ext_vector_type(16))) float f32x16;
 constexpr int kWaves = 8, kThreads = 64 * kWaves;
 constexpr int kWinRows = 256;                  // rows in LDS at a time
 constexpr int kPartLeast = 512, kPartMost = 2048;  // keys of a workgroup
-constexpr int kTiles = 4;                      // pass 2: tiles of 16 keys in a wave's registers
+constexpr int kTiles = 2;                      // pass 2: tiles of 16 keys in a wave's registers
 // Beyond 2^22 a reference and a logit no longer differ by what fp32 says they do (raw logits of 3e7: keys masked by a large
 // negative number, operands in the thousands).  References stop there; logits below weigh nothing, logits above are
 // held at the bound: in pass 1 where exponentials are formed again, in pass 2 by a plain loop over the rows that have such a
@@ -349,7 +349,7 @@ __global__ __launch_bounds__(kThreads, 4) void window_scores_kernel(Dims dm, Dev
             const int lane = here(threadIdx.x & 63), n = lane & 15, c = lane >> 4;
             int row_at[NS];
             row_places<D>(n, c, row_at);
-            f32x4 acc = (f32x4){0.f, 0.f, 0.f, 0.f};  // key 16 tile + n, the rows of lane group c
+            float acc[T] = {};  // key 16 tile + n, the rows of lane group c
             auto block = [&](int b, auto last_block) __attribute__((always_inline)) {
                 uint4 qa[NS];
 #pragma unroll
@@ -385,7 +385,7 @@ __global__ __launch_bounds__(kThreads, 4) void window_scores_kernel(Dims dm, Dev
 #pragma unroll 1
             for (int b = 0; b < n_blk - 1; ++b) block(b, std::false_type());
             block(n_blk - 1, std::true_type());
-            // over the lane groups; lane (n, c) stores key 16 c + n
+            // over the lane groups; lane (n, c), c < T, stores key 16 c + n
             float v = 0.f;
 #pragma unroll
             for (int tile = 0; tile < T; ++tile) {
@@ -394,9 +394,8 @@ __global__ __launch_bounds__(kThreads, 4) void window_scores_kernel(Dims dm, Dev
                 a += __shfl_xor(a, 32, 64);
                 if (c == tile) v = a;
             }
-            s_imp[key0 - key_lo + lane] += v;
+            if (c < T) s_imp[key0 - key_lo + lane] += v;
         };
-        static_assert(T == 4, "a key per lane");
         for (int key0 = key_lo + kGroup * wave; key0 < key_hi; key0 += kGroup * kWaves) {
             if (key0 + kGroup > u.sq.vis_len || (dm.vis_window && key0 + kGroup > prow0 + 1)) group(key0, std::true_type());
             else group(key0, std::false_type());
