@@ -1,5 +1,5 @@
-"""Windows of many rows (bf16, no threshold): runs of one, two and four chunks of keys per workgroup, logits that outrun their
-reference, scores that do not depend on how the layers are cut into calls, and their error against fp64."""
+"""Windows of many rows (bf16, no threshold): runs and parts of 512 to 2048 keys per workgroup, logits that outrun their reference,
+scores that do not depend on how the layers are cut into calls, their error against fp64 and the statistics formed from them."""
 import math
 
 import numpy as np
@@ -10,6 +10,13 @@ from oracle import aircache_oracle as O
 from tests import parity_util as P
 
 pytestmark = pytest.mark.gpu
+
+
+def _part_keys(n_vis, units, most, extra):
+    """Keys of a workgroup as the launcher chooses them: least rounds of 512 workgroups times what a round costs."""
+    groups = -(-n_vis // 64)
+    cost = {g: -(-units * -(-groups // g) // 512) * (g + extra) for g in range(8, most // 64 + 1)}
+    return 64 * min(cost, key=lambda g: (cost[g], -g))
 
 
 class _Prompt:
@@ -57,7 +64,7 @@ class _Prompt:
 
 
 @pytest.mark.parametrize("d,visual", [(128, False), (64, False), (128, True), (64, True)])
-@pytest.mark.parametrize("L", [5, 16, 34])  # runs of one, two and four chunks of 256 keys; 34 layers take two launches
+@pytest.mark.parametrize("L", [5, 16, 34])  # runs of 512, 512 and 1024 keys; 34 layers take two launches, in parts of 1024
 def test_scores_are_the_same_bits_however_the_layers_are_cut(L, d, visual):
     p = _Prompt(L, 6, 8, 2, d, 1000, 24, 20, visual)
     ac = p.context()
@@ -78,7 +85,7 @@ def test_scores_are_the_same_bits_however_the_layers_are_cut(L, d, visual):
 @pytest.mark.parametrize("L", [1, 34])
 def test_logits_that_outrun_their_reference(d, visual, shape, L):
     # raw logits that step by 240 (30 or 43 bits) every 64 keys, or stand 1600 above everything at single keys: a step's sums
-    # pass their limit, references are raised and sums scaled, in runs of one and of four chunks.  Small whole numbers, so that
+    # pass their limit, references are raised and sums scaled, in runs of 512 and of 1024 keys.  Small whole numbers, so that
     # every logit is exact in fp32.
     import torch
 
@@ -126,7 +133,7 @@ def test_edges_of_parts_and_row_blocks(n_vis, window, G, d, visual):
     p = _Prompt(3, 2, 2, G, d, n_vis, 48, window, visual)
     ac = p.context()
     got = p.score(ac)
-    one_by_one = p.score(ac, [(l, l + 1) for l in range(3)])  # pass 2 in parts of other sizes
+    one_by_one = p.score(ac, [(l, l + 1) for l in range(3)])  # (parts of 512 keys in both)
     ac.air_budget()
     s_t, s_k = ac.air_get_stats()
     ac.close()
@@ -156,3 +163,71 @@ def test_spans_of_many_runs(n_vis, window, G, d, visual):
         np.testing.assert_allclose(got[l][0, 0], p.oracle(l, 0, 0), rtol=P.SCORE_RTOL, atol=P.SCORE_ATOL)
         np.testing.assert_allclose(s_t[0, l], got[l][0, 0].astype(np.float64).sum(), rtol=1e-12)
         np.testing.assert_allclose(s_k[0, l], O.skewness(got[l][0, 0].astype(np.float64)), rtol=1e-9, atol=1e-12)
+
+
+@pytest.mark.parametrize("d,visual", [(128, False), (64, False), (128, True), (64, True)])
+@pytest.mark.parametrize("window,G", [(9, 4), (33, 8)])  # 36 and 264 rows: two groups of rows
+@pytest.mark.parametrize("n_vis,run,part", [(4160, 576, 1088), (7290, 960, 1856), (8192, 1024, 2048)])
+def test_parts_that_are_larger_in_one_call_than_layer_by_layer(n_vis, run, part, window, G, d, visual):
+    # 128 units in one launch, four layer by layer: units of several parts that are no power of two, and parts as large as LDS takes
+    L, B = 32, 4
+    assert (_part_keys(n_vis, L * B, 1024, 4), _part_keys(n_vis, L * B, 2048, 8), _part_keys(n_vis, B, 2048, 8)) == (run, part, 512)
+    p = _Prompt(L, B, 1, G, d, n_vis, 48, window, visual)
+    ac = p.context()
+    stats = []
+    got = []
+    for pieces in (None, [(l, l + 1) for l in range(L)]):
+        got.append(p.score(ac, pieces))
+        ac.air_budget()
+        stats.append(ac.air_get_stats())
+    ac.close()
+    assert all(np.array_equal(x, y) for x, y in zip(*got))
+    assert all(np.array_equal(x, y) for x, y in zip(*stats))
+    for (l, b) in [(0, 0), (L // 2, 1), (L - 1, B - 1)]:
+        np.testing.assert_allclose(got[0][l][b, 0], p.oracle(l, b, 0), rtol=P.SCORE_RTOL, atol=P.SCORE_ATOL)
+        np.testing.assert_allclose(stats[0][1][b, l], O.skewness(got[0][l][b, 0].astype(np.float64)), rtol=1e-9, atol=1e-12)
+
+
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("G", [2, 7])
+@pytest.mark.parametrize("spread", [1.0, 18.0, 100.0, 1e3, 1e4, 1e5])
+def test_weights_of_a_row_add_up_to_one_whatever_the_logits(spread, G, d):
+    # Pass 1 forms its logits with products of 32 x 32, pass 2 with products of 16 x 16: they have to be the same bits, or a weight is
+    # off by 2^(difference) where a key stands above all others (raw logits of 4e6 have a spacing of 0.5, that is 4 % of a weight).
+    # No text columns: every row's weights add up to 1, to the rounding of fp32 sums of 2304 terms in runs of 512.
+    p = _Prompt(2, 1, 2, G, d, 2304, 16, 32, True, spread)
+    ac = p.context()
+    got = p.score(ac)
+    ac.close()
+    for x in got:
+        np.testing.assert_allclose(x[0].astype(np.float64).sum(axis=1), 1.0, rtol=0, atol=1e-6)
+
+
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("visual", [False, True])
+@pytest.mark.parametrize("n_vis", [500, 3000])  # one part, several
+def test_skewness_of_rows_with_little_or_no_spread(n_vis, visual, d):
+    # visual keys that are equal, equal but for k 2^-21 in one element (below what fp32 scores resolve) and for k 2^-6
+    import torch
+
+    p = _Prompt(4, 2, 1, 7, d, n_vis, 48, 32, visual)
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(3)
+    for l, step in enumerate([None, 0.0, 2.0 ** -21, 2.0 ** -6]):
+        if step is None:
+            continue
+        vis = p.k[l][:, :, 9:9 + n_vis]
+        vis.copy_(vis[:, :, :1].clone())
+        vis[..., 5] = step * torch.randint(0, 4, vis.shape[:3], generator=gen, device="cuda:0").to(torch.bfloat16)
+    ac = p.context()
+    got = p.score(ac)
+    ac.air_budget()
+    s_t, s_k = ac.air_get_stats()
+    ac.close()
+    for l in range(4):
+        for b in range(2):
+            want = p.oracle(l, b, 0)
+            np.testing.assert_allclose(got[l][b, 0], want, rtol=P.SCORE_RTOL, atol=P.SCORE_ATOL)
+            np.testing.assert_allclose(s_k[b, l], O.skewness(got[l][b, 0].astype(np.float64)), rtol=1e-7, atol=1e-7)
+            if l in (1, 2) and not visual:  # (rows of a visual window do not see its last keys: their scores are smaller)
+                assert s_k[b, l] == 0.0 and O.skewness(want) == 0.0
