@@ -369,7 +369,7 @@ air_status air_score(air_ctx *ctx, void *stream, int32_t l0, int32_t l1, const a
     const int inline_rows = ctx->cfg.alpha > 0.0 && !ctx->dm.vis_window && ctx->tune.score_rows_kernel != 1;
     // Windows that are known to exceed the stash (alpha = 0 turns the whole candidate span into rows) read K_v twice, in
     // kernels that are bound by their exponentials: all layers in one pair of passes (224 rows, 28 x 4 x 7290 keys: one pair
-    // beats two of 14 layers, whose second read would come from the memory-side cache, by a quarter: fewer half-filled
+    // 170 us, two of 14 layers, whose second read would come from the memory-side cache, 191, four of seven 239: fewer half-filled
     // rounds of workgroups).  air_tuning.score_block_mb cuts the layers into groups.
     // (So do bf16 contexts whose workspace holds no stash, whatever their windows.)
     const int many_rows = ctx->dm.stash_rows == 0;

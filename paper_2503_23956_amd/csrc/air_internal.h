@@ -14,7 +14,7 @@ constexpr int kMaxLayersPerLaunch = 32;
 constexpr int kCUs = 256;
 constexpr int kMaxSplits = 16;        // largest split-K factor of the decode attention
 constexpr int kCacheRowAlign = 32;    // layer regions of the compacted cache start on multiples of this
-constexpr int kFinishChunks = 4;      // chunks finished (and summed into one moment entry) per workgroup of air_score's last kernel
+constexpr int kFinishChunks = 4;      // chunks finished (and summed into one moment entry) per workgroup of the finish kernels
 constexpr int kStashRows = 32;        // window rows per unit up to which air_score stashes exponentials (one pass over K_v)
 
 struct LayerPtrs {
@@ -51,7 +51,7 @@ struct WsLayout {
 struct Dims {
     int32_t L, Hq, Hkv, G, D, B;
     int32_t max_vis, max_window, n_chunks, max_steps;
-    int32_t n_entries;   // moment entries per unit: one per workgroup of air_score's last kernel, ceil(n_chunks / kFinishChunks)
+    int32_t n_entries;   // moment entries per unit: one per workgroup of the finish kernels, ceil(n_chunks / kFinishChunks) (many-row windows leave none)
     int32_t vis_window;  // 1: the window rows are visual tokens (causal over the visual keys, no text columns)
     int32_t causal_text; // 1: an elite row sees only the elite text keys at or before its own position (Eq.7 with a causal mask)
     uint32_t inv_B;      // floor(2^32 / B) + 1 (unused for B = 1): division of a 16-bit index by B as one multiply
@@ -74,7 +74,7 @@ struct DevTables {
     float *dec_o, *stash, *row_f;
     int2 *len_off;    // (base_len, layer_off) of a (sequence, layer) side by side: one read for the decode kernel
     int4 *by_length;  // per sequence, the layers in order of falling cache length: (base_len, layer_off, layer, 0)
-    int32_t *unit_cnt;  // per unit: workgroups of air_score's last kernel that have left their moment entry (zero between launches)
+    int32_t *unit_cnt;  // per unit: workgroups of air_score's last kernel that have left their moment entry or scores (zero between launches)
     int32_t *seq_cnt;   // per sequence: units whose statistics are complete (zero again once all L * H_kv have arrived)
     int32_t *unit_R;  // window rows of a unit (all heads of the group), left by the row-parameter kernel
     float2 *dec_ml;

@@ -11,14 +11,20 @@
 //   pass 2  forms maximum, fp64 normaliser and weight of the unit's rows from the partials, a thread per row, then
 //           I[key] = sum over the rows of w 2^(s kC - m): the keys of a wave are complete after the last row block (two steps
 //           across the lanes).  The unit's last workgroup forms its statistics from the scores.
-// Bound: instruction issue, of which the exponentials are half: 484 clocks per 64 keys and 16 rows in pass 2, 256 of them
-// exponentials, 64 products, 128 the multiply-adds; 43 us for 224 rows x 112 units x 7290 keys at the 1.97 GHz that the chip holds
-// under this load.  The rest: about 9 us in front (row lists, 57 KB of rows, parameters: chains of dependent accesses) and a
-// last round that is not full.  Four waves a SIMD need 128 registers: everything in front of the loops is kept out of
-// registers across them (`here`), because a spill in the prologue cost 15-30 us (its scratch is touched for the first time).
-// 224 rows per unit (7 heads x 32), 28 layers x 4 KV heads x 7290 keys, us for air_score with the elite kernel (16): 172.  Before, the
-// rows in registers, the keys through LDS with a barrier per 64 keys, four waves of 3 and 4 row blocks: 203.  10 rows a head 128 ->
-// 108, 48 rows of 8 heads 335 -> 280, four layers 79 -> 66, heads of 64 165 -> 134, 28 layers one by one 2080 -> 1740.
+// The products of the two passes differ in shape but give a logit the same bits, and have to: a weight would be off by
+// 2^(difference) where a key stands above all others.
+// Bound: instruction issue in pass 1 (71 % of the clocks, matrix unit 25 %; an exponential takes a SIMD 16 clocks, any other
+// instruction 4, and 15 % of the exponentials are formed a second time above a raised reference).  In pass 2 issue takes 55 % and
+// the matrix unit 23 %: a block's products stand in front of its exponentials, and the groups of 32 keys (58 in a part of 1856) are
+// dealt to eight waves unevenly.  In front of a workgroup's keys stand about 14 thousand clocks (row lists, 57 KB of rows,
+// parameters: chains of dependent accesses; by stamps, one workgroup a unit), behind them 9 thousand (statistics); the pass takes 200.
+// Four waves a SIMD need 128 registers: everything in front of the loops is kept out of registers across them (`here`).
+// 7290 keys, 28 layers x 4 KV heads, rows a head x heads, us for air_score with the elite kernel (19 for 32 x 7): 32 x 7 rows 172, 10 x 7 106,
+// 48 x 8 278, four layers 62, heads of 64 130, 28 layers one by one 1560.  With the rows in registers, the keys through LDS with a barrier
+// per 64 keys and four waves of 3 and 4 row blocks: 216, 134, 352, 81, 170, 2014.
+// Short spans of many units (28 x 16 x 4, 512 keys, 7 x 32 rows: 280; 128 keys, 4 x 9 rows: 99) were slower than with those kernels (296; 101)
+// with 64 keys a wave in pass 2, first exponentials formed twice, sixteen partial sums read where there is one, and a
+// unit's only workgroup reading its scores back from memory: 315; 108.
 // Precision: the argument of an exponential is rounded, to 2^-24 of itself, and the largest terms are the ones that count, so a
 // reference has to stay near the maximum; and a logit keeps its bits only if its sum starts at zero.  (With sums that
 // started at minus the reference, and the lane's first logit as reference up to 2^100, the scores were 9.7e-7 off fp64 in
