@@ -91,7 +91,7 @@ WsLayout make_layout(const air_config &c) {
     w.dec_cnt = take(L * B * Hkv * 4);
     w.unit_cnt = take(L * B * Hkv * 4);
     w.seq_cnt = take(B * 4);
-    w.dec_steps = take((L * B * Hkv + 1) * 4);
+    w.dec_steps = take((L * B * Hkv * kStepCopies + 1) * 4);
     w.moments = take(L * B * Hkv * (size_t)((w.n_chunks + kFinishChunks - 1) / kFinishChunks) * 4 * 8);
     w.indices = take(L * B * Hkv * NV * 4);
     // the cache pool, unless the cache is kept inside the prompt's own tensors
@@ -692,9 +692,6 @@ static air_status decode_attn(air_ctx *ctx, void *stream, int32_t l0, int32_t l1
         const bool longest_first = whole && ctx->tune.decode_order != 1 &&
                                    (ctx->tune.decode_order == 2 || (int64_t)nl * units_per_layer >= 512);
         const int column_parts = parts_of(nl, splits, waves, tiles);
-        // with device-counted steps the workgroups of a unit meet at the unit's arrival counter
-        if (e == hipSuccess && use_static && column_parts > 1 && ctx->cfg.device_steps && splits == 1)
-            e = launch_zero_counters(s, xch.cnt, (int)(nl * units_per_layer));
         if (e == hipSuccess)
             e = launch_decode(s, ctx->dm, ctx->tab, xch, ctx->cfg.dtype, c0, nl, c0 - l0, ll, q_new, k_new, v_new, out,
                               splits, waves, tiles, in_step ? ctx->appended[l0] : -1, longest_first, column_parts,
@@ -749,7 +746,7 @@ static air_status d2h(air_ctx *ctx, void *dst, const void *src, size_t bytes);
 // fails when a step ran with the cache full
 static air_status device_steps(air_ctx *ctx, std::vector<int32_t> &steps) {
     const int L = ctx->dm.L, B = ctx->dm.B, Hkv = ctx->dm.Hkv;
-    std::vector<int32_t> raw((size_t)L * B * Hkv + 1);
+    std::vector<int32_t> raw((size_t)L * B * Hkv * kStepCopies + 1);
     air_status st = d2h(ctx, raw.data(), ctx->tab.dec_steps, raw.size() * 4);
     if (st != AIR_OK) return st;
     bool any_compacted = false;  // until a layer is compacted again the flag is the previous prompt's
@@ -758,7 +755,7 @@ static air_status device_steps(air_ctx *ctx, std::vector<int32_t> &steps) {
         return fail(ctx, AIR_ERR_STATE, "a decode step ran with the cache full (max_decode_steps exhausted)");
     steps.assign((size_t)B * L, 0);
     for (int l = 0; l < L; ++l)
-        for (int b = 0; b < B; ++b) steps[(size_t)b * L + l] = raw[((size_t)l * B + b) * Hkv];  // the same for every KV head
+        for (int b = 0; b < B; ++b) steps[(size_t)b * L + l] = raw[((size_t)l * B + b) * Hkv * kStepCopies];  // the same for every KV head
     return AIR_OK;
 }
 
@@ -901,7 +898,7 @@ air_status air_get_cache(air_ctx *ctx, int32_t l, int32_t b, int32_t h, void *k_
     if (st != AIR_OK) return st;
     int32_t app = ctx->appended[l];
     if (ctx->cfg.device_steps) {
-        st = d2h(ctx, &app, ctx->tab.dec_steps + ((size_t)l * ctx->dm.B + b) * ctx->dm.Hkv + h, 4);
+        st = d2h(ctx, &app, ctx->tab.dec_steps + (((size_t)l * ctx->dm.B + b) * ctx->dm.Hkv + h) * kStepCopies, 4);
         if (st != AIR_OK) return st;
     }
     const int32_t len = base + app;

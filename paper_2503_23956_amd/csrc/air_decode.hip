@@ -94,14 +94,15 @@ hipError_t launch_zero_counters(hipStream_t s, int32_t *p, int n) {
 // What the MFMA decode kernel needs of the tables and of the per-layer launch block: a short
 // argument block (the kernel starts with the loads of its arguments).
 struct DecodeTabs {
+    // (side by side: one scalar load; a load of its own for the second, behind the first wait, cost 0.3 us a launch)
     const int2 *len_off;
+    int32_t *dec_steps;  // null: the host passes the count of appended tokens (DecodeSteps)
     const int4 *by_length;  // per sequence, (length, offset, layer) of the layers by falling cache length
     void *kcache, *vcache;
     float *dec_o;
     float2 *dec_ml;
     int32_t *dec_cnt;
-    int32_t *dec_steps;  // null: the host passes the count of appended tokens (DecodeSteps)
-    int32_t n_units;     // units of the whole context: dec_steps[n_units] is the cache-full flag
+    int32_t n_units;     // units of the whole context: the cache-full flag lies behind their counts
     const CachePtrs *cache_ptrs;  // in-place cache: the K / V tensor of every layer (else null: the cache is the workspace's pool)
     int64_t kv_b, kv_h;           // in-place cache: element strides between sequences / KV heads of those tensors
     int32_t x_local;     // 1: the exchange slots (dec_o, dec_ml, dec_cnt) are indexed by the unit inside the launch
@@ -139,6 +140,7 @@ __global__ __launch_bounds__(64 * NW) void decode_mfma_kernel(Dims dm, DecodeTab
     constexpr int kColsPer = kCols > 64 ? kCols / 64 : 1;  // columns of the appended V' row per lane (lanes < kCols)
     static_assert(kIter % kVTok == 0 && kCols >= 16, "whole V' blocks per iteration, whole output tiles");
     static_assert(VH == 1 || (!SPLIT && !SORTED), "column parts: VH workgroups per unit, no exchange");
+    static_assert(kStepCopies % VH == 0, "whole copies of the step count per part");
     // Non-finite values.  A logit of -inf weighs nothing, also in a chunk that has no other (its head then has no reference
     // yet); an infinite element of V' makes its output column infinite: every factor of V' is at least kLeast, also the one
     // of the last block read again behind the last key, whose infinities are in the column anyway (0 * inf would be NaN; of
@@ -205,21 +207,27 @@ __global__ __launch_bounds__(64 * NW) void decode_mfma_kernel(Dims dm, DecodeTab
     for (int h2 = 0; h2 < kColsPer; ++h2) vcol[h2] = v_new[new_src + kCols * vh + 64 * h2 + (kCols < 64 ? lane & (kCols - 1) : lane)];
     const int64_t unit = ((int64_t)l * dm.B + b) * dm.Hkv + kvh;
     // tokens appended so far: from the host with the launch, or counted on the device (a recorded launch
-    // that is replayed): the workgroup that finishes the unit advances the count, after every workgroup
-    // of the unit has read it
+    // that is replayed): a column part reads and advances copies of its own (count_step), of the splits of a unit the one that
+    // merges them advances all copies, after every split has read the first
     int appended = ll.uniform >= 0 ? ll.uniform : ll.appended[li];
-    // A workgroup past the last unit does not look at the device's count: it is not counted at the unit's arrival counter, so
-    // that the count may already be the next step's, and with it a cache that only looks full.  (A pointer it does not have, not
+    // A workgroup past the last unit does not look at the device's count: it redoes a part that may have finished, so that
+    // the count may already be the next step's, and with it a cache that only looks full.  (A pointer it does not have, not
     // a return in front of it: behind a branch the argument is fetched late, 0.15 us a launch.)
     const int32_t *const steps = VH > 1 && !live ? nullptr : t.dec_steps;
     if (steps) {
-        appended = steps[unit];
+        appended = steps[unit * kStepCopies + vh];
         if (appended >= dm.max_steps) {  // cache full: nothing is appended or written
-            if (threadIdx.x == 0) t.dec_steps[t.n_units] = 1;
+            if (threadIdx.x == 0) t.dec_steps[(int64_t)t.n_units * kStepCopies] = 1;
             return;
         }
     }
     if (VH > 1 && !live) return;
+    // The next step's count: part vh of VH reads copy vh and writes the copies vh, vh + VH, ..., so that the parts of a unit need
+    // not wait for one another and a launch of another shape finds every copy advanced.  (One count, advanced by the last part
+    // to arrive at an atomic counter: a recorded launch of one layer took 7.7 us where the same launch called eagerly took 6.8.)
+    auto count_step = [&]() {
+        if (threadIdx.x < kStepCopies / VH) t.dec_steps[unit * kStepCopies + vh + VH * threadIdx.x] = appended + 1;
+    };
     const int len = len_off.x + appended + 1;
     const int newrow = len - 1;  // the token appended by this call (Eq.2): scored from k_new / v_new, stored to the cache
     int k0 = 0, k1 = len;
@@ -538,18 +546,7 @@ __global__ __launch_bounds__(64 * NW) void decode_mfma_kernel(Dims dm, DecodeTab
                     stf(&o_unit[g * D + 16 * (NJ * vh + wave + NW * jj) + n], sizeof(T) == 4 ? acc[jj][i] / mrg_l[i] : acc[jj][i] * inv);
             }
         }
-        if (t.dec_steps && threadIdx.x == 0) {
-            if (VH == 1) {
-                t.dec_steps[unit] = appended + 1;
-            } else {
-                // the last workgroup of the unit to finish advances the count: the others have read it by then
-                const int64_t xu = t.x_local ? ((int64_t)li * dm.B + b) * dm.Hkv + kvh : unit;
-                if (__hip_atomic_fetch_add(&t.dec_cnt[xu], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == VH - 1) {
-                    __hip_atomic_store(&t.dec_cnt[xu], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // next launch
-                    t.dec_steps[unit] = appended + 1;
-                }
-            }
-        }
+        if (t.dec_steps) count_step();
         return;
     }
     if (!SPLIT) return;  // the instance for one workgroup per unit carries none of what follows
@@ -647,7 +644,7 @@ __global__ __launch_bounds__(64 * NW) void decode_mfma_kernel(Dims dm, DecodeTab
             for (int jj = 0; jj < kTiles; ++jj) stf(&o_unit[g * D + 16 * (wave + NW * jj) + n], num[jj][i] * inv);
         }
     }
-    if (t.dec_steps && threadIdx.x == 0) t.dec_steps[unit] = appended + 1;
+    if (t.dec_steps) count_step();
 }
 
 // ---------------------------------------------------------------------------------------

@@ -13,6 +13,7 @@ constexpr int kChunkKeys = 256;       // visual keys per workgroup in the score 
 constexpr int kMaxLayersPerLaunch = 32;
 constexpr int kCUs = 256;
 constexpr int kMaxSplits = 16;        // largest split-K factor of the decode attention
+constexpr int kStepCopies = 8;        // copies of a unit's device-counted steps: one for each of the most workgroups that share a unit without exchange
 constexpr int kCacheRowAlign = 32;    // layer regions of the compacted cache start on multiples of this
 constexpr int kFinishChunks = 4;      // chunks finished (and summed into one moment entry) per workgroup of the finish kernels
 constexpr int kStashRows = 32;        // window rows per unit up to which air_score stashes exponentials (one pass over K_v)
@@ -78,7 +79,7 @@ struct DevTables {
     int32_t *seq_cnt;   // per sequence: units whose statistics are complete (zero again once all L * H_kv have arrived)
     int32_t *unit_R;  // window rows of a unit (all heads of the group), left by the row-parameter kernel
     float2 *dec_ml;
-    int32_t *dec_steps;  // tokens appended so far per unit when the device counts them (else null); one overflow flag after the last unit
+    int32_t *dec_steps;  // tokens appended so far per unit, kStepCopies copies, when the device counts them (else null); one overflow flag after the last unit
     CachePtrs *cache_ptrs;  // in-place cache: K / V tensor of every layer, written by the compaction gather (else null)
     int64_t ip_kv_b, ip_kv_h;  // in-place cache: element strides between sequences and between KV heads of those tensors
 };

@@ -195,6 +195,12 @@ __global__ __launch_bounds__(NT) void select_kernel(Dims dm, DevTables t, int l0
     }
 }
 
+// A fresh cache: nothing appended yet, cache-full flag down (device-counted steps).
+__device__ __forceinline__ void fresh_steps(const Dims &dm, const DevTables &t, int64_t unit, bool flag) {
+    if (threadIdx.x < kStepCopies) t.dec_steps[unit * kStepCopies + threadIdx.x] = 0;
+    if (flag && threadIdx.x == 0) t.dec_steps[(int64_t)dm.L * dm.B * dm.Hkv * kStepCopies] = 0;
+}
+
 // The cache is written in the layouts the decode kernel feeds to MFMA.  One
 // workgroup stages 32 gathered K and V rows in LDS and writes K' as two 16-token
 // tiles (see k_tiled) and V' block-transposed (see v_tiled; one block of 32 tokens with bf16, two of 16 with fp32).
@@ -223,10 +229,7 @@ __global__ __launch_bounds__(256) void gather_vt_kernel(Dims dm, DevTables t, in
     const int64_t dst_row0 = ((int64_t)b * dm.Hkv + kvh) * dm.pool_rows + t.layer_off[(int64_t)b * dm.L + l];
     T *kdst = (T *)t.kcache + dst_row0 * D;
     T *vdst = (T *)t.vcache + dst_row0 * D;
-    if (t.dec_steps && blockIdx.x == 0 && threadIdx.x == 0) {  // a fresh cache: nothing appended yet, cache-full flag down
-        t.dec_steps[unit] = 0;
-        if (blockIdx.y == 0 && blockIdx.z == 0) t.dec_steps[(int64_t)dm.L * dm.B * dm.Hkv] = 0;
-    }
+    if (t.dec_steps && blockIdx.x == 0) fresh_steps(dm, t, unit, blockIdx.y == 0 && blockIdx.z == 0);
     __shared__ __align__(16) T tile[32][D + kVec];   // V rows, indexed [block, slot][column]; the pad keeps the 16-byte row alignment and spreads banks
     __shared__ __align__(16) T ktile[32][D + kVec];  // K rows, indexed [row][column]
     // The rows of the workgroup's next block are
@@ -318,11 +321,8 @@ __global__ __launch_bounds__(256) void gather_in_place_kernel(Dims dm, DevTables
             t.cache_ptrs[l].k = const_cast<void *>(ll.p[li].k);
             t.cache_ptrs[l].v = const_cast<void *>(ll.p[li].v);
         }
-        if (t.dec_steps) {  // a fresh cache: nothing appended yet, cache-full flag down
-            t.dec_steps[unit] = 0;
-            if (blockIdx.x == 0 && blockIdx.y == 0) t.dec_steps[(int64_t)dm.L * dm.B * dm.Hkv] = 0;
-        }
     }
+    if (t.dec_steps) fresh_steps(dm, t, unit, blockIdx.x == 0 && blockIdx.y == 0);
     __shared__ bf16_t tile[32][D + 8];   // V rows, indexed [slot][column]
     __shared__ bf16_t ktile[32][D + 8];  // K rows, indexed [row][column]
     uint4 kx[2], vx[2];

@@ -217,3 +217,33 @@ def test_last_permitted_step_on_a_busy_gpu_raises_no_flag():
         assert torch.equal(out, first)
     del b
     ac.close()
+
+
+def test_device_counted_steps_under_changing_launch_shapes():
+    """Every workgroup of a unit keeps a copy of the count: a launch finds it whatever shape the launch before had."""
+    import torch
+
+    from paper_2503_23956_amd.device_inputs import to_device
+
+    dev = torch.device("cuda:0")
+    shapes = [dict(), dict(decode_halves=1), dict(decode_splits=4, decode_waves=2, decode_tiles=2), dict(decode_waves=8), dict(),
+              dict(decode_splits=1, decode_waves=4, decode_tiles=4, decode_halves=2)]
+    steps = 2 * len(shapes)
+    w = synth.get_workload(2).scaled(n_layers=3, n_vis=2900, n_text=40, decode_steps=steps)
+    _, eager, counted, _, _, _ = _contexts(w, steps, dev)
+    out_e = torch.zeros((w.n_layers, w.batch, w.n_q_heads, w.head_dim), dtype=torch.bfloat16, device=dev)
+    out_c = torch.ones_like(out_e)
+    for step in range(steps):
+        ins = [to_device(np.stack(x), dev) for x in zip(*[synth.decode_inputs(w, l, step) for l in range(w.n_layers)])]
+        for ac, out in ((eager, out_e), (counted, out_c)):
+            ac.air_set_tuning(**shapes[step % len(shapes)])
+            if step % 2:  # all layers of the step, or one by one (eight column parts: caches of 640 keys and more)
+                ac.air_decode_attn(0, w.n_layers, *ins, out)
+            else:
+                for l in range(w.n_layers):
+                    ac.air_decode_attn(l, l + 1, *(x[l:l + 1] for x in ins), out[l:l + 1])
+        torch.cuda.synchronize()
+        assert torch.equal(out_e, out_c), f"step {step}"
+        assert np.array_equal(counted.air_get_lengths(), eager.air_get_lengths())
+    eager.close()
+    counted.close()
