@@ -6,25 +6,26 @@
 // takes its next keys, without a barrier.  Exponentials are 2^(s kC - m): one fused multiply-add and one exponential per
 // element, with a reference m that is a whole number, so that references are moved and partial sums merged exactly.
 //   pass 1  products of 32 keys x 32 rows: a lane holds 16 logits of ONE window row per block, so that it needs one sum and one
-//           reference per block.  Leaves (reference, sum) per (row, run of keys).  A lane whose 16 exponentials add up
-//           to more than its limit raises its reference to their maximum and forms them again.
+//           reference per block.  References start at the maximum over the first keys of all waves.  Leaves (reference, sum) per
+//           (run of keys, row).  A lane whose 16 exponentials add up to more than its limit raises its reference to their
+//           maximum and forms them again.
 //   pass 2  forms maximum, fp64 normaliser and weight of the unit's rows from the partials, a thread per row, then
 //           I[key] = sum over the rows of w 2^(s kC - m): the keys of a wave are complete after the last row block (two steps
 //           across the lanes).  The unit's last workgroup forms its statistics from the scores.
 // The products of the two passes differ in shape but give a logit the same bits, and have to: a weight would be off by
 // 2^(difference) where a key stands above all others.
-// Bound: instruction issue in pass 1 (71 % of the clocks, matrix unit 25 %; an exponential takes a SIMD 16 clocks, any other
-// instruction 4, and 15 % of the exponentials are formed a second time above a raised reference).  In pass 2 issue takes 55 % and
-// the matrix unit 23 %: a block's products stand in front of its exponentials, and the groups of 32 keys (58 in a part of 1856) are
-// dealt to eight waves unevenly.  In front of a workgroup's keys stand about 14 thousand clocks (row lists, 57 KB of rows,
-// parameters: chains of dependent accesses; by stamps, one workgroup a unit), behind them 9 thousand (statistics); the pass takes 200.
+// Bound (7290 keys, 7 x 32 rows, 28 x 4 units: 448 workgroups of 1856 keys, pass 1 70 us, pass 2 82): instruction issue, 59 % of the clocks
+// in pass 1 and 57 % in pass 2 (an exponential takes a SIMD 16 clocks, any other instruction 4; matrix unit 34 and 24 %), on the CUs that
+// have two workgroups, by stamps close to all of it between the first keys and the last; then the quarter of the CUs that have one
+// workgroup, 4 us in pass 1 and 8 in pass 2 in front of a workgroup's first keys, and 9 behind its last (statistics, allocation).
+// What stands in front are dependent accesses, so there are few of them: the rows follow from the window and are requested before the
+// counts of the lists are there, and a run's partial sums lie side by side (a thread per row used to touch a line for every one: 5 us).
+// With lists read first, partial sums a line apart, references that each wave found for itself and 832 keys a run: 78.5 and 86.8 us.
+// Two waves a SIMD with 64 keys each, products between exponentials, take as long for the keys and longer in front (101 and 86).
 // Four waves a SIMD need 128 registers: everything in front of the loops is kept out of registers across them (`here`).
-// 7290 keys, 28 layers x 4 KV heads, rows a head x heads, us for air_score with the elite kernel (19 for 32 x 7): 32 x 7 rows 172, 10 x 7 106,
-// 48 x 8 278, four layers 62, heads of 64 130, 28 layers one by one 1560.  With the rows in registers, the keys through LDS with a barrier
-// per 64 keys and four waves of 3 and 4 row blocks: 216, 134, 352, 81, 170, 2014.
-// Short spans of many units (28 x 16 x 4, 512 keys, 7 x 32 rows: 280; 128 keys, 4 x 9 rows: 99) were slower than with those kernels (296; 101)
-// with 64 keys a wave in pass 2, first exponentials formed twice, sixteen partial sums read where there is one, and a
-// unit's only workgroup reading its scores back from memory: 315; 108.
+// air_score with the elite kernel (17 for 32 x 7), rows a head x heads, us now / before: 7290 keys, 28 layers x 4 KV heads, 32 x 7 rows
+// 163 / 172, 5 x 7 97 / 99, 512 x 7 3771 / 3980, visual 151 / 160, heads of 64 121 / 128; eight layers 108 / 117; 16 prompts of 2304 keys
+// 747 / 759; 65536 keys, 2 units 82 / 94; 28 x 8 x 8 units of 300 keys 195 / 199; 32 x 64 x 8 of 128 keys, 4 x 9 rows 722 / 763.
 // Precision: the argument of an exponential is rounded, to 2^-24 of itself, and the largest terms are the ones that count, so a
 // reference has to stay near the maximum; and a logit keeps its bits only if its sum starts at zero.  (With sums that
 // started at minus the reference, and the lane's first logit as reference up to 2^100, the scores were 9.7e-7 off fp64 in
@@ -93,20 +94,49 @@ __device__ __forceinline__ const bf16_t *query_of(const UnitCtx &u, const air_st
     return u.q + (int64_t)(u.kvh * u.G + (int)((unsigned)word >> 27)) * st.q_h + (int64_t)(word & 0x7ffffff) * st.q_t;
 }
 
+// The unit's rows.  A window has every token of its span as a row of every head, but for logits that are no numbers; so the rows
+// are taken from the window itself and requested while the counts of the lists are on their way (`guess`), and only where a count
+// says otherwise are they taken from the lists.
+__device__ __forceinline__ int rows_of_lane(const DevTables &t, const UnitCtx &u) {  // rows of head `lane` of the group
+    const int lane = threadIdx.x & 63;
+    return t.elite_cnt[u.hrow0 + min(lane, u.G - 1)];
+}
+__device__ __forceinline__ int2 row_of(const UnitCtx &u, const int *s_pref, bool whole, int rho) {
+    if (whole) {  // rho / win_len: rho < 2^16, and (rho + 1/2) / win_len is farther from a whole number than it can be off by
+        const int g = (int)(((float)rho + 0.5f) * __builtin_amdgcn_rcpf((float)u.sq.win_len));
+        return make_int2(g, rho - g * u.sq.win_len);
+    }
+    const int g = head_of_row(s_pref, u.G, rho);
+    return make_int2(g, rho - s_pref[g]);
+}
+__device__ __forceinline__ int query_word(const DevTables &t, const UnitCtx &u, bool whole, int2 row) {
+    const int tok = whole ? row.y : t.elite_idx[(u.hrow0 + row.x) * u.W + row.y] - u.sq.win_start;
+    return (int)((unsigned)row.x << 27 | (unsigned)tok);
+}
+
 // The rows of a workgroup straight into LDS, n_load of them (whole blocks; those past the list repeat the last one); the
 // caller waits for them.
 template <int D>
 __device__ __forceinline__ void load_rows_lds(const UnitCtx &u, const air_strides &st, const int *s_query, bf16_t *s_rows, int n_rows, int n_load, int wave) {
     typedef __attribute__((address_space(1))) void gptr_t;
     typedef __attribute__((address_space(3))) void lptr_t;
-    constexpr int kPieces = D / 8, kRowsOfWave = 64 / kPieces;
+    constexpr int kPieces = D / 8, kRowsOfWave = 64 / kPieces, kStep = kRowsOfWave * kWaves, kIt = kWinRows / kStep;
     const int lane = here(threadIdx.x & 63);
-    for (int row0 = kRowsOfWave * wave; row0 < n_load; row0 += kRowsOfWave * kWaves) {
+    int word[kIt];
+#pragma unroll
+    for (int i = 0; i < kIt; ++i) word[i] = s_query[min(kStep * i + kRowsOfWave * wave + lane / kPieces, n_rows - 1)];
+#pragma unroll
+    for (int i = 0; i < kIt; ++i) {
+        const int row0 = kStep * i + kRowsOfWave * wave;
+        if (row0 >= n_load) break;
         const int row = row0 + lane / kPieces;  // lane i's 16 bytes land at the place of lane 0's + 16 i
-        const bf16_t *src = query_of(u, st, s_query[min(row, n_rows - 1)]) + 8 * ((lane % kPieces) ^ row_swizzle<D>(row));
+        const bf16_t *src = query_of(u, st, word[i]) + 8 * ((lane % kPieces) ^ row_swizzle<D>(row));
         __builtin_amdgcn_global_load_lds((gptr_t *)src, (lptr_t *)(s_rows + row0 * D), 16, 0, 0);
     }
 }
+// Partial sums of a unit: a run's rows side by side (row r of head g at g W + r), so that a thread per row reads whole lines.
+__device__ __forceinline__ float2 *unit_parts(const Dims &dm, const DevTables &t, const UnitCtx &u) { return t.part + u.hrow0 * u.W * dm.n_chunks; }
+
 __device__ __forceinline__ void rows_wait_barrier() {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     lds_barrier();
@@ -131,7 +161,8 @@ __global__ __launch_bounds__(kThreads, 4) void window_sums_kernel(Dims dm, DevTa
     __shared__ int s_slot[kWinRows];  // a row's place in the unit's row tables
     __shared__ int s_query[kWinRows];
     __shared__ int s_last[kWinRows];  // last key that a row sees
-    __shared__ float2 s_part[kWaves / 2][kWinRows];
+    static_assert(kWaves * kWinRows * sizeof(float2) <= sizeof(s_rows), "the partial sums of the waves take the place of the rows");
+    __shared__ int s_top[kWinRows];  // a row's first reference
     // a visual-window row at visual index p sees the keys up to p: keys behind the last row are never looked at
     const int prow0 = u.sq.win_start - u.sq.vis_start;
     const int run = blockIdx.x, key_first = run * run_keys + 32 * wave;
@@ -141,35 +172,39 @@ __global__ __launch_bounds__(kThreads, 4) void window_sums_kernel(Dims dm, DevTa
     uint4 kreg[NS];
     auto load_keys = [&](int key0) __attribute__((always_inline)) {
         const int lane = here(threadIdx.x & 63);
-        const bf16_t *src = u.k + (int64_t)(u.sq.vis_start + min(key0 + (lane & 31), u.sq.vis_len - 1)) * st.kv_t + 8 * (lane >> 5);
+        const bf16_t *src = u.k + (int64_t)(u.sq.vis_start + min(key0 + (lane & 31), key_hi - 1)) * st.kv_t + 8 * (lane >> 5);
 #pragma unroll
         for (int sl = 0; sl < NS; ++sl) kreg[sl] = *reinterpret_cast<const uint4 *>(src + 16 * sl);
     };
-    head_prefix(t, u.hrow0, u.G, s_pref);
-    u.R_total = s_pref[u.G];
-
+    const int count = rows_of_lane(t, u);
+    u.R_total = u.G * u.sq.win_len;
+    bool whole = true;
     for (int r0 = 0; r0 < u.R_total; r0 += kWinRows) {
-        const int rows_here = min(kWinRows, u.R_total - r0);
-        const int n_blk = (rows_here + 31) >> 5, tid = here(threadIdx.x);
-        if (tid < rows_here) {
-            const int rho = r0 + tid;
-            const int g = head_of_row(s_pref, u.G, rho);
-            const int place = g * u.W + (rho - s_pref[g]);
-            const int tok = t.elite_idx[u.hrow0 * u.W + place];
-            s_slot[tid] = place;
-            s_last[tid] = dm.vis_window ? prow0 + (rho - s_pref[g]) : u.sq.vis_len - 1;
-            s_query[tid] = (int)((unsigned)g << 27 | (unsigned)(tok - u.sq.win_start));
+        int rows_here = min(kWinRows, u.R_total - r0);
+        const int tid = here(threadIdx.x);
+        while (true) {
+            if (tid < rows_here) {
+                const int2 row = row_of(u, s_pref, whole, r0 + tid);
+                s_slot[tid] = row.x * u.W + row.y;
+                s_last[tid] = dm.vis_window ? prow0 + row.y : u.sq.vis_len - 1;
+                s_query[tid] = query_word(t, u, whole, row);
+            }
+            lds_barrier();
+            load_rows_lds<D>(u, st, s_query, s_rows, rows_here, (rows_here + 31) & ~31, wave);
+            if (!whole || __ballot(count != u.sq.win_len) == 0ull) break;
+            whole = false;
+            rows_wait_barrier();
+            head_prefix(t, u.hrow0, u.G, s_pref);
+            u.R_total = s_pref[u.G];
+            rows_here = min(kWinRows, u.R_total);
+            if (rows_here <= 0) return;
         }
-        lds_barrier();
-        load_rows_lds<D>(u, st, s_query, s_rows, rows_here, 32 * n_blk, wave);
+        const int n_blk = (rows_here + 31) >> 5;
+        if (tid < kWinRows) s_top[tid] = -(int)kFar;
         rows_wait_barrier();
         float ref[kBlocks1], sum[kBlocks1];  // of row 32 b + n
-#pragma unroll
-        for (int b = 0; b < kBlocks1; ++b) {
-            ref[b] = -kFar;
-            sum[b] = 0.f;
-        }
-        auto group = [&](int key0, auto masked) __attribute__((always_inline)) {
+        // the logits of the wave's keys and every block of rows, and what is done with them
+        auto logits = [&](int key0, auto masked, auto take) __attribute__((always_inline)) {
             asm volatile("" ::: "memory");  // the rows are read from LDS for every group: as values of the loop they would be spilled
             const int lane = here(threadIdx.x & 63), n = lane & 31, c = lane >> 5;
             int row_at[NS];  // the lane's 16 bytes of row n of a block
@@ -189,6 +224,42 @@ __global__ __launch_bounds__(kThreads, 4) void window_sums_kernel(Dims dm, DevTa
 #pragma unroll
                     for (int i = 0; i < 16; ++i) s[i] = 8 * (i >> 2) + (i & 3) > lim ? -INFINITY : s[i];  // key 8 (i / 4) + 4 c + i % 4
                 }
+                take(b, s);
+            }
+        };
+        constexpr float kFarRaw = kFar / kC;
+        // the largest of the lane's logits, as a reference
+        auto top_of = [&](const f32x16 &s, float &m) __attribute__((always_inline)) {
+            m = -kFarRaw;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) m = fmaxf(m, s[i]);
+            return rintf(fminf(m, kFarRaw) * kC);
+        };
+        auto for_keys = [&](int key0, auto take) __attribute__((always_inline)) {
+            if (key0 + kGroup > u.sq.vis_len || (dm.vis_window && key0 + kGroup > prow0 + 1)) logits(key0, std::true_type(), take);
+            else logits(key0, std::false_type(), take);
+        };
+        load_keys(key_first);
+        // The first reference of a row: its maximum over the first keys of all waves.  (Products are cheap here, a reference that
+        // turns out too low is not: the exponentials of its block are formed a second time.)  With up to two groups a wave it costs
+        // more than it saves, and a lane starts from the maximum of its own first keys: 28 x 8 x 8 units of 300 keys, 8 x 20 rows, 207
+        // us with shared references, 199 without; 28 x 16 x 4 units of 2304 keys, 7 x 32 rows, 751 and 773.
+        const bool shared_first = key_hi - run * run_keys > 2 * kGroup * kWaves;
+        if (shared_first && key_first < key_hi) {
+            for_keys(key_first, [&](int b, f32x16 &s) __attribute__((always_inline)) {
+                float m;
+                const float top = top_of(s, m);
+                atomicMax(&s_top[32 * b + (here(threadIdx.x) & 31)], (int)top);
+            });
+        }
+        lds_barrier();
+#pragma unroll
+        for (int b = 0; b < kBlocks1; ++b) {
+            ref[b] = (float)s_top[32 * b + (tid & 31)];
+            sum[b] = 0.f;
+        }
+        for (int key0 = key_first; key0 < key_hi; key0 += kGroup * kWaves) {
+            for_keys(key0, [&](int b, f32x16 &s) __attribute__((always_inline)) {
                 auto exps = [&](float r) __attribute__((always_inline)) {
                     f32x4 z;
 #pragma unroll
@@ -198,63 +269,50 @@ __global__ __launch_bounds__(kThreads, 4) void window_sums_kernel(Dims dm, DevTa
                     }
                     return (z[0] + z[1]) + (z[2] + z[3]);
                 };
-                float z = kSumLimit;  // a wave's first keys: no reference yet, whatever the exponentials above the lowest one are
-                if (key0 != key_first) z = exps(ref[b]);
+                float z = kSumLimit;  // no reference yet: whatever the exponentials above the lowest one are
+                if (shared_first || key0 != key_first) z = exps(ref[b]);
                 if (__ballot(z >= kSumLimit) != 0ull) {
                     // the lane's reference becomes its largest logit, if that lies above; logits above the bound are held at it
-                    constexpr float kFarRaw = kFar / kC;
-                    float m = -kFarRaw;
+                    float m;
+                    const float up = fmaxf(ref[b], top_of(s, m));
+                    if (__ballot(m > kFarRaw) != 0ull) {
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) {
-                        m = fmaxf(m, s[i]);
-                        s[i] = s[i] > kFarRaw ? kFarRaw : s[i];
+                        for (int i = 0; i < 16; ++i) s[i] = s[i] > kFarRaw ? kFarRaw : s[i];
                     }
-                    const float up = fmaxf(ref[b], rintf(fminf(m, kFarRaw) * kC));
                     sum[b] = ldexpf(sum[b], (int)(ref[b] - up));
                     ref[b] = up;
                     z = exps(up);
                 }
                 sum[b] += z;
-            }
-            if (key0 + kGroup * kWaves < key_hi) load_keys(key0 + kGroup * kWaves);
-        };
-        load_keys(key_first);
-        for (int key0 = key_first; key0 < key_hi; key0 += kGroup * kWaves) {
-            if (key0 + kGroup > u.sq.vis_len || (dm.vis_window && key0 + kGroup > prow0 + 1)) group(key0, std::true_type());
-            else group(key0, std::false_type());
+            });
+            load_keys(key0 + kGroup * kWaves);  // (the last key again where there are none)
         }
-        // one (reference, sum) per row: over the two lanes that share it, then over the waves (waves 4-7 leave theirs,
-        // waves 0-3 add their own, a thread per row adds the four).  (A lane or wave without a term has the lowest reference.)
+        // one (reference, sum) per row: over the two lanes that share it, then over the waves, a thread per row.  (A lane or wave without a term has the lowest reference.)
         auto merge = [](float &M, float &z, float m2, float z2) __attribute__((always_inline)) {
             const float top = fmaxf(M, m2);
             z = ldexpf(z, (int)(M - top)) + ldexpf(z2, (int)(m2 - top));
             M = top;
         };
+        lds_barrier();  // the rows have been read: their place holds the waves' references and sums
+        float2(*s_part)[kWinRows] = reinterpret_cast<float2(*)[kWinRows]>(s_rows);
         const int lane = tid & 63;
 #pragma unroll
         for (int b = 0; b < kBlocks1; ++b) {
             if (b >= n_blk) break;
-            merge(ref[b], sum[b], __shfl_xor(ref[b], 32, 64), __shfl_xor(sum[b], 32, 64));
-            if (wave >= kWaves / 2 && lane < 32) s_part[wave - kWaves / 2][32 * b + lane] = make_float2(ref[b], sum[b]);
-        }
-        lds_barrier();
-        if (wave < kWaves / 2 && lane < 32) {
-#pragma unroll
-            for (int b = 0; b < kBlocks1; ++b) {
-                if (b >= n_blk) break;
-                const float2 x = s_part[wave][32 * b + lane];
-                merge(ref[b], sum[b], x.x, x.y);
-                s_part[wave][32 * b + lane] = make_float2(ref[b], sum[b]);
-            }
+            const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(ref[b]), __float_as_uint(ref[b]), false, false);
+            const auto z = __builtin_amdgcn_permlane32_swap(__float_as_uint(sum[b]), __float_as_uint(sum[b]), false, false);
+            float M = __uint_as_float(r[0]), Z = __uint_as_float(z[0]);
+            merge(M, Z, __uint_as_float(r[1]), __uint_as_float(z[1]));
+            if (lane < 32) s_part[wave][32 * b + lane] = make_float2(M, Z);
         }
         lds_barrier();
         if (tid < rows_here) {
             float2 x = s_part[0][tid];
 #pragma unroll
-            for (int w = 1; w < kWaves / 2; ++w) merge(x.x, x.y, s_part[w][tid].x, s_part[w][tid].y);
+            for (int w = 1; w < kWaves; ++w) merge(x.x, x.y, s_part[w][tid].x, s_part[w][tid].y);
             // (the sum goes out as a fraction of 1 to 2: pass 2 takes the largest reference of a row, which its terms then stay below)
             const int up = x.y > 0.f && x.y < INFINITY ? ilogb_of(x.y) : 0;
-            t.part[(u.hrow0 * u.W + s_slot[tid]) * dm.n_chunks + run] =
+            unit_parts(dm, t, u)[(int64_t)run * u.G * u.W + s_slot[tid]] =
                 make_float2(x.y > 0.f ? x.x + (float)up : -INFINITY, ldexpf(x.y, -up));
         }
         lds_barrier();  // the partials have been read: the next group of rows may come
@@ -288,32 +346,49 @@ __global__ __launch_bounds__(kThreads, 4) void window_scores_kernel(Dims dm, Dev
     const int key_hi = min(key_lo + part_keys, dm.vis_window ? prow0 + u.sq.win_len : u.sq.vis_len);
     uint4 kreg[T][NS];  // the keys of the wave's next group
     if (tid == 0) s_any_far = 0;
-    head_prefix(t, u.hrow0, u.G, s_pref);
-    u.R_total = s_pref[u.G];
-    for (int i = tid; i < part_keys; i += kThreads) s_imp[i] = 0.f;
+    const int count = rows_of_lane(t, u);
+    u.R_total = u.G * u.sq.win_len;
+    bool whole = true;
     for (int r0 = 0; r0 < u.R_total; r0 += kWinRows) {
-        const int rows_here = min(kWinRows, u.R_total - r0);
-        const int n_blk = (rows_here + 15) >> 4, tid = here(threadIdx.x);
-        if (tid < rows_here) {
-            const int rho = r0 + tid, g = head_of_row(s_pref, u.G, rho);
-            const int tok = t.elite_idx[(u.hrow0 + g) * u.W + (rho - s_pref[g])];
-            s_query[tid] = (int)((unsigned)g << 27 | (unsigned)(tok - u.sq.win_start));
+        int rows_here = min(kWinRows, u.R_total - r0);
+        const int tid = here(threadIdx.x);
+        int2 row = make_int2(0, 0);  // of the thread
+        while (true) {
+            if (tid < rows_here) {
+                row = row_of(u, s_pref, whole, r0 + tid);
+                s_query[tid] = query_word(t, u, whole, row);
+            }
+            lds_barrier();
+            load_rows_lds<D>(u, st, s_query, s_rows, rows_here, (rows_here + 15) & ~15, wave);
+            if (!whole || __ballot(count != u.sq.win_len) == 0ull) break;
+            whole = false;
+            rows_wait_barrier();
+            head_prefix(t, u.hrow0, u.G, s_pref);
+            u.R_total = s_pref[u.G];
+            rows_here = min(kWinRows, u.R_total);
+            if (rows_here <= 0) break;
         }
-        lds_barrier();
-        load_rows_lds<D>(u, st, s_query, s_rows, rows_here, 16 * n_blk, wave);
+        if (r0 == 0)
+            for (int i = tid; i < part_keys; i += kThreads) s_imp[i] = 0.f;
+        if (rows_here <= 0) {  // no row: the scores are zero
+            lds_barrier();
+            break;
+        }
+        const int n_blk = (rows_here + 15) >> 4;
         if (tid < 16 * n_blk) {  // maximum, normaliser, weight
             float M = -INFINITY, w = 0.f;
-            const int tid = here(threadIdx.x), rho = r0 + min(tid, rows_here - 1), g = head_of_row(s_pref, u.G, rho);
+            const int tid = here(threadIdx.x);
             if (tid < rows_here) {
-                const int64_t slot = (u.hrow0 + g) * u.W + (rho - s_pref[g]);
-                const float2 *part = t.part + slot * dm.n_chunks;
+                const int place = row.x * u.W + row.y;
+                const int64_t slot = u.hrow0 * u.W + place, stride = (int64_t)u.G * u.W;
+                const float2 *part = unit_parts(dm, t, u) + place;
                 const float mt = t.row_mtext[slot], zt = t.row_ztext[slot];  // of raw logits
-                constexpr int kAtOnce = 16;  // partials requested together (a load for every one of them: rows lie far apart)
+                constexpr int kAtOnce = 16;  // partials requested together
                 float2 x[kAtOnce];
 #pragma unroll
                 for (int s = 0; s < kAtOnce; ++s) {
                     x[s] = make_float2(-INFINITY, 0.f);
-                    if (s < n_seg) x[s] = part[s];
+                    if (s < n_seg) x[s] = part[s * stride];
                 }
                 M = mt > -INFINITY ? rintf(held<D>(mt) * kC) : -INFINITY;
 #pragma unroll
@@ -323,7 +398,7 @@ __global__ __launch_bounds__(kThreads, 4) void window_scores_kernel(Dims dm, Dev
                 for (int s0 = kAtOnce; s0 < n_seg; s0 += kMore) {
                     float y[kMore];
 #pragma unroll
-                    for (int s = 0; s < kMore; ++s) y[s] = part[min(s0 + s, n_seg - 1)].x;
+                    for (int s = 0; s < kMore; ++s) y[s] = part[min(s0 + s, n_seg - 1) * stride].x;
 #pragma unroll
                     for (int s = 0; s < kMore; ++s) M = fmaxf(M, y[s]);
                 }
@@ -334,19 +409,19 @@ __global__ __launch_bounds__(kThreads, 4) void window_scores_kernel(Dims dm, Dev
                 for (int s0 = kAtOnce; s0 < n_seg; s0 += kMore) {
                     float2 y[kMore];
 #pragma unroll
-                    for (int s = 0; s < kMore; ++s) y[s] = part[min(s0 + s, n_seg - 1)];
+                    for (int s = 0; s < kMore; ++s) y[s] = part[min(s0 + s, n_seg - 1) * stride];
 #pragma unroll
                     for (int s = 0; s < kMore; ++s) Z += s0 + s < n_seg && y[s].y > 0.f ? (double)ldexpf(y[s].y, (int)(y[s].x - M)) : 0.0;
                 }
                 if (zt > 0.f) Z += (double)(zt * __builtin_amdgcn_exp2f(fmaf(held<D>(mt), kC, -M)));
                 if (fabsf(M) > 0.5f * kFar && M > -INFINITY) s_any_far = 1;
-                w = !(Z <= 0.0) ? (float)(1.0 / ((double)(s_pref[g + 1] - s_pref[g]) * (double)u.G * Z)) : 0.f;
+                w = !(Z <= 0.0) ? (float)(1.0 / ((double)(whole ? u.sq.win_len : s_pref[row.x + 1] - s_pref[row.x]) * (double)u.G * Z)) : 0.f;
                 if (!(Z > 0.0)) M = 0.f;  // a row that sees no key but far ones weighs nothing
             }
             s_M[tid] = tid < rows_here ? M : 0.f;
             s_ref[tid] = fabsf(M) > 0.5f * kFar ? -INFINITY : -M;  // (so does a row past the list)
             s_w[tid] = w;
-            s_last[tid] = dm.vis_window ? prow0 + (rho - s_pref[g]) : u.sq.vis_len - 1;
+            s_last[tid] = dm.vis_window && tid < rows_here ? prow0 + row.y : u.sq.vis_len - 1;
         }
         rows_wait_barrier();
         group_keys<T, NS>(u, st, key_lo + kGroup * wave, kreg);
@@ -450,10 +525,11 @@ static int part_keys(const Dims &dm, int64_t units, int most, int extra) {
 
 hipError_t launch_score_window(hipStream_t s, const Dims &dm, const DevTables &t, int pass, int l0, int nl, const LaunchLayers &ll,
                                const air_strides &st, const SeqArgs &seqs) {
+    // (Runs as long as parts: 7290 keys, 28 x 4 units, pass 1 70 us with 1856 keys a run, 78 with 832.)
     // A run of pass 1 decides references and partial sums, so it follows from the context alone, not from the layers of the call:
     // the scores are the same bits however the layers are cut into calls and launches.  Pass 2 leaves whole sums of a
     // key and the unit's statistics from whole units: its parts follow the launch.
-    const int run = part_keys(dm, (int64_t)dm.L * dm.B * dm.Hkv, 1024, 4);
+    const int run = part_keys(dm, (int64_t)dm.L * dm.B * dm.Hkv, kPartMost, 8);
     const int part = pass == 1 ? run : part_keys(dm, (int64_t)nl * dm.B * dm.Hkv, kPartMost, 8);
     const dim3 grid((dm.max_vis + part - 1) / part, dm.Hkv, nl * dm.B), block(kThreads);
     if (dm.D == 128) {

@@ -231,3 +231,31 @@ def test_skewness_of_rows_with_little_or_no_spread(n_vis, visual, d):
             np.testing.assert_allclose(s_k[b, l], O.skewness(got[l][b, 0].astype(np.float64)), rtol=1e-7, atol=1e-7)
             if l in (1, 2) and not visual:  # (rows of a visual window do not see its last keys: their scores are smaller)
                 assert s_k[b, l] == 0.0 and O.skewness(want) == 0.0
+
+
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("G,window,lost", [(7, 32, (3, 31)), (2, 20, (0,)), (8, 40, (17, 18, 39))])  # one and two rounds of 256 rows
+def test_text_keys_that_are_no_numbers_leave_the_window(d, G, window, lost):
+    # Eq.5 with a threshold of 0 takes every candidate whose logit is a number: the rows of the group are then fewer than the window
+    # has tokens, and come from the lists.
+    import torch
+
+    p = _Prompt(2, 1, 2, G, d, 1300, window + 5, window)
+    s = p.seqs[0]
+    for j in lost:
+        p.k[1][0, 1, s.win_start + j] = float("nan")
+    ac = p.context()
+    got = p.score(ac)
+    cnt, _ = ac.air_get_elite(1)
+    ac.close()
+    assert cnt[0].tolist() == [window] * G + [window - len(lost)] * G
+    rows = [j for j in range(window) if j not in lost]
+    k = p.k[1][0, 1].double()
+    want = torch.zeros(s.vis_len, dtype=torch.float64, device=k.device)
+    for g in range(G):
+        q = p.q[1][0, G + g, s.win_start - s.vis_start - s.vis_len:].double()[rows]
+        keys = torch.cat([k[s.vis_start:s.vis_start + s.vis_len], k[s.win_start:s.win_start + window][rows]])
+        want += torch.softmax(q @ keys.T / math.sqrt(d), dim=1)[:, :s.vis_len].mean(dim=0) / G
+    np.testing.assert_allclose(got[1][0, 1], want.cpu().numpy(), rtol=P.SCORE_RTOL, atol=P.SCORE_ATOL)
+    for l, h in [(0, 0), (0, 1), (1, 0)]:
+        np.testing.assert_allclose(got[l][0, h], p.oracle(l, 0, h), rtol=P.SCORE_RTOL, atol=P.SCORE_ATOL)
