@@ -1,19 +1,17 @@
-// air_score, fp32: window logits and importance (Eq.6-8) on the vector unit, a thread per visual key.
+// air_score, fp32: window logits and importance (Eq.6-8) on the fp32 matrix unit (air_tile.h), full fp32 products and sums.
 //
-// A logit is one chain of fp32 fused multiply-adds over the head's elements in their order, then one multiplication by
-// 1/sqrt(d).  (The fp32 matrix instructions have the same peak rate, add in another order, and would spend half of their
-// rows on padding: a unit has 7-10 window rows.)
-//
-//   score_stream_f32  reads K_v once.  Per (row, 256-key chunk) it leaves the maximum and the sum-exp; units of at most
-//                     kStashRows rows stash their logits.
+//   score_stream_f32  reads K_v once, whatever the number of rows.  Per (row, 256-key chunk) it leaves the maximum and the
+//                     sum-exp; units of at most kStashRows rows stash their logits.
 //   score_finish_f32  row maximum, fp64 normaliser and weight of every row from the chunk partials, then
-//                     I[key] = sum over the rows, in list order, of w exp(s - M), from the stash or from K_v again; the
-//                     moments, statistics and the allocation as in the bf16 path.
+//                     I[key] = sum over the rows of w exp(s - M), from the stash or from K_v again, by the products of the first
+//                     pass and in the same order; the moments, statistics and the allocation as in the bf16 path.
 //
-// Keys reach the threads through LDS: a wave reads 128-byte slices of its 64 keys, eight lanes to a key, and a lane then
-// picks up its own key's slice.  (One whole row per lane straight from global memory touches 64 lines with every
-// instruction and fetches each line eight times: 28 layers of 2304 keys with heads of 128 elements took 85 + 53 us for
-// the two passes, 41 + 24 us this way, with the rows' parameters, the statistics and the allocation in the second.)
+// A wave keeps its 32 keys in registers as matrix operands, straight from global memory (64-byte segments, all requested in front
+// of the row lists), blocks of 16 window rows are the other operand.  Bound: HBM and, with the two rounds of workgroups of 2304 keys
+// in 28 x 4 units, the row lists and rows that arrive behind the keys; the products of a block take 1024 clocks a tile of 16 keys, half
+// of them for padding with the usual 7 to 10 rows.  First pass on that shape, heads of 128 elements: 35.6 us (132 MB, 3.7 TB/s); with a thread
+// per key on the vector unit, keys and query rows through LDS (20 us of LDS time for the rows alone), 41.5; four waves of 64 keys 35.9,
+// three workgroups of them a CU 45.3.  Two layers x 2 heads of 576 keys of 64 elements: 6.6 and 8.2.
 #include "air_device.h"
 #include "air_internal.h"
 #include "air_score_dev.h"
@@ -21,8 +19,8 @@
 
 namespace air {
 
-constexpr int kGroupRows = 32;  // window rows whose logits a thread holds at a time
-constexpr int kSliceElems = 32; // elements of a key staged at a time: 128 bytes
+constexpr int kStreamWaves = 8;  // of the first pass: 32 keys a wave
+constexpr int kGroupRows = 32;  // window rows whose tables are staged at a time
 static_assert(kGroupRows * 8 == 256, "eight lanes to a row of the group");
 static_assert(kGroupRows == kStashRows, "a unit with a stash has one group of rows");
 
@@ -48,10 +46,7 @@ __device__ __forceinline__ void unit_of(const Dims &dm, const SeqArgs &seqs, int
     u.unit = ((int64_t)u.l * dm.B + u.b) * dm.Hkv + u.kvh;
 }
 
-template <int D>
 struct F32Lds {
-    __align__(16) float q[kGroupRows][D];                    // query rows of the group, read as broadcasts
-    __align__(16) float key[4][64][kSliceElems + 4];         // per wave: a slice of its 64 keys
     int pref[17], row[kGroupRows], head[kGroupRows], lim[kGroupRows];  // of a row: its place in the query tensor, head of the group, last visual index it sees
     int64_t slot[kGroupRows];                                // place of the row in the per-row tables
 };
@@ -65,14 +60,12 @@ __device__ __forceinline__ void row_prefix(const DevTables &t, int64_t hrow0, in
         }
         pref[G] = run;
     }
-    __syncthreads();
+    lds_barrier();
 }
 
-// table places (and, with QUERIES, the query rows) of list rows r0 .. r0 + nb of the unit
-template <int D, bool QUERIES>
-__device__ __forceinline__ void stage_rows(const Dims &dm, const DevTables &t, const F32Unit &u, const air_strides &st, int r0, int nb,
-                                           F32Lds<D> &s) {
-    __syncthreads();  // the group before has been used
+// tables of list rows r0 .. r0 + nb of the unit
+__device__ __forceinline__ void stage_rows(const Dims &dm, const DevTables &t, const F32Unit &u, int r0, int nb, F32Lds &s) {
+    lds_barrier();  // the group before has been used
     const int tid = threadIdx.x;
     if (tid < nb) {
         int g = 0;
@@ -83,120 +76,116 @@ __device__ __forceinline__ void stage_rows(const Dims &dm, const DevTables &t, c
         s.head[tid] = g;
         s.lim[tid] = dm.vis_window ? tok - u.sq.vis_start : 0x7fffffff;
     }
-    __syncthreads();
-    if (!QUERIES) return;
-    for (int p = tid; p < nb * (D / 4); p += 256) {
-        const int r = p / (D / 4), c = 4 * (p % (D / 4));
-        *reinterpret_cast<f32x4 *>(&s.q[r][c]) =
-            *reinterpret_cast<const f32x4 *>(u.q + (int64_t)(u.kvh * dm.G + s.head[r]) * st.q_h + (int64_t)s.row[r] * st.q_t + c);
-    }
-    __syncthreads();
+    lds_barrier();
 }
 
-// logits of the nb staged rows against key i = chunk * 256 + tid (keys past the end repeat the last one)
-template <int D>
-__device__ __forceinline__ void logits(const F32Unit &u, const air_strides &st, int chunk, int nb, F32Lds<D> &s,
-                                       float (&a)[kGroupRows]) {
-    constexpr int kSlices = D / kSliceElems, kPer = kSliceElems / 4;  // 16-byte pieces of a slice
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int key0 = chunk * kChunkKeys + wave * 64;
-    f32x4 next[kPer];
-    auto fetch = [&](int sl) __attribute__((always_inline)) {
+// the wave's 64 keys of a chunk as matrix operands, lane (n, c) the c-th quarter of every slice of key n of a tile (keys past the
+// end repeat the last one)
+template <int D, int TILES>
+__device__ __forceinline__ void keys_of(const F32Unit &u, const air_strides &st, int chunk, uint4 (&k)[TILES][D / 16]) {
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n = lane & 15, c = lane >> 4;
 #pragma unroll
-        for (int it = 0; it < kPer; ++it) {
-            const int key = min(key0 + (lane >> 3) + 8 * it, u.sq.vis_len - 1);
-            next[it] = *reinterpret_cast<const f32x4 *>(u.k + (int64_t)(u.sq.vis_start + key) * st.kv_t + kSliceElems * sl + 4 * (lane & 7));
-        }
-    };
+    for (int tile = 0; tile < TILES; ++tile) {
+        const int key = min(chunk * kChunkKeys + 16 * TILES * wave + 16 * tile + n, u.sq.vis_len - 1);
+        const float *src = u.k + (int64_t)(u.sq.vis_start + key) * st.kv_t + 4 * c;
 #pragma unroll
-    for (int r = 0; r < kGroupRows; ++r) a[r] = 0.f;
-    fetch(0);
-    for (int sl = 0; sl < kSlices; ++sl) {
+        for (int sl = 0; sl < D / 16; ++sl) k[tile][sl] = *reinterpret_cast<const uint4 *>(src + 16 * sl);
+    }
+}
+
+// Logits of the staged rows rb .. rb + 15 against those keys: lane (n, c) gets rows rb + 4 i + c of key n of every tile.  (Operand row
+// 4 c + i carries staged row 4 i + c, so that all lanes are done after (nb - rb + 3) / 4 values.)
+template <int D, int TILES>
+__device__ __forceinline__ void logits(const Dims &dm, const F32Unit &u, const air_strides &st, const F32Lds &s, int rb, int nb,
+                                       const uint4 (&k)[TILES][D / 16], f32x4 (&a)[TILES]) {
+    const int lane = threadIdx.x & 63, n = lane & 15, c = lane >> 4;
+    const int r = rb + 4 * (n & 3) + (n >> 2);
+    const float *src = u.q + (int64_t)(u.kvh * dm.G + s.head[min(r, nb - 1)]) * st.q_h + (int64_t)s.row[min(r, nb - 1)] * st.q_t + 4 * c;
+    uint4 q[D / 16];
 #pragma unroll
-        for (int it = 0; it < kPer; ++it) *reinterpret_cast<f32x4 *>(&s.key[wave][(lane >> 3) + 8 * it][4 * (lane & 7)]) = next[it];
-        if (sl + 1 < kSlices) fetch(sl + 1);
-        // a wave uses its own part of the LDS only: its accesses complete in order, no barrier
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        f32x4 k[kPer];
+    for (int sl = 0; sl < D / 16; ++sl) q[sl] = *reinterpret_cast<const uint4 *>(src + 16 * sl);
 #pragma unroll
-        for (int c = 0; c < kPer; ++c) k[c] = *reinterpret_cast<const f32x4 *>(&s.key[wave][lane][4 * c]);
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    for (int tile = 0; tile < TILES; ++tile) a[tile] = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int rb = 0; rb < kGroupRows; rb += 4) {
-            if (rb >= nb) break;  // rows past the list hold whatever was there: their logits are never used
+    for (int sl = 0; sl < D / 16; ++sl) {
 #pragma unroll
-            for (int c = 0; c < kPer; ++c) {
-#pragma unroll
-                for (int r = rb; r < rb + 4; ++r) {
-                    const f32x4 q = *reinterpret_cast<const f32x4 *>(&s.q[r][kSliceElems * sl + 4 * c]);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) a[r] = fmaf(q[e], k[c][e], a[r]);
-                }
-            }
-        }
+        for (int tile = 0; tile < TILES; ++tile) a[tile] = mma<float>(q[sl], k[tile][sl], a[tile]);
     }
     {
 #pragma clang fp contract(off)  // the scaled logit is rounded (it may be stashed): not fused into what follows
         const float scale = 1.0f / sqrtf((float)D);
 #pragma unroll
-        for (int r = 0; r < kGroupRows; ++r) a[r] *= scale;
+        for (int tile = 0; tile < TILES; ++tile)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) a[tile][i] *= scale;
     }
 }
 
 template <int D>
-__global__ __launch_bounds__(256) void score_stream_f32(Dims dm, DevTables t, int l0, LaunchLayers ll, air_strides st, SeqArgs seqs) {
-    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+__global__ __launch_bounds__(64 * kStreamWaves, 4) void score_stream_f32(Dims dm, DevTables t, int l0, LaunchLayers ll, air_strides st, SeqArgs seqs) {
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, n = lane & 15, c = lane >> 4;
     F32Unit u;
     unit_of(dm, seqs, l0, ll, st, u);
     const int chunk = blockIdx.x;
     if (chunk >= u.nch) return;
-    __shared__ F32Lds<D> s;
-    __shared__ float s_red[kGroupRows][4];
+    __shared__ F32Lds s;
+    __shared__ float s_m[kStreamWaves][16], s_z[kStreamWaves][16];
+    constexpr int T = 16 / kStreamWaves;  // tiles of a wave
+    uint4 k[T][D / 16];
+    keys_of<D, T>(u, st, chunk, k);
     row_prefix(t, u.hrow0, dm.G, s.pref);
     const int R_total = s.pref[dm.G];
     const bool stash = R_total <= dm.stash_rows;
-    const int i = chunk * kChunkKeys + tid;
-    const bool valid = i < u.sq.vis_len;
-    float *stash_base = t.stash + ((u.unit * dm.n_chunks + chunk) * (int64_t)kStashRows) * kChunkKeys;
+    auto over_waves = [&](const float(&x)[kStreamWaves][16], int r, auto op) {
+        float v = x[0][r];
+#pragma unroll
+        for (int w = 1; w < kStreamWaves; ++w) v = op(v, x[w][r]);
+        return v;
+    };
+    const int key0 = 16 * T * wave + n;  // of the lane's first tile, within the chunk
+    float *stash_base = t.stash + ((u.unit * dm.n_chunks + chunk) * (int64_t)kStashRows) * kChunkKeys + key0;
     for (int r0 = 0; r0 < R_total; r0 += kGroupRows) {
         const int nb = min(kGroupRows, R_total - r0);
-        stage_rows<D, true>(dm, t, u, st, r0, nb, s);
-        float a[kGroupRows];
-        logits<D>(u, st, chunk, nb, s, a);
-        if (stash) {
+        stage_rows(dm, t, u, r0, nb, s);
+        for (int rb = 0; rb < nb; rb += 16) {
+            f32x4 a[T];
+            logits<D, T>(dm, u, st, s, rb, nb, k, a);
+            const int n_i = min(4, (nb - rb + 3) >> 2);  // live values of i (uniform over the workgroup)
+            int lim[4];  // last key of the chunk that row i sees, relative to the lane's first
 #pragma unroll
-            for (int r = 0; r < kGroupRows; ++r)
-                if (r < nb) stash_base[r * kChunkKeys + tid] = a[r];
-        }
+            for (int i = 0; i < 4; ++i) lim[i] = min(s.lim[min(rb + 4 * i + c, nb - 1)], u.sq.vis_len - 1) - chunk * kChunkKeys - key0;
 #pragma unroll
-        for (int r = 0; r < kGroupRows; ++r) {
-            if (r >= nb) break;
-            const float m = wave_max(valid && i <= s.lim[r] ? a[r] : -INFINITY);
-            if (lane == 0) s_red[r][wave] = m;
-        }
-        __syncthreads();
-        float mrow = 0.f;  // of row tid, for the entry
-        if (tid < nb) mrow = fmaxf(fmaxf(s_red[tid][0], s_red[tid][1]), fmaxf(s_red[tid][2], s_red[tid][3]));
+            for (int i = 0; i < 4; ++i) {
+                if (i >= n_i) continue;
+                const int r = 4 * i + c;
+                float m = -INFINITY;
 #pragma unroll
-        for (int r = 0; r < kGroupRows; ++r) {
-            if (r >= nb) break;
-            const float m = fmaxf(fmaxf(s_red[r][0], s_red[r][1]), fmaxf(s_red[r][2], s_red[r][3]));
-            a[r] = wave_sum(valid && i <= s.lim[r] ? expf(a[r] - m) : 0.f);
-        }
-        __syncthreads();
+                for (int tile = 0; tile < T; ++tile) {
+                    if (stash && rb + r < nb) stash_base[(rb + r) * kChunkKeys + 16 * tile] = a[tile][i];
+                    m = fmaxf(m, 16 * tile <= lim[i] ? a[tile][i] : -INFINITY);
+                }
+                m = max16(m);
+                if (n == 0) s_m[wave][r] = m;
+            }
+            lds_barrier();
 #pragma unroll
-        for (int r = 0; r < kGroupRows; ++r) {
-            if (r >= nb) break;
-            if (lane == 0) s_red[r][wave] = a[r];
-        }
-        __syncthreads();
-        if (tid < nb) {
-            const float z = (s_red[tid][0] + s_red[tid][1]) + (s_red[tid][2] + s_red[tid][3]);
-            t.part[s.slot[tid] * dm.n_chunks + chunk] = make_float2(mrow, z);
+            for (int i = 0; i < 4; ++i) {
+                if (i >= n_i) continue;
+                const int r = 4 * i + c;
+                const float m = over_waves(s_m, r, [](float x, float y) { return fmaxf(x, y); });
+                float z = 0.f;
+#pragma unroll
+                for (int tile = 0; tile < T; ++tile) z += 16 * tile <= lim[i] ? expf(a[tile][i] - m) : 0.f;
+                z = sum16(z);
+                if (n == 0) s_z[wave][r] = z;
+            }
+            lds_barrier();
+            if (tid < 16 && rb + tid < nb) {
+                const float m = over_waves(s_m, tid, [](float x, float y) { return fmaxf(x, y); });
+                const float z = over_waves(s_z, tid, [](float x, float y) { return x + y; });
+                t.part[s.slot[rb + tid] * dm.n_chunks + chunk] = make_float2(m, z);
+            }
+            lds_barrier();  // the maxima have been read
         }
     }
 }
@@ -209,7 +198,7 @@ __global__ __launch_bounds__(256) void score_finish_f32(Dims dm, DevTables t, in
     const int first = (int)blockIdx.x * kFinishChunks;
     if (first >= u.nch) return;
     const int last = min(u.nch, first + kFinishChunks);
-    __shared__ F32Lds<D> s;
+    __shared__ F32Lds s;
     __shared__ float s_M[kGroupRows], s_w[kGroupRows];
     __shared__ double s_mom[4][3];
     row_prefix(t, u.hrow0, dm.G, s.pref);
@@ -218,8 +207,7 @@ __global__ __launch_bounds__(256) void score_finish_f32(Dims dm, DevTables t, in
     float imp[kFinishChunks] = {0.f, 0.f, 0.f, 0.f};
     for (int r0 = 0; r0 < R_total; r0 += kGroupRows) {
         const int nb = min(kGroupRows, R_total - r0);
-        if (stash) stage_rows<D, false>(dm, t, u, st, r0, nb, s);
-        else stage_rows<D, true>(dm, t, u, st, r0, nb, s);
+        stage_rows(dm, t, u, r0, nb, s);
         // Row maximum over the chunks and the elite-text columns, normaliser in fp64, weight: eight lanes to a row, all rows of
         // the group at once; the text columns are the item in front of the chunks.  (Sixteen lanes in two rounds, and the
         // stash read chunk by chunk below: 13.1 us for the kernel on the tiny workload, where it is all latency, 24.5 on 112
@@ -247,9 +235,10 @@ __global__ __launch_bounds__(256) void score_finish_f32(Dims dm, DevTables t, in
                 s_w[r] = (float)(1.0 / ((double)(s.pref[g + 1] - s.pref[g]) * (double)dm.G * Z));
             }
         }
-        __syncthreads();
+        lds_barrier();
         if (stash) {
             const float *sb = t.stash + ((u.unit * dm.n_chunks + first) * (int64_t)kStashRows) * kChunkKeys + tid;
+            float acc[kFinishChunks][4] = {};  // rows by their number modulo 4, as in the products' lane groups below
             for (int rb = 0; rb < nb; rb += 8) {
                 float a[kFinishChunks][8];
 #pragma unroll
@@ -262,19 +251,41 @@ __global__ __launch_bounds__(256) void score_finish_f32(Dims dm, DevTables t, in
                     const int i = (first + ci) * kChunkKeys + tid;
 #pragma unroll
                     for (int r = 0; r < 8; ++r)
-                        if (rb + r < nb && i <= s.lim[rb + r]) imp[ci] = fmaf(s_w[rb + r], expf(a[ci][r] - s_M[rb + r]), imp[ci]);
+                        if (rb + r < nb && i <= s.lim[rb + r])
+                            acc[ci][r & 3] = fmaf(s_w[rb + r], expf(a[ci][r] - s_M[rb + r]), acc[ci][r & 3]);
                 }
             }
+#pragma unroll
+            for (int ci = 0; ci < kFinishChunks; ++ci) imp[ci] += (acc[ci][0] + acc[ci][1]) + (acc[ci][2] + acc[ci][3]);
         } else {
-            float a[kGroupRows];
+            const int lane = tid & 63, c = lane >> 4;
 #pragma unroll
             for (int ci = 0; ci < kFinishChunks; ++ci) {
                 if (first + ci >= last) break;
-                logits<D>(u, st, first + ci, nb, s, a);
-                const int i = (first + ci) * kChunkKeys + tid;
+                uint4 k[4][D / 16];
+                keys_of<D, 4>(u, st, first + ci, k);
+                const int key0 = (first + ci) * kChunkKeys + (tid & ~63) + (lane & 15);
+                float acc[4] = {0.f, 0.f, 0.f, 0.f};  // rows of the lane, key of every tile
+                for (int rb = 0; rb < nb; rb += 16) {
+                    f32x4 a[4];
+                    logits<D, 4>(dm, u, st, s, rb, nb, k, a);
 #pragma unroll
-                for (int r = 0; r < kGroupRows; ++r)
-                    if (r < nb && i <= s.lim[r]) imp[ci] = fmaf(s_w[r], expf(a[r] - s_M[r]), imp[ci]);
+                    for (int i = 0; i < 4; ++i) {
+                        const int r = rb + 4 * i + c;
+                        if (r >= nb) continue;
+#pragma unroll
+                        for (int tile = 0; tile < 4; ++tile)
+                            if (key0 + 16 * tile <= s.lim[r]) acc[tile] = fmaf(s_w[r], expf(a[tile][i] - s_M[r]), acc[tile]);
+                    }
+                }
+                // over the rows of the four lane groups; lane (n, c) keeps key 16 c + n, the thread's own
+#pragma unroll
+                for (int tile = 0; tile < 4; ++tile) {
+                    float v = acc[tile];
+                    v += __shfl_xor(v, 16, 64);
+                    v += __shfl_xor(v, 32, 64);
+                    if (c == tile) imp[ci] += v;
+                }
             }
         }
     }
@@ -293,8 +304,8 @@ hipError_t launch_score_f32(hipStream_t s, const Dims &dm, const DevTables &t, i
                             const air_strides &st, const SeqArgs &seqs) {
     const dim3 stream_grid(dm.n_chunks, dm.Hkv, nl * dm.B), finish_grid(dm.n_entries, dm.Hkv, nl * dm.B);
     if (pass == 1) {
-        if (dm.D == 128) hipLaunchKernelGGL(score_stream_f32<128>, stream_grid, dim3(256), 0, s, dm, t, l0, ll, st, seqs);
-        else hipLaunchKernelGGL(score_stream_f32<64>, stream_grid, dim3(256), 0, s, dm, t, l0, ll, st, seqs);
+        if (dm.D == 128) hipLaunchKernelGGL(score_stream_f32<128>, stream_grid, dim3(64 * kStreamWaves), 0, s, dm, t, l0, ll, st, seqs);
+        else hipLaunchKernelGGL(score_stream_f32<64>, stream_grid, dim3(64 * kStreamWaves), 0, s, dm, t, l0, ll, st, seqs);
     } else {
         if (dm.D == 128) hipLaunchKernelGGL(score_finish_f32<128>, finish_grid, dim3(256), 0, s, dm, t, l0, ll, st, seqs);
         else hipLaunchKernelGGL(score_finish_f32<64>, finish_grid, dim3(256), 0, s, dm, t, l0, ll, st, seqs);

@@ -334,3 +334,31 @@ def test_a_low_threshold_that_leaves_more_rows_than_one_staging_round(dtype, d, 
     P.check_elite(cnt, idx, elites)
     P.check_scores(ac.air_get_scores(0), scores, seqs)
     ac.close()
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("n_vis", [1, 15, 17, 33, 256, 257, 300])
+@pytest.mark.parametrize("G,window", [(1, 1), (3, 1), (2, 3), (7, 1), (3, 5), (16, 1), (4, 8), (3, 11), (16, 5)])  # 1 to 80 rows
+def test_fp32_scores_at_the_edges_of_tiles_and_row_blocks(d, n_vis, G, window):
+    import numpy as np
+    import torch
+
+    import paper_2503_23956_amd as A
+
+    dev = torch.device("cuda:0")
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(3)
+    n = 2 + n_vis + window
+    seq = synth.configs.Seq(n, 2, n_vis, n - window, window)
+    k = torch.randn((1, 2, n, d), generator=gen, device=dev)
+    q = torch.randn((1, 2 * G, window, d), generator=gen, device=dev)
+    cfg = A.make_config(n_layers=1, n_q_heads=2 * G, n_kv_heads=2, head_dim=d, batch=1, max_vis_len=n_vis, max_nonvis_len=n - n_vis,
+                        max_window=window, max_decode_steps=1, dtype=A.AIR_F32, alpha=0.0)
+    ac = A.AirCache(cfg, dev)
+    ac.air_score(0, 1, [q], [k], [k], [seq])
+    got = ac.air_get_scores(0)[0]
+    ac.close()
+    want = torch.softmax(q[0].double().view(2, G, window, d) @ k[0, :, 2:].double().transpose(1, 2).unsqueeze(1) / d ** 0.5, dim=3)
+    want = want[..., :n_vis].mean(dim=(1, 2)).cpu().numpy()
+    # logits of a few units in fp32: sums of d products, each rounding 2^-24 of a partial sum, and as much again in the exponential
+    np.testing.assert_allclose(got, want, rtol=1e-5)
