@@ -465,6 +465,10 @@ __global__ __launch_bounds__(256, 4) void score_finish_kernel(Dims dm, DevTables
 //            Then the ordered compaction of the elite positions and the elite-text columns of Eq.7.
 // ---------------------------------------------------------------------------------------
 constexpr int kEliteWaves = 8;      // phase 2 takes one head per wave
+// Elite-text columns of up to 16 kKept rows: tiles kept between maximum and sums, keys requested together.  (Tile by tile, twice, the
+// 32 rows a head of a window of 32 tokens cost eight trips to memory one behind the other: 16.5 us for 28 x 4 units of 7 heads, 13.5 now; the
+// few rows of an elite window are a path of their own: 7.7 and 7.3 for one layer.)
+constexpr int kKept = 3;
 constexpr float kEliteMargin = 4e-3f;  // raw-logit units
 __device__ __forceinline__ uint4 masked(const uint4 &x, uint32_t keep) { return make_uint4(x.x & keep, x.y & keep, x.z & keep, x.w & keep); }
 
@@ -561,8 +565,10 @@ __global__ __launch_bounds__(64 * kEliteWaves) void elite_mfma_kernel(Dims dm, D
             for (int j = lane; j < wl; j += 64) m32 = fmaxf(m32, logit[j]);
             m32 = wave_max(m32);
             // exact maximum: every candidate within both logits' errors of the fp32 maximum is recomputed
-            double amax = -INFINITY;
-            for (int j0 = 0; j0 < wl; j0 += 64) {
+            // (with a threshold of 0 every number passes, whatever a finite maximum is)
+            const bool any_will_do = alpha == 0.0 && m32 < INFINITY;
+            double amax = any_will_do ? (double)m32 : -INFINITY;
+            for (int j0 = 0; j0 < wl && !any_will_do; j0 += 64) {
                 const int j = j0 + lane;
                 unsigned long long near = __ballot(j < wl && !(logit[j] < m32 - near_max));
                 while (near) {
@@ -598,7 +604,7 @@ __global__ __launch_bounds__(64 * kEliteWaves) void elite_mfma_kernel(Dims dm, D
             // R x R logits are formed on MFMA, 16 rows against 16 keys per tile; lane (n, c) of a tile holds
             // key n and rows 4c .. 4c+3, rows and keys past R re-read the last one.  Windows of more than 16
             // rows (alpha = 0 turns the whole span into rows) go over the keys twice (maximum, then sum);
-            // up to 16 rows the one tile is kept.  The maximum is kept as the RAW dot product (before the
+            // up to 48 rows the tiles are kept.  The maximum is kept as the RAW dot product (before the
             // 1/sqrt(d) scale), the sum is of exp((a - max) / sqrt(d)).
             for (int rb = 0; rb < R; rb += 16) {
                 uint4 qa2[NS];
@@ -608,30 +614,63 @@ __global__ __launch_bounds__(64 * kEliteWaves) void elite_mfma_kernel(Dims dm, D
                     for (int sl = 0; sl < NS; ++sl) qa2[sl] = *reinterpret_cast<const uint4 *>(qr + 32 * sl + 8 * c);
                 }
                 float m4[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY}, z4[4] = {0.f, 0.f, 0.f, 0.f};
-                f32x4 a4 = (f32x4){0.f, 0.f, 0.f, 0.f};
-                for (int pass = 0; pass < 2; ++pass) {
-                    for (int jb = 0; jb < R; jb += 16) {
-                        if (pass == 0 || R > 16) {
-                            const bf16_t *kr = k + (int64_t)elite[min(jb + n, R - 1)] * st.kv_t;
-                            a4 = (f32x4){0.f, 0.f, 0.f, 0.f};
+                // key jb + n of the elite list against row rb + 4c + i; the list is in position order, so with the causal option a
+                // row sees the keys up to its own place in it
+                auto sees = [&](int jb, int i) { return jb + n < R && (!dm.causal_text || jb + n <= rb + 4 * c + i); };
+                auto top = [&](const f32x4 &a4, int jb) {
 #pragma unroll
-                            for (int sl = 0; sl < NS; ++sl) {
-                                const uint4 kb2 = *reinterpret_cast<const uint4 *>(kr + 32 * sl + 8 * c);
-                                a4 = mma<bf16_t>(qa2[sl], kb2, a4);
-                            }
-                        }
+                    for (int i = 0; i < 4; ++i) m4[i] = fmaxf(m4[i], sees(jb, i) ? a4[i] : -INFINITY);
+                };
+                auto over_lanes = [&]() {
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) {
-                            // key jb + n of the elite list against row rb + 4c + i; the list is in position order, so
-                            // with the causal option a row sees the keys up to its own place in it
-                            const bool live = jb + n < R && (!dm.causal_text || jb + n <= rb + 4 * c + i);
-                            if (pass == 0) m4[i] = fmaxf(m4[i], live ? a4[i] : -INFINITY);
-                            else z4[i] += live ? expf((a4[i] - m4[i]) * scale) : 0.f;
-                        }
+                    for (int i = 0; i < 4; ++i) m4[i] = max16(m4[i]);
+                };
+                auto add = [&](const f32x4 &a4, int jb) {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) z4[i] += sees(jb, i) ? expf((a4[i] - m4[i]) * scale) : 0.f;
+                };
+                auto keys = [&](int jb, uint4(&kb2)[NS]) {
+                    const bf16_t *kr = k + (int64_t)elite[min(jb + n, R - 1)] * st.kv_t;
+#pragma unroll
+                    for (int sl = 0; sl < NS; ++sl) kb2[sl] = *reinterpret_cast<const uint4 *>(kr + 32 * sl + 8 * c);
+                };
+                auto tile = [&](const uint4(&kb2)[NS]) {
+                    f32x4 a4 = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int sl = 0; sl < NS; ++sl) a4 = mma<bf16_t>(qa2[sl], kb2[sl], a4);
+                    return a4;
+                };
+                uint4 kb2[NS];
+                if (R <= 16) {
+                    keys(0, kb2);
+                    const f32x4 a4 = tile(kb2);
+                    top(a4, 0);
+                    over_lanes();
+                    add(a4, 0);
+                } else if (R <= 16 * kKept) {
+                    // the keys of a row block requested together, their tiles kept for the sums
+                    uint4 kb[kKept][NS];
+                    f32x4 a4[kKept];
+#pragma unroll
+                    for (int j = 0; j < kKept; ++j) keys(16 * j, kb[j]);  // (past the list its last key again)
+#pragma unroll
+                    for (int j = 0; j < kKept; ++j) {
+                        a4[j] = tile(kb[j]);
+                        top(a4[j], 16 * j);
                     }
-                    if (pass == 0) {
+                    over_lanes();
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) m4[i] = max16(m4[i]);
+                    for (int j = 0; j < kKept; ++j)
+                        if (16 * j < R) add(a4[j], 16 * j);
+                } else {
+                    for (int jb = 0; jb < R; jb += 16) {
+                        keys(jb, kb2);
+                        top(tile(kb2), jb);
+                    }
+                    over_lanes();
+                    for (int jb = 0; jb < R; jb += 16) {
+                        keys(jb, kb2);
+                        add(tile(kb2), jb);
                     }
                 }
 #pragma unroll
