@@ -421,7 +421,8 @@ __global__ __launch_bounds__(kThreads, 4) void window_scores_kernel(Dims dm, Dev
             s_M[tid] = tid < rows_here ? M : 0.f;
             s_ref[tid] = fabsf(M) > 0.5f * kFar ? -INFINITY : -M;  // (so does a row past the list)
             s_w[tid] = w;
-            s_last[tid] = dm.vis_window && tid < rows_here ? prow0 + row.y : u.sq.vis_len - 1;
+            // (a row past the list sees what the unit's last row sees: its weight is 0, but a key behind the window may be NaN or infinite)
+            s_last[tid] = dm.vis_window ? prow0 + (tid < rows_here ? row.y : u.sq.win_len - 1) : u.sq.vis_len - 1;
         }
         rows_wait_barrier();
         group_keys<T, NS>(u, st, key_lo + kGroup * wave, kreg);

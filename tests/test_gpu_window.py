@@ -259,3 +259,30 @@ def test_text_keys_that_are_no_numbers_leave_the_window(d, G, window, lost):
     np.testing.assert_allclose(got[1][0, 1], want.cpu().numpy(), rtol=P.SCORE_RTOL, atol=P.SCORE_ATOL)
     for l, h in [(0, 0), (0, 1), (1, 0)]:
         np.testing.assert_allclose(got[l][0, h], p.oracle(l, 0, h), rtol=P.SCORE_RTOL, atol=P.SCORE_ATOL)
+
+
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("G,window", [(5, 7), (7, 33), (3, 43), (7, 43)])  # 35 to 301 rows, none a whole number of blocks of 16
+@pytest.mark.parametrize("behind", [1, 11, 700 - 333])  # keys that are no numbers: the first behind the window, the rest of its group of 32, all
+@pytest.mark.parametrize("value", ["nan", "inf", "-inf"])
+def test_keys_behind_a_visual_window_do_not_count_whatever_they_hold(d, G, window, behind, value):
+    # A row of a visual window is normalised over the keys at or before its own: behind the window's end every score is 0.
+    end = 333
+    p = _Prompt(2, 1, 2, G, d, 700, 16, window, True)
+    s = p.seqs[0]
+    p.seqs = [synth.configs.Seq(s.seq_len, s.vis_start, s.vis_len, s.vis_start + end - window, window)]
+    ac = p.context()
+    want = p.score(ac)
+    ac.air_budget()
+    want_stats = ac.air_get_stats()
+    for k in p.k:
+        k[:, :, s.vis_start + end:s.vis_start + end + behind] = float(value)
+    got = p.score(ac)
+    ac.air_budget()
+    stats = ac.air_get_stats()
+    ac.close()
+    for l in range(2):
+        assert np.array_equal(got[l], want[l])
+        assert not got[l][..., end:].any()
+        np.testing.assert_allclose(got[l].astype(np.float64).sum(axis=2), 1.0, rtol=0, atol=1e-6)
+    assert all(np.array_equal(x, y) for x, y in zip(stats, want_stats))
