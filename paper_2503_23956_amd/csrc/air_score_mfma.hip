@@ -565,8 +565,9 @@ __global__ __launch_bounds__(64 * kEliteWaves) void elite_mfma_kernel(Dims dm, D
             for (int j = lane; j < wl; j += 64) m32 = fmaxf(m32, logit[j]);
             m32 = wave_max(m32);
             // exact maximum: every candidate within both logits' errors of the fp32 maximum is recomputed
-            // (with a threshold of 0 every number passes, whatever a finite maximum is)
-            const bool any_will_do = alpha == 0.0 && m32 < INFINITY;
+            // (with a threshold of 0 every number passes, whatever the maximum is; where logits or their sums of magnitudes overflow
+            // fp32 the exact maximum decides which are numbers)
+            const bool any_will_do = alpha == 0.0 && fabsf(m32) < INFINITY && err < INFINITY;
             double amax = any_will_do ? (double)m32 : -INFINITY;
             for (int j0 = 0; j0 < wl && !any_will_do; j0 += 64) {
                 const int j = j0 + lane;

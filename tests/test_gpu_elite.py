@@ -149,6 +149,29 @@ def test_infinite_logits(d, alpha):
 
 
 @pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("n_text", [7, 40, 100])
+@pytest.mark.parametrize("above", [False, True])
+def test_infinite_logits_beside_logits_that_overflow_fp32(d, n_text, above):
+    # With a threshold of 0: a candidate of -inf below finite ones that overflow fp32 to -inf is in the set; one of +inf, which an
+    # overflow to -inf in fp32 makes no number, is not, and the finite ones beside it are.
+    w = synth.get_workload(2).scaled(head_dim=d, n_layers=1, n_vis=40, n_text=n_text, decode_steps=1)
+    li = synth.layer_inputs(w, 0, w.seqs())
+    q, k = (synth.storage_to_f64(x).copy() for x in (li.q_text, li.k))
+    s = w.seqs()[0]
+    t0 = s.vis_start + s.vis_len
+    q[..., :2] = (0.0, 1.0)
+    q[:, :, -1, 0] = 2.0 ** 100  # of the row that Eq.5 asks
+    k[..., :2] = 0.0
+    if not above:
+        k[:, :, t0:, 0] = -2.0 ** 100
+    k[:, :, t0 + 5, :2] = (-2.0 ** 100, np.inf) if above else (0.0, -np.inf)
+    seqs, cnt, idx = _elite_sets(w, _bf16(q), _bf16(k), 0.0)
+    want = [t for t in range(s.win_start, s.win_start + s.win_len) if not (above and t == t0 + 5)]
+    for h in range(w.n_q_heads):
+        assert idx[0, h, :cnt[0, h]].tolist() == want
+
+
+@pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("low", [-3000.0, -1e5, -3e7, -3e9, -1e20, -7e25, -3e30, -1e36])
 @pytest.mark.parametrize("alpha,n_text", [(0.9, 40), (0.0, 4), (0.0, 40)])  # the elite window, 28 rows, 280 rows
 def test_visual_keys_masked_by_a_large_negative_logit(d, low, alpha, n_text):
