@@ -403,7 +403,7 @@ air_status air_score(air_ctx *ctx, void *stream, int32_t l0, int32_t l1, const a
             for (int i = 0; i < gn; ++i) lg.p[i] = ll.p[g0 + i];
             for (int pass = 1; pass <= 2 && e == hipSuccess; ++pass)
                 e = dt != AIR_BF16 ? launch_score_f32(s, dm, ctx->tab, pass, c0 + g0, gn, lg, *strides, sa)
-                    : many_rows    ? launch_score_window(s, dm, ctx->tab, pass, c0 + g0, gn, lg, *strides, sa)
+                    : many_rows    ? launch_score_window(s, dm, ctx->tab, pass, c0 + g0, gn, lg, *strides, sa, ctx->cfg.alpha == 0.0)
                                    : launch_score_mfma(s, dm, ctx->tab, pass, c0 + g0, gn, lg, *strides, sa, inline_rows);
         }
         if (e != hipSuccess) return hip_fail(ctx, e, "air_score launch");

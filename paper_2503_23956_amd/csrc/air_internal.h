@@ -116,7 +116,7 @@ hipError_t launch_score_f32(hipStream_t s, const Dims &dm, const DevTables &t, i
 hipError_t launch_score_mfma(hipStream_t s, const Dims &dm, const DevTables &t, int pass, int l0, int nl,
                              const LaunchLayers &ll, const air_strides &st, const SeqArgs &seqs, int inline_rows);
 hipError_t launch_score_window(hipStream_t s, const Dims &dm, const DevTables &t, int pass, int l0, int nl, const LaunchLayers &ll,
-                               const air_strides &st, const SeqArgs &seqs);
+                               const air_strides &st, const SeqArgs &seqs, bool whole);
 hipError_t launch_budget(hipStream_t s, const Dims &dm, const DevTables &t, double retention, int mode,
                          int min_keep, int skip_allocation, const SeqArgs &seqs);
 hipError_t launch_select(hipStream_t s, const Dims &dm, const DevTables &t, int l0, int nl, int threads, int direct_max);

@@ -94,11 +94,19 @@ __device__ __forceinline__ const bf16_t *query_of(const UnitCtx &u, const air_st
     return u.q + (int64_t)(u.kvh * u.G + (int)((unsigned)word >> 27)) * st.q_h + (int64_t)(word & 0x7ffffff) * st.q_t;
 }
 
-// The unit's rows.  A window has every token of its span as a row of every head, but for logits that are no numbers; so the rows
-// are taken from the window itself and requested while the counts of the lists are on their way (`guess`), and only where a count
-// says otherwise are they taken from the lists.
-__device__ __forceinline__ int rows_of_lane(const DevTables &t, const UnitCtx &u) {  // rows of head `lane` of the group
+// The unit's rows.  Without a threshold a window has every token of its span as a row of every head, but for logits that are no
+// numbers (`whole`): the rows are then taken from the window itself and requested while the counts of the lists are on their way, and
+// only where a count says otherwise are they taken from the lists.  With a threshold (contexts whose workspace holds no stash) they are a few
+// of the window's, and the lists come first: air_score of 28 x 8 x 4 units, 4 heads of 64, 2304 keys, 128 text tokens, 135 us, with the window's rows
+// in front of them 152; 24 x 2 units of 7 heads, 7290 keys 44.8 and 47.8.
+__device__ __forceinline__ int rows_of_unit(const DevTables &t, UnitCtx &u, bool whole, int *s_pref) {  // also: rows of head `lane` of the group
     const int lane = threadIdx.x & 63;
+    if (!whole) {
+        head_prefix(t, u.hrow0, u.G, s_pref);
+        u.R_total = s_pref[u.G];
+        return 0;
+    }
+    u.R_total = u.G * u.sq.win_len;
     return t.elite_cnt[u.hrow0 + min(lane, u.G - 1)];
 }
 __device__ __forceinline__ int2 row_of(const UnitCtx &u, const int *s_pref, bool whole, int rho) {
@@ -148,7 +156,7 @@ __device__ __forceinline__ void rows_wait_barrier() {
 constexpr int kBlocks1 = kWinRows / 32;
 template <int D>
 __global__ __launch_bounds__(kThreads, 4) void window_sums_kernel(Dims dm, DevTables t, int l0, LaunchLayers ll, air_strides st, SeqArgs seqs,
-                                                               int run_keys) {
+                                                               int run_keys, bool whole) {
     constexpr int NS = D / 16, kGroup = 32;
     constexpr float kC = Log2Scale<D>::kHi;
     constexpr float kSumLimit = 64.0f;  // of a lane's exponentials of a block
@@ -176,9 +184,7 @@ __global__ __launch_bounds__(kThreads, 4) void window_sums_kernel(Dims dm, DevTa
 #pragma unroll
         for (int sl = 0; sl < NS; ++sl) kreg[sl] = *reinterpret_cast<const uint4 *>(src + 16 * sl);
     };
-    const int count = rows_of_lane(t, u);
-    u.R_total = u.G * u.sq.win_len;
-    bool whole = true;
+    const int count = rows_of_unit(t, u, whole, s_pref);
     for (int r0 = 0; r0 < u.R_total; r0 += kWinRows) {
         int rows_here = min(kWinRows, u.R_total - r0);
         const int tid = here(threadIdx.x);
@@ -323,7 +329,7 @@ __global__ __launch_bounds__(kThreads, 4) void window_sums_kernel(Dims dm, DevTa
 // Pass 2.  A workgroup takes part_keys keys of a unit.
 template <int D>
 __global__ __launch_bounds__(kThreads, 4) void window_scores_kernel(Dims dm, DevTables t, int l0, LaunchLayers ll, air_strides st, SeqArgs seqs,
-                                                                 int run_keys, int part_keys) {
+                                                                 int run_keys, int part_keys, bool whole) {
     constexpr int NS = D / 32, T = kTiles, kGroup = 16 * T;
     constexpr float kC = Log2Scale<D>::kHi;
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, n = lane & 15, c = lane >> 4;
@@ -346,9 +352,8 @@ __global__ __launch_bounds__(kThreads, 4) void window_scores_kernel(Dims dm, Dev
     const int key_hi = min(key_lo + part_keys, dm.vis_window ? prow0 + u.sq.win_len : u.sq.vis_len);
     uint4 kreg[T][NS];  // the keys of the wave's next group
     if (tid == 0) s_any_far = 0;
-    const int count = rows_of_lane(t, u);
-    u.R_total = u.G * u.sq.win_len;
-    bool whole = true;
+    for (int i = tid; i < part_keys && !whole; i += kThreads) s_imp[i] = 0.f;
+    const int count = rows_of_unit(t, u, whole, s_pref);
     for (int r0 = 0; r0 < u.R_total; r0 += kWinRows) {
         int rows_here = min(kWinRows, u.R_total - r0);
         const int tid = here(threadIdx.x);
@@ -525,7 +530,7 @@ static int part_keys(const Dims &dm, int64_t units, int most, int extra) {
 }
 
 hipError_t launch_score_window(hipStream_t s, const Dims &dm, const DevTables &t, int pass, int l0, int nl, const LaunchLayers &ll,
-                               const air_strides &st, const SeqArgs &seqs) {
+                               const air_strides &st, const SeqArgs &seqs, bool whole) {
     // (Runs as long as parts: 7290 keys, 28 x 4 units, pass 1 70 us with 1856 keys a run, 78 with 832.)
     // A run of pass 1 decides references and partial sums, so it follows from the context alone, not from the layers of the call:
     // the scores are the same bits however the layers are cut into calls and launches.  Pass 2 leaves whole sums of a
@@ -534,11 +539,11 @@ hipError_t launch_score_window(hipStream_t s, const Dims &dm, const DevTables &t
     const int part = pass == 1 ? run : part_keys(dm, (int64_t)nl * dm.B * dm.Hkv, kPartMost, 8);
     const dim3 grid((dm.max_vis + part - 1) / part, dm.Hkv, nl * dm.B), block(kThreads);
     if (dm.D == 128) {
-        if (pass == 1) hipLaunchKernelGGL((window_sums_kernel<128>), grid, block, 0, s, dm, t, l0, ll, st, seqs, run);
-        else hipLaunchKernelGGL((window_scores_kernel<128>), grid, block, 0, s, dm, t, l0, ll, st, seqs, run, part);
+        if (pass == 1) hipLaunchKernelGGL((window_sums_kernel<128>), grid, block, 0, s, dm, t, l0, ll, st, seqs, run, whole);
+        else hipLaunchKernelGGL((window_scores_kernel<128>), grid, block, 0, s, dm, t, l0, ll, st, seqs, run, part, whole);
     } else {
-        if (pass == 1) hipLaunchKernelGGL((window_sums_kernel<64>), grid, block, 0, s, dm, t, l0, ll, st, seqs, run);
-        else hipLaunchKernelGGL((window_scores_kernel<64>), grid, block, 0, s, dm, t, l0, ll, st, seqs, run, part);
+        if (pass == 1) hipLaunchKernelGGL((window_sums_kernel<64>), grid, block, 0, s, dm, t, l0, ll, st, seqs, run, whole);
+        else hipLaunchKernelGGL((window_scores_kernel<64>), grid, block, 0, s, dm, t, l0, ll, st, seqs, run, part, whole);
     }
     return hipGetLastError();
 }

@@ -36,13 +36,13 @@ class _Prompt:
         self.k = [torch.randn((B, hkv, n, d), generator=gen, device=dev).to(torch.bfloat16) for _ in range(L)]
         self.q = [(spread * torch.randn((B, hkv * G, self.n_q, d), generator=gen, device=dev)).to(torch.bfloat16) for _ in range(L)]
 
-    def context(self, **tuning):
+    def context(self, alpha=0.0, **tuning):
         import paper_2503_23956_amd as A
 
         s = self.seqs[0]
         cfg = A.make_config(n_layers=self.L, n_q_heads=self.hkv * self.G, n_kv_heads=self.hkv, head_dim=self.d, batch=self.B,
                             max_vis_len=s.vis_len, max_nonvis_len=s.seq_len - s.vis_len, max_window=s.win_len, max_decode_steps=1,
-                            dtype=A.AIR_BF16, alpha=0.0, window_kind=A.AIR_WINDOW_VISUAL if self.visual else A.AIR_WINDOW_TEXT)
+                            dtype=A.AIR_BF16, alpha=alpha, window_kind=A.AIR_WINDOW_VISUAL if self.visual else A.AIR_WINDOW_TEXT)
         ac = A.AirCache(cfg, "cuda:0")
         if tuning:
             ac.air_set_tuning(**tuning)
@@ -54,13 +54,13 @@ class _Prompt:
             ac.air_score(l0, l1, self.q[l0:l1], self.k[l0:l1], self.k[l0:l1], self.seqs)
         return [ac.air_get_scores(l) for l in range(self.L)]
 
-    def oracle(self, l, b, h):
+    def oracle(self, l, b, h, alpha=0.0):
         """fp64 importance of one unit."""
         s = self.seqs[b]
         q = self.q[l][b, h * self.G:(h + 1) * self.G].double().cpu().numpy()
         k = self.k[l][b, h:h + 1].double().cpu().numpy()
         seg = P.seg_of(s)
-        return (O.layer_importance_visual_window(q, k, seg) if self.visual else O.layer_importance(q, k, seg, 0.0))[0][0]
+        return (O.layer_importance_visual_window(q, k, seg) if self.visual else O.layer_importance(q, k, seg, alpha))[0][0]
 
 
 @pytest.mark.parametrize("d,visual", [(128, False), (64, False), (128, True), (64, True)])
@@ -286,3 +286,32 @@ def test_keys_behind_a_visual_window_do_not_count_whatever_they_hold(d, G, windo
         assert not got[l][..., end:].any()
         np.testing.assert_allclose(got[l].astype(np.float64).sum(axis=2), 1.0, rtol=0, atol=1e-6)
     assert all(np.array_equal(x, y) for x, y in zip(stats, want_stats))
+
+
+@pytest.mark.parametrize("d,alpha", [(128, 0.0), (64, 0.0), (64, 0.9)])
+def test_a_unit_without_rows_scores_zero(d, alpha):
+    # every text key of one unit is no number: no candidate passes, with a threshold (in a workspace without the stash) and without one
+    import ctypes as C
+
+    import torch
+
+    p = _Prompt(2, 1, 2, 7, d, 1300, 40, 32)
+    s = p.seqs[0]
+    p.k[1][0, 1, s.win_start:] = float("nan")
+    ac = p.context(alpha=alpha)
+    if alpha:
+        stash = 2 * 2 * 6 * 32 * 256 * 4
+        least = ac.workspace_bytes - stash - (stash // 256 + 255) // 256 * 256
+        ac.lib.air_destroy(ac.handle)
+        ac.workspace, ac.handle = torch.empty(least, dtype=torch.uint8, device="cuda:0"), C.c_void_p()
+        assert ac.lib.air_create(C.byref(ac.cfg), ac.workspace.data_ptr(), least, C.byref(ac.handle)) == 0
+    for _ in range(2):  # (the second time over the first one's scores)
+        got = p.score(ac)
+        cnt, _ = ac.air_get_elite(1)
+        assert not cnt[0, 7:].any() and cnt[0, :7].all()
+        assert not got[1][0, 1].any()
+        for l, h in [(0, 0), (0, 1), (1, 0)]:
+            np.testing.assert_allclose(got[l][0, h], p.oracle(l, 0, h, alpha), rtol=P.SCORE_RTOL, atol=P.SCORE_ATOL)
+    ac.air_budget()
+    assert ac.air_get_budgets().sum() > 0
+    ac.close()
