@@ -96,9 +96,9 @@ __device__ __forceinline__ const bf16_t *query_of(const UnitCtx &u, const air_st
 
 // The unit's rows.  Without a threshold a window has every token of its span as a row of every head, but for logits that are no
 // numbers (`whole`): the rows are then taken from the window itself and requested while the counts of the lists are on their way, and
-// only where a count says otherwise are they taken from the lists.  With a threshold (contexts whose workspace holds no stash) they are a few
-// of the window's, and the lists come first: air_score of 28 x 8 x 4 units, 4 heads of 64, 2304 keys, 128 text tokens, 135 us, with the window's rows
-// in front of them 152; 24 x 2 units of 7 heads, 7290 keys 44.8 and 47.8.
+// only where a count says otherwise are they taken from the lists (WHOLE).  With a threshold (contexts whose workspace holds no stash) they are a few
+// of the window's, and the lists come first: air_score of 28 x 8 x 4 units, 4 heads of 64, 2304 keys, 128 text tokens, 133 us, with the window's rows
+// in front of them 152; 24 x 2 units of 7 heads, 7290 keys 44.4 and 48.3.
 __device__ __forceinline__ int rows_of_unit(const DevTables &t, UnitCtx &u, bool whole, int *s_pref) {  // also: rows of head `lane` of the group
     const int lane = threadIdx.x & 63;
     if (!whole) {
@@ -151,18 +151,19 @@ __device__ __forceinline__ void rows_wait_barrier() {
 }
 
 // ---------------------------------------------------------------------------------------
-// Pass 1.  A workgroup takes a run of run_keys keys of a unit.  Products of 32 keys x 32 rows: lane (n, c),
+// Pass 1.  A workgroup takes a run of run_keys keys of a unit and one of `shares` shares of its rows.  Products of 32 keys x 32 rows: lane (n, c),
 // n = lane % 32, holds sixteen logits of row n.
 constexpr int kBlocks1 = kWinRows / 32;
-template <int D>
+template <int D, bool WHOLE>
 __global__ __launch_bounds__(kThreads, 4) void window_sums_kernel(Dims dm, DevTables t, int l0, LaunchLayers ll, air_strides st, SeqArgs seqs,
-                                                               int run_keys, bool whole) {
+                                                               int run_keys, int shares, uint32_t inv_shares, int share_rows) {
     constexpr int NS = D / 16, kGroup = 32;
     constexpr float kC = Log2Scale<D>::kHi;
     constexpr float kSumLimit = 64.0f;  // of a lane's exponentials of a block
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     UnitCtx u;
-    if (!unit_setup(dm, seqs, l0, ll, st, u, 0) || (int)blockIdx.x * run_keys >= u.sq.vis_len) return;
+    const int run = inv_shares ? (int)__umulhi(blockIdx.x, inv_shares) : (int)blockIdx.x;
+    if (!unit_setup(dm, seqs, l0, ll, st, u, 0) || run * run_keys >= u.sq.vis_len) return;
     u.q += (int64_t)(u.sq.win_start - u.qbase) * st.q_t;
     __shared__ int s_pref[17];
     __shared__ __align__(16) bf16_t s_rows[kWinRows * D];
@@ -173,7 +174,7 @@ __global__ __launch_bounds__(kThreads, 4) void window_sums_kernel(Dims dm, DevTa
     __shared__ int s_top[kWinRows];  // a row's first reference
     // a visual-window row at visual index p sees the keys up to p: keys behind the last row are never looked at
     const int prow0 = u.sq.win_start - u.sq.vis_start;
-    const int run = blockIdx.x, key_first = run * run_keys + 32 * wave;
+    const int key_first = run * run_keys + 32 * wave;
     const int key_hi = min((run + 1) * run_keys, dm.vis_window ? prow0 + u.sq.win_len : u.sq.vis_len);
     // the keys of the wave's next group, 16 elements a slice, eight of them in either half of the wave; requested at the end of
     // the group before
@@ -184,9 +185,13 @@ __global__ __launch_bounds__(kThreads, 4) void window_sums_kernel(Dims dm, DevTa
 #pragma unroll
         for (int sl = 0; sl < NS; ++sl) kreg[sl] = *reinterpret_cast<const uint4 *>(src + 16 * sl);
     };
+    bool whole = WHOLE;
     const int count = rows_of_unit(t, u, whole, s_pref);
-    for (int r0 = 0; r0 < u.R_total; r0 += kWinRows) {
-        int rows_here = min(kWinRows, u.R_total - r0);
+    // the workgroup's rows: whole blocks of 32 (a block's rows share their raised references: blocks are the same however the rows are dealt)
+    const int row_lo = ((int)blockIdx.x - run * shares) * share_rows;
+    int row_hi = min(u.R_total, row_lo + share_rows);
+    for (int r0 = row_lo; r0 < row_hi; r0 += kWinRows) {
+        int rows_here = min(kWinRows, row_hi - r0);
         const int tid = here(threadIdx.x);
         while (true) {
             if (tid < rows_here) {
@@ -202,7 +207,8 @@ __global__ __launch_bounds__(kThreads, 4) void window_sums_kernel(Dims dm, DevTa
             rows_wait_barrier();
             head_prefix(t, u.hrow0, u.G, s_pref);
             u.R_total = s_pref[u.G];
-            rows_here = min(kWinRows, u.R_total);
+            row_hi = min(u.R_total, row_lo + share_rows);
+            rows_here = min(kWinRows, row_hi - r0);
             if (rows_here <= 0) return;
         }
         const int n_blk = (rows_here + 31) >> 5;
@@ -327,9 +333,9 @@ __global__ __launch_bounds__(kThreads, 4) void window_sums_kernel(Dims dm, DevTa
 
 // ---------------------------------------------------------------------------------------
 // Pass 2.  A workgroup takes part_keys keys of a unit.
-template <int D>
+template <int D, bool WHOLE>
 __global__ __launch_bounds__(kThreads, 4) void window_scores_kernel(Dims dm, DevTables t, int l0, LaunchLayers ll, air_strides st, SeqArgs seqs,
-                                                                 int run_keys, int part_keys, bool whole) {
+                                                                 int run_keys, int part_keys) {
     constexpr int NS = D / 32, T = kTiles, kGroup = 16 * T;
     constexpr float kC = Log2Scale<D>::kHi;
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, n = lane & 15, c = lane >> 4;
@@ -352,7 +358,11 @@ __global__ __launch_bounds__(kThreads, 4) void window_scores_kernel(Dims dm, Dev
     const int key_hi = min(key_lo + part_keys, dm.vis_window ? prow0 + u.sq.win_len : u.sq.vis_len);
     uint4 kreg[T][NS];  // the keys of the wave's next group
     if (tid == 0) s_any_far = 0;
-    for (int i = tid; i < part_keys && !whole; i += kThreads) s_imp[i] = 0.f;
+    if (!WHOLE)
+        for (int i = tid; i < part_keys; i += kThreads) s_imp[i] = 0.f;
+    // (Known to be true at first, the compiler reserves 68 bytes of scratch a lane that no instruction touches; as a value it does not know, 28 x 16 x 4
+    // units of 128 keys, 4 x 9 rows take 94.5 us in place of 91.8.)
+    bool whole = WHOLE;
     const int count = rows_of_unit(t, u, whole, s_pref);
     for (int r0 = 0; r0 < u.R_total; r0 += kWinRows) {
         int rows_here = min(kWinRows, u.R_total - r0);
@@ -373,7 +383,7 @@ __global__ __launch_bounds__(kThreads, 4) void window_scores_kernel(Dims dm, Dev
             rows_here = min(kWinRows, u.R_total);
             if (rows_here <= 0) break;
         }
-        if (r0 == 0)
+        if (WHOLE && r0 == 0)
             for (int i = tid; i < part_keys; i += kThreads) s_imp[i] = 0.f;
         if (rows_here <= 0) {  // no row: the scores are zero
             lds_barrier();
@@ -512,15 +522,16 @@ __global__ __launch_bounds__(kThreads, 4) void window_scores_kernel(Dims dm, Dev
     leave_scores(dm, t, u.unit, u.b, u.sq, (u.sq.vis_len + part_keys - 1) / part_keys, s_imp, s_mom, s_is_last);
 }
 
-// Keys of a workgroup, a multiple of 64 from kPartLeast to `most`.  Two workgroups share a CU, 512 the chip: as many parts of max_vis
-// as make the rounds of 512 times the work of one least.  A round costs the keys and about `extra` groups of 64 keys for what is in front
-// and behind (rows into LDS, parameters, partial sums).
-static int part_keys(const Dims &dm, int64_t units, int most, int extra) {
+// Keys of a workgroup, a multiple of 64 from kPartLeast to kPartMost.  Two workgroups share a CU, 512 the chip: as many parts of max_vis
+// as make the rounds of 512 times the work of one least.  A round costs the keys and about kPartExtra groups of 64 keys for what is in
+// front and behind (rows into LDS, parameters, partial sums).
+constexpr int kPartExtra = 8;
+static int part_keys(const Dims &dm, int64_t units) {
     const int groups = (dm.max_vis + 63) / 64;
-    int best = most / 64;
+    int best = kPartMost / 64;
     int64_t best_cost = -1;
-    for (int g = most / 64; g >= kPartLeast / 64; --g) {
-        const int64_t cost = (units * ((groups + g - 1) / g) + 511) / 512 * (g + extra);
+    for (int g = kPartMost / 64; g >= kPartLeast / 64; --g) {
+        const int64_t cost = (units * ((groups + g - 1) / g) + 511) / 512 * (g + kPartExtra);
         if (best_cost < 0 || cost < best_cost) {
             best_cost = cost;
             best = g;
@@ -529,23 +540,45 @@ static int part_keys(const Dims &dm, int64_t units, int most, int extra) {
     return 64 * best;
 }
 
-hipError_t launch_score_window(hipStream_t s, const Dims &dm, const DevTables &t, int pass, int l0, int nl, const LaunchLayers &ll,
-                               const air_strides &st, const SeqArgs &seqs, bool whole) {
-    // (Runs as long as parts: 7290 keys, 28 x 4 units, pass 1 70 us with 1856 keys a run, 78 with 832.)
+// Workgroups among which the rows of a run are dealt in pass 1, whole blocks of 32: a call of few units (a layer of a context whose runs
+// are as long as a call of all layers likes them) would otherwise leave most of the chip idle.  As many as leave every workgroup a CU:
+// air_score of one layer after the other, in 1 / 2 / 3 / 4 / 7 shares, 7290 keys, 28 x 4 units, 7 x 32 rows (16 runs) 1788 / 1535 / 1461 / 1425 / 1403
+// us, 16384 keys, 40 x 8 units, 8 x 32 rows (64 runs) 3236 / 2693 / 2541 / 2607 / 3055.
+static int rows_of_share(const Dims &dm, int64_t runs) {
+    const int blocks = (dm.G * dm.max_window + 31) / 32;
+    int shares = (int)(runs < kCUs ? kCUs / runs : 1);
+    shares = shares < blocks ? shares : blocks;
+    return 32 * ((blocks + shares - 1) / shares);
+}
+
+template <int D, bool WHOLE>
+static hipError_t window_launch(hipStream_t s, const Dims &dm, const DevTables &t, int pass, int l0, int nl, const LaunchLayers &ll,
+                                const air_strides &st, const SeqArgs &seqs) {
     // A run of pass 1 decides references and partial sums, so it follows from the context alone, not from the layers of the call:
     // the scores are the same bits however the layers are cut into calls and launches.  Pass 2 leaves whole sums of a
     // key and the unit's statistics from whole units: its parts follow the launch.
-    const int run = part_keys(dm, (int64_t)dm.L * dm.B * dm.Hkv, kPartMost, 8);
-    const int part = pass == 1 ? run : part_keys(dm, (int64_t)nl * dm.B * dm.Hkv, kPartMost, 8);
-    const dim3 grid((dm.max_vis + part - 1) / part, dm.Hkv, nl * dm.B), block(kThreads);
-    if (dm.D == 128) {
-        if (pass == 1) hipLaunchKernelGGL((window_sums_kernel<128>), grid, block, 0, s, dm, t, l0, ll, st, seqs, run, whole);
-        else hipLaunchKernelGGL((window_scores_kernel<128>), grid, block, 0, s, dm, t, l0, ll, st, seqs, run, part, whole);
+    // (Runs as long as parts: 7290 keys, 28 x 4 units, pass 1 70 us with 1856 keys a run, 78 with 832.)
+    const int64_t units = (int64_t)nl * dm.B * dm.Hkv;
+    const int run = part_keys(dm, (int64_t)dm.L * dm.B * dm.Hkv);
+    const dim3 block(kThreads);
+    if (pass == 1) {
+        const int n_runs = (dm.max_vis + run - 1) / run, share_rows = rows_of_share(dm, units * n_runs);
+        const int shares = (dm.G * dm.max_window + share_rows - 1) / share_rows;
+        const uint32_t inv = shares > 1 ? (uint32_t)(0x100000000ull / (uint64_t)shares) + 1u : 0u;  // n_runs * shares is small then
+        hipLaunchKernelGGL((window_sums_kernel<D, WHOLE>), dim3(n_runs * shares, dm.Hkv, nl * dm.B), block, 0, s, dm, t, l0, ll, st, seqs, run,
+                           shares, inv, share_rows);
     } else {
-        if (pass == 1) hipLaunchKernelGGL((window_sums_kernel<64>), grid, block, 0, s, dm, t, l0, ll, st, seqs, run, whole);
-        else hipLaunchKernelGGL((window_scores_kernel<64>), grid, block, 0, s, dm, t, l0, ll, st, seqs, run, part, whole);
+        const int part = part_keys(dm, units);
+        hipLaunchKernelGGL((window_scores_kernel<D, WHOLE>), dim3((dm.max_vis + part - 1) / part, dm.Hkv, nl * dm.B), block, 0, s, dm, t, l0, ll,
+                           st, seqs, run, part);
     }
     return hipGetLastError();
+}
+
+hipError_t launch_score_window(hipStream_t s, const Dims &dm, const DevTables &t, int pass, int l0, int nl, const LaunchLayers &ll,
+                               const air_strides &st, const SeqArgs &seqs, bool whole) {
+    auto launch = dm.D == 128 ? (whole ? window_launch<128, true> : window_launch<128, false>) : (whole ? window_launch<64, true> : window_launch<64, false>);
+    return launch(s, dm, t, pass, l0, nl, ll, st, seqs);
 }
 
 }  // namespace air

@@ -12,11 +12,17 @@ from tests import parity_util as P
 pytestmark = pytest.mark.gpu
 
 
-def _part_keys(n_vis, units, most, extra):
+def _part_keys(n_vis, units):
     """Keys of a workgroup as the launcher chooses them: least rounds of 512 workgroups times what a round costs."""
     groups = -(-n_vis // 64)
-    cost = {g: -(-units * -(-groups // g) // 512) * (g + extra) for g in range(8, most // 64 + 1)}
+    cost = {g: -(-units * -(-groups // g) // 512) * (g + 8) for g in range(8, 33)}
     return 64 * min(cost, key=lambda g: (cost[g], -g))
+
+
+def _share_rows(rows, runs):
+    """Rows of a workgroup of the first pass: whole blocks of 32, dealt to as many workgroups as leave each a CU."""
+    blocks = -(-rows // 32)
+    return 32 * -(-blocks // max(1, min(256 // runs, blocks)))
 
 
 class _Prompt:
@@ -167,22 +173,25 @@ def test_spans_of_many_runs(n_vis, window, G, d, visual):
 
 @pytest.mark.parametrize("d,visual", [(128, False), (64, False), (128, True), (64, True)])
 @pytest.mark.parametrize("window,G", [(9, 4), (33, 8)])  # 36 and 264 rows: two groups of rows
-@pytest.mark.parametrize("n_vis,run,part", [(4160, 576, 1088), (7290, 960, 1856), (8192, 1024, 2048)])
-def test_parts_that_are_larger_in_one_call_than_layer_by_layer(n_vis, run, part, window, G, d, visual):
-    # 128 units in one launch, four layer by layer: units of several parts that are no power of two, and parts as large as LDS takes
+@pytest.mark.parametrize("n_vis,run", [(4160, 1088), (7290, 1856), (8192, 2048)])
+def test_parts_that_are_larger_in_one_call_than_layer_by_layer(n_vis, run, window, G, d, visual):
+    # 128 units in one launch, four layer by layer: units of several runs and parts that are no power of two, and as large as LDS
+    # takes.  Rows of a run in one workgroup, or dealt to several: 264 rows as 160 + 104 in calls of seven layers, 3 x 96 (the last 72) in calls
+    # of five, blocks of 32 in calls of one.
     L, B = 32, 4
-    assert (_part_keys(n_vis, L * B, 1024, 4), _part_keys(n_vis, L * B, 2048, 8), _part_keys(n_vis, B, 2048, 8)) == (run, part, 512)
+    assert (_part_keys(n_vis, L * B), _part_keys(n_vis, B)) == (run, 512)
+    assert [_share_rows(264, n * B * -(-n_vis // run)) for n in (32, 7, 5, 1)] == [288, 160, 96, 32]
     p = _Prompt(L, B, 1, G, d, n_vis, 48, window, visual)
     ac = p.context()
     stats = []
     got = []
-    for pieces in (None, [(l, l + 1) for l in range(L)]):
+    for pieces in (None, [(l, l + 1) for l in range(L)], [(0, 7), (7, 12), (12, 32)]):
         got.append(p.score(ac, pieces))
         ac.air_budget()
         stats.append(ac.air_get_stats())
     ac.close()
-    assert all(np.array_equal(x, y) for x, y in zip(*got))
-    assert all(np.array_equal(x, y) for x, y in zip(*stats))
+    assert all(np.array_equal(x, y) and np.array_equal(x, z) for x, y, z in zip(*got))
+    assert all(np.array_equal(x, y) and np.array_equal(x, z) for x, y, z in zip(*stats))
     for (l, b) in [(0, 0), (L // 2, 1), (L - 1, B - 1)]:
         np.testing.assert_allclose(got[0][l][b, 0], p.oracle(l, b, 0), rtol=P.SCORE_RTOL, atol=P.SCORE_ATOL)
         np.testing.assert_allclose(stats[0][1][b, l], O.skewness(got[0][l][b, 0].astype(np.float64)), rtol=1e-9, atol=1e-12)
@@ -234,7 +243,7 @@ def test_skewness_of_rows_with_little_or_no_spread(n_vis, visual, d):
 
 
 @pytest.mark.parametrize("d", [128, 64])
-@pytest.mark.parametrize("G,window,lost", [(7, 32, (3, 31)), (2, 20, (0,)), (8, 40, (17, 18, 39))])  # one and two rounds of 256 rows
+@pytest.mark.parametrize("G,window,lost", [(7, 32, (3, 31)), (2, 20, (0,)), (2, 17, (5,)), (8, 40, (17, 18, 39))])  # to 32 rows, none for the second share; more than 256
 def test_text_keys_that_are_no_numbers_leave_the_window(d, G, window, lost):
     # Eq.5 with a threshold of 0 takes every candidate whose logit is a number: the rows of the group are then fewer than the window
     # has tokens, and come from the lists.
