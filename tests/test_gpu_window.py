@@ -70,7 +70,7 @@ class _Prompt:
 
 
 @pytest.mark.parametrize("d,visual", [(128, False), (64, False), (128, True), (64, True)])
-@pytest.mark.parametrize("L", [5, 16, 34])  # runs of 512, 512 and 1024 keys; 34 layers take two launches, in parts of 1024
+@pytest.mark.parametrize("L", [5, 16, 34])  # runs of 512, 1024 and 1024 keys; 34 layers take two launches
 def test_scores_are_the_same_bits_however_the_layers_are_cut(L, d, visual):
     p = _Prompt(L, 6, 8, 2, d, 1000, 24, 20, visual)
     ac = p.context()
@@ -115,20 +115,22 @@ def test_logits_that_outrun_their_reference(d, visual, shape, L):
 @pytest.mark.parametrize("d", [128, 64])
 @pytest.mark.parametrize("visual", [False, True])
 @pytest.mark.parametrize("spread,bound", [(1.0, 1e-7), (5.0, 6e-7), (18.0, 1.5e-6)])
-def test_error_against_fp64(d, visual, spread, bound):
+@pytest.mark.parametrize("L,B,run", [(2, 1, 512), (16, 16, 1152)])  # lanes with references of their own, references over the first keys of a run
+def test_error_against_fp64(d, visual, spread, bound, L, B, run):
     # Relative 2-norm.  A logit near the maximum is about 4 spreads in size; its fp32 sum is rounded at partial sums of that size,
     # 4 spread 2^-24 = 2.4e-7 spread at the most for one row, and averages over the rows that share a key.  Sums from zero
     # with references near the maximum: 0.6e-7, 4.3e-7 and 8.7e-7 measured (with the logits of this kernel as with those of
     # the one before it); sums that start at minus the reference: 0.7e-7, 9.7e-7 and 4.0e-6.
-    p = _Prompt(2, 1, 2, 7, d, 2304, 64, 32, visual, spread)
+    assert _part_keys(2304, L * B * 2) == run
+    p = _Prompt(L, B, 2, 7, d, 2304, 64, 32, visual, spread)
     ac = p.context()
     got = p.score(ac)
     ac.close()
     errs = []
-    for l in range(2):
+    for l in (0, L - 1):
         for h in range(2):
-            want = p.oracle(l, 0, h)
-            errs.append(np.linalg.norm(got[l][0, h] - want) / np.linalg.norm(want))
+            want = p.oracle(l, l % B, h)
+            errs.append(np.linalg.norm(got[l][l % B, h] - want) / np.linalg.norm(want))
     assert math.sqrt(np.mean(np.square(errs))) <= bound, errs
 
 
@@ -200,16 +202,18 @@ def test_parts_that_are_larger_in_one_call_than_layer_by_layer(n_vis, run, windo
 @pytest.mark.parametrize("d", [128, 64])
 @pytest.mark.parametrize("G", [2, 7])
 @pytest.mark.parametrize("spread", [1.0, 18.0, 100.0, 1e3, 1e4, 1e5])
-def test_weights_of_a_row_add_up_to_one_whatever_the_logits(spread, G, d):
+@pytest.mark.parametrize("L,B,run", [(2, 1, 512), (16, 16, 1152)])
+def test_weights_of_a_row_add_up_to_one_whatever_the_logits(spread, G, d, L, B, run):
     # Pass 1 forms its logits with products of 32 x 32, pass 2 with products of 16 x 16: they have to be the same bits, or a weight is
     # off by 2^(difference) where a key stands above all others (raw logits of 4e6 have a spacing of 0.5, that is 4 % of a weight).
-    # No text columns: every row's weights add up to 1, to the rounding of fp32 sums of 2304 terms in runs of 512.
-    p = _Prompt(2, 1, 2, G, d, 2304, 16, 32, True, spread)
+    # No text columns: every row's weights add up to 1, to the rounding of fp32 sums of 2304 terms in runs of 512 or 1152.
+    assert _part_keys(2304, L * B * 2) == run
+    p = _Prompt(L, B, 2, G, d, 2304, 16, 32, True, spread)
     ac = p.context()
     got = p.score(ac)
     ac.close()
     for x in got:
-        np.testing.assert_allclose(x[0].astype(np.float64).sum(axis=1), 1.0, rtol=0, atol=1e-6)
+        np.testing.assert_allclose(x.astype(np.float64).sum(axis=2), 1.0, rtol=0, atol=1e-6)
 
 
 @pytest.mark.parametrize("d", [128, 64])
