@@ -328,3 +328,32 @@ def test_a_unit_without_rows_scores_zero(d, alpha):
     ac.air_budget()
     assert ac.air_get_budgets().sum() > 0
     ac.close()
+
+
+@pytest.mark.parametrize("d,visual", [(128, False), (64, False), (128, True), (64, True)])
+@pytest.mark.parametrize("value", ["-inf", "nan", "3e9", "-3e9"])
+def test_first_references_from_keys_that_are_far_or_no_numbers(value, d, visual):
+    # Runs of 1152 keys: a row's first reference is its maximum over the run's first 256 keys.  Here all of those are infinitely low, no
+    # numbers, or beyond the bound of the references on either side.
+    L = B = 16
+    assert _part_keys(2304, L * B * 2) == 1152
+    p = _Prompt(L, B, 2, 7, d, 2304, 40, 32, visual)
+    n0 = p.seqs[0].vis_start
+    for x, y in zip(p.q, p.k):
+        x[..., 1], y[..., 1] = 1.0, 0.0
+    ac = p.context()
+    want = p.score(ac)
+    units = [(0, 0, 0), (9, 3, 1), (L - 1, B - 1, 1)]
+    for l, b, h in units:
+        for lo in (n0, n0 + 1152) if value != "nan" else (n0,):
+            p.k[l][b, h, lo:lo + 256] = 0.0
+            p.k[l][b, h, lo:lo + 256, 1] = float(value)
+    got = p.score(ac)
+    ac.close()
+    for l, b, h in units:
+        if value == "nan":  # no row has a softmax then; the keys say so
+            assert np.isnan(got[l][b, h, :256]).all() and not np.isnan(got[l][b, h, 256:]).any()
+        else:
+            np.testing.assert_allclose(got[l][b, h], p.oracle(l, b, h), rtol=P.SCORE_RTOL, atol=P.SCORE_ATOL)
+        got[l][b, h] = want[l][b, h]
+    assert all(np.array_equal(x, y) for x, y in zip(got, want))
