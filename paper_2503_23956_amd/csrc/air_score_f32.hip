@@ -79,7 +79,7 @@ __device__ __forceinline__ void stage_rows(const Dims &dm, const DevTables &t, c
     lds_barrier();
 }
 
-// the wave's 64 keys of a chunk as matrix operands, lane (n, c) the c-th quarter of every slice of key n of a tile (keys past the
+// the wave's 16 TILES keys of a chunk as matrix operands, lane (n, c) the c-th quarter of every slice of key n of a tile (keys past the
 // end repeat the last one)
 template <int D, int TILES>
 __device__ __forceinline__ void keys_of(const F32Unit &u, const air_strides &st, int chunk, uint4 (&k)[TILES][D / 16]) {
@@ -94,7 +94,9 @@ __device__ __forceinline__ void keys_of(const F32Unit &u, const air_strides &st,
 }
 
 // Logits of the staged rows rb .. rb + 15 against those keys: lane (n, c) gets rows rb + 4 i + c of key n of every tile.  (Operand row
-// 4 c + i carries staged row 4 i + c, so that all lanes are done after (nb - rb + 3) / 4 values.)
+// 4 c + i carries staged row 4 i + c, so that all lanes are done after (nb - rb + 3) / 4 values.)  Even and odd slices have a sum each: in
+// one sum over the D products the scores were up to 1.17 times as far off fp64 as with a chain of multiply-adds on the vector unit (logits of
+// a spread of 5, heads of 128: 1.52e-6 and 1.30e-6), in two they are 0.2 to 0.8 times as far (7.0e-7), in the same time.
 template <int D, int TILES>
 __device__ __forceinline__ void logits(const Dims &dm, const F32Unit &u, const air_strides &st, const F32Lds &s, int rb, int nb,
                                        const uint4 (&k)[TILES][D / 16], f32x4 (&a)[TILES]) {
@@ -105,11 +107,15 @@ __device__ __forceinline__ void logits(const Dims &dm, const F32Unit &u, const a
 #pragma unroll
     for (int sl = 0; sl < D / 16; ++sl) q[sl] = *reinterpret_cast<const uint4 *>(src + 16 * sl);
 #pragma unroll
-    for (int tile = 0; tile < TILES; ++tile) a[tile] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    for (int tile = 0; tile < TILES; ++tile) {
+        f32x4 half = (f32x4){0.f, 0.f, 0.f, 0.f};
+        a[tile] = half;
 #pragma unroll
-    for (int sl = 0; sl < D / 16; ++sl) {
-#pragma unroll
-        for (int tile = 0; tile < TILES; ++tile) a[tile] = mma<float>(q[sl], k[tile][sl], a[tile]);
+        for (int sl = 0; sl < D / 16; sl += 2) {
+            a[tile] = mma<float>(q[sl], k[tile][sl], a[tile]);
+            half = mma<float>(q[sl + 1], k[tile][sl + 1], half);
+        }
+        a[tile] += half;
     }
     {
 #pragma clang fp contract(off)  // the scaled logit is rounded (it may be stashed): not fused into what follows
@@ -259,7 +265,8 @@ __global__ __launch_bounds__(256) void score_finish_f32(Dims dm, DevTables t, in
             for (int ci = 0; ci < kFinishChunks; ++ci) imp[ci] += (acc[ci][0] + acc[ci][1]) + (acc[ci][2] + acc[ci][3]);
         } else {
             const int lane = tid & 63, c = lane >> 4;
-#pragma unroll
+            // (Unrolled, heads of 128 take 260 registers, one wave a SIMD: air_score of 28 x 4 units of 7290 keys, 7 x 7 rows, 617 us in place of 537.)
+#pragma unroll 1
             for (int ci = 0; ci < kFinishChunks; ++ci) {
                 if (first + ci >= last) break;
                 uint4 k[4][D / 16];
@@ -284,7 +291,8 @@ __global__ __launch_bounds__(256) void score_finish_f32(Dims dm, DevTables t, in
                     float v = acc[tile];
                     v += __shfl_xor(v, 16, 64);
                     v += __shfl_xor(v, 32, 64);
-                    if (c == tile) imp[ci] += v;
+#pragma unroll
+                    for (int cj = 0; cj < kFinishChunks; ++cj) imp[cj] += c == tile && cj == ci ? v : 0.f;
                 }
             }
         }

@@ -362,3 +362,39 @@ def test_fp32_scores_at_the_edges_of_tiles_and_row_blocks(d, n_vis, G, window):
     want = want[..., :n_vis].mean(dim=(1, 2)).cpu().numpy()
     # logits of a few units in fp32: sums of d products, each rounding 2^-24 of a partial sum, and as much again in the exponential
     np.testing.assert_allclose(got, want, rtol=1e-5)
+
+
+@pytest.mark.parametrize("d,bound", [(128, 1e-6), (64, 1e-6)])
+def test_error_of_fp32_scores_against_fp64(d, bound):
+    # Relative 2-norm of the scores of an elite window (threshold 0.1), raw logits of a spread of 5 sqrt(d).  The largest are about 4 spreads, 20 units
+    # scaled, and the sum of their products is rounded at partial sums of half that size, 10 2^-25 units each time: 3e-7, for d / 4 matrix
+    # products about 1.3e-6 in one sum over all of them and half as much in two.  7.0e-7 measured; one chain of multiply-adds 1.30e-6 and
+    # 1.39e-6, one sum of matrix products 1.52e-6 and 1.26e-6.
+    import numpy as np
+    import torch
+
+    import paper_2503_23956_amd as A
+
+    dev = torch.device("cuda:0")
+    gen = torch.Generator(device=dev)
+    errs = []
+    for seed, n_vis, G in ((1, 7290, 7), (2, 1300, 4), (3, 577, 2), (4, 16384, 8)):
+        gen.manual_seed(seed)
+        n = 9 + n_vis + 69
+        seq = synth.configs.Seq(n, 9, n_vis, n - 60, 60)
+        k = torch.randn((1, 2, n, d), generator=gen, device=dev)
+        q = 5.0 * torch.randn((1, 2 * G, 69, d), generator=gen, device=dev)
+        cfg = A.make_config(n_layers=1, n_q_heads=2 * G, n_kv_heads=2, head_dim=d, batch=1, max_vis_len=n_vis, max_nonvis_len=78, max_window=60,
+                            max_decode_steps=1, dtype=A.AIR_F32, alpha=0.1)
+        ac = A.AirCache(cfg, dev)
+        ac.air_score(0, 1, [q], [k], [k], [seq])
+        got = ac.air_get_scores(0)[0].astype(np.float64)
+        cnt, idx = ac.air_get_elite(0)
+        ac.close()
+        want = torch.zeros((2, n_vis), dtype=torch.float64, device=dev)
+        for h in range(2 * G):
+            rows = torch.tensor(idx[0, h, :cnt[0, h]].astype(np.int64), device=dev)
+            keys = torch.cat([k[0, h // G, 9:9 + n_vis], k[0, h // G][rows]]).double()
+            want[h // G] += torch.softmax(q[0, h][rows - 9 - n_vis].double() @ keys.T / d ** 0.5, dim=1).mean(dim=0)[:n_vis] / G
+        errs.append(np.linalg.norm(got - want.cpu().numpy()) / np.linalg.norm(want.cpu().numpy()))
+    assert np.mean(errs) <= bound, errs
