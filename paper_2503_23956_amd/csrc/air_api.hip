@@ -91,7 +91,7 @@ WsLayout make_layout(const air_config &c) {
     w.dec_cnt = take(L * B * Hkv * 4);
     w.unit_cnt = take(L * B * Hkv * 4);
     w.seq_cnt = take(B * 4);
-    w.dec_steps = take((L * B * Hkv * kStepCopies + 1) * 4);
+    w.dec_steps = take((L * B * Hkv * (c.device_steps ? kStepCopies : 1) + 1) * 4);  // (unused without device_steps: the size of earlier layouts)
     w.moments = take(L * B * Hkv * (size_t)((w.n_chunks + kFinishChunks - 1) / kFinishChunks) * 4 * 8);
     w.indices = take(L * B * Hkv * NV * 4);
     // the cache pool, unless the cache is kept inside the prompt's own tensors

@@ -139,3 +139,19 @@ def test_workspace_holds_a_stash_only_where_scoring_can_use_it():
         factors = stash // 256 if dtype == A.AIR_BF16 else 0
         assert size(5, 0.9) - size(5, 0.0) == stash + factors  # 35 rows
         assert size(4, 0.9) == size(4, 0.0)  # 28 rows
+
+
+@pytest.mark.parametrize("size,kw", [
+    (1046528, dict(n_layers=2, n_q_heads=4, n_kv_heads=2, head_dim=64, batch=1, max_vis_len=576, max_nonvis_len=80, max_window=16, max_decode_steps=8)),
+    (74113536, dict(n_layers=24, n_q_heads=14, n_kv_heads=2, head_dim=64, batch=1, max_vis_len=7290, max_nonvis_len=142, max_window=128,
+                    max_decode_steps=32, dtype="bf16")),
+    (637648384, dict(n_layers=28, n_q_heads=28, n_kv_heads=4, head_dim=128, batch=3, max_vis_len=7290, max_nonvis_len=142, max_window=128,
+                     max_decode_steps=128, dtype="bf16")),
+    (66355968, dict(n_layers=28, n_q_heads=28, n_kv_heads=4, head_dim=128, batch=1, max_vis_len=2304, max_nonvis_len=142, max_window=32,
+                    max_decode_steps=8, alpha=0.0))])
+def test_workspace_sizes_that_programs_were_given_still_hold(size, kw):
+    # a context is created in no smaller a workspace than air_workspace_bytes says: it must not grow for contexts that gain nothing by it
+    import paper_2503_23956_amd as A
+
+    kw = dict(kw, dtype=A.AIR_BF16 if kw.get("dtype") else A.AIR_F32)
+    assert A.load_library().air_workspace_bytes(C.byref(A.make_config(**kw))) == size
