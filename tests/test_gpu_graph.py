@@ -10,7 +10,7 @@ from tests import parity_util as P
 pytestmark = pytest.mark.gpu
 
 
-def _contexts(w, steps, dev):
+def _contexts(w, steps, dev, retention=0.10):
     import paper_2503_23956_amd as A
     from paper_2503_23956_amd.device_inputs import config_for, to_device
 
@@ -20,8 +20,8 @@ def _contexts(w, steps, dev):
     q = [to_device(li.q_text, dev) for li in layers]
     k = [to_device(li.k, dev) for li in layers]
     v = [to_device(li.v, dev) for li in layers]
-    eager = A.AirCache(config_for(w, 0.10, max_decode_steps=steps, seqs=seqs), dev)
-    counted = A.AirCache(config_for(w, 0.10, max_decode_steps=steps, seqs=seqs, device_steps=1), dev)
+    eager = A.AirCache(config_for(w, retention, max_decode_steps=steps, seqs=seqs), dev)
+    counted = A.AirCache(config_for(w, retention, max_decode_steps=steps, seqs=seqs, device_steps=1), dev)
 
     def compress(ac, compact=True):
         ac.air_reset()
@@ -47,7 +47,7 @@ def test_replayed_decode_step_matches_eager_calls(shape):
     A, eager, counted, compress, seqs, layers = _contexts(w, steps, dev)
     if shape is not None:  # the same launch shape on both sides makes the outputs bitwise comparable
         for ac in (eager, counted):
-            # shape[3] = 2: two workgroups per unit that meet at the unit's arrival counter to advance the device-side count
+            # shape[3] = 2: two workgroups per unit, each with copies of the device-side count of its own
             ac.air_set_tuning(decode_splits=shape[0], decode_waves=shape[1], decode_tiles=shape[2], decode_halves=shape[3])
     L, B, Hkv, G, d = w.n_layers, w.batch, w.n_kv_heads, w.group, w.head_dim
     ins = []
@@ -226,24 +226,44 @@ def test_device_counted_steps_under_changing_launch_shapes():
     from paper_2503_23956_amd.device_inputs import to_device
 
     dev = torch.device("cuda:0")
-    shapes = [dict(), dict(decode_halves=1), dict(decode_splits=4, decode_waves=2, decode_tiles=2), dict(decode_waves=8), dict(),
-              dict(decode_splits=1, decode_waves=4, decode_tiles=4, decode_halves=2)]
-    steps = 2 * len(shapes)
-    w = synth.get_workload(2).scaled(n_layers=3, n_vis=2900, n_text=40, decode_steps=steps)
-    _, eager, counted, _, _, _ = _contexts(w, steps, dev)
+    # Column parts of a unit by the launch's units (caches of 640 keys and more): 80 in the call of all layers two, 48 four, 32 and 16 eight.
+    every, some, one = [(0, 5)], [(0, 3), (3, 5)], [(l, l + 1) for l in range(5)]
+    single, split, wide = dict(decode_halves=1), dict(decode_splits=4, decode_waves=2, decode_tiles=2), dict(decode_waves=8)
+    plan = [({}, one), ({}, every), ({}, one), ({}, some), (single, every), ({}, some), (split, one), ({}, one), (split, every), ({}, every),
+            (wide, some), ({}, some), ({}, one), (dict(decode_splits=1, decode_waves=4, decode_tiles=4, decode_halves=2), every), (single, one), ({}, one)]
+    w = synth.get_workload(2).scaled(n_layers=5, batch=4, n_vis=1300, n_text=40, decode_steps=len(plan) + 4)
+    _, eager, counted, _, seqs, _ = _contexts(w, len(plan) + 4, dev, retention=0.5)
+    assert w.n_kv_heads == 4 and all(640 <= s.seq_len - s.vis_len + 0.5 * s.vis_len < 1700 for s in seqs)
     out_e = torch.zeros((w.n_layers, w.batch, w.n_q_heads, w.head_dim), dtype=torch.bfloat16, device=dev)
     out_c = torch.ones_like(out_e)
-    for step in range(steps):
-        ins = [to_device(np.stack(x), dev) for x in zip(*[synth.decode_inputs(w, l, step) for l in range(w.n_layers)])]
-        for ac, out in ((eager, out_e), (counted, out_c)):
-            ac.air_set_tuning(**shapes[step % len(shapes)])
-            if step % 2:  # all layers of the step, or one by one (eight column parts: caches of 640 keys and more)
-                ac.air_decode_attn(0, w.n_layers, *ins, out)
-            else:
-                for l in range(w.n_layers):
-                    ac.air_decode_attn(l, l + 1, *(x[l:l + 1] for x in ins), out[l:l + 1])
+    ins = [[to_device(np.stack(x), dev) for x in zip(*[synth.decode_inputs(w, l, step) for l in range(w.n_layers)])] for step in range(len(plan) + 4)]
+    now = [torch.empty_like(x) for x in ins[0]]
+
+    def decode(ac, calls, new, out):
+        for l0, l1 in calls:
+            ac.air_decode_attn(l0, l1, *(x[l0:l1] for x in new), out[l0:l1])
+
+    def same(step):
         torch.cuda.synchronize()
         assert torch.equal(out_e, out_c), f"step {step}"
         assert np.array_equal(counted.air_get_lengths(), eager.air_get_lengths())
+
+    for step, (shape, calls) in enumerate(plan):
+        for ac, out in ((eager, out_e), (counted, out_c)):
+            ac.air_set_tuning(**shape)
+            decode(ac, calls, ins[step], out)
+        same(step)
+    # a recorded step, two layers in eight parts and three in four, replayed
+    eager.air_set_tuning()
+    counted.air_set_tuning()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        decode(counted, some, now, out_c)
+    for step in range(len(plan), len(plan) + 4):
+        for dst, src in zip(now, ins[step]):
+            dst.copy_(src)
+        g.replay()
+        decode(eager, some, ins[step], out_e)
+        same(step)
     eager.close()
     counted.close()
