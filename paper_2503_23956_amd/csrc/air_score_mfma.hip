@@ -467,7 +467,10 @@ __global__ __launch_bounds__(256, 4) void score_finish_kernel(Dims dm, DevTables
 constexpr int kEliteWaves = 8;      // phase 2 takes one head per wave
 // Elite-text columns of up to 16 kKept rows: tiles kept between maximum and sums, keys requested together.  (Tile by tile, twice, the
 // 32 rows a head of a window of 32 tokens cost eight trips to memory one behind the other: 16.5 us for 28 x 4 units of 7 heads, 13.5 now; the
-// few rows of an elite window are a path of their own: 7.7 and 7.3 for one layer.)
+// few rows of an elite window are a path of their own: 7.7 and 7.3 for one layer.)  Three tiles take 113 registers with heads of 128 elements
+// (96 without them: four waves a SIMD in place of five, which calls of many units do not show), four 131, and a workgroup a CU is lost: air_score
+// of 28 x 8 x 4 units of 64 keys with two / three / four tiles, 32 rows a head 90 / 93 / 106 us, 48 rows 152 / 127 / 145, 64 rows 205 / 205 / 178,
+// elite window 47.3 / 47.6 / 53.8 (47.3 without); 28 x 4 units 35.0 / 35.8 / 36.6, 52.2 / 45.8 / 46.7, 66.4 / 66.4 / 55.8.
 constexpr int kKept = 3;
 constexpr float kEliteMargin = 4e-3f;  // raw-logit units
 __device__ __forceinline__ uint4 masked(const uint4 &x, uint32_t keep) { return make_uint4(x.x & keep, x.y & keep, x.z & keep, x.w & keep); }
@@ -603,9 +606,9 @@ __global__ __launch_bounds__(64 * kEliteWaves) void elite_mfma_kernel(Dims dm, D
             if (lane == 0) t.elite_cnt[hrow] = R;
             // elite-text columns of Eq.7: (max, sum-exp) of every elite row over the elite text keys.  The
             // R x R logits are formed on MFMA, 16 rows against 16 keys per tile; lane (n, c) of a tile holds
-            // key n and rows 4c .. 4c+3, rows and keys past R re-read the last one.  Windows of more than 16
-            // rows (alpha = 0 turns the whole span into rows) go over the keys twice (maximum, then sum);
-            // up to 48 rows the tiles are kept.  The maximum is kept as the RAW dot product (before the
+            // key n and rows 4c .. 4c+3, rows and keys past R re-read the last one.  Up to 16 kKept rows the
+            // tiles are kept; longer windows (alpha = 0 turns the whole span into rows) go over the keys
+            // twice (maximum, then sum).  The maximum is kept as the RAW dot product (before the
             // 1/sqrt(d) scale), the sum is of exp((a - max) / sqrt(d)).
             for (int rb = 0; rb < R; rb += 16) {
                 uint4 qa2[NS];
