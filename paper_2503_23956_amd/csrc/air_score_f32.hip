@@ -9,9 +9,11 @@
 // A wave keeps its 32 keys in registers as matrix operands, straight from global memory (64-byte segments, all requested in front
 // of the row lists), blocks of 16 window rows are the other operand.  Bound: HBM and, with the two rounds of workgroups of 2304 keys
 // in 28 x 4 units, the row lists and rows that arrive behind the keys; the products of a block take 1024 clocks a tile of 16 keys, half
-// of them for padding with the usual 7 to 10 rows.  First pass on that shape, heads of 128 elements: 35.6 us (132 MB, 3.7 TB/s); with a thread
-// per key on the vector unit, keys and query rows through LDS (20 us of LDS time for the rows alone), 41.5; four waves of 64 keys 35.9,
-// three workgroups of them a CU 45.3.  Two layers x 2 heads of 576 keys of 64 elements: 6.6 and 8.2.
+// of them for padding with the usual 7 to 10 rows.  First pass on that shape, heads of 128 elements: 36.4 us (132 MB, 3.6 TB/s; 35.6 with one
+// sum of products a logit); with a thread per key on the vector unit, keys and query rows through LDS (20 us of LDS time for the rows alone), 41.5;
+// four waves of 64 keys 35.9, three workgroups of them a CU 45.3.  Two layers x 2 heads of 576 keys of 64 elements: 6.5 and 8.2.
+// More rows than the stash holds: every wave requests the rows of a block from memory, in either pass.  air_score, 28 x 4 units of 2304 keys, 7 heads,
+// 5 / 32 rows a head 199 / 1590 us, with the vector unit 255 / 2080; heads of 64 136 / 1290 and 182 / 1620; 7290 keys, 7 rows a head 537 and 773.
 #include "air_device.h"
 #include "air_internal.h"
 #include "air_score_dev.h"

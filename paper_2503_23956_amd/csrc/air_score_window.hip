@@ -1,5 +1,6 @@
 // air_score, bf16, windows that turn their whole span into rows (a continuous, all-text or visual window of dozens to
-// hundreds of rows per unit): Eq.6-8 with the ROWS in LDS, once per workgroup, and the keys of a wave in its registers, twice.
+// hundreds of rows per unit; bf16 contexts whose workspace holds no stash come here with an elite window too): Eq.6-8 with the ROWS in
+// LDS, once per workgroup, and the keys of a wave in its registers, twice.
 //
 // A workgroup of eight waves takes a part of a unit's keys; its waves share up to 256 window rows in LDS (loaded straight into
 // it) and go their own ways: a wave loads 32 keys from memory as MFMA operands, walks the row blocks over them and
@@ -14,18 +15,19 @@
 //           across the lanes).  The unit's last workgroup forms its statistics from the scores.
 // The products of the two passes differ in shape but give a logit the same bits, and have to: a weight would be off by
 // 2^(difference) where a key stands above all others.
-// Bound (7290 keys, 7 x 32 rows, 28 x 4 units: 448 workgroups of 1856 keys, pass 1 70 us, pass 2 82): instruction issue, 59 % of the clocks
+// Bound (7290 keys, 7 x 32 rows, 28 x 4 units: 448 workgroups of 1856 keys, pass 1 69 us, pass 2 82): instruction issue, 60 % of the clocks
 // in pass 1 and 57 % in pass 2 (an exponential takes a SIMD 16 clocks, any other instruction 4; matrix unit 34 and 24 %), on the CUs that
 // have two workgroups, by stamps close to all of it between the first keys and the last; then the quarter of the CUs that have one
 // workgroup, 4 us in pass 1 and 8 in pass 2 in front of a workgroup's first keys, and 9 behind its last (statistics, allocation).
 // What stands in front are dependent accesses, so there are few of them: the rows follow from the window and are requested before the
-// counts of the lists are there, and a run's partial sums lie side by side (a thread per row used to touch a line for every one: 5 us).
+// counts of the lists are there (without a threshold), and a run's partial sums lie side by side (a thread per row used to touch a line for every one: 5 us).
 // With lists read first, partial sums a line apart, references that each wave found for itself and 832 keys a run: 78.5 and 86.8 us.
 // Two waves a SIMD with 64 keys each, products between exponentials, take as long for the keys and longer in front (101 and 86).
 // Four waves a SIMD need 128 registers: everything in front of the loops is kept out of registers across them (`here`).
-// air_score with the elite kernel (17 for 32 x 7), rows a head x heads, us now / before: 7290 keys, 28 layers x 4 KV heads, 32 x 7 rows
-// 163 / 172, 5 x 7 97 / 99, 512 x 7 3771 / 3980, visual 151 / 160, heads of 64 121 / 128; eight layers 108 / 117; 16 prompts of 2304 keys
-// 747 / 759; 65536 keys, 2 units 82 / 94; 28 x 8 x 8 units of 300 keys 195 / 199; 32 x 64 x 8 of 128 keys, 4 x 9 rows 722 / 763.
+// air_score with the elite kernel (14 for 32 x 7), rows a head x heads, us now / with those and an elite kernel that kept no tiles: 7290 keys, 28
+// layers x 4 KV heads, 32 x 7 rows 161 / 169, 5 x 7 97 / 98, 512 x 7 3700 / 3970, visual 152 / 159, heads of 64 117 / 128; eight layers 103 / 118;
+// 16 prompts of 2304 keys 738 / 762; 65536 keys, 2 units 80 / 96; 28 x 8 x 8 units of 300 keys 183 / 197; 32 x 64 x 8 of 128 keys, 4 x 9 rows 695 /
+// 764; 28 layers of 7290 keys one by one 1389 / 1562, visual 1104 / 1190.
 // Precision: the argument of an exponential is rounded, to 2^-24 of itself, and the largest terms are the ones that count, so a
 // reference has to stay near the maximum; and a logit keeps its bits only if its sum starts at zero.  (With sums that
 // started at minus the reference, and the lane's first logit as reference up to 2^100, the scores were 9.7e-7 off fp64 in
