@@ -25,9 +25,10 @@
 // Two waves a SIMD with 64 keys each, products between exponentials, take as long for the keys and longer in front (101 and 86).
 // Four waves a SIMD need 128 registers: everything in front of the loops is kept out of registers across them (`here`).
 // air_score with the elite kernel (14 for 32 x 7), rows a head x heads, us now / with those and an elite kernel that kept no tiles: 7290 keys, 28
-// layers x 4 KV heads, 32 x 7 rows 161 / 169, 5 x 7 97 / 98, 512 x 7 3700 / 3970, visual 152 / 159, heads of 64 117 / 128; eight layers 103 / 118;
+// layers x 4 KV heads, 32 x 7 rows 161 / 169, 5 x 7 95 / 97, 512 x 7 3700 / 3970, visual 152 / 159, heads of 64 117 / 128; eight layers 103 / 118;
 // 16 prompts of 2304 keys 738 / 762; 65536 keys, 2 units 80 / 96; 28 x 8 x 8 units of 300 keys 183 / 197; 32 x 64 x 8 of 128 keys, 4 x 9 rows 695 /
-// 764; 28 layers of 7290 keys one by one 1389 / 1562, visual 1104 / 1190.
+// 764; 28 layers of 7290 keys one by one 1380 / 1645, visual 1100 / 1280, 5 x 7 rows 903 / 976 (1086 with
+// 1856 keys a run, 1113 with four groups of a wave's keys on their way as well).
 // Precision: the argument of an exponential is rounded, to 2^-24 of itself, and the largest terms are the ones that count, so a
 // reference has to stay near the maximum; and a logit keeps its bits only if its sum starts at zero.  (With sums that
 // started at minus the reference, and the lane's first logit as reference up to 2^100, the scores were 9.7e-7 off fp64 in
@@ -543,21 +544,34 @@ __global__ __launch_bounds__(kThreads, 4) void window_scores_kernel(Dims dm, Dev
 }
 
 // Keys of a workgroup, a multiple of 64 from kPartLeast to kPartMost.  Two workgroups share a CU, 512 the chip: as many parts of max_vis
-// as make the rounds of 512 times the work of one least.  A round costs the keys and about kPartExtra groups of 64 keys for what is in
+// as make the rounds of 512 times the work of one least.  A round costs the keys and about `extra` groups of 64 keys for what is in
 // front and behind (rows into LDS, parameters, partial sums).
 constexpr int kPartExtra = 8;
-static int part_keys(const Dims &dm, int64_t units) {
+static int part_keys(const Dims &dm, int64_t units, int most = kPartMost, int extra = kPartExtra) {
     const int groups = (dm.max_vis + 63) / 64;
-    int best = kPartMost / 64;
+    int best = most / 64;
     int64_t best_cost = -1;
-    for (int g = kPartMost / 64; g >= kPartLeast / 64; --g) {
-        const int64_t cost = (units * ((groups + g - 1) / g) + 511) / 512 * (g + kPartExtra);
+    for (int g = most / 64; g >= kPartLeast / 64; --g) {
+        const int64_t cost = (units * ((groups + g - 1) / g) + 511) / 512 * (g + extra);
         if (best_cost < 0 || cost < best_cost) {
             best_cost = cost;
             best = g;
         }
     }
     return 64 * best;
+}
+
+// Keys of a run of pass 1.  It decides references and partial sums, so it follows from the context alone, not from the layers of the call:
+// the scores are the same bits however the layers are cut into calls and launches.  Runs as long as parts suit a call of all layers (7290 keys,
+// 28 x 4 units, 7 x 32 rows: pass 1 70 us with 1856 keys a run, 78 with 832).  In a call of one layer a run's rows go to several workgroups
+// (below); up to three blocks of rows are too few for that: there a workgroup is bound by the keys that its CU can fetch, and runs are shorter.  air_score
+// of all layers / one by one, long and shorter runs, us: 28 x 4 units of 7290 keys, 7 heads of 5 rows 93.5 / 1086 and 96.0 / 902, of 13 rows 100 /
+// 1110 and 103 / 929, visual 94.5 / 980 and 98 / 797; 40 x 8 units of 16384 keys, 8 x 12 rows 568 / 1935 and 573 / 1820; with four blocks (7 x 18 rows) all
+// layers take 107.9 and 113.7.
+constexpr int kFewRows = 96, kRunMost = 1536, kRunExtra = 4;
+static int run_keys(const Dims &dm) {
+    const int64_t units = (int64_t)dm.L * dm.B * dm.Hkv;
+    return dm.G * dm.max_window <= kFewRows ? part_keys(dm, units, kRunMost, kRunExtra) : part_keys(dm, units);
 }
 
 // Workgroups among which the rows of a run are dealt in pass 1, whole blocks of 32: a call of few units (a layer of a context whose runs
@@ -574,12 +588,9 @@ static int rows_of_share(const Dims &dm, int64_t runs) {
 template <int D, bool WHOLE>
 static hipError_t window_launch(hipStream_t s, const Dims &dm, const DevTables &t, int pass, int l0, int nl, const LaunchLayers &ll,
                                 const air_strides &st, const SeqArgs &seqs) {
-    // A run of pass 1 decides references and partial sums, so it follows from the context alone, not from the layers of the call:
-    // the scores are the same bits however the layers are cut into calls and launches.  Pass 2 leaves whole sums of a
-    // key and the unit's statistics from whole units: its parts follow the launch.
-    // (Runs as long as parts: 7290 keys, 28 x 4 units, pass 1 70 us with 1856 keys a run, 78 with 832.)
+    // Pass 2 leaves whole sums of a key and the unit's statistics from whole units: its parts follow the launch.
     const int64_t units = (int64_t)nl * dm.B * dm.Hkv;
-    const int run = part_keys(dm, (int64_t)dm.L * dm.B * dm.Hkv);
+    const int run = run_keys(dm);
     const dim3 block(kThreads);
     if (pass == 1) {
         const int n_runs = (dm.max_vis + run - 1) / run, share_rows = rows_of_share(dm, units * n_runs);

@@ -12,11 +12,16 @@ from tests import parity_util as P
 pytestmark = pytest.mark.gpu
 
 
-def _part_keys(n_vis, units):
+def _part_keys(n_vis, units, most=2048, extra=8):
     """Keys of a workgroup as the launcher chooses them: least rounds of 512 workgroups times what a round costs."""
     groups = -(-n_vis // 64)
-    cost = {g: -(-units * -(-groups // g) // 512) * (g + 8) for g in range(8, 33)}
+    cost = {g: -(-units * -(-groups // g) // 512) * (g + extra) for g in range(8, most // 64 + 1)}
     return 64 * min(cost, key=lambda g: (cost[g], -g))
+
+
+def _run_keys(n_vis, units, rows):
+    """Keys of a run of the first pass, by the units of the context and the rows of a unit."""
+    return _part_keys(n_vis, units, 1536, 4) if rows <= 96 else _part_keys(n_vis, units)
 
 
 def _share_rows(rows, runs):
@@ -121,7 +126,7 @@ def test_error_against_fp64(d, visual, spread, bound, L, B, run):
     # 4 spread 2^-24 = 2.4e-7 spread at the most for one row, and averages over the rows that share a key.  Sums from zero
     # with references near the maximum: 0.6e-7, 4.3e-7 and 8.7e-7 measured (with the logits of this kernel as with those of
     # the one before it); sums that start at minus the reference: 0.7e-7, 9.7e-7 and 4.0e-6.
-    assert _part_keys(2304, L * B * 2) == run
+    assert _run_keys(2304, L * B * 2, 7 * 32) == run
     p = _Prompt(L, B, 2, 7, d, 2304, 64, 32, visual, spread)
     ac = p.context()
     got = p.score(ac)
@@ -174,14 +179,15 @@ def test_spans_of_many_runs(n_vis, window, G, d, visual):
 
 
 @pytest.mark.parametrize("d,visual", [(128, False), (64, False), (128, True), (64, True)])
-@pytest.mark.parametrize("window,G", [(9, 4), (33, 8)])  # 36 and 264 rows: two groups of rows
-@pytest.mark.parametrize("n_vis,run", [(4160, 1088), (7290, 1856), (8192, 2048)])
-def test_parts_that_are_larger_in_one_call_than_layer_by_layer(n_vis, run, window, G, d, visual):
+@pytest.mark.parametrize("window,G", [(9, 4), (33, 8)])  # 36 rows: runs of at most 1536 keys, and 264 rows: two groups of rows
+@pytest.mark.parametrize("n_vis,few,run", [(4160, 1088, 1088), (7290, 960, 1856), (8192, 1024, 2048)])
+def test_parts_that_are_larger_in_one_call_than_layer_by_layer(n_vis, few, run, window, G, d, visual):
     # 128 units in one launch, four layer by layer: units of several runs and parts that are no power of two, and as large as LDS
     # takes.  Rows of a run in one workgroup, or dealt to several: 264 rows as 160 + 104 in calls of seven layers, 3 x 96 (the last 72) in calls
     # of five, blocks of 32 in calls of one.
     L, B = 32, 4
     assert (_part_keys(n_vis, L * B), _part_keys(n_vis, B)) == (run, 512)
+    assert (_run_keys(n_vis, L * B, 36), _run_keys(n_vis, L * B, 96), _run_keys(n_vis, L * B, 97)) == (few, few, run)
     assert [_share_rows(264, n * B * -(-n_vis // run)) for n in (32, 7, 5, 1)] == [288, 160, 96, 32]
     p = _Prompt(L, B, 1, G, d, n_vis, 48, window, visual)
     ac = p.context()
@@ -207,7 +213,7 @@ def test_weights_of_a_row_add_up_to_one_whatever_the_logits(spread, G, d, L, B, 
     # Pass 1 forms its logits with products of 32 x 32, pass 2 with products of 16 x 16: they have to be the same bits, or a weight is
     # off by 2^(difference) where a key stands above all others (raw logits of 4e6 have a spacing of 0.5, that is 4 % of a weight).
     # No text columns: every row's weights add up to 1, to the rounding of fp32 sums of 2304 terms in runs of 512 or 1152.
-    assert _part_keys(2304, L * B * 2) == run
+    assert _run_keys(2304, L * B * 2, G * 32) == run
     p = _Prompt(L, B, 2, G, d, 2304, 16, 32, True, spread)
     ac = p.context()
     got = p.score(ac)
@@ -336,7 +342,7 @@ def test_first_references_from_keys_that_are_far_or_no_numbers(value, d, visual)
     # Runs of 1152 keys: a row's first reference is its maximum over the run's first 256 keys.  Here all of those are infinitely low, no
     # numbers, or beyond the bound of the references on either side.
     L = B = 16
-    assert _part_keys(2304, L * B * 2) == 1152
+    assert _run_keys(2304, L * B * 2, 7 * 32) == 1152
     p = _Prompt(L, B, 2, 7, d, 2304, 40, 32, visual)
     n0 = p.seqs[0].vis_start
     for x, y in zip(p.q, p.k):
