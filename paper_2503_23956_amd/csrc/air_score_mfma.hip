@@ -471,6 +471,9 @@ constexpr int kEliteWaves = 8;      // phase 2 takes one head per wave
 // (96 without them: four waves a SIMD in place of five, which calls of many units do not show), four 131, and a workgroup a CU is lost: air_score
 // of 28 x 8 x 4 units of 64 keys with two / three / four tiles, 32 rows a head 90 / 93 / 106 us, 48 rows 152 / 127 / 145, 64 rows 205 / 205 / 178,
 // elite window 47.3 / 47.6 / 53.8 (47.3 without); 28 x 4 units 35.0 / 35.8 / 36.6, 52.2 / 45.8 / 46.7, 66.4 / 66.4 / 55.8.
+// Heads of 64 elements take 90 registers with three tiles, 80 without: two workgroups a CU in place of three, which calls of several rounds of
+// workgroups do show.  air_score of 30 x 16 x 8 units, 4 heads, 714 keys without / with: elite window 172 / 182 us (threshold 0.2: 358 / 368), 7 / 20 / 32 rows
+// a head 255 / 263, 269 / 273, 307 / 314, 45 rows 416 / 411; of 28 x 8 x 4 units, 7 heads, 400 keys 52.6 / 52.9, 59.3 / 59.4, 81.8 / 80.9, 98.2 / 96.1, 142.6 / 132.8.
 constexpr int kKept = 3;
 constexpr float kEliteMargin = 4e-3f;  // raw-logit units
 __device__ __forceinline__ uint4 masked(const uint4 &x, uint32_t keep) { return make_uint4(x.x & keep, x.y & keep, x.z & keep, x.w & keep); }
@@ -487,7 +490,7 @@ __device__ __forceinline__ double dot64_wave(const bf16_t *a, const bf16_t *b, i
     return wave_sum(p);
 }
 
-template <int D>
+template <int D, int KEPT>
 __global__ __launch_bounds__(64 * kEliteWaves) void elite_mfma_kernel(Dims dm, DevTables t, int l0, LaunchLayers ll, air_strides st,
                                                          SeqArgs seqs, double alpha, double ln_alpha, int gb) {
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, n = lane & 15, c = lane >> 4;
@@ -606,7 +609,7 @@ __global__ __launch_bounds__(64 * kEliteWaves) void elite_mfma_kernel(Dims dm, D
             if (lane == 0) t.elite_cnt[hrow] = R;
             // elite-text columns of Eq.7: (max, sum-exp) of every elite row over the elite text keys.  The
             // R x R logits are formed on MFMA, 16 rows against 16 keys per tile; lane (n, c) of a tile holds
-            // key n and rows 4c .. 4c+3, rows and keys past R re-read the last one.  Up to 16 kKept rows the
+            // key n and rows 4c .. 4c+3, rows and keys past R re-read the last one.  Up to 16 KEPT rows the
             // tiles are kept; longer windows (alpha = 0 turns the whole span into rows) go over the keys
             // twice (maximum, then sum).  The maximum is kept as the RAW dot product (before the
             // 1/sqrt(d) scale), the sum is of exp((a - max) / sqrt(d)).
@@ -651,20 +654,20 @@ __global__ __launch_bounds__(64 * kEliteWaves) void elite_mfma_kernel(Dims dm, D
                     top(a4, 0);
                     over_lanes();
                     add(a4, 0);
-                } else if (R <= 16 * kKept) {
+                } else if (KEPT > 1 && R <= 16 * KEPT) {
                     // the keys of a row block requested together, their tiles kept for the sums
-                    uint4 kb[kKept][NS];
-                    f32x4 a4[kKept];
+                    uint4 kb[KEPT][NS];
+                    f32x4 a4[KEPT];
 #pragma unroll
-                    for (int j = 0; j < kKept; ++j) keys(16 * j, kb[j]);  // (past the list its last key again)
+                    for (int j = 0; j < KEPT; ++j) keys(16 * j, kb[j]);  // (past the list its last key again)
 #pragma unroll
-                    for (int j = 0; j < kKept; ++j) {
+                    for (int j = 0; j < KEPT; ++j) {
                         a4[j] = tile(kb[j]);
                         top(a4[j], 16 * j);
                     }
                     over_lanes();
 #pragma unroll
-                    for (int j = 0; j < kKept; ++j)
+                    for (int j = 0; j < KEPT; ++j)
                         if (16 * j < R) add(a4[j], 16 * j);
                 } else {
                     for (int jb = 0; jb < R; jb += 16) {
@@ -699,10 +702,9 @@ hipError_t launch_elite_mfma(hipStream_t s, const Dims &dm, const DevTables &t, 
     gb = gb < 1 ? 1 : (gb > dm.G ? dm.G : gb);
     const double ln_alpha = alpha > 0.0 ? log(alpha) : -INFINITY;
     const dim3 grid(dm.Hkv, dm.B, nl), block(64 * kEliteWaves);
-    if (dm.D == 128)
-        hipLaunchKernelGGL(elite_mfma_kernel<128>, grid, block, gb * per_head, s, dm, t, l0, ll, st, seqs, alpha, ln_alpha, gb);
-    else
-        hipLaunchKernelGGL(elite_mfma_kernel<64>, grid, block, gb * per_head, s, dm, t, l0, ll, st, seqs, alpha, ln_alpha, gb);
+    const bool tiles_kept = (int64_t)nl * dm.B * dm.Hkv <= 4 * kCUs || (alpha == 0.0 && dm.max_window > 32);
+    auto kernel = dm.D == 128 ? elite_mfma_kernel<128, kKept> : tiles_kept ? elite_mfma_kernel<64, kKept> : elite_mfma_kernel<64, 1>;
+    hipLaunchKernelGGL(kernel, grid, block, gb * per_head, s, dm, t, l0, ll, st, seqs, alpha, ln_alpha, gb);
     return hipGetLastError();
 }
 

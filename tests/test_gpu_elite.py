@@ -236,3 +236,41 @@ def test_visual_keys_of_a_large_positive_logit(d, high, alpha, n_text, visual):
     want = (O.layer_importance_visual_window(q64, k64, P.seg_of(seqs[0])) if visual else O.layer_importance(q64, k64, P.seg_of(seqs[0]), alpha))[0]
     P.check_scores(got, [want], seqs, f"high={high}")
     assert visual or np.allclose(got[0][:, [300, 700]], 0.5)
+
+
+@pytest.mark.parametrize("n_text,window,alpha", [(48, 20, 0.0), (48, 33, 0.0), (48, 48, 0.02), (90, 90, 0.02)])  # up to 20, 33, 48, 90 rows a head
+def test_many_units_of_heads_of_64_elements_are_those_of_small_calls(n_text, window, alpha):
+    # A launch of more than 1024 units keeps no tiles of the text columns: sets, columns (through the scores) and statistics are the same
+    # bits as those of a call for every layer, which keeps them.
+    import torch
+
+    import paper_2503_23956_amd as A
+
+    L, B, hkv, G, d, n_vis, n_sys = 33, 16, 3, 4, 64, 130, 5  # 32 layers a launch: 1536 units
+    dev = torch.device("cuda:0")
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(64)
+    n = n_sys + n_vis + n_text
+    seqs = [synth.configs.Seq(n, n_sys, n_vis, n - window, window)] * B
+    k = [torch.randn((B, hkv, n, d), generator=gen, device=dev).to(torch.bfloat16) for _ in range(L)]
+    q = [torch.randn((B, hkv * G, n_text, d), generator=gen, device=dev).to(torch.bfloat16) for _ in range(L)]
+    ac = A.AirCache(A.make_config(n_layers=L, n_q_heads=hkv * G, n_kv_heads=hkv, head_dim=d, batch=B, max_vis_len=n_vis, max_nonvis_len=n - n_vis,
+                                  max_window=window, max_decode_steps=1, dtype=A.AIR_BF16, alpha=alpha), dev)
+    got = []
+    for calls in ([(0, L)], [(l, l + 1) for l in range(L)]):
+        ac.air_reset()
+        for l0, l1 in calls:
+            ac.air_score(l0, l1, q[l0:l1], k[l0:l1], k[l0:l1], seqs)
+        ac.air_budget()
+        sets = []
+        for l in range(L):
+            cnt, idx = ac.air_get_elite(l)
+            sets += [(cnt, [idx[b, h, :cnt[b, h]] for b in range(B) for h in range(hkv * G)])]
+        got.append((sets, [ac.air_get_scores(l) for l in range(L)], ac.air_get_stats()))
+    ac.close()
+    rows = np.concatenate([cnt.ravel() for cnt, _ in got[0][0]])
+    assert (rows.max() > 16) and (alpha or (rows == window).all())
+    for (c0, i0), (c1, i1) in zip(got[0][0], got[1][0]):
+        assert np.array_equal(c0, c1) and all(np.array_equal(x, y) for x, y in zip(i0, i1))
+    assert all(np.array_equal(x, y) for x, y in zip(got[0][1], got[1][1]))
+    assert all(np.array_equal(x, y) for x, y in zip(got[0][2], got[1][2]))
