@@ -9,15 +9,17 @@
 // A wave keeps its 32 keys in registers as matrix operands, straight from global memory (64-byte segments, all requested in front
 // of the row lists), blocks of 16 window rows are the other operand.  Bound: HBM and, with the two rounds of workgroups of 2304 keys
 // in 28 x 4 units, the row lists and rows that arrive behind the keys; the products of a block take 1024 clocks a tile of 16 keys, half
-// of them for padding with the usual 7 to 10 rows.  First pass on that shape, heads of 128 elements: 36.4 us (132 MB, 3.6 TB/s; 35.6 with one
-// sum of products a logit); with a thread per key on the vector unit, keys and query rows through LDS (20 us of LDS time for the rows alone), 41.5;
-// four waves of 64 keys 35.9, three workgroups of them a CU 45.3.  Two layers x 2 heads of 576 keys of 64 elements: 6.5 and 8.2.
+// of them for padding with the usual 7 to 10 rows.  First pass on that shape, heads of 128 elements: 32.5 us (132 MB, 4.1 TB/s; 35 to 36
+// with the places of a lane's rows and keys held in registers across the rows); with a thread per key on the vector unit, keys and query rows through LDS (20 us of LDS time for the rows alone), 41.5;
+// four waves of 64 keys 35.9, three workgroups of them a CU 45.3.  Two layers x 2 heads of 576 keys of 64 elements: 6.1 and 8.2.
 // More rows than the stash holds: every wave requests the rows of a block from memory, in either pass.  air_score, 28 x 4 units of 2304 keys, 7 heads,
 // 5 / 32 rows a head 199 / 1590 us, with the vector unit 255 / 2080; heads of 64 136 / 1290 and 182 / 1620; 7290 keys, 7 rows a head 537 and 773.
 #include "air_device.h"
 #include "air_internal.h"
 #include "air_score_dev.h"
 #include "air_tile.h"
+
+#include <type_traits>
 
 namespace air {
 
@@ -95,29 +97,68 @@ __device__ __forceinline__ void keys_of(const F32Unit &u, const air_strides &st,
     }
 }
 
+// Up to four rows (one or two heads a KV head): sixteen products of 4 rows x 4 keys at a time, one for every four keys of a tile and quarter c of
+// their slices, in a quarter of the clocks.  The operands are those of the large products but for the row, n % 4; lane (n, c) gets the four rows'
+// sums over its quarters, and keeps row c of the sum over the quarters, in a[.][0].  (With 12 of 16 rows padding the matrix unit took what the vector unit
+// did not: air_score of 28 x 2 x 4 units of 2304 keys of 128 elements, one head / two, 89.6 / 91.9 us, 83.2 / 87.1 this way, 80.3 / 85.2 on the vector unit; heads
+// of 64 63.2 / 65.8, 58.6 / 61.3, 60.9 / 65.4.)  Eight sums of D / 8 products: scores 0.3 to 0.5 times as far off fp64 as on the vector unit.
+template <int D, int TILES>
+__device__ __forceinline__ void few_logits(const uint4 (&q)[D / 16], const uint4 (&k)[TILES][D / 16], f32x4 (&a)[TILES]) {
+    // over the two halves of two registers, or over the quarters: what each has of the first in the lower (even) ones, of the second in the others
+    auto halves = [](float x, float y) __attribute__((always_inline)) {
+        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+        return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    };
+    auto quarters = [](float x, float y) __attribute__((always_inline)) {
+        const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+        return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    };
+#pragma unroll
+    for (int tile = 0; tile < TILES; ++tile) {
+        f32x4 x = (f32x4){0.f, 0.f, 0.f, 0.f}, half = x;
+#pragma unroll
+        for (int sl = 0; sl < D / 16; sl += 2) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                x = __builtin_amdgcn_mfma_f32_4x4x1f32(__builtin_bit_cast(f32x4, q[sl])[e], __builtin_bit_cast(f32x4, k[tile][sl])[e], x, 0, 0, 0);
+                half = __builtin_amdgcn_mfma_f32_4x4x1f32(__builtin_bit_cast(f32x4, q[sl + 1])[e], __builtin_bit_cast(f32x4, k[tile][sl + 1])[e], half, 0, 0, 0);
+            }
+        }
+        x += half;
+        a[tile] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        a[tile][0] = quarters(halves(x[0], x[2]), halves(x[1], x[3]));
+    }
+}
+
 // Logits of the staged rows rb .. rb + 15 against those keys: lane (n, c) gets rows rb + 4 i + c of key n of every tile.  (Operand row
 // 4 c + i carries staged row 4 i + c, so that all lanes are done after (nb - rb + 3) / 4 values.)  Even and odd slices have a sum each: in
 // one sum over the D products the scores were up to 1.17 times as far off fp64 as with a chain of multiply-adds on the vector unit (logits of
 // a spread of 5, heads of 128: 1.52e-6 and 1.30e-6), in two they are 0.2 to 0.8 times as far (7.0e-7), in the same time.
-template <int D, int TILES>
+template <int D, bool FEW, int TILES>
 __device__ __forceinline__ void logits(const Dims &dm, const F32Unit &u, const air_strides &st, const F32Lds &s, int rb, int nb,
                                        const uint4 (&k)[TILES][D / 16], f32x4 (&a)[TILES]) {
-    const int lane = threadIdx.x & 63, n = lane & 15, c = lane >> 4;
-    const int r = rb + 4 * (n & 3) + (n >> 2);
+    int lane = threadIdx.x & 63;
+    asm volatile("" : "+v"(lane));  // what follows from it is formed here, not held across the rows: registers for a workgroup a CU more
+    const int n = lane & 15, c = lane >> 4;
+    const int r = rb + (FEW ? n & 3 : 4 * (n & 3) + (n >> 2));
     const float *src = u.q + (int64_t)(u.kvh * dm.G + s.head[min(r, nb - 1)]) * st.q_h + (int64_t)s.row[min(r, nb - 1)] * st.q_t + 4 * c;
     uint4 q[D / 16];
 #pragma unroll
     for (int sl = 0; sl < D / 16; ++sl) q[sl] = *reinterpret_cast<const uint4 *>(src + 16 * sl);
+    if constexpr (FEW) {
+        few_logits<D, TILES>(q, k, a);
+    } else {
 #pragma unroll
-    for (int tile = 0; tile < TILES; ++tile) {
-        f32x4 half = (f32x4){0.f, 0.f, 0.f, 0.f};
-        a[tile] = half;
+        for (int tile = 0; tile < TILES; ++tile) {
+            f32x4 half = (f32x4){0.f, 0.f, 0.f, 0.f};
+            a[tile] = half;
 #pragma unroll
-        for (int sl = 0; sl < D / 16; sl += 2) {
-            a[tile] = mma<float>(q[sl], k[tile][sl], a[tile]);
-            half = mma<float>(q[sl + 1], k[tile][sl + 1], half);
+            for (int sl = 0; sl < D / 16; sl += 2) {
+                a[tile] = mma<float>(q[sl], k[tile][sl], a[tile]);
+                half = mma<float>(q[sl + 1], k[tile][sl + 1], half);
+            }
+            a[tile] += half;
         }
-        a[tile] += half;
     }
     {
 #pragma clang fp contract(off)  // the scaled logit is rounded (it may be stashed): not fused into what follows
@@ -130,8 +171,8 @@ __device__ __forceinline__ void logits(const Dims &dm, const F32Unit &u, const a
 }
 
 template <int D>
-__global__ __launch_bounds__(64 * kStreamWaves, 4) void score_stream_f32(Dims dm, DevTables t, int l0, LaunchLayers ll, air_strides st, SeqArgs seqs) {
-    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, n = lane & 15, c = lane >> 4;
+__global__ __launch_bounds__(64 * kStreamWaves, D == 64 ? 6 : 4) void score_stream_f32(Dims dm, DevTables t, int l0, LaunchLayers ll, air_strides st, SeqArgs seqs) {
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     F32Unit u;
     unit_of(dm, seqs, l0, ll, st, u);
     const int chunk = blockIdx.x;
@@ -150,20 +191,24 @@ __global__ __launch_bounds__(64 * kStreamWaves, 4) void score_stream_f32(Dims dm
         for (int w = 1; w < kStreamWaves; ++w) v = op(v, x[w][r]);
         return v;
     };
-    const int key0 = 16 * T * wave + n;  // of the lane's first tile, within the chunk
-    float *stash_base = t.stash + ((u.unit * dm.n_chunks + chunk) * (int64_t)kStashRows) * kChunkKeys + key0;
+    float *stash_of = t.stash + ((u.unit * dm.n_chunks + chunk) * (int64_t)kStashRows) * kChunkKeys;
     for (int r0 = 0; r0 < R_total; r0 += kGroupRows) {
         const int nb = min(kGroupRows, R_total - r0);
         stage_rows(dm, t, u, r0, nb, s);
-        for (int rb = 0; rb < nb; rb += 16) {
+        auto block = [&](int rb, auto few) __attribute__((always_inline)) {
+            constexpr int I = decltype(few)::value ? 1 : 4;  // values of a lane
+            int lane = threadIdx.x & 63;
+            asm volatile("" : "+v"(lane));  // (as above)
+            const int n = lane & 15, c = lane >> 4, key0 = 16 * T * wave + n;
+            float *stash_base = stash_of + key0;
             f32x4 a[T];
-            logits<D, T>(dm, u, st, s, rb, nb, k, a);
+            logits<D, I == 1, T>(dm, u, st, s, rb, nb, k, a);
             const int n_i = min(4, (nb - rb + 3) >> 2);  // live values of i (uniform over the workgroup)
-            int lim[4];  // last key of the chunk that row i sees, relative to the lane's first
+            int lim[I];  // last key of the chunk that row i sees, relative to the lane's first
 #pragma unroll
-            for (int i = 0; i < 4; ++i) lim[i] = min(s.lim[min(rb + 4 * i + c, nb - 1)], u.sq.vis_len - 1) - chunk * kChunkKeys - key0;
+            for (int i = 0; i < I; ++i) lim[i] = min(s.lim[min(rb + 4 * i + c, nb - 1)], u.sq.vis_len - 1) - chunk * kChunkKeys - key0;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
+            for (int i = 0; i < I; ++i) {
                 if (i >= n_i) continue;
                 const int r = 4 * i + c;
                 float m = -INFINITY;
@@ -177,7 +222,7 @@ __global__ __launch_bounds__(64 * kStreamWaves, 4) void score_stream_f32(Dims dm
             }
             lds_barrier();
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
+            for (int i = 0; i < I; ++i) {
                 if (i >= n_i) continue;
                 const int r = 4 * i + c;
                 const float m = over_waves(s_m, r, [](float x, float y) { return fmaxf(x, y); });
@@ -194,6 +239,10 @@ __global__ __launch_bounds__(64 * kStreamWaves, 4) void score_stream_f32(Dims dm
                 t.part[s.slot[rb + tid] * dm.n_chunks + chunk] = make_float2(m, z);
             }
             lds_barrier();  // the maxima have been read
+        };
+        for (int rb = 0; rb < nb; rb += 16) {
+            if (nb - rb <= 4) block(rb, std::true_type());
+            else block(rb, std::false_type());
         }
     }
 }
@@ -275,17 +324,21 @@ __global__ __launch_bounds__(256) void score_finish_f32(Dims dm, DevTables t, in
                 keys_of<D, 4>(u, st, first + ci, k);
                 const int key0 = (first + ci) * kChunkKeys + (tid & ~63) + (lane & 15);
                 float acc[4] = {0.f, 0.f, 0.f, 0.f};  // rows of the lane, key of every tile
-                for (int rb = 0; rb < nb; rb += 16) {
+                auto block = [&](int rb, auto few) __attribute__((always_inline)) {
                     f32x4 a[4];
-                    logits<D, 4>(dm, u, st, s, rb, nb, k, a);
+                    logits<D, decltype(few)::value, 4>(dm, u, st, s, rb, nb, k, a);
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
+                    for (int i = 0; i < (decltype(few)::value ? 1 : 4); ++i) {
                         const int r = rb + 4 * i + c;
                         if (r >= nb) continue;
 #pragma unroll
                         for (int tile = 0; tile < 4; ++tile)
                             if (key0 + 16 * tile <= s.lim[r]) acc[tile] = fmaf(s_w[r], expf(a[tile][i] - s_M[r]), acc[tile]);
                     }
+                };
+                for (int rb = 0; rb < nb; rb += 16) {
+                    if (nb - rb <= 4) block(rb, std::true_type());
+                    else block(rb, std::false_type());
                 }
                 // over the rows of the four lane groups; lane (n, c) keeps key 16 c + n, the thread's own
 #pragma unroll

@@ -398,3 +398,43 @@ def test_error_of_fp32_scores_against_fp64(d, bound):
             want[h // G] += torch.softmax(q[0, h][rows - 9 - n_vis].double() @ keys.T / d ** 0.5, dim=1).mean(dim=0)[:n_vis] / G
         errs.append(np.linalg.norm(got - want.cpu().numpy()) / np.linalg.norm(want.cpu().numpy()))
     assert np.mean(errs) <= bound, errs
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("G", [1, 2, 3, 4, 5])  # rows of a unit: products of four rows, of sixteen from the fifth on
+@pytest.mark.parametrize("spread", [1.0, 300.0])
+def test_fp32_scores_of_few_rows_are_the_same_bits_without_the_stash(d, G, spread):
+    # Both passes form the logits there: raw ones in the thousands, of which a last bit would change a weight by a per cent.
+    import ctypes as C
+
+    import numpy as np
+    import torch
+
+    import paper_2503_23956_amd as A
+
+    dev = torch.device("cuda:0")
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(8)
+    n_vis, n = 777, 3 + 777 + 1
+    seq = synth.configs.Seq(n, 3, n_vis, n - 1, 1)
+    k = [torch.randn((1, 2, n, d), generator=gen, device=dev) for _ in range(2)]
+    q = [spread * torch.randn((1, 2 * G, 1, d), generator=gen, device=dev) for _ in range(2)]
+    cfg = A.make_config(n_layers=2, n_q_heads=2 * G, n_kv_heads=2, head_dim=d, batch=1, max_vis_len=n_vis, max_nonvis_len=n - n_vis, max_window=1,
+                        max_decode_steps=1, dtype=A.AIR_F32, alpha=0.9)
+    full, small = A.AirCache(cfg, dev), A.AirCache(cfg, dev)
+    least = full.workspace_bytes - 2 * 2 * 4 * 32 * 256 * 4
+    small.lib.air_destroy(small.handle)
+    small.workspace, small.handle = torch.empty(least, dtype=torch.uint8, device=dev), C.c_void_p()
+    assert small.lib.air_create(C.byref(cfg), small.workspace.data_ptr(), least, C.byref(small.handle)) == 0
+    got = []
+    for ac in (full, small):
+        ac.air_score(0, 2, q, k, k, [seq])
+        got.append([ac.air_get_scores(l)[0] for l in range(2)])
+        ac.close()
+    for l in range(2):
+        assert np.array_equal(got[0][l], got[1][l])
+        want = torch.softmax(q[l][0].double().view(2, G, d) @ k[l][0, :, 3:].double().transpose(1, 2) / d ** 0.5, dim=2)
+        want = want[..., :n_vis].mean(dim=1).cpu().numpy()
+        # sums of d products in eight parts, each rounded at d / 8 partial sums of up to `spread` 4 sqrt(d) / 2 raw units, scaled by 1 / sqrt(d)
+        bound = 2.0 ** -24 * (d / 8 + 3) * 2 * spread * 4 + 1e-6
+        assert np.linalg.norm(got[0][l] - want) <= bound * np.linalg.norm(want)
