@@ -473,7 +473,8 @@ constexpr int kEliteWaves = 8;      // phase 2 takes one head per wave
 // elite window 47.3 / 47.6 / 53.8 (47.3 without); 28 x 4 units 35.0 / 35.8 / 36.6, 52.2 / 45.8 / 46.7, 66.4 / 66.4 / 55.8.
 // Heads of 64 elements take 90 registers with three tiles, 80 without: two workgroups a CU in place of three, which calls of several rounds of
 // workgroups do show.  air_score of 30 x 16 x 8 units, 4 heads, 714 keys without / with: elite window 172 / 182 us (threshold 0.2: 358 / 368), 7 / 20 / 32 rows
-// a head 255 / 263, 269 / 273, 307 / 314, 45 rows 416 / 411; of 28 x 8 x 4 units, 7 heads, 400 keys 52.6 / 52.9, 59.3 / 59.4, 81.8 / 80.9, 98.2 / 96.1, 142.6 / 132.8.
+// a head 255 / 263, 269 / 273, 307 / 314, 45 rows 416 / 411; of 28 x 8 x 4 units, 7 heads, 400 keys 52.6 / 52.9 (with 0.2 147 / 145), 59.3 / 59.4, 81.8 / 80.9,
+// 98.2 / 96.1, 142.6 / 132.8.  With a threshold, where few heads have more than 16 rows, calls of less than two full rounds show it too: 24 x 3 x 8 units, 900 keys 42.1 / 44.6.
 constexpr int kKept = 3;
 constexpr float kEliteMargin = 4e-3f;  // raw-logit units
 __device__ __forceinline__ uint4 masked(const uint4 &x, uint32_t keep) { return make_uint4(x.x & keep, x.y & keep, x.z & keep, x.w & keep); }
@@ -702,7 +703,7 @@ hipError_t launch_elite_mfma(hipStream_t s, const Dims &dm, const DevTables &t, 
     gb = gb < 1 ? 1 : (gb > dm.G ? dm.G : gb);
     const double ln_alpha = alpha > 0.0 ? log(alpha) : -INFINITY;
     const dim3 grid(dm.Hkv, dm.B, nl), block(64 * kEliteWaves);
-    const bool tiles_kept = (int64_t)nl * dm.B * dm.Hkv <= 4 * kCUs || (alpha == 0.0 && dm.max_window > 32);
+    const bool tiles_kept = (int64_t)nl * dm.B * dm.Hkv <= (alpha > 0.0 ? 2 : 4) * kCUs || (alpha == 0.0 && dm.max_window > 32);
     auto kernel = dm.D == 128 ? elite_mfma_kernel<128, kKept> : tiles_kept ? elite_mfma_kernel<64, kKept> : elite_mfma_kernel<64, 1>;
     hipLaunchKernelGGL(kernel, grid, block, gb * per_head, s, dm, t, l0, ll, st, seqs, alpha, ln_alpha, gb);
     return hipGetLastError();

@@ -567,7 +567,8 @@ static int part_keys(const Dims &dm, int64_t units, int most = kPartMost, int ex
 // (below); up to three blocks of rows are too few for that: there a workgroup is bound by the keys that its CU can fetch, and runs are shorter.  air_score
 // of all layers / one by one, long and shorter runs, us: 28 x 4 units of 7290 keys, 7 heads of 5 rows 93.5 / 1086 and 96.0 / 902, of 13 rows 100 /
 // 1110 and 103 / 929, visual 94.5 / 980 and 98 / 797; 40 x 8 units of 16384 keys, 8 x 12 rows 568 / 1935 and 573 / 1820; with four blocks (7 x 18 rows) all
-// layers take 107.9 and 113.7.
+// layers take 107.9 and 113.7.  With a threshold (no stash) the rows of a unit are not known here: 28 x 8 x 4 units of 2304 keys, heads of 64, take 131 / 863
+// with runs of 1152 keys, 141 / 804 with 768.
 constexpr int kFewRows = 96, kRunMost = 1536, kRunExtra = 4;
 static int run_keys(const Dims &dm) {
     const int64_t units = (int64_t)dm.L * dm.B * dm.Hkv;

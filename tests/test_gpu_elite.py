@@ -240,7 +240,7 @@ def test_visual_keys_of_a_large_positive_logit(d, high, alpha, n_text, visual):
 
 @pytest.mark.parametrize("n_text,window,alpha", [(48, 20, 0.0), (48, 33, 0.0), (48, 48, 0.02), (90, 90, 0.02)])  # up to 20, 33, 48, 90 rows a head
 def test_many_units_of_heads_of_64_elements_are_those_of_small_calls(n_text, window, alpha):
-    # A launch of more than 1024 units keeps no tiles of the text columns: sets, columns (through the scores) and statistics are the same
+    # A launch of more than 1024 units (512 with a threshold) keeps no tiles of the text columns: sets, columns (through the scores) and statistics are the same
     # bits as those of a call for every layer, which keeps them.
     import torch
 
