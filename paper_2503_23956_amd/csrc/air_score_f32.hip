@@ -13,7 +13,7 @@
 // with the places of a lane's rows and keys held in registers across the rows); with a thread per key on the vector unit, keys and query rows through LDS (20 us of LDS time for the rows alone), 41.5;
 // four waves of 64 keys 35.9, three workgroups of them a CU 45.3.  Two layers x 2 heads of 576 keys of 64 elements: 6.1 and 8.2.
 // More rows than the stash holds: every wave requests the rows of a block from memory, in either pass.  air_score, 28 x 4 units of 2304 keys, 7 heads,
-// 5 / 32 rows a head 199 / 1590 us, with the vector unit 255 / 2080; heads of 64 136 / 1290 and 182 / 1620; 7290 keys, 7 rows a head 537 and 773.
+// 5 / 32 rows a head 200 / 1610 us, with the vector unit 262 / 2100; heads of 64 133 / 1305 and 183 / 1633; 7290 keys, 7 rows a head 514 and 790.
 #include "air_device.h"
 #include "air_internal.h"
 #include "air_score_dev.h"
